@@ -83,17 +83,24 @@ __global__ void __launch_bounds__(64 * NWAVES) __attribute__((amdgpu_waves_per_e
     bf16x8_t qf[QB][MK];
     float ss_row = 0.f;
     if (QN) {
-        // lane L adds one half (L & 1) of the partial sums of query row L / 2 of this wave: contiguous 16-byte loads, all issued
-        // before the first add, in a fixed order (the result is bit-reproducible); the two halves meet through one shuffle
+        // lane L adds one half (L & 1) of the partial sums of query row L / 2 of this wave: contiguous 16-byte loads, sixteen issued
+        // before the first add, in a fixed order (the result is bit-reproducible); the two halves meet through one shuffle.  Rows
+        // are padded to whole float4 per half; what lies past n_parts is not counted.
         int r = qtile * QT + wave * 32 + (lane >> 1);
         if (r > n_q - 1) r = n_q - 1;
-        const int per4 = qn.n_parts / 8;  // float4 loads per lane, at most 16 (d_model <= 8192)
-        const float4 *pp = reinterpret_cast<const float4 *>(qn.sumsq + (size_t)r * qn.ld + (lane & 1) * (qn.n_parts / 2));
-        float4 part[16];
+        const int per4 = (qn.n_parts + 7) / 8;  // float4 loads per lane
+        const int left = qn.n_parts - (lane & 1) * per4 * 4;
+        const float4 *pp = reinterpret_cast<const float4 *>(qn.sumsq + (size_t)r * qn.ld) + (lane & 1) * per4;
+        for (int i0 = 0; i0 < per4; i0 += 16) {
+            float4 part[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) part[i] = i < per4 ? pp[i] : make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int i = 0; i < 16; ++i) part[i] = i0 + i < per4 ? pp[i0 + i] : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) ss_row += (part[i].x + part[i].y) + (part[i].z + part[i].w);
+            for (int i = 0; i < 16; ++i) {
+                const int k = (i0 + i) * 4;
+                ss_row += ((k < left ? part[i].x : 0.f) + (k + 1 < left ? part[i].y : 0.f)) + ((k + 2 < left ? part[i].z : 0.f) + (k + 3 < left ? part[i].w : 0.f));
+            }
+        }
         ss_row += __shfl_xor(ss_row, 1);
     }
 #pragma unroll
@@ -466,8 +473,8 @@ lvx_status_t lvx_launch_attention(const bf16_t *q, int64_t ld_q, int n_q, int H,
     if (D == 128) return launch<128, 4, 2, 1>(q, ld_q, n_q, H, k_packed, vt_packed, cap, n_keys, scale, out, ld_out, stream, amax_slots);
 #endif
     if (qnorm != nullptr) {  // the kernel normalises and scales the queries as it loads them (cross-attention of a bf16 stage)
-        LVX_REQUIRE(D == 128 && qnorm->sumsq != nullptr && qnorm->gain != nullptr && qnorm->n_parts > 0 && qnorm->n_parts % 8 == 0 &&
-                        qnorm->n_parts <= 128 && qnorm->ld % 4 == 0 && qnorm->d_model == H * D,
+        LVX_REQUIRE(D == 128 && qnorm->sumsq != nullptr && qnorm->gain != nullptr && qnorm->n_parts > 0 &&
+                        qnorm->ld >= (qnorm->n_parts + 7) / 8 * 8 && qnorm->ld % 4 == 0 && qnorm->d_model == H * D,
                     LVX_ERR_INVALID_ARG,
                     "attention: query norm needs head_dim 128, partial sums and a gain");
         return launch<128, 8, 2, 1, true, true>(q, ld_q, n_q, H, k_packed, vt_packed, cap, n_keys, scale, out, ld_out, stream, amax_slots, qnorm);

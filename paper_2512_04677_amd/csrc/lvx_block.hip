@@ -92,8 +92,8 @@ ws_layout_t ws_layout(const lvx_stage_t *s, int n_tokens, int n_ctx) {
     w.big = off;     off += round256((size_t)n_tokens * (wide + WS_PAD) * 2);
     w.qk32 = off;    // fp32 k columns of the QKV projection (bf16 stages only; an FP8 stage stores them in bf16)
     if (s->blocks_fp8 == nullptr) off += round256((size_t)n_tokens * w.ld_qk32 * 4);
-    w.q_sumsq = off;  // partial sums of squares of the cross-attention's query rows (bf16 stages), d / 64 per row
-    if (s->blocks_fp8 == nullptr) off += round256((size_t)n_tokens * LVX_GEMM_SUMSQ_PARTS(d) * 4);
+    w.q_sumsq = off;  // partial sums of squares of the cross-attention's query rows (bf16 stages)
+    if (s->blocks_fp8 == nullptr) off += round256((size_t)n_tokens * (LVX_GEMM_MAX_SUMSQ_PARTS(d) + 8) * 4);
     // context K | V rows and their packed forms for a group of layers at once (bf16 stages; an FP8 stage uses one slot)
     w.ctx_group = s->blocks_fp8 != nullptr ? 1 : ctx_group_size(s->n_layers, n_ctx, d);
     w.ctx_kv = off;  off += round256((size_t)w.ctx_group * n_ctx * w.ld_ckv * 2);
@@ -164,6 +164,7 @@ lvx_status_t precompute_ctx(const lvx_stage_t *s, int l0, int l1, const bf16_t *
     const int64_t slot_rows = (int64_t)n_ctx * ldk, slot_packed = (int64_t)L.cap_ctx * d, ld32 = L.ld_u, slot_rows32 = (int64_t)n_ctx * ld32;
     lvx_gemm_segs_t segs;
     segs.n = 2 * g;
+    segs.order = LVX_GEMM_ORDER_ONE;
     const float *gains[CTX_GROUP];
     for (int j = 0; j < g; ++j) {
         const lvx_block_weights_t &w = s->blocks[l0 + j];
@@ -238,6 +239,7 @@ lvx_status_t run_block(const lvx_stage_t *s, int layer, lvx_kvcache *c, float *x
             const bf16_t *Wq = (const bf16_t *)w.W_qkv;
             lvx_gemm_segs_t segs;
             segs.n = 3;
+            segs.order = LVX_GEMM_ORDER_LAUNCH;
             segs.s[0] = {Wq, big, ldq, d, 0, 0, 0};
             segs.s[1] = {Wq + (size_t)d * ldw, k32, ld32, d, 0, 1, 0};
             segs.s[2] = {Wq + (size_t)2 * d * ldw, big + 2 * d, ldq, d, 0, 0, 0};
@@ -299,15 +301,16 @@ lvx_status_t run_block(const lvx_stage_t *s, int layer, lvx_kvcache *c, float *x
     { prof_scope_t ps(LVX_PROF_LAYERNORM, st); LVX_TRY(lvx_launch_layernorm(x, 1, d, nullptr, nullptr, eps, n, d, u, ldu, st, amax_out())); }
     // bf16 stage with a query gain: the projection leaves each row's partial sums of squares beside its bf16 output and the
     // attention kernel normalises, scales and rounds the queries as it loads them (no norm-only pass over q)
-    const bool fuse_qnorm = w8 == nullptr && w.gc_q != nullptr && D == 128 && d % 512 == 0 && d <= 8192;
+    const bool fuse_qnorm = w8 == nullptr && w.gc_q != nullptr && D == 128 && d <= 8192;
     float *q_sumsq = (float *)(ws + L.q_sumsq);
-    const int q_parts = LVX_GEMM_SUMSQ_PARTS(d);
+    const int q_parts = fuse_qnorm ? lvx_gemm_sumsq_parts(n, d, d) : 0, ld_parts = (q_parts + 7) / 8 * 8;
     {
         prof_scope_t ps(LVX_PROF_GEMM_CROSS, st);
         if (fuse_qnorm) {
             lvx_gemm_segs_t segs;
             segs.n = 1;
-            segs.s[0] = {(const bf16_t *)w.Wc_q, big, ldc, d, 0, 0, q_parts, q_sumsq};
+            segs.order = LVX_GEMM_ORDER_LAUNCH;
+            segs.s[0] = {(const bf16_t *)w.Wc_q, big, ldc, d, 0, 0, ld_parts, q_sumsq};
             LVX_TRY(lvx_launch_linear_segments(u, ldu, ldw, segs, n, d, st));
         } else
             LVX_TRY(linear(u, ldu, w.Wc_q, 2, big, ldc, n, d, d, LVX_EPI_STORE, nullptr, 0, nullptr, false, false, true, false));
@@ -326,7 +329,7 @@ lvx_status_t run_block(const lvx_stage_t *s, int layer, lvx_kvcache *c, float *x
     }
     {
         prof_scope_t ps(LVX_PROF_ATTN_CROSS, st);
-        const lvx_attn_qnorm_t qn = {q_sumsq, w.gc_q, q_parts, q_parts, d, s->rope.eps};
+        const lvx_attn_qnorm_t qn = {q_sumsq, w.gc_q, q_parts, ld_parts, d, s->rope.eps};
         LVX_TRY(lvx_launch_attention(big, ldc, n, H, D, pack_k, pack_v, L.cap_ctx, n_ctx, scale, u, ldu, st, amax_out(), false, fuse_qnorm ? &qn : nullptr));
     }
     { prof_scope_t ps(LVX_PROF_GEMM_CROSS, st); LVX_TRY(linear(u, ldu, w.Wc_o, 5, x, d, n, d, d, LVX_EPI_RESID_GATE_F32, x, d, nullptr, false, false, true, false)); }

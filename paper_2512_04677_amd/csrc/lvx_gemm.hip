@@ -13,76 +13,12 @@
 // that XCD's L2.
 // The same kernel serves the decoder's 3x3x3 convolution as an implicit GEMM (CONV): its A rows are gathered from a
 // zero-padded volume, a tap being a constant shift of the row addresses.
-#include "lvx_internal.h"
+#include "lvx_gemm_core.h"
 
 namespace {
 
 constexpr int BK = 64;
 constexpr int GROUP_M = 8;
-
-// Epilogue.  Accumulator register e of 16 x 16 block (i,j) holds row m0 + 16i + e and column n0 + 16j of C (m0, n0 already
-// include the lane's 4*q4 / l16 offsets): for a fixed register, each group of 16 lanes writes 16 consecutive columns of one
-// row.  Interior tiles take the branch-free path; only tiles on the M or N edge check every element.
-template <int FM, int FN, int EPI>
-__device__ __forceinline__ void lvx_gemm_epilogue(f32x4_t (&acc)[FM][FN], f32x4_t (&rres)[FM][FN], bf16_t *C, int64_t ldc, const bf16_t *R,
-                                                  int64_t ldr, const float *__restrict__ gate, int M, int N, int m0, int n0) {
-    const bool interior = (m0 - (m0 & 12) + FM * 16 <= M) && (n0 - (n0 & 15) + FN * 16 <= N);
-    float gt[FN];  // per column block: the gate (residual epilogues) or the bias of this lane's column
-#pragma unroll
-    for (int j = 0; j < FN; ++j) {
-        const int n = n0 + j * 16 < N ? n0 + j * 16 : N - 1;
-        gt[j] = 1.f;
-        if ((EPI == LVX_EPI_RESID_GATE || EPI == LVX_EPI_RESID_GATE_F32) && gate != nullptr) gt[j] = gate[n];
-        if (EPI == LVX_EPI_BIAS || EPI == LVX_EPI_BIAS_SILU) gt[j] = gate != nullptr ? gate[n] : 0.f;
-    }
-    // rows outermost, column blocks innermost: the FN stores of one row follow each other, so neighbouring 32-byte (fp32:
-    // 64-byte) runs of a cache line reach L2 together
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int m = m0 + i * 16 + e;
-            if (!interior && m >= M) continue;
-            bf16_t *cp = C + (size_t)m * ldc + n0;
-            float *cpf = reinterpret_cast<float *>(C) + (size_t)m * ldc + n0;
-            const bf16_t *rp = R + (size_t)m * ldr + n0;
-#pragma unroll
-            for (int j = 0; j < FN; ++j) {
-                if (!interior && n0 + j * 16 >= N) continue;
-                float v = acc[i][j][e];
-                if (EPI == LVX_EPI_GELU_TANH) v = gelu_tanh_f32(v);
-                if (EPI == LVX_EPI_BIAS || EPI == LVX_EPI_BIAS_SILU) v += gt[j];
-                if (EPI == LVX_EPI_BIAS_SILU) v = v * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * v));
-                if (EPI == LVX_EPI_RESID_GATE) v = bf16_bits_to_f32(rp[j * 16]) + gt[j] * v;
-                if (EPI == LVX_EPI_RESID_GATE_F32)
-                    cpf[j * 16] = rres[i][j][e] + gt[j] * v;
-                else if (EPI == LVX_EPI_STORE_F32)
-                    cpf[j * 16] = v;
-                else
-                    cp[j * 16] = (bf16_t)(pack_bf16x2(v, 0.f) & 0xffffu);
-            }
-        }
-    }
-}
-
-// Sum of squares of this wave's FN * 16 columns for each of its rows (fp32 accumulators), one float per row at out[m * ld + part].
-template <int FM, int FN>
-__device__ __forceinline__ void lvx_gemm_row_sumsq(const f32x4_t (&acc)[FM][FN], float *out, int64_t ld, int part, int M, int m0, int l16) {
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            float ss = 0.f;
-#pragma unroll
-            for (int j = 0; j < FN; ++j) ss += acc[i][j][e] * acc[i][j][e];
-            ss += __shfl_xor(ss, 1);
-            ss += __shfl_xor(ss, 2);
-            ss += __shfl_xor(ss, 4);
-            ss += __shfl_xor(ss, 8);
-            const int m = m0 + i * 16 + e;
-            if (l16 == 0 && m < M) out[(size_t)m * ld + part] = ss;
-        }
-}
 
 // gfx950's global_load_lds_dwordx4 moves 16 bytes per lane from
 // global memory straight into LDS (LDS byte address = M0 + 16*lane), so a slab needs no staging registers, no ds_write
@@ -114,21 +50,6 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N)
     __shared__ __attribute__((aligned(1024))) char lds[NSTAGE * STAGE_B];
 
     const int total = tiles_m * tiles_n;
-#ifdef LVX_GEMM_NPART
-    // experiment: XCD x owns the column tiles [x * tn_per, (x + 1) * tn_per) and walks all row tiles of them, bands of 8 row tiles
-    const int tn_per = (tiles_n + 7) / 8;
-    const int tn_lo = (blockIdx.x & 7) * tn_per;
-    const int tn_cnt = tiles_n - tn_lo < tn_per ? tiles_n - tn_lo : tn_per;
-    const int kx = blockIdx.x >> 3;
-    if (tn_cnt <= 0 || kx >= tiles_m * tn_cnt) return;
-    const int band = kx / (GROUP_M * tn_cnt);
-    const int first_m = band * GROUP_M;
-    const int band_m = tiles_m - first_m < GROUP_M ? tiles_m - first_m : GROUP_M;
-    const int in_band = kx - band * GROUP_M * tn_cnt;
-    const int tm = first_m + in_band % band_m;
-    int tn = tn_lo + in_band / band_m;
-    const int widx = tm * tiles_n + tn;
-#else
     const int widx = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     if (widx >= total) return;
     const int band = widx / (GROUP_M * tiles_n);
@@ -137,7 +58,6 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N)
     const int in_band = widx - band * GROUP_M * tiles_n;
     const int tm = first_m + in_band % band_m;
     int tn = in_band / band_m;
-#endif
     // several projections of the same activations in one launch (tiles_n counts all of them): the column tile's segment gives
     // the weight matrix, the output, its width, its row stride and whether it is stored in fp32 (workgroup-uniform)
     bool seg_f32 = false;
@@ -315,202 +235,14 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N)
 
     if (EPI == LVX_EPI_SEGMENTS) {
         if (seg_f32)
-            lvx_gemm_epilogue<FM, FN, LVX_EPI_STORE_F32>(acc, rres, C, ldc, R, ldr, gate, M, N, m0, n0);
+            lvx_gemm_epilogue<FM, FN, LVX_EPI_STORE_F32, false, true>(acc, rres, C, ldc, R, ldr, gate, M, N, m0, n0, 1.f);
         else
-            lvx_gemm_epilogue<FM, FN, LVX_EPI_STORE>(acc, rres, C, ldc, R, ldr, gate, M, N, m0, n0);
-        if (seg_sumsq != nullptr) lvx_gemm_row_sumsq<FM, FN>(acc, seg_sumsq, seg_ld_sumsq, tn * WAVES_N + wn, M, m0, l16);
+            lvx_gemm_epilogue<FM, FN, LVX_EPI_STORE, false, true>(acc, rres, C, ldc, R, ldr, gate, M, N, m0, n0, 1.f);
+        if (seg_sumsq != nullptr && n0 - l16 < N) lvx_gemm_row_sumsq<FM, FN>(acc, seg_sumsq, seg_ld_sumsq, tn * WAVES_N + wn, M, m0, l16);
     } else {
-        lvx_gemm_epilogue<FM, FN, EPI>(acc, rres, C, ldc, R, ldr, gate, M, N, m0, n0);
+        lvx_gemm_epilogue<FM, FN, EPI, false, true>(acc, rres, C, ldc, R, ldr, gate, M, N, m0, n0, 1.f);
     }
 }
-
-// Experiment, compiled only with -DLVX_GEMM_BIG (lvx_linear then uses it for the plain-store and GELU epilogues): 256 x 256 tile,
-// 8 waves of 64 x 128 (4 x 2), two 64 KB LDS stages.  Per flop a third fewer bytes go from L2 to LDS and a quarter fewer LDS
-// fragment reads than with the 128 x 256 tile.  Slab t lives in stage t & 1.  Per slab one barrier, half-way through the second
-// k-step (its fragments are in registers by then); right after it the stage just released takes slab t+2, a whole slab of MFMAs
-// ahead of its use, and the first fragments of slab t+1 are read under the remaining MFMAs.  Measured: 5 % faster than the
-// 128 x 256 kernel when the tile count is a multiple of 256 (4096 x 16384 x 5120), 7 to 14 % slower on the block's own shapes,
-// whose 19 x 60 and 19 x 54 tiles need 5 rounds of the chip where the smaller tile wastes under 4 %.
-#ifdef LVX_GEMM_BIG
-template <int EPI>
-__global__ void __launch_bounds__(512)
-    lvx_gemm_big_kernel(const bf16_t *__restrict__ A, int64_t lda, const bf16_t *__restrict__ W, int64_t ldw, bf16_t *C, int64_t ldc,
-                        int M, int N, int K, const bf16_t *R, int64_t ldr, const float *__restrict__ gate, int tiles_m, int tiles_n,
-                        int per_xcd, lvx_gemm_segs_t segs) {
-    constexpr int BM = 256, BN = 256, WAVES_N = 2, NW = 8;
-    constexpr int WTM = 64, WTN = 128, FM = 4, FN = 8;
-    constexpr int ROW_B = BK * 2;
-    constexpr int A_B = BM * ROW_B, STAGE_B = (BM + BN) * ROW_B;
-    constexpr int QPW = (BM + BN) / 8 / NW;  // 8 DMA instructions per wave per slab
-    constexpr int A_Q = (BM / 8) / NW;       // the first 4 fetch A rows
-
-    __shared__ __attribute__((aligned(1024))) char lds[2 * STAGE_B];
-
-    const int total = tiles_m * tiles_n;
-    const int widx = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (widx >= total) return;
-    constexpr int GM = 4;  // bands of 4 row tiles: 4 x 8 tiles of an XCD's 32 compute units share 4 A panels and 8 W panels
-    const int band = widx / (GM * tiles_n);
-    const int first_m = band * GM;
-    const int band_m = tiles_m - first_m < GM ? tiles_m - first_m : GM;
-    const int in_band = widx - band * GM * tiles_n;
-    const int tm = first_m + in_band % band_m;
-    int tn = in_band / band_m;
-    bool seg_f32 = false;
-    if (EPI == LVX_EPI_SEGMENTS) {
-        int sg = 0;
-        for (int i = 1; i < segs.n; ++i)
-            if (tn >= segs.s[i].tn_begin) sg = i;
-        tn -= segs.s[sg].tn_begin;
-        W = segs.s[sg].W;
-        C = reinterpret_cast<bf16_t *>(segs.s[sg].C);
-        ldc = segs.s[sg].ldc;
-        N = segs.s[sg].N;
-        seg_f32 = segs.s[sg].f32 != 0;
-    }
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int l16 = lane & 15, q4 = lane >> 4;
-    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-
-    uint32_t doff[QPW];
-#pragma unroll
-    for (int q = 0; q < QPW; ++q) {
-        const int row_s = 8 * (wave + NW * q) + (lane >> 3);
-        const int chunk = (lane & 7) ^ ((row_s >> 1) & 7);
-        if (q < A_Q) {
-            int r = tm * BM + row_s;
-            if (r > M - 1) r = M - 1;
-            doff[q] = (uint32_t)(((size_t)r * lda + chunk * 8) * sizeof(bf16_t));
-        } else {
-            int r = tn * BN + (row_s - BM);
-            if (r > N - 1) r = N - 1;
-            doff[q] = (uint32_t)(((size_t)r * ldw + chunk * 8) * sizeof(bf16_t));
-        }
-    }
-    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
-    const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds_base + wave * 1024);
-#define LVX_BIG_DMA(stage_, kt_, q_)                                                                                               \
-    lvx_dma16(reinterpret_cast<const char *>((q_) < A_Q ? (const void *)A : (const void *)W) + (size_t)(kt_) * ROW_B, doff[q_], \
-              lds_wave + (uint32_t)((stage_) * STAGE_B + (q_) * NW * 1024))
-
-    const int swz = (l16 >> 1) & 7;
-    const char *a_rd = lds + (wm * WTM + l16) * ROW_B;
-    const char *w_rd = lds + A_B + (wn * WTN + l16) * ROW_B;
-    bf16x8_t af[2][FM], wf[2][FN];
-#define LVX_BIG_READ_A(stage_, ks_, i0_, i1_)                                                                               \
-    {                                                                                                                       \
-        const int co_ = (((ks_) * 4 + q4) ^ swz) * 16 + (stage_) * STAGE_B;                                                 \
-        _Pragma("unroll") for (int i = i0_; i < i1_; ++i) af[(ks_) & 1][i] = *reinterpret_cast<const bf16x8_t *>(a_rd + i * 16 * ROW_B + co_); \
-    }
-#define LVX_BIG_READ_W(stage_, ks_, j0_, j1_)                                                                               \
-    {                                                                                                                       \
-        const int co_ = (((ks_) * 4 + q4) ^ swz) * 16 + (stage_) * STAGE_B;                                                 \
-        _Pragma("unroll") for (int j = j0_; j < j1_; ++j) wf[(ks_) & 1][j] = *reinterpret_cast<const bf16x8_t *>(w_rd + j * 16 * ROW_B + co_); \
-    }
-#define LVX_BIG_MFMAS(ks_, i0_, i1_)                                                                         \
-    _Pragma("unroll") for (int i = i0_; i < i1_; ++i) _Pragma("unroll") for (int j = 0; j < FN; ++j)         \
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[(ks_) & 1][i], wf[(ks_) & 1][j], acc[i][j], 0, 0, 0);
-
-    f32x4_t acc[FM][FN];
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
-
-    const int n_k = K / BK;
-    const int last = n_k - 1;
-#pragma unroll
-    for (int q = 0; q < QPW; ++q) LVX_BIG_DMA(0, 0, q);
-#pragma unroll
-    for (int q = 0; q < QPW; ++q) LVX_BIG_DMA(1, (last < 1 ? last : 1), q);
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(QPW) : "memory");
-    __syncthreads();
-    LVX_BIG_READ_A(0, 0, 0, FM);
-    LVX_BIG_READ_W(0, 0, 0, FN);
-
-    for (int t = 0; t < n_k; ++t) {
-        const int cur = t & 1, nxt = cur ^ 1;
-        const int kt_load = t + 2 < last ? t + 2 : last;  // past the end: a harmless reload of the last slab
-        LVX_BIG_READ_W(cur, 1, 0, FN);
-        __builtin_amdgcn_sched_barrier(0);
-        LVX_BIG_MFMAS(0, 0, 2);
-        __builtin_amdgcn_sched_barrier(0);
-        LVX_BIG_READ_A(cur, 1, 0, FM);
-        __builtin_amdgcn_sched_barrier(0);
-        LVX_BIG_MFMAS(0, 2, 4);
-        __builtin_amdgcn_sched_barrier(0);
-        LVX_BIG_MFMAS(1, 0, 2);
-        __builtin_amdgcn_sched_barrier(0);
-        // this wave's part of slab t+1 has landed and every wave has read the last fragment of slab t: one barrier, then stage
-        // cur takes slab t+2 (a whole slab of MFMAs ahead of its use) and the first fragments of slab t+1 are read
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int q = 0; q < QPW; ++q) LVX_BIG_DMA(cur, kt_load, q);
-        LVX_BIG_READ_W(nxt, 0, 0, FN);
-        LVX_BIG_READ_A(nxt, 0, 0, FM);
-        __builtin_amdgcn_sched_barrier(0);
-        LVX_BIG_MFMAS(1, 2, 4);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-
-    const int m0 = tm * BM + wm * WTM + 4 * q4, n0 = tn * BN + wn * WTN + l16;
-    f32x4_t rres[FM][FN];
-    if (EPI == LVX_EPI_SEGMENTS) {
-        if (seg_f32)
-            lvx_gemm_epilogue<FM, FN, LVX_EPI_STORE_F32>(acc, rres, C, ldc, R, ldr, gate, M, N, m0, n0);
-        else
-            lvx_gemm_epilogue<FM, FN, LVX_EPI_STORE>(acc, rres, C, ldc, R, ldr, gate, M, N, m0, n0);
-    } else {
-        lvx_gemm_epilogue<FM, FN, EPI>(acc, rres, C, ldc, R, ldr, gate, M, N, m0, n0);
-    }
-#undef LVX_BIG_DMA
-#undef LVX_BIG_READ_A
-#undef LVX_BIG_READ_W
-#undef LVX_BIG_MFMAS
-}
-
-lvx_status_t launch_big(const bf16_t *A, int64_t lda, const bf16_t *W, int64_t ldw, bf16_t *C, int64_t ldc, int M, int N, int K, int epi,
-                        hipStream_t stream, const lvx_gemm_segs_t *seg_table = nullptr) {
-    constexpr int BM = 256, BN = 256;
-    lvx_gemm_segs_t segs;
-    segs.n = 0;
-    int tiles_n = (N + BN - 1) / BN;
-    if (seg_table != nullptr) {
-        segs = *seg_table;
-        tiles_n = 0;
-        for (int i = 0; i < segs.n; ++i) {
-            segs.s[i].tn_begin = tiles_n;
-            tiles_n += (segs.s[i].N + BN - 1) / BN;
-        }
-    }
-    const int tiles_m = (M + BM - 1) / BM;
-    const int total = tiles_m * tiles_n;
-    const int per_xcd = (total + 7) / 8;
-    const dim3 grid(per_xcd * 8), block(512);
-#define LVX_BIG_LAUNCH(EPI_)                                                                                                        \
-    hipLaunchKernelGGL((lvx_gemm_big_kernel<EPI_>), grid, block, 0, stream, A, lda, W, ldw, C, ldc, M, N, K, (const bf16_t *)nullptr, \
-                       (int64_t)0, (const float *)nullptr, tiles_m, tiles_n, per_xcd, segs)
-    if (epi == LVX_EPI_STORE) {
-        LVX_BIG_LAUNCH(LVX_EPI_STORE);
-    } else if (epi == LVX_EPI_GELU_TANH) {
-        LVX_BIG_LAUNCH(LVX_EPI_GELU_TANH);
-    } else if (epi == LVX_EPI_SEGMENTS) {
-        LVX_BIG_LAUNCH(LVX_EPI_SEGMENTS);
-    } else {
-        return lvx_fail(LVX_ERR_UNSUPPORTED, "256 x 256 tiles: epilogue %d not built", epi);
-    }
-#undef LVX_BIG_LAUNCH
-    LVX_CHECK_HIP(hipGetLastError());
-    return LVX_OK;
-}
-#endif  // LVX_GEMM_BIG
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool CONV = false>
 lvx_status_t launch(const bf16_t *A, int64_t lda, const bf16_t *W, int64_t ldw, bf16_t *C, int64_t ldc, int M, int N, int K, int epi,
@@ -520,6 +252,7 @@ lvx_status_t launch(const bf16_t *A, int64_t lda, const bf16_t *W, int64_t ldw, 
     if (conv != nullptr) cm = *conv;
     lvx_gemm_segs_t segs;
     segs.n = 0;
+    segs.order = 0;
     int tiles_n = (N + BN - 1) / BN;
     if (seg_table != nullptr) {  // column tiles of all segments, one after the other
         segs = *seg_table;
@@ -531,11 +264,7 @@ lvx_status_t launch(const bf16_t *A, int64_t lda, const bf16_t *W, int64_t ldw, 
     }
     const int tiles_m = (M + BM - 1) / BM;
     const int total = tiles_m * tiles_n;
-#ifdef LVX_GEMM_NPART
-    const int per_xcd = tiles_m * ((tiles_n + 7) / 8);
-#else
     const int per_xcd = (total + 7) / 8;
-#endif
     const dim3 grid(per_xcd * 8), block(64 * WAVES_M * WAVES_N);
 #define LVX_GEMM_LAUNCH(EPI_)                                                                                                      \
     hipLaunchKernelGGL((lvx_gemm_dma_kernel<BM, BN, WAVES_M, WAVES_N, EPI_, CONV>), grid, block, 0, stream, A, lda, W, ldw, C, ldc, M, N, K, \
@@ -560,6 +289,23 @@ lvx_status_t launch(const bf16_t *A, int64_t lda, const bf16_t *W, int64_t ldw, 
 #undef LVX_GEMM_LAUNCH
     LVX_CHECK_HIP(hipGetLastError());
     return LVX_OK;
+}
+
+// The linears: the 128 x 256 kernel, or a small tile where that one would leave compute units idle.
+lvx_status_t launch_linear(const bf16_t *A, int64_t lda, const bf16_t *W, int64_t ldw, bf16_t *C, int64_t ldc, int M, int N, int K, int epi,
+                           const bf16_t *R, int64_t ldr, const float *gate, hipStream_t stream, const lvx_gemm_segs_t *segs = nullptr) {
+    const int tile = lvx_gemm_pick_small(segs, M, N, K / BK);
+    if (tile < 0) return launch<128, 256, 2, 4>(A, lda, W, ldw, C, ldc, M, N, K, epi, R, ldr, gate, stream, segs);
+    lvx_gemm_args_t p = {};
+    p.A = (const char *)A, p.lda = lda * 2;
+    p.W = (const char *)W, p.ldw = ldw * 2;
+    p.C = C, p.ldc = ldc;
+    p.R = R, p.ldr = ldr;
+    p.gate = gate;
+    p.M = M, p.N = N, p.n_slabs = K / BK;
+    p.epi = epi;
+    if (segs != nullptr) p.segs = *segs;
+    return lvx_gemm_launch_small<false>(tile, p, stream);
 }
 
 }  // namespace
@@ -588,9 +334,10 @@ lvx_status_t lvx_launch_linear_dual(const bf16_t *A, int64_t lda, const bf16_t *
     if (M == 0) return LVX_OK;
     lvx_gemm_segs_t segs;
     segs.n = 2;
+    segs.order = LVX_GEMM_ORDER_FIRST;
     segs.s[0] = {W1, C1, ldc1, N1, 0, c1_is_f32 ? 1 : 0, 0};
     segs.s[1] = {W2, C2, ldc2, N2, 0, 0, 0};
-    return launch<128, 256, 2, 4>(A, lda, W1, ldw, (bf16_t *)C1, ldc1, M, N1, K, (int)LVX_EPI_SEGMENTS, nullptr, 0, nullptr, stream, &segs);
+    return launch_linear(A, lda, W1, ldw, (bf16_t *)C1, ldc1, M, N1, K, (int)LVX_EPI_SEGMENTS, nullptr, 0, nullptr, stream, &segs);
 }
 
 // Up to LVX_GEMM_MAX_SEGS projections of the same activations in one launch (same K, same weight row stride; each with its own
@@ -600,12 +347,15 @@ lvx_status_t lvx_launch_linear_segments(const bf16_t *A, int64_t lda, int64_t ld
     for (int i = 0; i < segs.n; ++i)
         LVX_TRY(check_dual(A, lda, segs.s[i].W, segs.s[i].W, ldw, segs.s[i].C, segs.s[i].ldc, segs.s[i].C, segs.s[i].ldc, M, segs.s[i].N, segs.s[i].N, K));
     for (int i = 0; i < segs.n; ++i)
-        LVX_REQUIRE(segs.s[i].sumsq == nullptr || (segs.s[i].N % 256 == 0 && !segs.s[i].f32 && segs.s[i].ld_sumsq >= LVX_GEMM_SUMSQ_PARTS(segs.s[i].N)),
-                    LVX_ERR_SHAPE, "linear segments: row sums of squares need a bf16 segment of N %% 256 == 0 and ld_sumsq >= N / 64");
+        LVX_REQUIRE(segs.s[i].sumsq == nullptr || (segs.s[i].N % 64 == 0 && !segs.s[i].f32 && segs.n == 1 &&
+                                                   segs.s[i].ld_sumsq >= lvx_gemm_sumsq_parts(M, segs.s[i].N, K)),
+                    LVX_ERR_SHAPE, "linear segments: row sums of squares need one bf16 segment of N %% 64 == 0 and room for its partial sums");
     if (M == 0) return LVX_OK;
-    return launch<128, 256, 2, 4>(A, lda, segs.s[0].W, ldw, (bf16_t *)segs.s[0].C, segs.s[0].ldc, M, segs.s[0].N, K, (int)LVX_EPI_SEGMENTS, nullptr, 0,
+    return launch_linear(A, lda, segs.s[0].W, ldw, (bf16_t *)segs.s[0].C, segs.s[0].ldc, M, segs.s[0].N, K, (int)LVX_EPI_SEGMENTS, nullptr, 0,
                                   nullptr, stream, &segs);
 }
+
+int lvx_gemm_sumsq_parts(int M, int N, int K) { return N / lvx_gemm_part_cols(lvx_gemm_pick_small(nullptr, M, N, K / BK)); }
 
 extern "C" lvx_status_t lvx_linear_dual(const void *dev_a, int64_t lda, const void *dev_w1, const void *dev_w2, int64_t ldw, void *dev_c1,
                                         int64_t ldc1, int32_t c1_is_f32, void *dev_c2, int64_t ldc2, int32_t M, int32_t N1, int32_t N2,
@@ -641,10 +391,6 @@ extern "C" lvx_status_t lvx_linear(const void *dev_a, int64_t lda, const void *d
         LVX_REQUIRE(ldr >= N, LVX_ERR_SHAPE, "bad residual leading dimension");
     }
     if (M == 0) return LVX_OK;
-#ifdef LVX_GEMM_BIG
-    if (epi == LVX_EPI_STORE || epi == LVX_EPI_GELU_TANH)
-        return launch_big((const bf16_t *)dev_a, lda, (const bf16_t *)dev_w, ldw, (bf16_t *)dev_c, ldc, M, N, K, (int)epi, (hipStream_t)stream);
-#endif
-    return launch<128, 256, 2, 4>((const bf16_t *)dev_a, lda, (const bf16_t *)dev_w, ldw, (bf16_t *)dev_c, ldc, M, N, K, (int)epi,
+    return launch_linear((const bf16_t *)dev_a, lda, (const bf16_t *)dev_w, ldw, (bf16_t *)dev_c, ldc, M, N, K, (int)epi,
                                   (const bf16_t *)dev_resid, ldr, dev_gate, (hipStream_t)stream);
 }

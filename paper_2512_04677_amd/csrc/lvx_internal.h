@@ -163,14 +163,19 @@ struct lvx_gemm_seg_t {
     void *C;
     int64_t ldc;
     int32_t N, tn_begin, f32, ld_sumsq;
-    // NULL, or [M][ld_sumsq] floats: besides the bf16 store, every wave leaves the sum of squares of its 64 columns (taken on the
-    // fp32 accumulators) of each of its rows at column index (column tile within the segment) * 4 + (wave column): the partial
-    // sums of a row's RMS, added up in a fixed order by the consumer (no atomics: results stay bit-reproducible).  N % 256 == 0.
+    // NULL, or [M][ld_sumsq] floats: besides the bf16 store, the kernel leaves for each row the sums of squares (taken on the fp32
+    // accumulators) of lvx_gemm_sumsq_parts(M, N, K) equal groups of columns: the partial sums of a row's RMS, added up in a fixed
+    // order by the consumer (no atomics: results stay bit-reproducible).  One segment only, N % 64 == 0.
     float *sumsq;
 };
-#define LVX_GEMM_SUMSQ_PARTS(N_) ((N_) / 64)
+#define LVX_GEMM_MAX_SUMSQ_PARTS(N_) ((N_) / 16)
+int lvx_gemm_sumsq_parts(int M, int N, int K);  // how many groups: the chosen tile's (N / 16 at most)
+// Who decides how many K groups a launch sums in (its order of summation): the first product as if it were launched alone (its bits
+// then do not depend on its company), the launch as a whole (products that are only ever launched together), or nobody: one
+// group (products launched with more or fewer others, like the context's projections of a group of layers).
+enum { LVX_GEMM_ORDER_FIRST = 0, LVX_GEMM_ORDER_LAUNCH = 1, LVX_GEMM_ORDER_ONE = 2 };
 struct lvx_gemm_segs_t {
-    int32_t n, pad;
+    int32_t n, order;
     lvx_gemm_seg_t s[LVX_GEMM_MAX_SEGS];
 };
 lvx_status_t lvx_launch_linear_segments(const bf16_t *A, int64_t lda, int64_t ldw, const lvx_gemm_segs_t &segs, int M, int K, hipStream_t stream);

@@ -1,0 +1,59 @@
+"""The GEMM's tile shapes against the fp64 oracle at the sizes where each can go wrong: one row / column less and more than a
+tile, a contraction of a single slab, slab counts that do not divide over the K groups or the stages in flight."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import lvx_synth as S
+from oracle import lvx_oracle as O
+from test_gpu_parity import DEV, assert_close
+
+pytestmark = pytest.mark.gpu
+
+# M x N x K with the tile the launcher's rule picks for it (rows x columns, K groups)
+SHAPES = [(31, 24, 192), (33, 136, 320), (65, 1920, 448),                                 # 32 x 32, four groups
+          (64, 5760, 128), (63, 7000, 320), (95, 5000, 1088),                             # 32 x 64, two groups
+          (1, 8, 64), (64, 2560, 64), (250, 2568, 192), (257, 2560, 704),                 # 64 x 64
+          (600, 2560, 64), (577, 2696, 576), (1151, 1544, 832),                           # 64 x 128
+          (1170, 4616, 192), (1901, 2568, 128)]                                           # 128 x 256
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_linear_tile_edges(lvx, M, N, K):
+    a = S.randn_bf16((M, K + 8), S.seed_of("gt_a", M, K), device=DEV)[:, :K]
+    w = S.randn_bf16((N, K + 64), S.seed_of("gt_w", N, K), 1.0 / math.sqrt(K), device=DEV)[:, :K]
+    g = S.randn_f32((N,), 7, 0.5, 1.0, device=DEV)
+    r = S.randn_f32((M, N), S.seed_of("gt_r", M, N), device=DEV)
+    ref = O.linear(S.to_f64(a), S.to_f64(w))
+    out = torch.full((M, N + 8), 7.0, dtype=torch.bfloat16, device=DEV)
+    lvx.lvx_linear(a, w, out[:, :N], lvx.EPI_STORE)
+    gelu = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
+    lvx.lvx_linear(a, w, gelu, lvx.EPI_GELU_TANH)
+    x = r.clone()
+    lvx.lvx_linear(a, w, x, lvx.EPI_RESID_GATE_F32, resid=x, gate=g)       # in place on the fp32 stream
+    f32 = torch.full((M, N + 8), 7.0, dtype=torch.float32, device=DEV)
+    lvx.lvx_linear(a, w, f32[:, :N], lvx.EPI_STORE_F32)
+    torch.cuda.synchronize()
+    assert_close(out[:, :N], ref, "store %dx%dx%d" % (M, N, K))
+    assert_close(gelu, O.gelu_tanh(ref), "gelu")
+    assert bool((out[:, N:] == 7.0).all()) and bool((f32[:, N:] == 7.0).all())
+    # fp32 accumulation of K products of size 1/sqrt(K): at most K roundings of 2^-24 of a partial sum of size about 1 each
+    bound = 4.0 * K * 2.0 ** -24 + 1e-6
+    assert np.abs(S.to_f64(f32[:, :N]) - ref).max() <= bound
+    assert np.abs(S.to_f64(x) - (S.to_f64(r) + S.to_f64(g) * ref)).max() <= 4.0 * bound
+
+
+@pytest.mark.parametrize("M,N1,N2,K", [(40, 512, 512, 512), (33, 520, 264, 320), (390, 1536, 512, 512)])
+def test_product_bits_do_not_depend_on_its_company(lvx, M, N1, N2, K):
+    """A projection launched with another one of the same input sums in the same order as alone."""
+    a = S.randn_bf16((M, K), S.seed_of("co_a", M, K), device=DEV)
+    w = S.randn_bf16((N1 + N2, K), S.seed_of("co_w", N1, N2, K), 1.0 / math.sqrt(K), device=DEV)
+    c1 = torch.empty((M, N1), dtype=torch.float32, device=DEV)
+    c2 = torch.empty((M, N2), dtype=torch.bfloat16, device=DEV)
+    alone = torch.empty_like(c1)
+    lvx.lvx_linear_dual(a, w[:N1], w[N1:], c1, c2)
+    lvx.lvx_linear(a, w[:N1], alone, lvx.EPI_STORE_F32)
+    torch.cuda.synchronize()
+    assert torch.equal(c1, alone)
