@@ -8,11 +8,12 @@
 // The two scale factors and the product x * (448/amax) are formed in fp32: that product is what decides the 8-bit code.
 // gfx950 converts to and multiplies the OCP form of E4M3 (bias 7, largest finite value 448, no infinities).
 //
-// The GEMM is the direct-to-LDS design of the bf16 kernel with one-byte elements: a 128 x 256 tile, 8 waves of 64 x 64,
+// Products that would not fill the chip with 128 x 256 tiles run on the small tiles of lvx_gemm_core.h.
+// The GEMM here is the direct-to-LDS design of the bf16 kernel with one-byte elements: a 128 x 256 tile, 8 waves of 64 x 64,
 // K walked in slabs of 128 elements (again 128-byte LDS rows, XOR-swizzled, three 48 KB stages), and
 // v_mfma_f32_32x32x64_f8f6f4 (64 clocks for 131072 flop: twice the bf16 rate; the older 32x32x16 fp8 form runs at the bf16
 // rate on this chip).  A fragment is 32 bytes per lane: row l%32, k = 32*(l/32) .. +31 of the 64-wide k-step.
-#include "lvx_internal.h"
+#include "lvx_gemm_core.h"
 
 #include <mutex>
 
@@ -46,8 +47,6 @@ lvx_status_t static_scratch(uint32_t **out) {
     *out = g_scratch_ptr[dev];
     return LVX_OK;
 }
-
-typedef __attribute__((__vector_size__(8 * sizeof(int)))) int i32x8_t;
 
 // ---- quantisation ---------------------------------------------------------------------------------------------------
 // amax_slots: LVX_AMAX_SLOTS fp32 bit patterns whose maximum is max|x| (non-negative floats order like their bit patterns),
@@ -398,6 +397,20 @@ lvx_status_t lvx_launch_linear_fp8(const void *dev_aq, int64_t lda, const float 
         LVX_REQUIRE(ldr >= N, LVX_ERR_SHAPE, "bad residual leading dimension");
     }
     if (M == 0) return LVX_OK;
+    const int tile = lvx_gemm_pick_small(nullptr, M, N, K / 128);
+    if (tile >= 0) {  // a small tile where the 128 x 256 one would leave compute units idle
+        lvx_gemm_args_t p = {};
+        p.A = (const char *)dev_aq, p.lda = lda;
+        p.W = (const char *)dev_wq, p.ldw = ldw;
+        p.C = dev_c, p.ldc = ldc;
+        p.R = dev_resid, p.ldr = ldr;
+        p.gate = dev_gate;
+        p.scale_a = dev_scale_a, p.scale_w = dev_scale_w;
+        p.amax = amax_slots;
+        p.M = M, p.N = N, p.n_slabs = K / 128;
+        p.epi = (int)epi;
+        return lvx_gemm_launch_small<true>(tile, p, stream);
+    }
     constexpr int BM = 128, BN = 256;
     const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
     const int total = tiles_m * tiles_n;

@@ -57,3 +57,29 @@ def test_product_bits_do_not_depend_on_its_company(lvx, M, N1, N2, K):
     lvx.lvx_linear(a, w[:N1], alone, lvx.EPI_STORE_F32)
     torch.cuda.synchronize()
     assert torch.equal(c1, alone)
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 8, 128), (33, 136, 640), (65, 1920, 896), (64, 5760, 256), (95, 5000, 1152), (257, 2560, 1408),
+                                   (600, 2560, 128), (1151, 1544, 1664)])
+def test_linear_fp8_tile_edges(lvx, M, N, K):
+    """FP8 codes are exact inputs: the product of the decoded values, scaled, is what every tile has to give."""
+    aq, sa = lvx.lvx_fp8_quantize(S.randn_bf16((M, K), S.seed_of("g8_a", M, K), device=DEV), row_pad=16)
+    wq, sw = lvx.lvx_fp8_quantize(S.randn_bf16((N, K), S.seed_of("g8_w", N, K), 1.0 / math.sqrt(K), device=DEV), row_pad=128)
+    g = S.randn_f32((N,), 7, 0.5, 1.0, device=DEV)
+    r = S.randn_f32((M, N), S.seed_of("g8_r", M, N), device=DEV)
+    dec = [S.to_f64(q.contiguous().view(torch.float8_e4m3fn).float()) * float(s.item()) for q, s in ((aq, sa), (wq, sw))]
+    ref = O.linear(dec[0], dec[1])
+    out = torch.full((M, N + 8), 7.0, dtype=torch.bfloat16, device=DEV)
+    lvx.lvx_linear_fp8(aq, sa, wq, sw, out[:, :N], lvx.EPI_STORE)
+    gelu = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
+    lvx.lvx_linear_fp8(aq, sa, wq, sw, gelu, lvx.EPI_GELU_TANH)
+    x = r.clone()
+    lvx.lvx_linear_fp8(aq, sa, wq, sw, x, lvx.EPI_RESID_GATE_F32, resid=x, gate=g)
+    torch.cuda.synchronize()
+    assert_close(out[:, :N], ref, "fp8 store %dx%dx%d" % (M, N, K))
+    assert_close(gelu, O.gelu_tanh(ref), "fp8 gelu")
+    assert bool((out[:, N:] == 7.0).all())
+    # the matrix core aligns the FP8 products it adds up to the largest of them, so a sum of products of size 1 / sqrt(K) each,
+    # up to 448 * 448 quantisation steps wide, carries errors up to about 1e-4 (measured 6e-5 .. 1.9e-4 at a gate of 1, the same
+    # for both shapes of the instruction); bound as for the FP8 linear of test_gpu_fp8.py
+    assert np.abs(S.to_f64(x) - (S.to_f64(r) + S.to_f64(g) * ref)).max() <= 1e-4 * math.sqrt(K)
