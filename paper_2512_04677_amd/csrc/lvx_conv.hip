@@ -4,7 +4,7 @@
 //
 // State of one layer = a zero-padded channels-last volume P[max_frames + 2][H + 2][W + 2][C_in] in caller-owned device memory:
 // frames 0 and 1 are the feature cache (zeros before the first frame), frames 2.. receive the new input frames, the one-pixel
-// border stays zero (spatial padding).  A step copies the cache forward, scatters the new frames into the interior and runs
+// border stays zero (spatial padding).  A step moves the cache forward and the new frames into the interior in one pass and runs
 // one implicit GEMM on the matrix cores: rows = output pixels, K = 27 taps x C_in channels read straight from P by the GEMM's
 // direct-to-LDS loads (a tap is a constant shift in P), columns = C_out.  No im2col buffer is ever written.
 #include "lvx_internal.h"
@@ -20,19 +20,27 @@ struct lvx_causal_conv {
 
 namespace {
 
-// interior copy: x [n_frames][H][W][C] -> P[2 + f][1 + y][1 + x][:]
-__global__ void __launch_bounds__(256) lvx_conv_scatter_kernel(const bf16_t *__restrict__ x, bf16_t *__restrict__ vol, int n_frames, int H,
+// One step's data movement.  A thread owns one 16-byte chunk of one interior pixel through all frames: it moves the two most recent
+// frames of the previous step to the front (read before anything is written: the frames overlap when that step had a single
+// one; last_frames = 0: the history is already in place) and puts the new frames behind them: x [n_frames][H][W][c] ->
+// P[2 + f][1 + y][1 + x][:].  The zero border is never written.  Bound by launches for
+// one small frame and by memory for several large ones; one launch instead of three took 5 us off a 100 x 180 x 384, four-frame step of
+// 545 us.
+__global__ void __launch_bounds__(256) lvx_conv_advance_kernel(const bf16_t *__restrict__ x, bf16_t *vol, int n_frames, int last_frames, int n_pixels,
                                                                int W, int chunks_per_pixel, int64_t frame_elems, int row_pitch) {
-    const size_t total = (size_t)n_frames * H * W * chunks_per_pixel;
-    const int C = chunks_per_pixel * 8;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256) {
-        const size_t pix = i / chunks_per_pixel;
-        const int c = (int)(i % chunks_per_pixel);
-        const int xw = (int)(pix % W);
-        const int y = (int)((pix / W) % H);
-        const int f = (int)(pix / ((size_t)W * H));
-        const uint4 v = reinterpret_cast<const uint4 *>(x + pix * C)[c];
-        reinterpret_cast<uint4 *>(vol + (size_t)(f + 2) * frame_elems + (size_t)(y + 1) * row_pitch + (size_t)(xw + 1) * C)[c] = v;
+    const size_t frame_chunks = (size_t)n_pixels * chunks_per_pixel;
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < frame_chunks; i += (size_t)gridDim.x * 256) {
+        const int pix = (int)(i / chunks_per_pixel), c = (int)(i % chunks_per_pixel);
+        const int y = pix / W, xw = pix - y * W;
+        bf16_t *at = vol + (size_t)(y + 1) * row_pitch + (size_t)((xw + 1) * chunks_per_pixel + c) * 8;
+        if (last_frames > 0) {
+            const uint4 h0 = *reinterpret_cast<const uint4 *>(at + (size_t)last_frames * frame_elems);
+            const uint4 h1 = *reinterpret_cast<const uint4 *>(at + (size_t)(last_frames + 1) * frame_elems);
+            *reinterpret_cast<uint4 *>(at) = h0;
+            *reinterpret_cast<uint4 *>(at + frame_elems) = h1;
+        }
+        for (int f = 0; f < n_frames; ++f)
+            *reinterpret_cast<uint4 *>(at + (size_t)(f + 2) * frame_elems) = reinterpret_cast<const uint4 *>(x)[f * frame_chunks + i];
     }
 }
 
@@ -112,17 +120,9 @@ extern "C" lvx_status_t lvx_causal_conv_step(lvx_causal_conv_t *c, const void *d
     LVX_REQUIRE(act == 0 || act == 1, LVX_ERR_INVALID_ARG, "act %d must be 0 (none) or 1 (SiLU)", act);
     hipStream_t st = (hipStream_t)stream;
     const int row_pitch = (d.width + 2) * d.c_in;
-    // the two most recent input frames of the previous step become frames 0 and 1 (frame by frame, oldest first: the ranges
-    // overlap when the previous step had a single frame)
-    if (c->last_frames > 0) {
-        const int lf = c->last_frames;
-        for (int j = 0; j < 2; ++j)
-            LVX_TRY(lvx_launch_copy_rows(c->vol + (size_t)(lf + j) * c->frame_elems, c->frame_elems, c->vol + (size_t)j * c->frame_elems,
-                                         c->frame_elems, 1, (int)c->frame_elems, st));
-    }
-    const size_t chunks = (size_t)n_frames * d.height * d.width * (d.c_in / 8);
-    hipLaunchKernelGGL(lvx_conv_scatter_kernel, dim3(grid_for(chunks)), dim3(256), 0, st, (const bf16_t *)dev_x, c->vol, n_frames, d.height,
-                       d.width, d.c_in / 8, c->frame_elems, row_pitch);
+    const int n_pixels = d.height * d.width;
+    hipLaunchKernelGGL(lvx_conv_advance_kernel, dim3(grid_for((size_t)n_pixels * (d.c_in / 8))), dim3(256), 0, st, (const bf16_t *)dev_x, c->vol, n_frames,
+                       c->last_frames, n_pixels, d.width, d.c_in / 8, c->frame_elems, row_pitch);
     LVX_CHECK_HIP(hipGetLastError());
     lvx_conv_map_t cm;
     cm.enabled = 1;
@@ -132,8 +132,8 @@ extern "C" lvx_status_t lvx_causal_conv_step(lvx_causal_conv_t *c, const void *d
     cm.slabs_per_tap = d.c_in / 64;
     cm.row_pitch = row_pitch;
     cm.frame_pitch = (int32_t)c->frame_elems;
-    LVX_TRY(lvx_launch_conv_gemm(c->vol, cm, (const bf16_t *)dev_w, ldw, dev_bias, act, (bf16_t *)dev_y, d.c_out, n_frames * d.height * d.width,
-                                 d.c_out, st));
+    LVX_TRY(lvx_launch_conv_gemm(c->vol, cm, (const bf16_t *)dev_w, ldw, dev_bias, act, (bf16_t *)dev_y, d.c_out, n_frames * n_pixels,
+                                 d.max_frames * n_pixels, d.c_out, st));
     c->last_frames = n_frames;
     return LVX_OK;
 }

@@ -91,14 +91,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N)
         if (q < A_Q) {
             int r = tm * BM + row_s;
             if (r > M - 1) r = M - 1;
-            size_t e = (size_t)r * lda;
-            if (CONV) {  // output pixel r = (t, y, x) -> its position in the padded volume (tap (0,0,0))
-                const int hw = cm.H * cm.W;
-                const int t = r / hw, rem = r - t * hw;
-                const int y = rem / cm.W, x = rem - y * cm.W;
-                e = (size_t)t * cm.frame_pitch + (size_t)y * cm.row_pitch + (size_t)x * cm.C;
-            }
-            doff[q] = (uint32_t)((e + chunk * 8) * sizeof(bf16_t));
+            doff[q] = (uint32_t)((CONV ? lvx_conv_pixel_offset(cm, r) : (size_t)r * lda * sizeof(bf16_t)) + chunk * 16);
         } else {
             int r = tn * BN + (row_s - BM);
             if (r > N - 1) r = N - 1;
@@ -109,12 +102,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N)
     const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds_base + wave * 1024);
     // byte offset of K slab kt in the A operand: plain GEMM kt * 128; convolution: the tap's shift in the padded volume plus
     // the slab's channel offset inside the tap (wave-uniform scalar arithmetic)
-    auto a_slab = [&](int kt) -> size_t {
-        if (!CONV) return (size_t)kt * ROW_B;
-        const int tap = kt / cm.slabs_per_tap, kc = kt - tap * cm.slabs_per_tap;
-        const int dt = tap / 9, dy = (tap - dt * 9) / 3, dx = tap - dt * 9 - dy * 3;
-        return ((size_t)dt * cm.frame_pitch + (size_t)dy * cm.row_pitch + (size_t)dx * cm.C) * sizeof(bf16_t) + (size_t)kc * ROW_B;
-    };
+    auto a_slab = [&](int kt) -> size_t { return CONV ? lvx_conv_slab_offset(cm, kt) : (size_t)kt * ROW_B; };
 #define LVX_DMA_ISSUE(stage_, kt_, q_)                                                                                      \
     lvx_dma16((q_) < A_Q ? reinterpret_cast<const char *>(A) + a_off_ : reinterpret_cast<const char *>(W) + (size_t)(kt_) * ROW_B, \
               doff[q_], lds_wave + (uint32_t)((stage_) * STAGE_B + (q_) * NW * 1024))
@@ -364,13 +352,47 @@ extern "C" lvx_status_t lvx_linear_dual(const void *dev_a, int64_t lda, const vo
                                   (bf16_t *)dev_c2, ldc2, M, N1, N2, K, (hipStream_t)stream);
 }
 
+// The small tile of a convolution, or -1 for the 256 x 128 kernel: least rounds of the chip times slabs times time per slab, as for the
+// linears.  The number of K groups (the order of summation) follows from max_m, the pixels of the longest step the layer takes, so
+// that a pixel's bits do not depend on how many frames arrive with it.
+static int pick_conv_tile(int M, int max_m, int N, int n_slabs) {
+    int groups = 0, best = -1;
+    for (int pass = 0; pass < 2; ++pass) {
+        const int m = pass == 0 ? max_m : M;
+        auto rounds = [&](int bm, int bn) { return (double)(((long)((m + bm - 1) / bm) * ((N + bn - 1) / bn) + 255) / 256); };
+        double best_cost = groups <= 1 ? rounds(256, 128) * n_slabs * LVX_GEMM_SLAB_US_128X256 : 1e30;
+        int best_groups = 1;
+        best = -1;
+#define LVX_TILE_COST(ID_, BM_, BN_, WM_, WN_, NST_, KG_, PC_, US_)                   \
+    if (groups == 0 || KG_ == groups) {                                               \
+        const double c_ = rounds(BM_, BN_) * ((n_slabs + KG_ - 1) / KG_ * KG_) * US_; \
+        if (c_ < best_cost) best_cost = c_, best = ID_, best_groups = KG_;            \
+    }
+        LVX_GEMM_SMALL_TILES(LVX_TILE_COST)
+#undef LVX_TILE_COST
+        groups = best_groups;
+    }
+    return best;
+}
+
 // Implicit-GEMM 3x3x3 convolution: rows = output pixels, K = 27 taps x C channels gathered from the padded volume P.
-// 256 x 128 tiles (C_out is 128 ... 512 in the decoder this serves; 128-wide column tiles waste nothing there).
+// 256 x 128 tiles where they fill the chip (C_out is 128 ... 512 in the decoder this serves; 128-wide column tiles waste nothing
+// there), small tiles below that: one 50 x 90 frame, 384 -> 192 channels, is 36 large
+// tiles on 256 compute units, 213 of 64 x 64 (a whole step of it 119 -> 61 us, with the history's move fused: see lvx_conv.hip).
 lvx_status_t lvx_launch_conv_gemm(const bf16_t *P, const lvx_conv_map_t &cm, const bf16_t *Wt, int64_t ldw, const float *bias, int act,
-                                  bf16_t *Y, int64_t ldy, int M, int N, hipStream_t stream) {
-    const int K = 27 * cm.C;
-    return launch<256, 128, 4, 2, true>(P, 0, Wt, ldw, Y, ldy, M, N, K, act ? (int)LVX_EPI_BIAS_SILU : (int)LVX_EPI_BIAS, nullptr, 0, bias, stream,
-                                        nullptr, &cm);
+                                  bf16_t *Y, int64_t ldy, int M, int max_m, int N, hipStream_t stream) {
+    const int K = 27 * cm.C, epi = act ? (int)LVX_EPI_BIAS_SILU : (int)LVX_EPI_BIAS;
+    const int tile = pick_conv_tile(M, max_m, N, K / BK);
+    if (tile < 0) return launch<256, 128, 4, 2, true>(P, 0, Wt, ldw, Y, ldy, M, N, K, epi, nullptr, 0, bias, stream, nullptr, &cm);
+    lvx_gemm_args_t p = {};
+    p.A = (const char *)P;
+    p.W = (const char *)Wt, p.ldw = ldw * 2;
+    p.C = Y, p.ldc = ldy;
+    p.gate = bias;
+    p.M = M, p.N = N, p.n_slabs = K / BK;
+    p.epi = epi;
+    p.conv = cm;
+    return lvx_gemm_launch_small<false, true>(tile, p, stream);
 }
 
 extern "C" lvx_status_t lvx_linear(const void *dev_a, int64_t lda, const void *dev_w, int64_t ldw, void *dev_c, int64_t ldc, int32_t M,

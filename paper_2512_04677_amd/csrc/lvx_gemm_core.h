@@ -28,7 +28,22 @@ struct lvx_gemm_args_t {
     int32_t M, N, n_slabs, epi;
     int32_t tiles_m, tiles_n, per_xcd, group_m;
     lvx_gemm_segs_t segs;
+    lvx_conv_map_t conv;
 };
+
+// Convolution: byte offset in the padded volume of output pixel r's tap (0,0,0), and of K slab kt relative to it (the tap's shift
+// plus the slab's channel offset inside the tap: wave-uniform scalar arithmetic).
+__device__ __forceinline__ size_t lvx_conv_pixel_offset(const lvx_conv_map_t &cm, int r) {
+    const int hw = cm.H * cm.W;
+    const int t = r / hw, rem = r - t * hw;
+    const int y = rem / cm.W, x = rem - y * cm.W;
+    return ((size_t)t * cm.frame_pitch + (size_t)y * cm.row_pitch + (size_t)x * cm.C) * sizeof(bf16_t);
+}
+__device__ __forceinline__ size_t lvx_conv_slab_offset(const lvx_conv_map_t &cm, int kt) {
+    const int tap = kt / cm.slabs_per_tap, kc = kt - tap * cm.slabs_per_tap;
+    const int dt = tap / 9, dy = (tap - dt * 9) / 3, dx = tap - dt * 9 - dy * 3;
+    return ((size_t)dt * cm.frame_pitch + (size_t)dy * cm.row_pitch + (size_t)dx * cm.C) * sizeof(bf16_t) + (size_t)kc * 128;
+}
 
 // One MFMA operand fragment: the two 16-byte chunks of a lane's row.
 template <bool FP8>
@@ -208,7 +223,7 @@ __device__ __forceinline__ void lvx_amax_publish(uint32_t amax_b, uint32_t *slot
 // Measured (microseconds, weights read from HBM; before: the 128 x 256 kernel): 64 x 1920 x 6144 77 -> 16.5 (32 x 32, four
 // groups), 64 x 5760 x 1920 28 -> 10 (32 x 64, two groups), 256 x 2560 x 6912 95 -> 32 (64 x 64), 1170 x 1536 x 6144 69 -> 38
 // (64 x 128), the same shapes in FP8 40 -> 9.7, 16 -> 6.8, 50 -> 18, 38 -> 20.
-template <int BM, int BN, int WM, int WN, int NST, int KG, bool FP8>
+template <int BM, int BN, int WM, int WN, int NST, int KG, bool FP8, bool CONV>
 __global__ void __launch_bounds__(64 * WM * WN * KG) lvx_gemm_tile_kernel(const lvx_gemm_args_t p) {
     constexpr int NW = WM * WN, WTM = BM / WM, WTN = BN / WN, FM = WTM / 16, FN = WTN / 16;
     constexpr int STAGE_B = (BM + BN) * 128;
@@ -236,7 +251,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KG) lvx_gemm_tile_kernel(const 
         if (q < A_Q) {
             int r = tm * BM + row_s;
             if (r > M - 1) r = M - 1;
-            doff[q] = (uint32_t)((size_t)r * p.lda + chunk * 16);
+            doff[q] = (uint32_t)((CONV ? lvx_conv_pixel_offset(p.conv, r) : (size_t)r * p.lda) + chunk * 16);
         } else {
             int r = tn * BN + row_s - BM;
             if (r > N - 1) r = N - 1;
@@ -248,9 +263,10 @@ __global__ void __launch_bounds__(64 * WM * WN * KG) lvx_gemm_tile_kernel(const 
     auto issue = [&](int stage, int it) {  // the group's it-th slab; past the end: a harmless reload of the last slab
         int kt = it * KG + kg;
         kt = kt < last ? kt : last;
+        const size_t a_off = CONV ? lvx_conv_slab_offset(p.conv, kt) : (size_t)kt * 128;
 #pragma unroll
         for (int q = 0; q < QPW; ++q)
-            lvx_dma16((q < A_Q ? p.A : o.W) + (size_t)kt * 128, doff[q], ring_wave + (uint32_t)(stage * STAGE_B + q * NW * 1024));
+            lvx_dma16(q < A_Q ? p.A + a_off : o.W + (size_t)kt * 128, doff[q], ring_wave + (uint32_t)(stage * STAGE_B + q * NW * 1024));
     };
     const int swz = (l16 >> 1) & 7;
     const char *a_rd = ring + (wm * WTM + l16) * 128, *w_rd = ring + BM * 128 + (wn * WTN + l16) * 128;
@@ -394,7 +410,7 @@ static inline int lvx_gemm_part_cols(int tile) {
 }
 
 // Launch of small tile `tile` (arguments checked, p.M > 0, p.segs filled but for tn_begin).
-template <bool FP8>
+template <bool FP8, bool CONV = false>
 static lvx_status_t lvx_gemm_launch_small(int tile, lvx_gemm_args_t &p, hipStream_t stream) {
 #define LVX_TILE_LAUNCH(ID_, BM_, BN_, WM_, WN_, NST_, KG_, PC_, US_)                                                                  \
     case ID_: {                                                                                                                         \
@@ -403,7 +419,7 @@ static lvx_status_t lvx_gemm_launch_small(int tile, lvx_gemm_args_t &p, hipStrea
         for (int i = 0, t = 0; i < p.segs.n; ++i) p.segs.s[i].tn_begin = t, t += (p.segs.s[i].N + BN_ - 1) / BN_;                       \
         p.per_xcd = (p.tiles_m * p.tiles_n + 7) / 8;                                                                                    \
         p.group_m = 8;                                                                                                                  \
-        hipLaunchKernelGGL((lvx_gemm_tile_kernel<BM_, BN_, WM_, WN_, NST_, KG_, FP8>), dim3(p.per_xcd * 8), dim3(64 * WM_ * WN_ * KG_), 0, stream, p); \
+        hipLaunchKernelGGL((lvx_gemm_tile_kernel<BM_, BN_, WM_, WN_, NST_, KG_, FP8, CONV>), dim3(p.per_xcd * 8), dim3(64 * WM_ * WN_ * KG_), 0, stream, p); \
         break;                                                                                                                          \
     }
     switch (tile) { LVX_GEMM_SMALL_TILES(LVX_TILE_LAUNCH) }

@@ -151,7 +151,7 @@ struct lvx_conv_map_t {
     int32_t frame_pitch;       // elements between padded frames: (H + 2) * (W + 2) * C
 };
 lvx_status_t lvx_launch_conv_gemm(const bf16_t *P, const lvx_conv_map_t &cm, const bf16_t *Wt, int64_t ldw, const float *bias, int act,
-                                  bf16_t *Y, int64_t ldy, int M, int N, hipStream_t stream);
+                                  bf16_t *Y, int64_t ldy, int M, int max_m, int N, hipStream_t stream);
 // C1[M][N1] = A W1^T (bf16, or fp32 if c1_is_f32), C2[M][N2] = A W2^T (bf16) in one launch, plain store.
 lvx_status_t lvx_launch_linear_dual(const bf16_t *A, int64_t lda, const bf16_t *W1, const bf16_t *W2, int64_t ldw, void *C1, int64_t ldc1,
                                     int c1_is_f32, bf16_t *C2, int64_t ldc2, int M, int N1, int N2, int K, hipStream_t stream);

@@ -74,3 +74,28 @@ def test_linear_bias_and_silu_epilogues(lvx):
     lvx.lvx_linear(a, w, c, lvx.EPI_BIAS_SILU, gate=b)
     torch.cuda.synchronize()
     assert_close(c, O.silu(ref), "linear + bias + silu")
+
+
+@pytest.mark.parametrize("H,W,Ci,Co,frames", [
+    (7, 5, 64, 24, 3),          # 32 x 32 tiles, four K groups, 27 slabs
+    (31, 33, 64, 136, 2),       # 32 x 64, two groups, ragged rows and columns
+    (45, 45, 64, 136, 2),       # 64 x 64 (groups decided by the two-frame step)
+    (77, 79, 64, 136, 1),       # 64 x 128
+    (110, 111, 64, 136, 1),     # 256 x 128
+])
+def test_conv_tiles_and_chunking(lvx, H, W, Ci, Co, frames):
+    """Every tile the rule can pick, against the oracle; a frame's bits do not depend on how many frames arrive with it."""
+    x, w, b = conv_inputs("ct_%d_%d_%d_%d" % (H, W, Ci, Co), frames, H, W, Ci, Co, pad=8)
+    ref = O.causal_conv3d(S.to_f64(x), S.to_f64(w).reshape(Co, 3, 3, 3, Ci), S.to_f64(b))
+    conv = lvx.CausalConv(Ci, Co, H, W, frames, DEV)
+    y = torch.empty((frames, H, W, Co), dtype=torch.bfloat16, device=DEV)
+    conv.step(x, w, b, 0, y)
+    torch.cuda.synchronize()
+    assert_close(y, ref, "conv %dx%d C %d->%d, %d frames" % (H, W, Ci, Co, frames))
+    conv.reset()
+    one = torch.empty_like(y)
+    for t in range(frames):
+        conv.step(x[t:t + 1], w, b, 0, one[t:t + 1])
+    torch.cuda.synchronize()
+    assert torch.equal(one, y)
+    conv.close()
