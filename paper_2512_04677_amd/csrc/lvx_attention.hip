@@ -23,6 +23,9 @@
 //     taken after the first tile); the final division by the row sum absorbs whatever reference was used.
 //   * workgroup -> (head, query tile) mapping keeps all query tiles of a head on one XCD (hardware deals consecutive
 //     workgroup ids round-robin over the 8 XCDs), so a head's K/V stream is fetched into one L2 only.
+//   * KS = 2 (few queries: see split_keys): the halves of the workgroup, which run half a period apart anyway, take the same 128 queries
+//     and different key tiles instead of different queries and the same tiles; a stage then carries two tiles, one for each half,
+//     and the halves' outputs meet in LDS at the end.
 //   * template switches: TP = 64-key tiles per pipeline phase (2 from 1024 visible keys on: half the barriers, pipeline fills and
 //     drains per key); PRE = the queries arrive multiplied by scale * log2(e) and the score accumulators start at minus the
 //     softmax reference, so a score leaves the MFMA as the exponent (one FMA per score less; used inside a block, where the
@@ -37,12 +40,13 @@ constexpr int KT = LVX_KEY_TILE;
 // keys, equal at 1560, 3 to 4 % faster from 6240 keys on)
 constexpr int TP2_MIN_KEYS = 16 * KT;
 
-template <int D, int NWAVES, int QB = 2, int TP = 1, bool PRE = false, bool QN = false>
-__global__ void __launch_bounds__(64 * NWAVES) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <int D, int TP, bool PRE, bool QN, int KS>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
     lvx_attention_kernel(const bf16_t *__restrict__ q, int64_t ld_q, int n_q, const bf16_t *__restrict__ kp,
                          const bf16_t *__restrict__ vtp, int cap, int n_keys, float c_exp2, bf16_t *__restrict__ out,
                          int64_t ld_out, int n_qtiles, int total_wg, int per_xcd, uint32_t *amax_slots, lvx_attn_qnorm_t qn) {
-    constexpr int QT = 16 * QB * NWAVES;  // QB blocks of 16 queries per wave
+    constexpr int NWAVES = 8, QB = 2;     // QB blocks of 16 queries per wave
+    constexpr int QT = 16 * QB * NWAVES / KS;
     constexpr int MK = D / 32;  // MFMA k-steps (32 wide) over head_dim
     constexpr int DB = D / 16;  // 16-row blocks of O^T
     constexpr int NV = DB * 2;  // V^T fragments per 64-key tile (each feeds two PV MFMAs, one per 16-query block)
@@ -53,8 +57,9 @@ __global__ void __launch_bounds__(64 * NWAVES) __attribute__((amdgpu_waves_per_e
     // chunk c of row r is stored at position c ^ swz(r) instead (the lane fetches the matching global chunk), with
     // swz(r) = r & 15 for 256-byte rows and (r >> 1) & 7 for 128-byte rows: 16 consecutive rows then hit 16 distinct
     // 16-byte units of a 256-byte bank row.
-    constexpr int NS = NWAVES == 4 ? 2 : 4;  // two stages of TP tiles each (the 8-wave form keeps four slots at TP = 1 as well)
-    static_assert(NS >= 2 * TP && (TP == 1 || TP == 2), "two stages of TP tiles must fit the ring");
+    constexpr int TS = TP * KS;  // tiles per stage
+    constexpr int NS = 4;        // two stages of TS tiles each (the ring keeps four slots at TS = 1 as well)
+    static_assert((TP == 1 || TP == 2) && (KS == 1 || KS == 2) && NS >= 2 * TS, "two stages of TS tiles must fit the ring");
     constexpr int TILE_B = KT * D * 2;        // bytes per K tile = per V^T tile
     constexpr int K_ROW_B = D * 2;
     constexpr int K_RPI = 1024 / K_ROW_B;     // K rows per DMA instruction (4 or 8)
@@ -77,6 +82,9 @@ __global__ void __launch_bounds__(64 * NWAVES) __attribute__((amdgpu_waves_per_e
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, q4 = lane >> 4;
+    const int grp = wave / (NWAVES / 2);                  // half of the workgroup, see "pipeline" below
+    const int qw = KS == 1 ? wave : wave % (NWAVES / 2);  // which 32 of the workgroup's queries
+    const int kg = KS == 1 ? 0 : grp;                     // KS = 2: which of a stage's two tiles
 
     // Q fragments (B operand of S^T = K Q^T, v_mfma_f32_16x16x32_bf16): for query block qb, lane (l16, q4) holds
     // Q[query 16qb + l16][d = 32m + 8q4 .. +7]
@@ -86,7 +94,7 @@ __global__ void __launch_bounds__(64 * NWAVES) __attribute__((amdgpu_waves_per_e
         // lane L adds one half (L & 1) of the partial sums of query row L / 2 of this wave: contiguous 16-byte loads, sixteen issued
         // before the first add, in a fixed order (the result is bit-reproducible); the two halves meet through one shuffle.  Rows
         // are padded to whole float4 per half; what lies past n_parts is not counted.
-        int r = qtile * QT + wave * 32 + (lane >> 1);
+        int r = qtile * QT + qw * 32 + (lane >> 1);
         if (r > n_q - 1) r = n_q - 1;
         const int per4 = (qn.n_parts + 7) / 8;  // float4 loads per lane
         const int left = qn.n_parts - (lane & 1) * per4 * 4;
@@ -105,7 +113,7 @@ __global__ void __launch_bounds__(64 * NWAVES) __attribute__((amdgpu_waves_per_e
     }
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-        int row = qtile * QT + wave * (16 * QB) + 16 * qb + l16;
+        int row = qtile * QT + qw * (16 * QB) + 16 * qb + l16;
         if (row > n_q - 1) row = n_q - 1;
         const bf16_t *qp = q + (size_t)row * ld_q + (size_t)head * D + q4 * 8;
 #pragma unroll
@@ -114,7 +122,7 @@ __global__ void __launch_bounds__(64 * NWAVES) __attribute__((amdgpu_waves_per_e
             // RMSNorm of the query row over all d_model channels, its gain and the logit scale, applied in fp32 to the bf16
             // projection output and rounded once.  ss_row (computed once per wave, above) holds the sum of squares of query
             // row lane / 2 of this wave in every lane.
-            static_assert(!QN || (PRE && QB == 2), "normalised queries are also pre-scaled; 32 query rows per wave");
+            static_assert(!QN || PRE, "normalised queries are also pre-scaled");
             const float ss = __shfl(ss_row, 2 * (16 * qb + l16));
             const float rinv = c_exp2 / sqrtf(ss / (float)qn.d_model + qn.eps);
             const float *gp = qn.gain + head * D + q4 * 8;
@@ -132,7 +140,8 @@ __global__ void __launch_bounds__(64 * NWAVES) __attribute__((amdgpu_waves_per_e
     }
 
     const int n_tiles = (n_keys + KT - 1) / KT;
-    const int n_ph = (n_tiles + TP - 1) / TP;  // phases: TP consecutive tiles each
+    const int n_ph = (n_tiles + TS - 1) / TS;                          // phases: TP consecutive tiles for each key group
+    const int n_mine = KS == 1 ? n_ph : (n_tiles + KS - 1 - kg) / KS;  // phases in which this wave's key group has a tile
     const char *k_src = reinterpret_cast<const char *>(kp + (size_t)head * cap * D);   // K tile t at k_src + t * TILE_B
     const char *v_src = reinterpret_cast<const char *>(vtp + (size_t)head * cap * D);  // V^T tile t at v_src + t * TILE_B
 
@@ -175,12 +184,12 @@ __global__ void __launch_bounds__(64 * NWAVES) __attribute__((amdgpu_waves_per_e
         _Pragma("unroll") for (int e = 0; e < DPW; ++e)                                                                     \
             lvx_dma16(v_src + (size_t)tt_ * TILE_B, vdoff[e], vs_wave + (uint32_t)(((t_) & (NS - 1)) * TILE_B + e * NWAVES * 1024)); \
     }
-    // stage u = { V^T(TP u + i), K(TP (u+1) + i), i < TP }: what the matrix phase X(u) reads
+    // stage u = { V^T(TS u + i), K(TS (u+1) + i), i < TS }: what the matrix phase X(u) reads
 #define LVX_ATTN_STAGE_DMA(u_)                                   \
     {                                                            \
-        _Pragma("unroll") for (int i_ = 0; i_ < TP; ++i_) {      \
-            LVX_ATTN_DMA_V(TP * (u_) + i_);                      \
-            LVX_ATTN_DMA_K(TP * ((u_) + 1) + i_);                \
+        _Pragma("unroll") for (int i_ = 0; i_ < TS; ++i_) {      \
+            LVX_ATTN_DMA_V(TS * (u_) + i_);                      \
+            LVX_ATTN_DMA_K(TS * ((u_) + 1) + i_);                \
         }                                                        \
     }
 #define LVX_ATTN_WAIT_DMA(n_) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n_) : "memory")
@@ -208,7 +217,6 @@ __global__ void __launch_bounds__(64 * NWAVES) __attribute__((amdgpu_waves_per_e
     // iteration i, into the slots of stage i-2, whose last reader (group 1's X(i-2), second half of iteration i-1) ended at
     // the barrier just passed, and waits for its own part before the barrier that ends iteration i; stage i is first read
     // by group 0 in X(i), right after that barrier: a whole iteration of both groups' work covers the load.
-    const int grp = wave / (NWAVES / 2);
 
     // o[db][qb][e] = O^T[d = 16 db + 4 q4 + e][query 16 qb + l16];  s[kb][qb][e] = score of key row 4 q4 + e of block kb
     f32x4_t o[DB][QB];
@@ -238,7 +246,7 @@ __global__ void __launch_bounds__(64 * NWAVES) __attribute__((amdgpu_waves_per_e
             _Pragma("unroll") for (int qb = 0; qb < QB; ++qb) _Pragma("unroll") for (int e = 0; e < 4; ++e) s[kb][qb][e] = 0.f; \
             bf16x8_t a[MK];                                                                                    \
             _Pragma("unroll") for (int m = 0; m < MK; ++m)                                                     \
-                a[m] = *reinterpret_cast<const bf16x8_t *>(ks + (kb >> 2) * TILE_B + (kb & 3) * 16 * K_ROW_B + kfo[m]); \
+                a[m] = *reinterpret_cast<const bf16x8_t *>(ks + (kg + (kb >> 2)) * TILE_B + (kb & 3) * 16 * K_ROW_B + kfo[m]); \
             _Pragma("unroll") for (int m = 0; m < MK; ++m) _Pragma("unroll") for (int qb = 0; qb < QB; ++qb)   \
                 s[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], qf[qb][m], s[kb][qb], 0, 0, 0);      \
         }                                                                                                      \
@@ -259,8 +267,8 @@ __global__ void __launch_bounds__(64 * NWAVES) __attribute__((amdgpu_waves_per_e
         __builtin_amdgcn_s_setprio(2); /* the matrix phase wins instruction arbitration over the other wave's VALU */ \
         const char *vr[TP], *kr[TP];                                                                           \
         _Pragma("unroll") for (int i_ = 0; i_ < TP; ++i_) {                                                    \
-            vr[i_] = vs + ((TP * (j_) + i_) & (NS - 1)) * TILE_B;                                              \
-            kr[i_] = ks + ((TP * ((j_) + 1) + i_) & (NS - 1)) * TILE_B;                                        \
+            vr[i_] = vs + ((TS * (j_) + kg + i_) & (NS - 1)) * TILE_B;                                              \
+            kr[i_] = ks + ((TS * ((j_) + 1) + kg + i_) & (NS - 1)) * TILE_B;                                        \
         }                                                                                                      \
         bf16x8_t fr[PD];                                                                                       \
         _Pragma("unroll") for (int f = 0; f < PD; ++f) fr[f] = LVX_ATTN_FRAG(f);                               \
@@ -292,8 +300,8 @@ __global__ void __launch_bounds__(64 * NWAVES) __attribute__((amdgpu_waves_per_e
 #define LVX_ATTN_Y(t_)                                                                                         \
     {                                                                                                          \
         __builtin_amdgcn_s_setprio(0); /* the matrix phase's priority is kept through its DMA issue, up to here */ \
-        if ((t_) == n_ph - 1 && (n_keys % (TP * KT)) != 0) {                                                   \
-            int lim_ = n_keys - (t_) * (TP * KT) - 8 * q4; /* valid keys, counted from this lane group's first key */ \
+        if ((t_) == n_mine - 1 && (n_keys % (TP * KT)) != 0) {                                                 \
+            int lim_ = n_keys - ((t_) * TS + kg) * KT - 8 * q4; /* valid keys, counted from this lane group's first key */ \
             asm volatile("" : "+v"(lim_));          /* keep the compares out of the loop preheader */          \
             _Pragma("unroll") for (int kb = 0; kb < 4 * TP; ++kb) _Pragma("unroll") for (int e = 0; e < 4; ++e) \
                 if (32 * (kb >> 1) + 4 * (kb & 1) + e >= lim_) {                                               \
@@ -352,7 +360,7 @@ __global__ void __launch_bounds__(64 * NWAVES) __attribute__((amdgpu_waves_per_e
     }
 
 #pragma unroll
-    for (int i = 0; i < TP; ++i) LVX_ATTN_DMA_K(i);
+    for (int i = 0; i < TS; ++i) LVX_ATTN_DMA_K(i);
     LVX_ATTN_STAGE_DMA(0);
     LVX_ATTN_WAIT_DMA(0);
     __syncthreads();
@@ -362,7 +370,7 @@ __global__ void __launch_bounds__(64 * NWAVES) __attribute__((amdgpu_waves_per_e
     // A wave whose 32 queries all lie past n_q (ragged last query tile: 4680 = 18 x 256 + 72) only keeps up the DMA and
     // barrier protocol: no LDS reads, no MFMAs, no softmax.  Its SIMD partner then has the matrix core to itself, so such a
     // workgroup finishes early and frees its CU, and the padding costs no energy on a chip that is power-limited.
-    const bool active = __builtin_amdgcn_readfirstlane(qtile * QT + wave * (16 * QB)) < n_q;
+    const bool active = __builtin_amdgcn_readfirstlane(qtile * QT + qw * (16 * QB)) < n_q;
     if (!active) {
         __syncthreads();
         __syncthreads();
@@ -396,22 +404,54 @@ __global__ void __launch_bounds__(64 * NWAVES) __attribute__((amdgpu_waves_per_e
         __syncthreads();
         for (int i = 1; i <= n_ph; ++i) {
             if (i < n_ph) LVX_ATTN_STAGE_DMA(i);
-            LVX_ATTN_Y(i - 1);
+            if (KS == 1 || i <= n_mine) LVX_ATTN_Y(i - 1);
             __syncthreads();
-            LVX_ATTN_X(i - 1);
+            if (KS == 1 || i <= n_mine) LVX_ATTN_X(i - 1);
             if (i < n_ph) LVX_ATTN_WAIT_DMA(0);
             __syncthreads();
         }
     }
     LVX_ATTN_WAIT_DMA(0);  // no DMA may still be in flight when the workgroup releases its LDS
 
+    // KS = 2: the two waves that share 32 queries exchange halves through the rings' LDS: each hands over the query block the other
+    // finishes (group 0 block 0, group 1 block 1), as outputs in units of 2^-reference with the reference and the row sum beside them
+    float l_tot[QB];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        l_tot[qb] = l_run[qb] + __shfl_xor(l_run[qb], 16);
+        l_tot[qb] += __shfl_xor(l_tot[qb], 32);
+    }
+    if (KS == 2) {
+        static_assert(NWAVES / 2 * QB * DB * 1024 <= NS * TILE_B, "the exchanged outputs must fit the K ring");
+        if (n_mine == 0) mc[0] = mc[1] = -3.0e38f;  // a single tile: group 1 saw no key
+        float2 *stat = reinterpret_cast<float2 *>(vs);
+        __syncthreads();
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb)
+            if (qb != grp) {
+#pragma unroll
+                for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4_t *>(ks + (((qw * QB + qb) * DB + db) * 64 + lane) * 16) = o[db][qb];
+                stat[(qw * QB + qb) * 64 + lane] = make_float2(mc[qb], l_tot[qb]);
+            }
+        __syncthreads();
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb)
+            if (qb == grp) {
+                const float2 other = stat[(qw * QB + qb) * 64 + lane];
+                const float m = fmaxf(mc[qb], other.x), w_own = __builtin_amdgcn_exp2f(mc[qb] - m), w_other = __builtin_amdgcn_exp2f(other.x - m);
+                l_tot[qb] = l_tot[qb] * w_own + other.y * w_other;
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+                    o[db][qb] = o[db][qb] * w_own + *reinterpret_cast<const f32x4_t *>(ks + (((qw * QB + qb) * DB + db) * 64 + lane) * 16) * w_other;
+            }
+    }
+
     uint32_t amax_b = 0;  // largest magnitude among the bf16 values this lane stores (bit pattern without sign)
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-        float l_tot = l_run[qb] + __shfl_xor(l_run[qb], 16);
-        l_tot += __shfl_xor(l_tot, 32);
-        const float inv = 1.0f / l_tot;
-        const int row = qtile * QT + wave * (16 * QB) + 16 * qb + l16;
+        if (KS == 2 && qb != grp) continue;
+        const float inv = 1.0f / l_tot[qb];
+        const int row = qtile * QT + qw * (16 * QB) + 16 * qb + l16;
         if (row < n_q) {
             bf16_t *op = out + (size_t)row * ld_out + (size_t)head * D;
             // accumulator register e of block (db, qb) holds O^T[d = 16db + 4q4 + e][query 16qb + l16]
@@ -442,20 +482,36 @@ __global__ void __launch_bounds__(64 * NWAVES) __attribute__((amdgpu_waves_per_e
     }
 }
 
-template <int D, int NWAVES, int QB = 2, int TP = 1, bool PRE = false, bool QN = false>
+template <int D, int TP, bool PRE, bool QN, int KS>
 lvx_status_t launch(const bf16_t *q, int64_t ld_q, int n_q, int H, const bf16_t *kp, const bf16_t *vtp, int cap, int n_keys,
                     float scale, bf16_t *out, int64_t ld_out, hipStream_t stream, uint32_t *amax_slots, const lvx_attn_qnorm_t *qnorm = nullptr) {
-    constexpr int QT = 16 * QB * NWAVES;
+    constexpr int QT = 256 / KS;
     const int n_qtiles = (n_q + QT - 1) / QT;
     const int total = n_qtiles * H;
     const int per_xcd = (total + 7) / 8;
     const float c = scale * LVX_LOG2E;
     lvx_attn_qnorm_t qn = {};
     if (qnorm != nullptr) qn = *qnorm;
-    hipLaunchKernelGGL((lvx_attention_kernel<D, NWAVES, QB, TP, PRE, QN>), dim3(per_xcd * 8), dim3(64 * NWAVES), 0, stream, q, ld_q, n_q, kp, vtp, cap,
+    hipLaunchKernelGGL((lvx_attention_kernel<D, TP, PRE, QN, KS>), dim3(per_xcd * 8), dim3(512), 0, stream, q, ld_q, n_q, kp, vtp, cap,
                        n_keys, c, out, ld_out, n_qtiles, total, per_xcd, amax_slots, qn);
     LVX_CHECK_HIP(hipGetLastError());
     return LVX_OK;
+}
+
+// Whether a workgroup takes 128 queries and splits the keys over its halves (KS = 2) instead of 256 queries.  A round of the chip with
+// KS = 2 takes 0.62 to 0.66 of a round without (measured from 9 to 150 key tiles, head_dim 64 and 128: half the tiles per wave, but
+// twice the K / V stream per tile), so it pays where the smaller workgroups need less than half as many more rounds: always
+// while they fit one round, e.g. 12 heads x 1170 queries x 6240 keys 134 -> 90 us, but 20 x 1886 x 8487 (160 workgroups become 300)
+// 191 -> 236 us.  A last query tile of one or two waves' rows ends early and is not counted as a workgroup.  Up to 128 queries half
+// of the waves idle without the split; with less than 8 key tiles the exchange at the end then costs what it saves (9.3 against
+// 10.2 us at 4 tiles, 15.1 against 14.4 at 9).
+bool split_keys(int n_q, int H, int n_keys) {
+    if (n_q <= 128 && n_keys <= 7 * KT) return false;
+    auto rounds = [&](int qt) {
+        const long tiles = (n_q + qt - 1 - qt / 4) / qt;
+        return ((tiles > 0 ? tiles : 1) * H + 255) / 256;
+    };
+    return 0.65 * rounds(128) < rounds(256);
 }
 
 }  // namespace
@@ -466,31 +522,26 @@ lvx_status_t lvx_launch_attention(const bf16_t *q, int64_t ld_q, int n_q, int H,
     LVX_REQUIRE(n_q > 0 && n_keys > 0 && n_keys <= cap && cap % KT == 0, LVX_ERR_SHAPE, "attention: n_q %d, n_keys %d, cap %d", n_q,
                 n_keys, cap);
     LVX_REQUIRE(scale > 0.f, LVX_ERR_INVALID_ARG, "attention: scale must be positive");
-#ifdef LVX_ATTN_16W
-    if (D == 128) return launch<128, 16, 1>(q, ld_q, n_q, H, k_packed, vt_packed, cap, n_keys, scale, out, ld_out, stream, amax_slots);
-#endif
-#ifdef LVX_ATTN_2WG  // experiment: workgroups of 4 waves (128 queries, 64 KB of LDS), two of them per CU
-    if (D == 128) return launch<128, 4, 2, 1>(q, ld_q, n_q, H, k_packed, vt_packed, cap, n_keys, scale, out, ld_out, stream, amax_slots);
-#endif
+    LVX_REQUIRE(D == 64 || D == 128, LVX_ERR_UNSUPPORTED, "head_dim %d not supported (64 or 128)", D);
+    const bool two = split_keys(n_q, H, n_keys);
+#define LVX_ATTN_LAUNCH(D_, TP_, PRE_, QN_, KS_) \
+    launch<D_, TP_, PRE_, QN_, KS_>(q, ld_q, n_q, H, k_packed, vt_packed, cap, n_keys, scale, out, ld_out, stream, amax_slots, qnorm)
     if (qnorm != nullptr) {  // the kernel normalises and scales the queries as it loads them (cross-attention of a bf16 stage)
         LVX_REQUIRE(D == 128 && qnorm->sumsq != nullptr && qnorm->gain != nullptr && qnorm->n_parts > 0 &&
                         qnorm->ld >= (qnorm->n_parts + 7) / 8 * 8 && qnorm->ld % 4 == 0 && qnorm->d_model == H * D,
                     LVX_ERR_INVALID_ARG,
                     "attention: query norm needs head_dim 128, partial sums and a gain");
-        return launch<128, 8, 2, 1, true, true>(q, ld_q, n_q, H, k_packed, vt_packed, cap, n_keys, scale, out, ld_out, stream, amax_slots, qnorm);
+        return two ? LVX_ATTN_LAUNCH(128, 1, true, true, 2) : LVX_ATTN_LAUNCH(128, 1, true, true, 1);
     }
     if (q_prescaled) {  // q already carries scale * log2(e): see PRE in the kernel
-        if (D == 128 && n_keys >= TP2_MIN_KEYS)
-            return launch<128, 8, 2, 2, true>(q, ld_q, n_q, H, k_packed, vt_packed, cap, n_keys, scale, out, ld_out, stream, amax_slots);
-        if (D == 128) return launch<128, 8, 2, 1, true>(q, ld_q, n_q, H, k_packed, vt_packed, cap, n_keys, scale, out, ld_out, stream, amax_slots);
-        if (D == 64) return launch<64, 8, 2, 1, true>(q, ld_q, n_q, H, k_packed, vt_packed, cap, n_keys, scale, out, ld_out, stream, amax_slots);
-        return lvx_fail(LVX_ERR_UNSUPPORTED, "head_dim %d not supported (64 or 128)", D);
+        if (D == 64) return two ? LVX_ATTN_LAUNCH(64, 1, true, false, 2) : LVX_ATTN_LAUNCH(64, 1, true, false, 1);
+        if (two) return LVX_ATTN_LAUNCH(128, 1, true, false, 2);
+        return n_keys >= TP2_MIN_KEYS ? LVX_ATTN_LAUNCH(128, 2, true, false, 1) : LVX_ATTN_LAUNCH(128, 1, true, false, 1);
     }
-    if (D == 128 && n_keys >= TP2_MIN_KEYS)
-        return launch<128, 8, 2, 2>(q, ld_q, n_q, H, k_packed, vt_packed, cap, n_keys, scale, out, ld_out, stream, amax_slots);
-    if (D == 128) return launch<128, 8>(q, ld_q, n_q, H, k_packed, vt_packed, cap, n_keys, scale, out, ld_out, stream, amax_slots);
-    if (D == 64) return launch<64, 8>(q, ld_q, n_q, H, k_packed, vt_packed, cap, n_keys, scale, out, ld_out, stream, amax_slots);
-    return lvx_fail(LVX_ERR_UNSUPPORTED, "head_dim %d not supported (64 or 128)", D);
+    if (D == 64) return two ? LVX_ATTN_LAUNCH(64, 1, false, false, 2) : LVX_ATTN_LAUNCH(64, 1, false, false, 1);
+    if (two) return LVX_ATTN_LAUNCH(128, 1, false, false, 2);
+    return n_keys >= TP2_MIN_KEYS ? LVX_ATTN_LAUNCH(128, 2, false, false, 1) : LVX_ATTN_LAUNCH(128, 1, false, false, 1);
+#undef LVX_ATTN_LAUNCH
 }
 
 static lvx_status_t chunk_attention_entry(const lvx_kvcache_t *c, int32_t layer, const void *dev_q, int64_t ld_q, int32_t n_q, float scale,
