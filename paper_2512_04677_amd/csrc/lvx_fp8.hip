@@ -397,41 +397,46 @@ lvx_status_t lvx_launch_linear_fp8(const void *dev_aq, int64_t lda, const float 
         LVX_REQUIRE(ldr >= N, LVX_ERR_SHAPE, "bad residual leading dimension");
     }
     if (M == 0) return LVX_OK;
-    const int tile = lvx_gemm_pick_small(nullptr, M, N, K / 128);
-    if (tile >= 0) {  // a small tile where the 128 x 256 one would leave compute units idle
-        lvx_gemm_args_t p = {};
-        p.A = (const char *)dev_aq, p.lda = lda;
-        p.W = (const char *)dev_wq, p.ldw = ldw;
-        p.C = dev_c, p.ldc = ldc;
-        p.R = dev_resid, p.ldr = ldr;
-        p.gate = dev_gate;
-        p.scale_a = dev_scale_a, p.scale_w = dev_scale_w;
-        p.amax = amax_slots;
-        p.M = M, p.N = N, p.n_slabs = K / 128;
-        p.epi = (int)epi;
-        return lvx_gemm_launch_small<true>(tile, p, stream);
-    }
-    constexpr int BM = 128, BN = 256;
-    const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-    const int total = tiles_m * tiles_n;
-    const int per_xcd = (total + 7) / 8;
-    const dim3 grid(per_xcd * 8), block(512);
+    double us = 0;
+    int tile = lvx_gemm_pick_tile(nullptr, M, N, K / 128, false, &us), m1 = 0;  // m1: rows the 128 x 256 kernel takes, the others go to a small tile
+    if (tile < 0) {
+        m1 = lvx_gemm_split_rows(nullptr, M, N, K / 128, us, &tile);
+        const int rows = m1 > 0 ? m1 : M;
+        constexpr int BM = 128, BN = 256;
+        const int tiles_m = (rows + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+        const int total = tiles_m * tiles_n;
+        const int per_xcd = (total + 7) / 8;
+        const dim3 grid(per_xcd * 8), block(512);
 #define LVX8_LAUNCH(EPI_)                                                                                                         \
-    hipLaunchKernelGGL((lvx_gemm_fp8_kernel<BM, BN, 2, 4, EPI_>), grid, block, 0, (hipStream_t)stream, (const uint8_t *)dev_aq, lda, \
-                       (const uint8_t *)dev_wq, ldw, dev_scale_a, dev_scale_w, (bf16_t *)dev_c, ldc, M, N, K, (const bf16_t *)dev_resid, \
-                       ldr, dev_gate, tiles_m, tiles_n, per_xcd, amax_slots)
-    if (epi == LVX_EPI_STORE) {
-        LVX8_LAUNCH(LVX_EPI_STORE);
-    } else if (epi == LVX_EPI_GELU_TANH) {
-        LVX8_LAUNCH(LVX_EPI_GELU_TANH);
-    } else if (epi == LVX_EPI_RESID_GATE) {
-        LVX8_LAUNCH(LVX_EPI_RESID_GATE);
-    } else {
-        LVX8_LAUNCH(LVX_EPI_RESID_GATE_F32);
-    }
+        hipLaunchKernelGGL((lvx_gemm_fp8_kernel<BM, BN, 2, 4, EPI_>), grid, block, 0, (hipStream_t)stream, (const uint8_t *)dev_aq, lda, \
+                           (const uint8_t *)dev_wq, ldw, dev_scale_a, dev_scale_w, (bf16_t *)dev_c, ldc, rows, N, K, (const bf16_t *)dev_resid, \
+                           ldr, dev_gate, tiles_m, tiles_n, per_xcd, amax_slots)
+        if (epi == LVX_EPI_STORE) {
+            LVX8_LAUNCH(LVX_EPI_STORE);
+        } else if (epi == LVX_EPI_GELU_TANH) {
+            LVX8_LAUNCH(LVX_EPI_GELU_TANH);
+        } else if (epi == LVX_EPI_RESID_GATE) {
+            LVX8_LAUNCH(LVX_EPI_RESID_GATE);
+        } else {
+            LVX8_LAUNCH(LVX_EPI_RESID_GATE_F32);
+        }
 #undef LVX8_LAUNCH
-    LVX_CHECK_HIP(hipGetLastError());
-    return LVX_OK;
+        LVX_CHECK_HIP(hipGetLastError());
+        if (m1 == 0) return LVX_OK;
+    }
+    const int64_t c_bytes = epi == LVX_EPI_RESID_GATE_F32 ? 4 : 2;
+    lvx_gemm_args_t p = {};
+    p.A = (const char *)dev_aq + (size_t)m1 * lda, p.lda = lda;
+    p.W = (const char *)dev_wq, p.ldw = ldw;
+    p.C = (char *)dev_c + (size_t)m1 * ldc * c_bytes, p.ldc = ldc;
+    if (dev_resid != nullptr) p.R = (const char *)dev_resid + (size_t)m1 * ldr * c_bytes;
+    p.ldr = ldr;
+    p.gate = dev_gate;
+    p.scale_a = dev_scale_a, p.scale_w = dev_scale_w;
+    p.amax = amax_slots;
+    p.M = M - m1, p.N = N, p.n_slabs = K / 128;
+    p.epi = (int)epi;
+    return lvx_gemm_launch_small<true>(tile, p, stream);
 }
 
 extern "C" lvx_status_t lvx_linear_fp8(const void *dev_aq, int64_t lda, const float *dev_scale_a, const void *dev_wq, int64_t ldw,

@@ -279,20 +279,32 @@ lvx_status_t launch(const bf16_t *A, int64_t lda, const bf16_t *W, int64_t ldw, 
     return LVX_OK;
 }
 
-// The linears: the 128 x 256 kernel, or a small tile where that one would leave compute units idle.
+// The linears: the 128 x 256 kernel, a small tile where that one would leave compute units idle, or both for different rows.
 lvx_status_t launch_linear(const bf16_t *A, int64_t lda, const bf16_t *W, int64_t ldw, bf16_t *C, int64_t ldc, int M, int N, int K, int epi,
                            const bf16_t *R, int64_t ldr, const float *gate, hipStream_t stream, const lvx_gemm_segs_t *segs = nullptr) {
-    const int tile = lvx_gemm_pick_small(segs, M, N, K / BK);
-    if (tile < 0) return launch<128, 256, 2, 4>(A, lda, W, ldw, C, ldc, M, N, K, epi, R, ldr, gate, stream, segs);
+    double us = 0;
+    const bool sumsq = segs != nullptr && segs->s[0].sumsq != nullptr;  // (a 48-column wave cannot give sums of 64 columns)
+    int tile = lvx_gemm_pick_tile(segs, M, N, K / BK, !sumsq, &us), m1 = 0;  // m1: rows the 128 x 256 kernel takes of a split product
+    if (tile < 0) {
+        int rest = tile;
+        m1 = lvx_gemm_split_rows(segs, M, N, K / BK, us, &rest);
+        if (m1 == 0 && tile == LVX_GEMM_TILE_128X192) return launch<128, 192, 2, 4>(A, lda, W, ldw, C, ldc, M, N, K, epi, R, ldr, gate, stream, segs);
+        tile = rest;
+        LVX_TRY((launch<128, 256, 2, 4>(A, lda, W, ldw, C, ldc, m1 > 0 ? m1 : M, N, K, epi, R, ldr, gate, stream, segs)));
+        if (m1 == 0) return LVX_OK;
+    }
+    const bool c_f32 = epi == LVX_EPI_RESID_GATE_F32 || epi == LVX_EPI_STORE_F32;
     lvx_gemm_args_t p = {};
-    p.A = (const char *)A, p.lda = lda * 2;
+    p.A = (const char *)(A + (size_t)m1 * lda), p.lda = lda * 2;
     p.W = (const char *)W, p.ldw = ldw * 2;
-    p.C = C, p.ldc = ldc;
-    p.R = R, p.ldr = ldr;
+    p.C = (char *)C + (size_t)m1 * ldc * (c_f32 ? 4 : 2), p.ldc = ldc;
+    if (R != nullptr) p.R = (const char *)R + (size_t)m1 * ldr * (epi == LVX_EPI_RESID_GATE_F32 ? 4 : 2);
+    p.ldr = ldr;
     p.gate = gate;
-    p.M = M, p.N = N, p.n_slabs = K / BK;
+    p.M = M - m1, p.N = N, p.n_slabs = K / BK;
     p.epi = epi;
     if (segs != nullptr) p.segs = *segs;
+    for (int i = 0; i < p.segs.n; ++i) p.segs.s[i].C = (char *)p.segs.s[i].C + (size_t)m1 * p.segs.s[i].ldc * (p.segs.s[i].f32 ? 4 : 2);
     return lvx_gemm_launch_small<false>(tile, p, stream);
 }
 
@@ -343,7 +355,7 @@ lvx_status_t lvx_launch_linear_segments(const bf16_t *A, int64_t lda, int64_t ld
                                   nullptr, stream, &segs);
 }
 
-int lvx_gemm_sumsq_parts(int M, int N, int K) { return N / lvx_gemm_part_cols(lvx_gemm_pick_small(nullptr, M, N, K / BK)); }
+int lvx_gemm_sumsq_parts(int M, int N, int K) { return N / lvx_gemm_part_cols(lvx_gemm_pick_tile(nullptr, M, N, K / BK)); }
 
 extern "C" lvx_status_t lvx_linear_dual(const void *dev_a, int64_t lda, const void *dev_w1, const void *dev_w2, int64_t ldw, void *dev_c1,
                                         int64_t ldc1, int32_t c1_is_f32, void *dev_c2, int64_t ldc2, int32_t M, int32_t N1, int32_t N2,

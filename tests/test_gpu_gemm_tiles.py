@@ -83,3 +83,51 @@ def test_linear_fp8_tile_edges(lvx, M, N, K):
     # up to 448 * 448 quantisation steps wide, carries errors up to about 1e-4 (measured 6e-5 .. 1.9e-4 at a gate of 1, the same
     # for both shapes of the instruction); bound as for the FP8 linear of test_gpu_fp8.py
     assert np.abs(S.to_f64(x) - (S.to_f64(r) + S.to_f64(g) * ref)).max() <= 1e-4 * math.sqrt(K)
+
+
+@pytest.mark.parametrize("M,N,K", [(1550, 5120, 1152),     # 12 row tiles in one round, 14 rows in a small tile
+                                   (1567, 5112, 1408),     # the same with ragged columns, 31 rows
+                                   (1550, 5112, 576), (1886, 2568, 192), (2048, 3072, 64)])   # 128 x 192 tiles, ragged and whole
+def test_rows_split_over_two_launches_and_narrow_tiles(lvx, M, N, K):
+    a = S.randn_bf16((M, K + 8), S.seed_of("rs_a", M, K), device=DEV)[:, :K]
+    w = S.randn_bf16((N, K + 64), S.seed_of("rs_w", N, K), 1.0 / math.sqrt(K), device=DEV)[:, :K]
+    g = S.randn_f32((N,), 7, 0.5, 1.0, device=DEV)
+    r = S.randn_f32((M, N + 8), S.seed_of("rs_r", M, N), device=DEV)
+    ref = O.linear(S.to_f64(a), S.to_f64(w))
+    out = torch.full((M + 1, N + 8), 7.0, dtype=torch.bfloat16, device=DEV)
+    lvx.lvx_linear(a, w, out[:M, :N], lvx.EPI_STORE)
+    x = r.clone()
+    lvx.lvx_linear(a, w, x[:, :N], lvx.EPI_RESID_GATE_F32, resid=x[:, :N], gate=g)
+    rb = r.to(torch.bfloat16)
+    xb = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
+    lvx.lvx_linear(a, w, xb, lvx.EPI_RESID_GATE, resid=rb[:, :N], gate=g)
+    c1 = torch.empty((M, N), dtype=torch.float32, device=DEV)
+    c2 = torch.empty((M, 8), dtype=torch.bfloat16, device=DEV)
+    lvx.lvx_linear_dual(a, w, w[:8], c1, c2)
+    torch.cuda.synchronize()
+    assert_close(out[:M, :N], ref, "store %dx%dx%d" % (M, N, K))
+    assert bool((out[M] == 7.0).all()) and bool((out[:, N:] == 7.0).all())
+    bound = 4.0 * K * 2.0 ** -24 + 1e-6
+    assert np.abs(S.to_f64(x[:, :N]) - (S.to_f64(r[:, :N]) + S.to_f64(g) * ref)).max() <= 4.0 * bound
+    assert torch.equal(x[:, N:], r[:, N:])
+    assert_close(xb, S.to_f64(rb[:, :N]) + S.to_f64(g) * ref, "bf16 residual")
+    assert np.abs(S.to_f64(c1) - ref).max() <= bound
+    assert_close(c2, ref[:, :8], "second product")
+
+
+@pytest.mark.parametrize("M,N,K", [(1550, 5120, 1152), (1567, 5112, 1408)])
+def test_fp8_rows_split_over_two_launches(lvx, M, N, K):
+    aq, sa = lvx.lvx_fp8_quantize(S.randn_bf16((M, K), S.seed_of("r8_a", M, K), device=DEV), row_pad=16)
+    wq, sw = lvx.lvx_fp8_quantize(S.randn_bf16((N, K), S.seed_of("r8_w", N, K), 1.0 / math.sqrt(K), device=DEV), row_pad=128)
+    dec = [S.to_f64(q.contiguous().view(torch.float8_e4m3fn).float()) * float(s.item()) for q, s in ((aq, sa), (wq, sw))]
+    ref = O.linear(dec[0], dec[1])
+    r = S.randn_f32((M, N), S.seed_of("r8_r", M, N), device=DEV)
+    out = torch.full((M + 1, N + 8), 7.0, dtype=torch.bfloat16, device=DEV)
+    lvx.lvx_linear_fp8(aq, sa, wq, sw, out[:M, :N], lvx.EPI_STORE)
+    x = r.clone()
+    lvx.lvx_linear_fp8(aq, sa, wq, sw, x, lvx.EPI_RESID_GATE_F32, resid=x)
+    torch.cuda.synchronize()
+    assert_close(out[:M, :N], ref, "fp8 store %dx%dx%d" % (M, N, K))
+    assert bool((out[M] == 7.0).all()) and bool((out[:, N:] == 7.0).all())
+    # the FP8 products' alignment in the matrix core: see test_linear_fp8_tile_edges
+    assert np.abs(S.to_f64(x) - (S.to_f64(r) + ref)).max() <= 1e-4 * math.sqrt(K)
