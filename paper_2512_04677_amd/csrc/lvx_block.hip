@@ -1,7 +1,7 @@
 // DiT block and denoise stage: host-side sequencing of the kernels on one HIP stream, no synchronisation inside.
 // (Paper Alg. 4, DiT-device branch: forward with the device's local rolling KV cache, cache update, Euler step;
 // Sec. 3.4: throughput of the pipeline is set by this single denoise forward.)
-#include "lvx_internal.h"
+#include "lvx_pack.h"
 
 #include <math.h>
 
@@ -154,7 +154,7 @@ lvx_status_t check_stage(const lvx_stage_t *s, const lvx_kvcache *c, int n_token
 // Context K / V of layers [l0, l1) (at most CTX_GROUP; bf16 stages): the context is the same for every layer of a forward
 // (Alg. 4 hands one condition set C_i to the whole stack), so their 2 (l1 - l0) projections run as ONE GEMM launch (a single
 // layer's pair is 200 tiles on 256 compute units), followed by one launch that normalises the K rows straight into the
-// packed layout the attention kernel reads and one that transposes the V rows into it.  Slot j of the group holds layer l0 + j.
+// packed layout the attention kernel reads and transposes the V rows into it.  Slot j of the group holds layer l0 + j.
 lvx_status_t precompute_ctx(const lvx_stage_t *s, int l0, int l1, const bf16_t *ctx, int n_ctx, char *ws, const ws_layout_t &L, hipStream_t st) {
     const int H = s->rope.n_heads, D = s->rope.head_dim, d = H * D;
     const int64_t ldw = s->ldw_d > 0 ? s->ldw_d : d, ldk = L.ld_ckv;
@@ -174,8 +174,8 @@ lvx_status_t precompute_ctx(const lvx_stage_t *s, int l0, int l1, const bf16_t *
     }
     prof_scope_t ps(LVX_PROF_CTX_KV, st);
     LVX_TRY(lvx_launch_linear_segments(ctx, d, ldw, segs, n_ctx, d, st));
-    LVX_TRY(lvx_launch_norm_to_packed_k(&s->rope, ctx_k32, 1, ld32, n_ctx, gains, pack_k, L.cap_ctx, g, slot_rows32, slot_packed, st));
-    return lvx_launch_pack_kv(nullptr, ctx_kv + d, ldk, n_ctx, H, D, L.cap_ctx, 0, pack_k, pack_v, st, g, slot_rows, slot_packed);
+    const lvx_pack_job_t values = lvx_pack_job(ctx_kv + d, ldk, n_ctx, H, L.cap_ctx, 0, pack_v, g, slot_rows, slot_packed);
+    return lvx_launch_norm_to_packed_k(&s->rope, ctx_k32, 1, ld32, n_ctx, gains, pack_k, L.cap_ctx, g, slot_rows32, slot_packed, st, &values);
 }
 
 // ctx_slot: slot of the context group that holds this layer's packed context K / V (bf16 stages, see precompute_ctx).
@@ -249,25 +249,19 @@ lvx_status_t run_block(const lvx_stage_t *s, int layer, lvx_kvcache *c, float *x
     }
     if (!sink_prefill) {
         {
-            // the RoPE kernel writes the chunk's keys straight into their ring slot of the cache (one write instead of a write, a
-            // read and a write); the append then only has the values left to transpose.  bf16 stage: k comes un-rounded (fp32).
+            // the RoPE launch writes the chunk's keys straight into their ring slot of the cache (one write instead of a write, a
+            // read and a write) and transposes the values into it.  bf16 stage: k comes un-rounded (fp32).
             lvx_slot_info_t slot;
             LVX_TRY(lvx_cache_append_begin(c, layer, chunk_index, &slot));
             bf16_t *k_slot = const_cast<bf16_t *>(lvx_cache_k(c, layer)) + (size_t)slot.key_offset * D;
-            {
-                prof_scope_t ps(LVX_PROF_ROPE_NORM, st);
-                if (w8 == nullptr)
-                    LVX_TRY(lvx_launch_rope_qk(&s->rope, big, ldq, k32, 1, ld32, w.g_q, w.g_k, n, t0, big, ldq, k_slot, D, (int64_t)c->cap_keys * D,
-                                               scale * LVX_LOG2E, st));
-                else
-                    LVX_TRY(lvx_launch_rope_qk(&s->rope, big, ldq, big + d, 0, ldq, w.g_q, w.g_k, n, t0, big, ldq, k_slot, D,
-                                               (int64_t)c->cap_keys * D, scale * LVX_LOG2E, st));
-            }
-            {
-                prof_scope_t ps(LVX_PROF_APPEND, st);
-                LVX_TRY(lvx_launch_pack_kv(nullptr, big + 2 * d, ldq, n, H, D, c->cap_keys, slot.key_offset, const_cast<bf16_t *>(lvx_cache_k(c, layer)),
-                                           const_cast<bf16_t *>(lvx_cache_vt(c, layer)), st));
-            }
+            const lvx_pack_job_t values = lvx_pack_job(big + 2 * d, ldq, n, H, c->cap_keys, slot.key_offset, const_cast<bf16_t *>(lvx_cache_vt(c, layer)));
+            prof_scope_t ps(LVX_PROF_ROPE_NORM, st);
+            if (w8 == nullptr)
+                LVX_TRY(lvx_launch_rope_qk(&s->rope, big, ldq, k32, 1, ld32, w.g_q, w.g_k, n, t0, big, ldq, k_slot, D, (int64_t)c->cap_keys * D,
+                                           scale * LVX_LOG2E, st, &values));
+            else
+                LVX_TRY(lvx_launch_rope_qk(&s->rope, big, ldq, big + d, 0, ldq, w.g_q, w.g_k, n, t0, big, ldq, k_slot, D, (int64_t)c->cap_keys * D,
+                                           scale * LVX_LOG2E, st, &values));
             lvx_cache_append_commit(c, layer, chunk_index, &slot);
         }
         {
@@ -324,8 +318,8 @@ lvx_status_t run_block(const lvx_stage_t *s, int layer, lvx_kvcache *c, float *x
         LVX_TRY(linear(ctx, d, w.Wc_k, 3, ctx_kv, ldk, n_ctx, d, d, LVX_EPI_STORE, nullptr, 0, nullptr, true, ctx_codes_ready, false, false));
         LVX_TRY(linear(ctx, d, w.Wc_v, 4, ctx_kv + d, ldk, n_ctx, d, d, LVX_EPI_STORE, nullptr, 0, nullptr, true, true, false, false));
         const float *gains[1] = {w.gc_k};
-        LVX_TRY(lvx_launch_norm_to_packed_k(&s->rope, ctx_kv, 0, ldk, n_ctx, gains, pack_k, L.cap_ctx, 1, 0, 0, st));
-        LVX_TRY(lvx_launch_pack_kv(nullptr, ctx_kv + d, ldk, n_ctx, H, D, L.cap_ctx, 0, pack_k, pack_v, st));
+        const lvx_pack_job_t values = lvx_pack_job(ctx_kv + d, ldk, n_ctx, H, L.cap_ctx, 0, pack_v);
+        LVX_TRY(lvx_launch_norm_to_packed_k(&s->rope, ctx_kv, 0, ldk, n_ctx, gains, pack_k, L.cap_ctx, 1, 0, 0, st, &values));
     }
     {
         prof_scope_t ps(LVX_PROF_ATTN_CROSS, st);

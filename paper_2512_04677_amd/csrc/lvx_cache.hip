@@ -10,7 +10,7 @@
 //                                 V^T[head][cap_keys/64][D][64]     -> a 64-key V tile is stored transposed, contiguous,
 // so both tiles stream into LDS with 16-byte loads and are direct MFMA A-operands (contraction index contiguous).
 // Key rows: [0, sink_keys) sink, then slot s at sink_keys + s*chunk_keys.
-#include "lvx_internal.h"
+#include "lvx_pack.h"
 
 #include <new>
 #include <string.h>
@@ -37,64 +37,14 @@ __global__ void __launch_bounds__(256) lvx_fill_zero_kernel(uint4 *p, size_t n16
     for (; i < n16; i += stride) p[i] = z;
 }
 
-// One workgroup = one head x one 64-key tile of the destination.  Copies the rows of K that fall into the tile and
-// writes the matching part of the transposed V tile (through LDS).  Only keys in [key0, key0+n) are touched: a tile
-// shared with a neighbouring slot keeps the neighbour's keys.
 template <int D>
 __global__ void __launch_bounds__(256) lvx_pack_kv_kernel(const bf16_t *__restrict__ k, const bf16_t *__restrict__ v, int64_t ld,
                                                           int n, int cap, int key0, int tile0, bf16_t *__restrict__ kp,
                                                           bf16_t *__restrict__ vtp, int64_t batch_stride_src, int64_t batch_stride_dst) {
-    // blockIdx.z: independent row set / packed array (the context values of several layers in one launch)
+    // blockIdx.z: independent row set / packed array
     if (k != nullptr) k += (size_t)blockIdx.z * batch_stride_src;
-    v += (size_t)blockIdx.z * batch_stride_src;
-    kp += (size_t)blockIdx.z * batch_stride_dst;
-    vtp += (size_t)blockIdx.z * batch_stride_dst;
-    constexpr int KT = LVX_KEY_TILE;
-    constexpr int CPR = D / 8;        // 16-byte chunks per row
-    constexpr int LDS_LD = D + 8;     // padded row, keeps 16-byte alignment
-    __shared__ __attribute__((aligned(16))) bf16_t vs[KT * LDS_LD];
-
-    const int tile = tile0 + blockIdx.x;
-    const int h = blockIdx.y;
-    const int tid = threadIdx.x;
-    const int key_lo = tile * KT;
-    const int n_tiles = cap / KT;
-
-    for (int g = tid; g < KT * CPR; g += 256) {
-        const int r = g / CPR, c = g % CPR;
-        const int key = key_lo + r;
-        const int src = key - key0;
-        uint4 val = make_uint4(0, 0, 0, 0);
-        if (src >= 0 && src < n) {
-            const size_t so = (size_t)src * ld + (size_t)h * D + c * 8;
-            if (k != nullptr) *reinterpret_cast<uint4 *>(kp + ((size_t)h * cap + key) * D + c * 8) = *reinterpret_cast<const uint4 *>(k + so);
-            val = *reinterpret_cast<const uint4 *>(v + so);
-        }
-        *reinterpret_cast<uint4 *>(&vs[r * LDS_LD + c * 8]) = val;
-    }
-    __syncthreads();
-    bf16_t *vt_tile = vtp + ((size_t)h * n_tiles + tile) * (size_t)D * KT;
-    for (int g = tid; g < D * (KT / 8); g += 256) {
-        const int d = g / (KT / 8), kc = g % (KT / 8);
-        const int lo = key_lo + kc * 8 - key0;  // source index of the first of 8 keys
-        if (lo + 7 < 0 || lo >= n) continue;
-        bf16_t e[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) e[j] = vs[(kc * 8 + j) * LDS_LD + d];
-        bf16_t *dst = vt_tile + (size_t)d * KT + kc * 8;
-        if (lo >= 0 && lo + 7 < n) {
-            uint4 o;
-            o.x = e[0] | ((uint32_t)e[1] << 16);
-            o.y = e[2] | ((uint32_t)e[3] << 16);
-            o.z = e[4] | ((uint32_t)e[5] << 16);
-            o.w = e[6] | ((uint32_t)e[7] << 16);
-            *reinterpret_cast<uint4 *>(dst) = o;
-        } else {
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (lo + j >= 0 && lo + j < n) dst[j] = e[j];
-        }
-    }
+    lvx_pack_tile<D>(k, v + (size_t)blockIdx.z * batch_stride_src, ld, n, cap, key0, tile0 + blockIdx.x, blockIdx.y, kp + (size_t)blockIdx.z * batch_stride_dst,
+                     vtp + (size_t)blockIdx.z * batch_stride_dst);
 }
 
 // Inverse of the pack: thread = (key, head, 16-byte chunk).  Check / off-load path, not tuned.

@@ -120,10 +120,12 @@ lvx_status_t lvx_launch_copy_rows(const bf16_t *src, int64_t ld_src, bf16_t *dst
 lvx_status_t lvx_launch_rope_to_packed_k(const lvx_rope_desc_t *desc, const float *src, int64_t ld_src, int n_tokens, int t0,
                                          bf16_t *k_packed, int cap, int n_layers, int64_t layer_stride_src, int64_t layer_stride_dst,
                                          hipStream_t stream);
-// RMSNorm + RoPE with q rows in bf16 and k rows in fp32 (outputs bf16).
+// RMSNorm + RoPE with q rows in bf16 and k rows in fp32 (outputs bf16).  values (here and below, see lvx_pack.h; may be NULL): value
+// rows to transpose into the cache in the same launch.
 lvx_status_t lvx_launch_rope_qk(const lvx_rope_desc_t *desc, const bf16_t *q_in, int64_t ld_q, const void *k_in, int k_is_f32, int64_t ld_k,
                                 const float *g_q, const float *g_k, int n_tokens, int t0, bf16_t *q_out, int64_t ld_out, bf16_t *k_out,
-                                int64_t ld_out_k, int64_t ld_out_head_k, float q_scale, hipStream_t stream);
+                                int64_t ld_out_k, int64_t ld_out_head_k, float q_scale, hipStream_t stream,
+                                const struct lvx_pack_job_t *values = nullptr);
 // Append in two steps for a producer that writes the chunk's keys into the cache itself: begin validates and names the slot
 // (nothing changes), commit records the chunk in the layer's ring state.
 lvx_status_t lvx_cache_append_begin(const lvx_kvcache *c, int layer, int64_t chunk_index, lvx_slot_info_t *info);
@@ -132,7 +134,7 @@ void lvx_cache_append_commit(lvx_kvcache *c, int layer, int64_t chunk_index, con
 // from key 0 on; gains[b] is batch b's gain vector (NULL: that batch is copied un-normalised).  n_batch <= LVX_GEMM_MAX_SEGS.
 lvx_status_t lvx_launch_norm_to_packed_k(const lvx_rope_desc_t *desc, const void *src, int src_is_f32, int64_t ld_src, int n_tokens,
                                          const float *const *gains, bf16_t *k_packed, int cap, int n_batch, int64_t batch_stride_src,
-                                         int64_t batch_stride_dst, hipStream_t stream);
+                                         int64_t batch_stride_dst, hipStream_t stream, const struct lvx_pack_job_t *values = nullptr);
 // y = x / sqrt(mean(x^2) + eps) * g on fp32 rows, fp32 out, no rounding (g NULL: plain copy): the sink warm-up's un-rotated keys.
 lvx_status_t lvx_launch_rmsnorm_f32(const lvx_rope_desc_t *desc, const float *x, int64_t ld_in, const float *g, int n_tokens, float *y,
                                     int64_t ld_out, hipStream_t stream);

@@ -6,7 +6,7 @@
 // 10 000 s experiment), where an fp32 product pos*freq already loses ~1e-3 rad, so each token's head_dim/2 angles
 // are formed and reduced in fp64 (one per lane, shared by all heads and by q and k) and only the resulting
 // sin/cos are kept in fp32.
-#include "lvx_internal.h"
+#include "lvx_pack.h"
 
 #include <math.h>
 
@@ -33,17 +33,23 @@ constexpr int ROWS_PER_WG = 4;
 // CPL = 8-element chunks per lane (row length <= 64*8*CPL).  IN_MODE: 0 = q and k rows are bf16, 1 = both fp32, 2 = q bf16 and
 // k fp32 (row strides and batch strides of an fp32 input count fp32 elements; ld_in is q's row stride, ld_in_k is k's).
 // F32OUT (norm-only form, needs fp32 input): the result is stored in fp32, token-major, un-rounded
-template <int CPL, int IN_MODE, bool F32OUT = false>
+// PACK_D (0 or the head_dim): the first pack_x columns of workgroups transpose the values of the same keys into the cache.  The two
+// jobs are independent and each is too small to fill the chip; a launch of its own for the values cost 5 to 8 us per block.
+template <int CPL, int IN_MODE, bool F32OUT = false, int PACK_D = 0>
 __global__ void __launch_bounds__(64 * ROWS_PER_WG)
     lvx_rope_norm_kernel(const void *q_in, const void *k_in, int64_t ld_in, int64_t ld_in_k,
                          const float *__restrict__ g_q, const float *__restrict__ g_k, int n_tokens, int t0, bf16_t *q_out,
                          bf16_t *k_out, int64_t ld_out, int64_t ld_out_head, int d_model, int head_dim, int frame_h, int frame_w,
                          float eps, int apply_rope, rope_table_t tab, int n_batch, int64_t batch_stride_in, int64_t batch_stride_out,
-                         gain_table_t gtab, float q_scale, int64_t ld_out_k, int64_t ld_out_head_k) {
+                         gain_table_t gtab, float q_scale, int64_t ld_out_k, int64_t ld_out_head_k, lvx_pack_job_t pack, int pack_x) {
+    if (PACK_D != 0 && (int)blockIdx.x < pack_x) {
+        lvx_pack_job_tile<PACK_D == 64 ? 64 : 128>(pack, (int)(blockIdx.x * gridDim.y + blockIdx.y));
+        return;
+    }
     // n_batch independent row sets of n_tokens rows each (the sink keys of several layers in one launch); positions and t0
     // are those of the row inside its set
     const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * ROWS_PER_WG + (threadIdx.x >> 6);
+    const int64_t row = (int64_t)((int)blockIdx.x - pack_x) * ROWS_PER_WG + (threadIdx.x >> 6);
     if (row >= (int64_t)n_tokens * n_batch) return;
     const int batch = (int)(row / n_tokens);
     const int token = (int)(row % n_tokens);
@@ -257,7 +263,7 @@ static lvx_status_t launch_rope(const lvx_rope_desc_t *desc, const void *q_in, c
                                 const float *g_k, int n_tokens, int t0, bf16_t *q_out, bf16_t *k_out, int64_t ld_out, int64_t ld_out_head,
                                 hipStream_t stream, int n_batch = 1, int64_t batch_stride_in = 0, int64_t batch_stride_out = 0,
                                 int in_mode = 0, const gain_table_t *gains = nullptr, int64_t ld_in_k = -1, float q_scale = 1.0f,
-                                int64_t ld_out_k = -1, int64_t ld_out_head_k = -1) {
+                                int64_t ld_out_k = -1, int64_t ld_out_head_k = -1, const lvx_pack_job_t *pack_job = nullptr) {
     if (ld_in_k < 0) ld_in_k = ld_in;
     if (ld_out_k < 0) ld_out_k = ld_out, ld_out_head_k = ld_out_head;
     gain_table_t gtab = {};
@@ -278,29 +284,41 @@ static lvx_status_t launch_rope(const lvx_rope_desc_t *desc, const void *q_in, c
     }
     // with both inputs present the q rows and the k rows are handled by different workgroups (twice the waves in flight,
     // half the dependent load -> reduce -> store chain per wave)
-    const dim3 grid((unsigned)(((int64_t)n_tokens * n_batch + ROWS_PER_WG - 1) / ROWS_PER_WG), (q_in != nullptr && k_in != nullptr) ? 2 : 1),
-        block(64 * ROWS_PER_WG);
+    const int grid_y = (q_in != nullptr && k_in != nullptr) ? 2 : 1;
+    lvx_pack_job_t pack = {};
+    if (pack_job != nullptr) pack = *pack_job;
+    const int pack_x = (pack.n_tiles * pack.H * pack.n_batch + grid_y - 1) / grid_y;
+    const dim3 grid((unsigned)(pack_x + ((int64_t)n_tokens * n_batch + ROWS_PER_WG - 1) / ROWS_PER_WG), grid_y), block(64 * ROWS_PER_WG);
     const int cpl = (d / 8 + 63) / 64;
-#define LVX_ROPE_LAUNCH(CPL, MODE)                                                                                               \
-    hipLaunchKernelGGL((lvx_rope_norm_kernel<CPL, MODE>), grid, block, 0, stream, q_in, k_in, ld_in, ld_in_k, g_q, g_k, n_tokens, t0, q_out, \
+#define LVX_ROPE_LAUNCH_PACK(CPL, MODE, PD)                                                                                      \
+    hipLaunchKernelGGL((lvx_rope_norm_kernel<CPL, MODE, false, PD>), grid, block, 0, stream, q_in, k_in, ld_in, ld_in_k, g_q, g_k, n_tokens, t0, q_out, \
                        k_out, ld_out, ld_out_head, d, desc->head_dim, desc->frame_h, desc->frame_w, desc->eps, desc->apply_rope, tab,    \
-                       n_batch, batch_stride_in, batch_stride_out, gtab, q_scale, ld_out_k, ld_out_head_k)
+                       n_batch, batch_stride_in, batch_stride_out, gtab, q_scale, ld_out_k, ld_out_head_k, pack, pack_x)
+#define LVX_ROPE_LAUNCH(CPL, MODE)              \
+    if (pack_x == 0)                            \
+        LVX_ROPE_LAUNCH_PACK(CPL, MODE, 0);     \
+    else if (desc->head_dim == 64)              \
+        LVX_ROPE_LAUNCH_PACK(CPL, MODE, 64);    \
+    else                                        \
+        LVX_ROPE_LAUNCH_PACK(CPL, MODE, 128)
 #define LVX_ROPE_LAUNCH_MODE(MODE)          \
-    if (cpl <= 2)                           \
+    if (cpl <= 2) {                         \
         LVX_ROPE_LAUNCH(2, MODE);           \
-    else if (cpl <= 10)                     \
+    } else if (cpl <= 10) {                 \
         LVX_ROPE_LAUNCH(10, MODE);          \
-    else                                    \
-        LVX_ROPE_LAUNCH(16, MODE)
+    } else {                                \
+        LVX_ROPE_LAUNCH(16, MODE);          \
+    }
     if (in_mode == 1) {
-        LVX_ROPE_LAUNCH_MODE(1);
+        LVX_ROPE_LAUNCH_MODE(1)
     } else if (in_mode == 2) {
-        LVX_ROPE_LAUNCH_MODE(2);
+        LVX_ROPE_LAUNCH_MODE(2)
     } else {
-        LVX_ROPE_LAUNCH_MODE(0);
+        LVX_ROPE_LAUNCH_MODE(0)
     }
 #undef LVX_ROPE_LAUNCH_MODE
 #undef LVX_ROPE_LAUNCH
+#undef LVX_ROPE_LAUNCH_PACK
     LVX_CHECK_HIP(hipGetLastError());
     return LVX_OK;
 }
@@ -344,12 +362,12 @@ extern "C" lvx_status_t lvx_rope3d_f32in(const lvx_rope_desc_t *desc, const floa
 // token * ld_out_k + head * ld_out_head_k + e (token-major rows, or straight into the cache's packed rows).
 lvx_status_t lvx_launch_rope_qk(const lvx_rope_desc_t *desc, const bf16_t *q_in, int64_t ld_q, const void *k_in, int k_is_f32, int64_t ld_k,
                                 const float *g_q, const float *g_k, int n_tokens, int t0, bf16_t *q_out, int64_t ld_out, bf16_t *k_out,
-                                int64_t ld_out_k, int64_t ld_out_head_k, float q_scale, hipStream_t stream) {
+                                int64_t ld_out_k, int64_t ld_out_head_k, float q_scale, hipStream_t stream, const lvx_pack_job_t *values) {
     lvx_status_t st = check_rope_desc(desc);
     if (st != LVX_OK) return st;
     if (n_tokens == 0) return LVX_OK;
     return launch_rope(desc, q_in, k_in, ld_q, g_q, g_k, n_tokens, t0, q_out, k_out, ld_out, desc->head_dim, stream, 1, 0, 0, k_is_f32 ? 2 : 0,
-                       nullptr, ld_k, q_scale, ld_out_k, ld_out_head_k);
+                       nullptr, ld_k, q_scale, ld_out_k, ld_out_head_k, values);
 }
 
 lvx_status_t lvx_launch_rope_to_packed_k(const lvx_rope_desc_t *desc, const float *src, int64_t ld_src, int n_tokens, int t0,
@@ -364,7 +382,7 @@ lvx_status_t lvx_launch_rope_to_packed_k(const lvx_rope_desc_t *desc, const floa
 
 lvx_status_t lvx_launch_norm_to_packed_k(const lvx_rope_desc_t *desc, const void *src, int src_is_f32, int64_t ld_src, int n_tokens,
                                          const float *const *gains, bf16_t *k_packed, int cap, int n_batch, int64_t batch_stride_src,
-                                         int64_t batch_stride_dst, hipStream_t stream) {
+                                         int64_t batch_stride_dst, hipStream_t stream, const lvx_pack_job_t *values) {
     lvx_status_t st = check_rope_desc(desc);
     if (st != LVX_OK) return st;
     LVX_REQUIRE(n_batch >= 0 && n_batch <= LVX_GEMM_MAX_SEGS, LVX_ERR_INVALID_ARG, "norm to packed K: %d batches (0..%d)", n_batch, LVX_GEMM_MAX_SEGS);
@@ -375,7 +393,7 @@ lvx_status_t lvx_launch_norm_to_packed_k(const lvx_rope_desc_t *desc, const void
     gt.n = n_batch;
     for (int b = 0; b < n_batch; ++b) gt.g[b] = gains[b];
     return launch_rope(&norm_only, nullptr, src, ld_src, nullptr, nullptr, n_tokens, 0, nullptr, k_packed, desc->head_dim,
-                       (int64_t)cap * desc->head_dim, stream, n_batch, batch_stride_src, batch_stride_dst, src_is_f32 ? 1 : 0, &gt);
+                       (int64_t)cap * desc->head_dim, stream, n_batch, batch_stride_src, batch_stride_dst, src_is_f32 ? 1 : 0, &gt, -1, 1.0f, -1, -1, values);
 }
 
 lvx_status_t lvx_launch_rmsnorm_f32(const lvx_rope_desc_t *desc, const float *x, int64_t ld_in, const float *g, int n_tokens, float *y,
@@ -390,7 +408,7 @@ lvx_status_t lvx_launch_rmsnorm_f32(const lvx_rope_desc_t *desc, const float *x,
 #define LVX_NORM32_LAUNCH(CPL)                                                                                                     \
     hipLaunchKernelGGL((lvx_rope_norm_kernel<CPL, 1, true>), grid, block, 0, stream, (const void *)nullptr, (const void *)x, ld_in, ld_in, \
                        (const float *)nullptr, g, n_tokens, 0, (bf16_t *)nullptr, (bf16_t *)y, ld_out, (int64_t)desc->head_dim, d,    \
-                       desc->head_dim, desc->frame_h, desc->frame_w, desc->eps, 0, tab, 1, (int64_t)0, (int64_t)0, gain_table_t{}, 1.0f, ld_out, (int64_t)desc->head_dim)
+                       desc->head_dim, desc->frame_h, desc->frame_w, desc->eps, 0, tab, 1, (int64_t)0, (int64_t)0, gain_table_t{}, 1.0f, ld_out, (int64_t)desc->head_dim, lvx_pack_job_t{}, 0)
     if (cpl <= 2)
         LVX_NORM32_LAUNCH(2);
     else if (cpl <= 10)
