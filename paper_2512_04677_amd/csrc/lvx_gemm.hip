@@ -11,9 +11,9 @@
 // Workgroup ids are dealt to XCDs round-robin by hardware; each XCD gets a contiguous range of tiles, walked in
 // column-major order inside bands of 8 row tiles, so concurrently running workgroups of one XCD share A and W slabs in
 // that XCD's L2.
-// The same kernel serves the decoder's 3x3x3 convolution as an implicit GEMM (CONV): its A rows are gathered from a
-// zero-padded volume, a tap being a constant shift of the row addresses.
-#include "lvx_gemm_core.h"
+// The same kernel serves the decoder's 3x3x3 convolution as an implicit GEMM (CONV) where its tiles fill the chip: its A rows are
+// gathered from a zero-padded volume, a tap being a constant shift of the row addresses.
+#include "lvx_conv_gemm.h"
 
 namespace {
 
@@ -364,44 +364,51 @@ extern "C" lvx_status_t lvx_linear_dual(const void *dev_a, int64_t lda, const vo
                                   (bf16_t *)dev_c2, ldc2, M, N1, N2, K, (hipStream_t)stream);
 }
 
-// The small tile of a convolution, or -1 for the 256 x 128 kernel: least rounds of the chip times slabs times time per slab, as for the
-// linears.  The number of K groups (the order of summation) follows from max_m, the pixels of the longest step the layer takes, so
-// that a pixel's bits do not depend on how many frames arrive with it.
-static int pick_conv_tile(int M, int max_m, int N, int n_slabs) {
-    int groups = 0, best = -1;
-    for (int pass = 0; pass < 2; ++pass) {
-        const int m = pass == 0 ? max_m : M;
-        auto rounds = [&](int bm, int bn) { return (double)(((long)((m + bm - 1) / bm) * ((N + bn - 1) / bn) + 255) / 256); };
-        double best_cost = groups <= 1 ? rounds(256, 128) * n_slabs * LVX_GEMM_SLAB_US_128X256 : 1e30;
-        int best_groups = 1;
-        best = -1;
-#define LVX_TILE_COST(ID_, BM_, BN_, WM_, WN_, NST_, KG_, PC_, US_)                   \
-    if (groups == 0 || KG_ == groups) {                                               \
-        const double c_ = rounds(BM_, BN_) * ((n_slabs + KG_ - 1) / KG_ * KG_) * US_; \
-        if (c_ < best_cost) best_cost = c_, best = ID_, best_groups = KG_;            \
-    }
-        LVX_GEMM_SMALL_TILES(LVX_TILE_COST)
-#undef LVX_TILE_COST
-        groups = best_groups;
-    }
-    return best;
-}
-
-// Implicit-GEMM 3x3x3 convolution: rows = output pixels, K = 27 taps x C channels gathered from the padded volume P.
-// 256 x 128 tiles where they fill the chip (C_out is 128 ... 512 in the decoder this serves; 128-wide column tiles waste nothing
-// there), small tiles below that: one 50 x 90 frame, 384 -> 192 channels, is 36 large
-// tiles on 256 compute units, 213 of 64 x 64 (a whole step of it 119 -> 61 us, with the history's move fused: see lvx_conv.hip).
+// Implicit-GEMM 3x3x3 convolution: rows = output pixels, K = 27 taps x C channels gathered from the padded volume P.  The kernel is the
+// one with the least rounds of the chip times slabs (or stages of three) times time of each: the 256 x 128 tiles of the linears' kernel
+// where they fill the chip (C_out is 128 ... 512 in the decoder this serves; 128-wide column tiles waste nothing there), the tiles with shared
+// input rows below that and where their rounds come out better, the 32 x 32 tile with four K groups for a few thousand outputs.  The kinds differ in the order of
+// summation, so the kind follows from max_m, the pixels of the longest step the layer takes: a pixel's bits do not depend on how many
+// frames arrive with it.  Measured (us a step, before: 256 x 128 only or the linears' small tiles): one 50 x 90 frame 384 -> 192 channels
+// 119, 61 -> 45; four 25 x 45 frames 512 -> 512 146 -> 105; four 240 x 400 64 -> 64 199 -> 139; two 200 x 360 192 -> 96 238 -> 202.
 lvx_status_t lvx_launch_conv_gemm(const bf16_t *P, const lvx_conv_map_t &cm, const bf16_t *Wt, int64_t ldw, const float *bias, int act,
                                   bf16_t *Y, int64_t ldy, int M, int max_m, int N, hipStream_t stream) {
-    const int K = 27 * cm.C, epi = act ? (int)LVX_EPI_BIAS_SILU : (int)LVX_EPI_BIAS;
-    const int tile = pick_conv_tile(M, max_m, N, K / BK);
-    if (tile < 0) return launch<256, 128, 4, 2, true>(P, 0, Wt, ldw, Y, ldy, M, N, K, epi, nullptr, 0, bias, stream, nullptr, &cm);
+    const int K = 27 * cm.C, n_slabs = K / BK, epi = act ? (int)LVX_EPI_BIAS_SILU : (int)LVX_EPI_BIAS;
+    enum { LARGE, ROWS, GROUPS };
+    int kind = -1, tile = -1;
+    for (int pass = 0; pass < 2; ++pass) {  // 0: the kind, at the longest step; 1: the tile, at this one
+        const int m = pass == 0 ? max_m : M;
+        double best = 1e30;
+        int best_kind = kind;
+        auto rounds = [&](long rows, int bm, int bn) { return (double)(((rows + bm - 1) / bm * ((N + bn - 1) / bn) + 255) / 256); };
+        auto offer = [&](int k, int id, double us) {
+            if ((kind < 0 || k == kind) && us < best) best = us, best_kind = k, tile = id;
+        };
+        offer(LARGE, 0, rounds(m, 256, 128) * n_slabs * 0.82);
+        const long padded = (long)m / cm.W * (cm.W + 2);
+#define LVX_TILE_COST(ID_, BM_, BN_, WM_, WN_, NST_, US_) offer(ROWS, ID_, rounds(padded, BM_, BN_) * (n_slabs / 3) * US_);
+        LVX_CONV_ROW_TILES(LVX_TILE_COST)
+#undef LVX_TILE_COST
+#define LVX_TILE_COST(ID_, BM_, BN_, WM_, WN_, NST_, KG_, PC_, US_) \
+    if (KG_ > 2) offer(GROUPS, ID_, rounds(m, BM_, BN_) * ((n_slabs + KG_ - 1) / KG_ * KG_) * US_);
+        LVX_GEMM_SMALL_TILES(LVX_TILE_COST)
+#undef LVX_TILE_COST
+        kind = best_kind;
+    }
+    if (kind == LARGE) return launch<256, 128, 4, 2, true>(P, 0, Wt, ldw, Y, ldy, M, N, K, epi, nullptr, 0, bias, stream, nullptr, &cm);
+    if (kind == ROWS) {
+        lvx_conv_args_t c = {(const char *)P, (const char *)Wt, ldw * 2, Y, ldy, bias, M / cm.W * (cm.W + 2), N, n_slabs / 3, act, 0, 0, 0, 0, cm};
+#define LVX_TILE_LAUNCH(ID_, BM_, BN_, WM_, WN_, NST_, US_) \
+    if (tile == ID_) return lvx_conv_rows_launch<BM_, BN_, WM_, WN_, NST_>(c, stream);
+        LVX_CONV_ROW_TILES(LVX_TILE_LAUNCH)
+#undef LVX_TILE_LAUNCH
+    }
     lvx_gemm_args_t p = {};
     p.A = (const char *)P;
     p.W = (const char *)Wt, p.ldw = ldw * 2;
     p.C = Y, p.ldc = ldy;
     p.gate = bias;
-    p.M = M, p.N = N, p.n_slabs = K / BK;
+    p.M = M, p.N = N, p.n_slabs = n_slabs;
     p.epi = epi;
     p.conv = cm;
     return lvx_gemm_launch_small<false, true>(tile, p, stream);

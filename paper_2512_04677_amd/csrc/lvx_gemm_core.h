@@ -449,7 +449,8 @@ static lvx_status_t lvx_gemm_launch_small(int tile, lvx_gemm_args_t &p, hipStrea
         for (int i = 0, t = 0; i < p.segs.n; ++i) p.segs.s[i].tn_begin = t, t += (p.segs.s[i].N + BN_ - 1) / BN_;                       \
         p.per_xcd = (p.tiles_m * p.tiles_n + 7) / 8;                                                                                    \
         p.group_m = 8;                                                                                                                  \
-        hipLaunchKernelGGL((lvx_gemm_tile_kernel<BM_, BN_, WM_, WN_, NST_, KG_, FP8, CONV>), dim3(p.per_xcd * 8), dim3(64 * WM_ * WN_ * KG_), 0, stream, p); \
+        if constexpr (!CONV || KG_ > 2)  /* convolutions have tiles of their own above the smallest */                                 \
+            hipLaunchKernelGGL((lvx_gemm_tile_kernel<BM_, BN_, WM_, WN_, NST_, KG_, FP8, CONV>), dim3(p.per_xcd * 8), dim3(64 * WM_ * WN_ * KG_), 0, stream, p); \
         break;                                                                                                                          \
     }
     switch (tile) { LVX_GEMM_SMALL_TILES(LVX_TILE_LAUNCH) }

@@ -78,10 +78,12 @@ def test_linear_bias_and_silu_epilogues(lvx):
 
 @pytest.mark.parametrize("H,W,Ci,Co,frames", [
     (7, 5, 64, 24, 3),          # 32 x 32 tiles, four K groups, 27 slabs
-    (31, 33, 64, 136, 2),       # 32 x 64, two groups, ragged rows and columns
-    (45, 45, 64, 136, 2),       # 64 x 64 (groups decided by the two-frame step)
-    (77, 79, 64, 136, 1),       # 64 x 128
-    (110, 111, 64, 136, 1),     # 256 x 128
+    (45, 45, 64, 136, 2),       # shared rows, 64 x 64, ragged rows and columns
+    (77, 79, 128, 136, 1),      # shared rows, 128 x 64
+    (100, 101, 64, 72, 2),      # shared rows, 256 x 64 for two frames, 128 x 64 for one
+    (150, 151, 64, 136, 1),     # shared rows, 192 x 128
+    (2, 2, 64, 600, 160),       # rows of two pixels: tiles across many frames
+    (181, 181, 64, 256, 1),     # 256 x 128
 ])
 def test_conv_tiles_and_chunking(lvx, H, W, Ci, Co, frames):
     """Every tile the rule can pick, against the oracle; a frame's bits do not depend on how many frames arrive with it."""
