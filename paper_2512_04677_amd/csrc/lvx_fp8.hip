@@ -199,16 +199,23 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N)
         dst_[0] = (int)lo_[0], dst_[1] = (int)lo_[1], dst_[2] = (int)lo_[2], dst_[3] = (int)lo_[3];   \
         dst_[4] = (int)hi_[0], dst_[5] = (int)hi_[1], dst_[6] = (int)hi_[2], dst_[7] = (int)hi_[3];   \
     }
-#define LVX8_READ_FRAGS(stage_, kk_)                                                                  \
+#define LVX8_READ_A(stage_, kk_, i0_, i1_)                                                            \
     {                                                                                                 \
         const int c0_ = (((kk_) * 4 + 2 * hh) ^ swz) * 16 + (stage_) * STAGE_B;                        \
         const int c1_ = (((kk_) * 4 + 2 * hh + 1) ^ swz) * 16 + (stage_) * STAGE_B;                    \
-        _Pragma("unroll") for (int i = 0; i < FM; ++i) LVX8_READ_ONE(af[(kk_) & 1][i], a_rd + i * 32 * ROW_B); \
+        _Pragma("unroll") for (int i = i0_; i < i1_; ++i) LVX8_READ_ONE(af[(kk_) & 1][i], a_rd + i * 32 * ROW_B); \
+    }
+#define LVX8_READ_W(stage_, kk_)                                                                      \
+    {                                                                                                 \
+        const int c0_ = (((kk_) * 4 + 2 * hh) ^ swz) * 16 + (stage_) * STAGE_B;                        \
+        const int c1_ = (((kk_) * 4 + 2 * hh + 1) ^ swz) * 16 + (stage_) * STAGE_B;                    \
         _Pragma("unroll") for (int j = 0; j < FN; ++j) LVX8_READ_ONE(wf[(kk_) & 1][j], w_rd + j * 32 * ROW_B); \
     }
-#define LVX8_MFMAS(kk_)                                                                                          \
-    _Pragma("unroll") for (int i = 0; i < FM; ++i) _Pragma("unroll") for (int j = 0; j < FN; ++j)                \
+#define LVX8_MFMAS(kk_, i0_, i1_)                                                                                \
+    _Pragma("unroll") for (int i = i0_; i < i1_; ++i) _Pragma("unroll") for (int j = 0; j < FN; ++j)             \
         acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(af[(kk_) & 1][i], wf[(kk_) & 1][j], acc[i][j], 0, 0, 0, 0, 0, 0);
+#define LVX8_DMA_THIRD(third_) \
+    _Pragma("unroll") for (int q = 0; q < QPW; ++q) if ((q * 3) / QPW == (third_)) LVX8_DMA_ISSUE(nx2, kt_load, q);
 
     f32x16_t acc[FM][FN];
 #pragma unroll
@@ -247,27 +254,39 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N)
     for (int q = 0; q < QPW; ++q) LVX8_DMA_ISSUE(1, (last < 1 ? last : 1), q);
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(QPW) : "memory");
     __syncthreads();
-    LVX8_READ_FRAGS(0, 0);
+    LVX8_READ_A(0, 0, 0, FM);
+    LVX8_READ_W(0, 0);
 
-    // Slab t is in stage t % 3.  Per slab: the first k-step's MFMAs run while the second k-step's fragments are read and the
-    // DMA for slab t+2 is issued (into the stage that was last read during slab t-1, before that slab's barrier); then this
-    // wave's DMA for slab t+1 must have landed, one workgroup barrier, and the second k-step's MFMAs run while k-step 0 of
-    // slab t+1 is read.
+    // Slab t is in stage t % 3.  Per slab four MFMA groups (each k-step as two halves of the accumulator rows): the first three read the
+    // fragments still missing for what follows and issue a third of the DMA for slab t+2 each (into the stage that was read
+    // during slab t-1); then this wave's DMA for slab t+1 must have landed, one workgroup barrier, and the fourth group, which
+    // already reads k-step 0 of slab t+1.  (Two groups per slab, with all loads and the barrier in the middle, before: 4680 x 15360 x 5120 325
+    // -> 319 us, 4680 x 13824 x 5120 293 -> 284.)
     int cur = 0, nxt = 1, nx2 = 2;
     for (int t = 0; t < n_k; ++t) {
         const int kt_load = t + 2 < last ? t + 2 : last;
-        LVX8_READ_FRAGS(cur, 1);
+        LVX8_READ_W(cur, 1);
         __builtin_amdgcn_sched_barrier(0);
-        LVX8_MFMAS(0);
-#pragma unroll
-        for (int q = 0; q < QPW; ++q) LVX8_DMA_ISSUE(nx2, kt_load, q);
+        LVX8_MFMAS(0, 0, FM / 2);
+        LVX8_DMA_THIRD(0);
+        __builtin_amdgcn_sched_barrier(0);
+        LVX8_READ_A(cur, 1, 0, FM / 2);
+        __builtin_amdgcn_sched_barrier(0);
+        LVX8_MFMAS(0, FM / 2, FM);
+        LVX8_DMA_THIRD(1);
+        __builtin_amdgcn_sched_barrier(0);
+        LVX8_READ_A(cur, 1, FM / 2, FM);
+        __builtin_amdgcn_sched_barrier(0);
+        LVX8_MFMAS(1, 0, FM / 2);
+        LVX8_DMA_THIRD(2);
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(QPW) : "memory");
         __syncthreads();
         __builtin_amdgcn_sched_barrier(0);
-        LVX8_READ_FRAGS(nxt, 0);
+        LVX8_READ_A(nxt, 0, 0, FM);
+        LVX8_READ_W(nxt, 0);
         __builtin_amdgcn_sched_barrier(0);
-        LVX8_MFMAS(1);
+        LVX8_MFMAS(1, FM / 2, FM);
         __builtin_amdgcn_sched_barrier(0);
         const int tmp = cur;
         cur = nxt;
