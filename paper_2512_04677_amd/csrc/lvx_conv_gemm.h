@@ -138,7 +138,7 @@ __global__ void __launch_bounds__(64 * WM * WN) lvx_conv_rows_kernel(const lvx_c
     X_(0, 64, 64, 2, 4, 4, 0.70)       \
     X_(1, 128, 64, 4, 2, 3, 0.90)      \
     X_(2, 256, 64, 4, 2, 2, 1.48)      \
-    X_(3, 192, 128, 4, 2, 2, 1.95)
+    X_(3, 192, 128, 4, 2, 2, 2.00)
 
 template <int BM, int BN, int WM, int WN, int NST>
 static lvx_status_t lvx_conv_rows_launch(lvx_conv_args_t &p, hipStream_t stream) {
