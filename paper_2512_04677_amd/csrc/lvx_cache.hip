@@ -40,11 +40,8 @@ __global__ void __launch_bounds__(256) lvx_fill_zero_kernel(uint4 *p, size_t n16
 template <int D>
 __global__ void __launch_bounds__(256) lvx_pack_kv_kernel(const bf16_t *__restrict__ k, const bf16_t *__restrict__ v, int64_t ld,
                                                           int n, int cap, int key0, int tile0, bf16_t *__restrict__ kp,
-                                                          bf16_t *__restrict__ vtp, int64_t batch_stride_src, int64_t batch_stride_dst) {
-    // blockIdx.z: independent row set / packed array
-    if (k != nullptr) k += (size_t)blockIdx.z * batch_stride_src;
-    lvx_pack_tile<D>(k, v + (size_t)blockIdx.z * batch_stride_src, ld, n, cap, key0, tile0 + blockIdx.x, blockIdx.y, kp + (size_t)blockIdx.z * batch_stride_dst,
-                     vtp + (size_t)blockIdx.z * batch_stride_dst);
+                                                          bf16_t *__restrict__ vtp) {
+    lvx_pack_tile<D>(k, v, ld, n, cap, key0, tile0 + blockIdx.x, blockIdx.y, kp, vtp);
 }
 
 // Inverse of the pack: thread = (key, head, 16-byte chunk).  Check / off-load path, not tuned.
@@ -162,18 +159,15 @@ lvx_status_t lvx_launch_fill_zero(void *dst, size_t bytes, hipStream_t stream) {
 }
 
 lvx_status_t lvx_launch_pack_kv(const bf16_t *k, const bf16_t *v, int64_t ld, int n, int H, int D, int cap, int key0,
-                                bf16_t *k_packed, bf16_t *vt_packed, hipStream_t stream, int n_batch, int64_t batch_stride_src,
-                                int64_t batch_stride_dst) {
-    if (n <= 0 || n_batch <= 0) return LVX_OK;
+                                bf16_t *k_packed, bf16_t *vt_packed, hipStream_t stream) {
+    if (n <= 0) return LVX_OK;
     const int tile0 = key0 / LVX_KEY_TILE;
     const int tile1 = (key0 + n - 1) / LVX_KEY_TILE;
-    dim3 grid(tile1 - tile0 + 1, H, n_batch);
+    dim3 grid(tile1 - tile0 + 1, H);
     if (D == 128)
-        hipLaunchKernelGGL(lvx_pack_kv_kernel<128>, grid, dim3(256), 0, stream, k, v, ld, n, cap, key0, tile0, k_packed, vt_packed,
-                           batch_stride_src, batch_stride_dst);
+        hipLaunchKernelGGL(lvx_pack_kv_kernel<128>, grid, dim3(256), 0, stream, k, v, ld, n, cap, key0, tile0, k_packed, vt_packed);
     else if (D == 64)
-        hipLaunchKernelGGL(lvx_pack_kv_kernel<64>, grid, dim3(256), 0, stream, k, v, ld, n, cap, key0, tile0, k_packed, vt_packed,
-                           batch_stride_src, batch_stride_dst);
+        hipLaunchKernelGGL(lvx_pack_kv_kernel<64>, grid, dim3(256), 0, stream, k, v, ld, n, cap, key0, tile0, k_packed, vt_packed);
     else
         return lvx_fail(LVX_ERR_UNSUPPORTED, "head_dim %d not supported (64 or 128)", D);
     LVX_CHECK_HIP(hipGetLastError());

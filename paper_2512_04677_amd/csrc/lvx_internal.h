@@ -88,10 +88,8 @@ static inline const bf16_t *lvx_cache_vt(const lvx_kvcache *c, int layer) { retu
 
 // ---- internal launchers (all enqueue on `stream`, arguments already validated) ----------------
 // Token-major K/V rows [n][ld] -> packed K [H][cap][D] rows key0.. and V^T tiles [H][cap/64][D][64] (k NULL: values only).
-// n_batch > 1: that many independent row sets / packed arrays, batch_stride_src / batch_stride_dst elements apart.
 lvx_status_t lvx_launch_pack_kv(const bf16_t *k, const bf16_t *v, int64_t ld, int n, int H, int D, int cap, int key0,
-                                bf16_t *k_packed, bf16_t *vt_packed, hipStream_t stream, int n_batch = 1, int64_t batch_stride_src = 0,
-                                int64_t batch_stride_dst = 0);
+                                bf16_t *k_packed, bf16_t *vt_packed, hipStream_t stream);
 // Attention of q [n_q][ld_q] against packed K / V^T holding n_keys visible keys per head.
 // Optional transform of the queries as the attention kernel loads them: RMSNorm over all d_model channels with the row's sum of
 // squares given as n_parts partial sums (lvx_gemm_seg_t::sumsq) and a per-channel gain; the kernel also multiplies by
