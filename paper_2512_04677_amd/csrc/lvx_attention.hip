@@ -25,7 +25,8 @@
 //     workgroup ids round-robin over the 8 XCDs), so a head's K/V stream is fetched into one L2 only.
 //   * KS = 2 (few queries: see split_keys): the halves of the workgroup, which run half a period apart anyway, take the same 128 queries
 //     and different key tiles instead of different queries and the same tiles; a stage then carries two tiles, one for each half,
-//     and the halves' outputs meet in LDS at the end.
+//     and the halves' outputs meet in LDS at the end.  Both halves start from the first tile's row maximum (the second half, half a
+//     period behind, finds it in LDS): a later tile of scores that are all -inf then adds nothing, whichever half it falls to.
 //   * template switches: TP = 64-key tiles per pipeline phase (2 from 1024 visible keys on: half the barriers, pipeline fills and
 //     drains per key); PRE = the queries arrive multiplied by scale * log2(e) and the score accumulators start at minus the
 //     softmax reference, so a score leaves the MFMA as the exponent (one FMA per score less; used inside a block, where the
@@ -71,6 +72,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
 
     __shared__ __attribute__((aligned(1024))) char ks[NS * TILE_B];
     __shared__ __attribute__((aligned(1024))) char vs[NS * TILE_B];
+    __shared__ float first_ref[KS == 2 ? NWAVES / 2 * QB * 16 : 1];  // KS = 2: the first half's references, for the second half
 
     // XCD-aware decode: consecutive block ids go to consecutive XCDs; give each XCD a contiguous range of work
     const int xcd = blockIdx.x & 7;
@@ -267,8 +269,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
         __builtin_amdgcn_s_setprio(2); /* the matrix phase wins instruction arbitration over the other wave's VALU */ \
         const char *vr[TP], *kr[TP];                                                                           \
         _Pragma("unroll") for (int i_ = 0; i_ < TP; ++i_) {                                                    \
-            vr[i_] = vs + ((TS * (j_) + kg + i_) & (NS - 1)) * TILE_B;                                              \
-            kr[i_] = ks + ((TS * ((j_) + 1) + kg + i_) & (NS - 1)) * TILE_B;                                        \
+            vr[i_] = vs + ((TS * (j_) + kg + i_) & (NS - 1)) * TILE_B;                                         \
+            kr[i_] = ks + ((TS * ((j_) + 1) + kg + i_) & (NS - 1)) * TILE_B;                                   \
         }                                                                                                      \
         bf16x8_t fr[PD];                                                                                       \
         _Pragma("unroll") for (int f = 0; f < PD; ++f) fr[f] = LVX_ATTN_FRAG(f);                               \
@@ -313,7 +315,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
            maximum as the new reference and the accumulators rescaled.  The four lane groups that share a query decide     \
            together (wave-wide vote); the final division by the row sum absorbs whatever reference was used. */            \
         float lsum[QB];                                                                                        \
-        bool rebase_ = (t_) == 0;                                                                              \
+        bool rebase_ = (t_) == 0 && kg == 0;                                                                   \
         for (;;) {                                                                                             \
             if (rebase_) {                                                                                     \
                 _Pragma("unroll") for (int qb = 0; qb < QB; ++qb) {                                            \
@@ -322,7 +324,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
                         tmax = fmaxf(tmax, s[kb][qb][e]);                                                      \
                     tmax = fmaxf(tmax, __shfl_xor(tmax, 16));                                                  \
                     tmax = fmaxf(tmax, __shfl_xor(tmax, 32));                                                  \
-                    const bool first_ = (t_) == 0;                                                             \
+                    const bool first_ = (t_) == 0 && kg == 0;                                                  \
                     const float tmc = PRE ? tmax + sub[qb] : tmax * c_exp2;                                    \
                     const bool need = first_ || tmc > mc[qb] + 6.0f;                                           \
                     const float alpha = (need && !first_) ? __builtin_amdgcn_exp2f(mc[qb] - tmc) : 1.0f;       \
@@ -386,6 +388,10 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
         LVX_ATTN_S0();
         __syncthreads();
         LVX_ATTN_Y(0);
+        if (KS == 2 && q4 == 0) {
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) first_ref[(qw * QB + qb) * 16 + l16] = mc[qb];
+        }
         __syncthreads();
         for (int i = 1; i < n_ph; ++i) {
             LVX_ATTN_STAGE_DMA(i);
@@ -402,6 +408,10 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
         __syncthreads();
         LVX_ATTN_S0();
         __syncthreads();
+        if (KS == 2) {
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) mc[qb] = first_ref[(qw * QB + qb) * 16 + l16];
+        }
         for (int i = 1; i <= n_ph; ++i) {
             if (i < n_ph) LVX_ATTN_STAGE_DMA(i);
             if (KS == 1 || i <= n_mine) LVX_ATTN_Y(i - 1);

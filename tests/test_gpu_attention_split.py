@@ -49,3 +49,44 @@ def test_attention_key_split_edges(lvx, D, H, prescaled):
                 worst = (np.abs(S.to_f64(out[:n_q, c]) - p @ V) / bound).max()
                 assert worst <= 1.0, (D, H, n_keys, n_q, h, worst)
         cache.close()
+
+
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("prescaled", [False, True])
+def test_later_tiles_without_a_finite_score(lvx, D, prescaled):
+    """Key tiles after the first whose scores are all -inf (finite keys and queries whose products overflow) carry no weight, whichever
+    half of a workgroup they fall to and whatever follows them."""
+    H = 2
+    d = H * D
+    for n_keys, dead in ((128, (1,)), (100, (1,)), (192, (1,)), (256, (1, 3)), (320, (1, 2)), (320, (1, 2, 3, 4)), (1090, (1, 2, 9, 17))):
+        cache = lvx.KVCache(lvx.cache_desc(1, H, D, 1, n_keys, 1, 1, 1), DEV)
+        k = S.randn_bf16((n_keys, d), S.seed_of("dt_k", D, n_keys), device=DEV)
+        v = S.randn_bf16((n_keys, d), S.seed_of("dt_v", D, n_keys), device=DEV)
+        q = S.randn_bf16((150, d), S.seed_of("dt_q", D, n_keys), device=DEV)
+        q[:, ::D] = 16.0                      # one channel of every head carries the tiles' fate
+        k[:, ::D] = 0.0
+        live = torch.ones(n_keys, dtype=torch.bool)
+        for t in dead:
+            k[64 * t:64 * t + 64, ::D] = -3.0e38
+            live[64 * t:64 * t + 64] = False
+        lvx.lvx_kvcache_set_sink(cache, 0, k, v)
+        scale = 1.0 / math.sqrt(D)
+        out = torch.empty((150, d), dtype=torch.bfloat16, device=DEV)
+        if prescaled:
+            lvx.lvx_chunk_attention_prescaled(cache, 0, q, out)
+            scale = math.log(2.0)
+        else:
+            lvx.lvx_chunk_attention(cache, 0, q, scale, out)
+        torch.cuda.synchronize()
+        live = live.numpy()
+        for h in range(H):
+            c = slice(h * D, (h + 1) * D)
+            Q, K, V = S.to_f64(q[:, c]), S.to_f64(k[:, c])[live], S.to_f64(v[:, c])[live]
+            s = scale * (Q @ K.T)
+            p = np.exp(s - s.max(axis=1, keepdims=True))
+            p /= p.sum(axis=1, keepdims=True)
+            got = S.to_f64(out[:, c])
+            assert np.isfinite(got).all(), (D, n_keys, dead, h)
+            bound = 1.1 * 2.0 ** -7 * (p @ np.abs(V)) + 1e-6      # as above
+            assert (np.abs(got - p @ V) / bound).max() <= 1.0, (D, n_keys, dead, h)
+        cache.close()
