@@ -23,7 +23,7 @@
 //     taken after the first tile); the final division by the row sum absorbs whatever reference was used.
 //   * workgroup -> (head, query tile) mapping keeps all query tiles of a head on one XCD (hardware deals consecutive
 //     workgroup ids round-robin over the 8 XCDs), so a head's K/V stream is fetched into one L2 only.
-//   * KS = 2 (few queries: see split_keys): the halves of the workgroup, which run half a period apart anyway, take the same 128 queries
+//   * KS = 2 (few queries: see lvx_attention_splits_keys): the halves of the workgroup, which run half a period apart anyway, take the same 128 queries
 //     and different key tiles instead of different queries and the same tiles; a stage then carries two tiles, one for each half,
 //     and the halves' outputs meet in LDS at the end.  Both halves start from the first tile's row maximum (the second half, half a
 //     period behind, finds it in LDS): a later tile of scores that are all -inf then adds nothing, whichever half it falls to.
@@ -508,22 +508,6 @@ lvx_status_t launch(const bf16_t *q, int64_t ld_q, int n_q, int H, const bf16_t 
     return LVX_OK;
 }
 
-// Whether a workgroup takes 128 queries and splits the keys over its halves (KS = 2) instead of 256 queries.  A round of the chip with
-// KS = 2 takes 0.62 to 0.66 of a round without (measured from 9 to 150 key tiles, head_dim 64 and 128: half the tiles per wave, but
-// twice the K / V stream per tile), so it pays where the smaller workgroups need less than half as many more rounds: always
-// while they fit one round, e.g. 12 heads x 1170 queries x 6240 keys 134 -> 90 us, but 20 x 1886 x 8487 (160 workgroups become 300)
-// 191 -> 236 us.  A last query tile of one or two waves' rows ends early and is not counted as a workgroup.  Up to 128 queries half
-// of the waves idle without the split; with less than 8 key tiles the exchange at the end then costs what it saves (9.3 against
-// 10.2 us at 4 tiles, 15.1 against 14.4 at 9).
-bool split_keys(int n_q, int H, int n_keys) {
-    if (n_q <= 128 && n_keys <= 7 * KT) return false;
-    auto rounds = [&](int qt) {
-        const long tiles = (n_q + qt - 1 - qt / 4) / qt;
-        return ((tiles > 0 ? tiles : 1) * H + 255) / 256;
-    };
-    return 0.65 * rounds(128) < rounds(256);
-}
-
 }  // namespace
 
 lvx_status_t lvx_launch_attention(const bf16_t *q, int64_t ld_q, int n_q, int H, int D, const bf16_t *k_packed,
@@ -533,7 +517,7 @@ lvx_status_t lvx_launch_attention(const bf16_t *q, int64_t ld_q, int n_q, int H,
                 n_keys, cap);
     LVX_REQUIRE(scale > 0.f, LVX_ERR_INVALID_ARG, "attention: scale must be positive");
     LVX_REQUIRE(D == 64 || D == 128, LVX_ERR_UNSUPPORTED, "head_dim %d not supported (64 or 128)", D);
-    const bool two = split_keys(n_q, H, n_keys);
+    const bool two = lvx_attention_splits_keys(n_q, H, n_keys);
 #define LVX_ATTN_LAUNCH(D_, TP_, PRE_, QN_, KS_) \
     launch<D_, TP_, PRE_, QN_, KS_>(q, ld_q, n_q, H, k_packed, vt_packed, cap, n_keys, scale, out, ld_out, stream, amax_slots, qnorm)
     if (qnorm != nullptr) {  // the kernel normalises and scales the queries as it loads them (cross-attention of a bf16 stage)

@@ -133,13 +133,6 @@ __global__ void __launch_bounds__(64 * WM * WN) lvx_conv_rows_kernel(const lvx_c
         }
 }
 
-// id, BM, BN, WM, WN, NST and the time in microseconds that a compute unit needs per stage (64 channels of three taps)
-#define LVX_CONV_ROW_TILES(X_)         \
-    X_(0, 64, 64, 2, 4, 4, 0.70)       \
-    X_(1, 128, 64, 4, 2, 3, 0.90)      \
-    X_(2, 256, 64, 4, 2, 2, 1.48)      \
-    X_(3, 192, 128, 4, 2, 2, 2.00)
-
 template <int BM, int BN, int WM, int WN, int NST>
 static lvx_status_t lvx_conv_rows_launch(lvx_conv_args_t &p, hipStream_t stream) {
     p.tiles_m = (p.M + BM - 1) / BM;

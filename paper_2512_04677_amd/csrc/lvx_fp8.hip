@@ -416,10 +416,9 @@ lvx_status_t lvx_launch_linear_fp8(const void *dev_aq, int64_t lda, const float 
         LVX_REQUIRE(ldr >= N, LVX_ERR_SHAPE, "bad residual leading dimension");
     }
     if (M == 0) return LVX_OK;
-    double us = 0;
-    int tile = lvx_gemm_pick_tile(nullptr, M, N, K / 128, false, &us), m1 = 0;  // m1: rows the 128 x 256 kernel takes, the others go to a small tile
-    if (tile < 0) {
-        m1 = lvx_gemm_split_rows(nullptr, M, N, K / 128, us, &tile);
+    const lvx_gemm_plan_t plan = lvx_gemm_plan(nullptr, M, N, K / 128, false);
+    const int m1 = plan.m1;  // rows the 128 x 256 kernel takes, the others go to a small tile
+    if (m1 > 0 || plan.tile == LVX_GEMM_TILE_128X256) {
         const int rows = m1 > 0 ? m1 : M;
         constexpr int BM = 128, BN = 256;
         const int tiles_m = (rows + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
@@ -455,7 +454,7 @@ lvx_status_t lvx_launch_linear_fp8(const void *dev_aq, int64_t lda, const float 
     p.amax = amax_slots;
     p.M = M - m1, p.N = N, p.n_slabs = K / 128;
     p.epi = (int)epi;
-    return lvx_gemm_launch_small<true>(tile, p, stream);
+    return lvx_gemm_launch_small<true>(plan.tile, p, stream);
 }
 
 extern "C" lvx_status_t lvx_linear_fp8(const void *dev_aq, int64_t lda, const float *dev_scale_a, const void *dev_wq, int64_t ldw,

@@ -282,14 +282,11 @@ lvx_status_t launch(const bf16_t *A, int64_t lda, const bf16_t *W, int64_t ldw, 
 // The linears: the 128 x 256 kernel, a small tile where that one would leave compute units idle, or both for different rows.
 lvx_status_t launch_linear(const bf16_t *A, int64_t lda, const bf16_t *W, int64_t ldw, bf16_t *C, int64_t ldc, int M, int N, int K, int epi,
                            const bf16_t *R, int64_t ldr, const float *gate, hipStream_t stream, const lvx_gemm_segs_t *segs = nullptr) {
-    double us = 0;
     const bool sumsq = segs != nullptr && segs->s[0].sumsq != nullptr;  // (a 48-column wave cannot give sums of 64 columns)
-    int tile = lvx_gemm_pick_tile(segs, M, N, K / BK, !sumsq, &us), m1 = 0;  // m1: rows the 128 x 256 kernel takes of a split product
-    if (tile < 0) {
-        int rest = tile;
-        m1 = lvx_gemm_split_rows(segs, M, N, K / BK, us, &rest);
-        if (m1 == 0 && tile == LVX_GEMM_TILE_128X192) return launch<128, 192, 2, 4>(A, lda, W, ldw, C, ldc, M, N, K, epi, R, ldr, gate, stream, segs);
-        tile = rest;
+    const lvx_gemm_plan_t plan = lvx_gemm_plan(segs, M, N, K / BK, !sumsq);
+    const int m1 = plan.m1;  // rows the 128 x 256 kernel takes of a split product
+    if (m1 == 0 && plan.tile == LVX_GEMM_TILE_128X192) return launch<128, 192, 2, 4>(A, lda, W, ldw, C, ldc, M, N, K, epi, R, ldr, gate, stream, segs);
+    if (m1 > 0 || plan.tile == LVX_GEMM_TILE_128X256) {
         LVX_TRY((launch<128, 256, 2, 4>(A, lda, W, ldw, C, ldc, m1 > 0 ? m1 : M, N, K, epi, R, ldr, gate, stream, segs)));
         if (m1 == 0) return LVX_OK;
     }
@@ -305,7 +302,7 @@ lvx_status_t launch_linear(const bf16_t *A, int64_t lda, const bf16_t *W, int64_
     p.epi = epi;
     if (segs != nullptr) p.segs = *segs;
     for (int i = 0; i < p.segs.n; ++i) p.segs.s[i].C = (char *)p.segs.s[i].C + (size_t)m1 * p.segs.s[i].ldc * (p.segs.s[i].f32 ? 4 : 2);
-    return lvx_gemm_launch_small<false>(tile, p, stream);
+    return lvx_gemm_launch_small<false>(plan.tile, p, stream);
 }
 
 }  // namespace
@@ -364,42 +361,17 @@ extern "C" lvx_status_t lvx_linear_dual(const void *dev_a, int64_t lda, const vo
                                   (bf16_t *)dev_c2, ldc2, M, N1, N2, K, (hipStream_t)stream);
 }
 
-// Implicit-GEMM 3x3x3 convolution: rows = output pixels, K = 27 taps x C channels gathered from the padded volume P.  The kernel is the
-// one with the least rounds of the chip times slabs (or stages of three) times time of each: the 256 x 128 tiles of the linears' kernel
-// where they fill the chip (C_out is 128 ... 512 in the decoder this serves; 128-wide column tiles waste nothing there), the tiles with shared
-// input rows below that and where their rounds come out better, the 32 x 32 tile with four K groups for a few thousand outputs.  The kinds differ in the order of
-// summation, so the kind follows from max_m, the pixels of the longest step the layer takes: a pixel's bits do not depend on how many
-// frames arrive with it.  Measured (us a step, before: 256 x 128 only or the linears' small tiles): one 50 x 90 frame 384 -> 192 channels
-// 119, 61 -> 45; four 25 x 45 frames 512 -> 512 146 -> 105; four 240 x 400 64 -> 64 199 -> 139; two 200 x 360 192 -> 96 238 -> 202.
+// Implicit-GEMM 3x3x3 convolution: rows = output pixels, K = 27 taps x C channels gathered from the padded volume P; lvx_conv_plan says
+// which kernel.
 lvx_status_t lvx_launch_conv_gemm(const bf16_t *P, const lvx_conv_map_t &cm, const bf16_t *Wt, int64_t ldw, const float *bias, int act,
                                   bf16_t *Y, int64_t ldy, int M, int max_m, int N, hipStream_t stream) {
     const int K = 27 * cm.C, n_slabs = K / BK, epi = act ? (int)LVX_EPI_BIAS_SILU : (int)LVX_EPI_BIAS;
-    enum { LARGE, ROWS, GROUPS };
-    int kind = -1, tile = -1;
-    for (int pass = 0; pass < 2; ++pass) {  // 0: the kind, at the longest step; 1: the tile, at this one
-        const int m = pass == 0 ? max_m : M;
-        double best = 1e30;
-        int best_kind = kind;
-        auto rounds = [&](long rows, int bm, int bn) { return (double)(((rows + bm - 1) / bm * ((N + bn - 1) / bn) + 255) / 256); };
-        auto offer = [&](int k, int id, double us) {
-            if ((kind < 0 || k == kind) && us < best) best = us, best_kind = k, tile = id;
-        };
-        offer(LARGE, 0, rounds(m, 256, 128) * n_slabs * 0.82);
-        const long padded = (long)m / cm.W * (cm.W + 2);
-#define LVX_TILE_COST(ID_, BM_, BN_, WM_, WN_, NST_, US_) offer(ROWS, ID_, rounds(padded, BM_, BN_) * (n_slabs / 3) * US_);
-        LVX_CONV_ROW_TILES(LVX_TILE_COST)
-#undef LVX_TILE_COST
-#define LVX_TILE_COST(ID_, BM_, BN_, WM_, WN_, NST_, KG_, PC_, US_) \
-    if (KG_ > 2) offer(GROUPS, ID_, rounds(m, BM_, BN_) * ((n_slabs + KG_ - 1) / KG_ * KG_) * US_);
-        LVX_GEMM_SMALL_TILES(LVX_TILE_COST)
-#undef LVX_TILE_COST
-        kind = best_kind;
-    }
-    if (kind == LARGE) return launch<256, 128, 4, 2, true>(P, 0, Wt, ldw, Y, ldy, M, N, K, epi, nullptr, 0, bias, stream, nullptr, &cm);
-    if (kind == ROWS) {
+    const lvx_conv_plan_t plan = lvx_conv_plan(cm.W, N, n_slabs, M, max_m);
+    if (plan.kind == LVX_CONV_LARGE) return launch<256, 128, 4, 2, true>(P, 0, Wt, ldw, Y, ldy, M, N, K, epi, nullptr, 0, bias, stream, nullptr, &cm);
+    if (plan.kind == LVX_CONV_ROWS) {
         lvx_conv_args_t c = {(const char *)P, (const char *)Wt, ldw * 2, Y, ldy, bias, M / cm.W * (cm.W + 2), N, n_slabs / 3, act, 0, 0, 0, 0, cm};
 #define LVX_TILE_LAUNCH(ID_, BM_, BN_, WM_, WN_, NST_, US_) \
-    if (tile == ID_) return lvx_conv_rows_launch<BM_, BN_, WM_, WN_, NST_>(c, stream);
+    if (plan.tile == ID_) return lvx_conv_rows_launch<BM_, BN_, WM_, WN_, NST_>(c, stream);
         LVX_CONV_ROW_TILES(LVX_TILE_LAUNCH)
 #undef LVX_TILE_LAUNCH
     }
@@ -411,7 +383,7 @@ lvx_status_t lvx_launch_conv_gemm(const bf16_t *P, const lvx_conv_map_t &cm, con
     p.M = M, p.N = N, p.n_slabs = n_slabs;
     p.epi = epi;
     p.conv = cm;
-    return lvx_gemm_launch_small<false, true>(tile, p, stream);
+    return lvx_gemm_launch_small<false, true>(plan.tile, p, stream);
 }
 
 extern "C" lvx_status_t lvx_linear(const void *dev_a, int64_t lda, const void *dev_w, int64_t ldw, void *dev_c, int64_t ldc, int32_t M,

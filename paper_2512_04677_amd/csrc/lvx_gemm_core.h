@@ -355,90 +355,6 @@ __global__ void __launch_bounds__(64 * WM * WN * KG) lvx_gemm_tile_kernel(const 
     if (FP8 && p.amax != nullptr) lvx_amax_publish(amax_b, p.amax, (int)blockIdx.x * NW * KG + wv, lane);
 }
 
-// The small tiles, widest first: id, BM, BN, WM, WN, NST, KG, columns per partial sum of squares (a wave's columns; 16 where K
-// groups reduce in LDS), and the time in microseconds that a compute unit needs per slab of such a tile (measured while the
-// tiles stream their weights from HBM; a slab is 128 bytes of every row in bf16 and in FP8 alike).
-#define LVX_GEMM_SMALL_TILES(X_)          \
-    X_(0, 64, 128, 2, 4, 6, 1, 32, 0.42f) \
-    X_(1, 64, 64, 2, 4, 4, 1, 16, 0.31f)  \
-    X_(2, 32, 64, 1, 4, 5, 2, 16, 0.235f) \
-    X_(3, 32, 32, 1, 2, 4, 4, 16, 0.16f)
-#define LVX_GEMM_SLAB_US_128X256 0.80f  // the 128 x 256 kernels, per slab and compute unit
-#define LVX_GEMM_SLAB_US_128X192 0.66f  // the same kernel with 128 x 192 tiles (bf16): 1886 x 2560 x 6912 80 -> 74 us, 2048 x 3072 x 3072 44 -> 40.5
-enum { LVX_GEMM_TILE_128X256 = -1, LVX_GEMM_TILE_128X192 = -2 };
-
-// Column tiles of width bn of the product(s).
-static inline long lvx_gemm_col_tiles(const lvx_gemm_segs_t *segs, int N, int bn) {
-    if (segs == nullptr || segs->n == 0) return (N + bn - 1) / bn;
-    long t = 0;
-    for (int i = 0; i < segs->n; ++i) t += (segs->s[i].N + bn - 1) / bn;
-    return t;
-}
-
-// Which small tile to use, or one of the large ones (128 x 192 only if `narrow` says that the caller has it): the one whose rounds of the chip (tiles over 256 compute units, rounded
-// up: a compute unit that gets two tiles needs twice the time, whether one after the other or side by side) times slabs
-// times time per slab is least.  A small tile costs more per flop but less per tile, so it wins exactly where the larger ones do
-// not fill the chip: at K = 2560, N = 2560 the 64 x 128 tile up to about 1500 rows, 64 x 64 up to 400, 32 x 64 up to 200.
-// The number of K groups fixes the order in which a product is summed, and a product that may be launched alone or with others must
-// give the same bits either way: segs->order says who decides it (see lvx_gemm_segs_t).
-static inline int lvx_gemm_pick_tile(const lvx_gemm_segs_t *segs, int M, int N, int n_slabs, bool narrow = false, double *cost_us = nullptr) {
-    const bool many = segs != nullptr && segs->n > 0;
-    const int order = many ? segs->order : LVX_GEMM_ORDER_LAUNCH;
-    int groups = order == LVX_GEMM_ORDER_ONE ? 1 : 0, best = LVX_GEMM_TILE_128X256;  // 0: not decided yet
-    for (int pass = order == LVX_GEMM_ORDER_FIRST ? 0 : 1; pass < 2; ++pass) {  // 0: the first product alone decides the groups; 1: the tile
-        const lvx_gemm_segs_t *sg = pass == 0 ? nullptr : segs;
-        const int n = many ? segs->s[0].N : N;
-        auto rounds = [&](int bm, int bn) { return (double)(((long)((M + bm - 1) / bm) * lvx_gemm_col_tiles(sg, n, bn) + 255) / 256); };
-        double best_cost = groups <= 1 ? rounds(128, 256) * n_slabs * LVX_GEMM_SLAB_US_128X256 : 1e30;
-        int best_groups = 1;
-        best = LVX_GEMM_TILE_128X256;
-        if (narrow && groups <= 1 && rounds(128, 192) * n_slabs * LVX_GEMM_SLAB_US_128X192 < best_cost)
-            best_cost = rounds(128, 192) * n_slabs * LVX_GEMM_SLAB_US_128X192, best = LVX_GEMM_TILE_128X192;
-#define LVX_TILE_COST(ID_, BM_, BN_, WM_, WN_, NST_, KG_, PC_, US_)                                         \
-    if (groups == 0 || KG_ == groups) {                                                                     \
-        const double c_ = rounds(BM_, BN_) * ((n_slabs + KG_ - 1) / KG_ * KG_) * US_;                       \
-        if (c_ < best_cost) best_cost = c_, best = ID_, best_groups = KG_;                                  \
-    }
-        LVX_GEMM_SMALL_TILES(LVX_TILE_COST)
-#undef LVX_TILE_COST
-        groups = best_groups;
-        if (cost_us != nullptr) *cost_us = best_cost;
-    }
-    return best;
-}
-
-// Rows of a product that the 128 x 256 kernel takes in whole rounds of the chip, the rest (*rest_tile) going to a small tile in a second
-// launch; 0: all rows in one launch.  A product of 260 large tiles on 256 compute units takes two rounds, the second nearly empty:
-// 1560 x 5120 x 13824 as 1536 rows in one round and 24 rows in 64 x 64 tiles 306 -> 234 microseconds, x 5120 x 5120 124 -> 91.  Chosen where the sum of both, and a
-// launch's LVX_GEMM_LAUNCH_US, is less than best_us, the time of the single launch.  Only tiles without K groups, which sum in the
-// order of the large kernel: a row's bits are those of the single launch.  Partial sums of squares need one column grouping for all rows,
-// so such a product is not split.
-#define LVX_GEMM_LAUNCH_US 3.0
-static inline int lvx_gemm_split_rows(const lvx_gemm_segs_t *segs, int M, int N, int n_slabs, double best_us, int *rest_tile) {
-    const bool many = segs != nullptr && segs->n > 0;
-    if (many && segs->s[0].sumsq != nullptr) return 0;
-    const int n = many ? segs->s[0].N : N;
-    const long cols = lvx_gemm_col_tiles(segs, n, 256), total = (long)((M + 127) / 128) * cols, rounds = total / 256;
-    const int m1 = (int)(rounds * 256 / cols * 128);
-    if (m1 == 0 || m1 >= M) return 0;
-    auto cost = [&](int m, int bm, int bn, double us) { return (double)(((long)((m + bm - 1) / bm) * lvx_gemm_col_tiles(segs, n, bn) + 255) / 256) * n_slabs * us; };
-    double best = best_us - cost(m1, 128, 256, LVX_GEMM_SLAB_US_128X256) - LVX_GEMM_LAUNCH_US;
-    int tile = LVX_GEMM_TILE_128X256;
-#define LVX_TILE_COST(ID_, BM_, BN_, WM_, WN_, NST_, KG_, PC_, US_) \
-    if (KG_ == 1 && cost(M - m1, BM_, BN_, US_) < best) best = cost(M - m1, BM_, BN_, US_), tile = ID_;
-    LVX_GEMM_SMALL_TILES(LVX_TILE_COST)
-#undef LVX_TILE_COST
-    *rest_tile = tile;
-    return tile < 0 ? 0 : m1;
-}
-static inline int lvx_gemm_part_cols(int tile) {
-#define LVX_TILE_PART(ID_, BM_, BN_, WM_, WN_, NST_, KG_, PC_, US_) \
-    if (tile == ID_) return PC_;
-    LVX_GEMM_SMALL_TILES(LVX_TILE_PART)
-#undef LVX_TILE_PART
-    return 64;
-}
-
 // Launch of small tile `tile` (arguments checked, p.M > 0, p.segs filled but for tn_begin).
 template <bool FP8, bool CONV = false>
 static lvx_status_t lvx_gemm_launch_small(int tile, lvx_gemm_args_t &p, hipStream_t stream) {

@@ -6,8 +6,7 @@
 #include <stdarg.h>
 
 #include "lvx.h"
-
-typedef uint16_t bf16_t;  // raw bf16 bits in memory
+#include "lvx_launch_rules.h"
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4_t;
@@ -15,8 +14,6 @@ typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2_t;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4_t;
-
-#define LVX_KEY_TILE 64  // keys per V^T tile in the cache and per LDS stage of the attention kernel
 
 lvx_status_t lvx_fail(lvx_status_t code, const char *fmt, ...);
 
@@ -155,29 +152,8 @@ lvx_status_t lvx_launch_conv_gemm(const bf16_t *P, const lvx_conv_map_t &cm, con
 // C1[M][N1] = A W1^T (bf16, or fp32 if c1_is_f32), C2[M][N2] = A W2^T (bf16) in one launch, plain store.
 lvx_status_t lvx_launch_linear_dual(const bf16_t *A, int64_t lda, const bf16_t *W1, const bf16_t *W2, int64_t ldw, void *C1, int64_t ldc1,
                                     int c1_is_f32, bf16_t *C2, int64_t ldc2, int M, int N1, int N2, int K, hipStream_t stream);
-// Several projections of the same activations in one GEMM launch: segment i owns the column tiles from tn_begin on (filled in
-// by the launcher) and has its own weight matrix [N][ldw], output (bf16, or fp32 if f32), output row stride and width.
-#define LVX_GEMM_MAX_SEGS 16
-struct lvx_gemm_seg_t {
-    const bf16_t *W;
-    void *C;
-    int64_t ldc;
-    int32_t N, tn_begin, f32, ld_sumsq;
-    // NULL, or [M][ld_sumsq] floats: besides the bf16 store, the kernel leaves for each row the sums of squares (taken on the fp32
-    // accumulators) of lvx_gemm_sumsq_parts(M, N, K) equal groups of columns: the partial sums of a row's RMS, added up in a fixed
-    // order by the consumer (no atomics: results stay bit-reproducible).  One segment only, N % 64 == 0.
-    float *sumsq;
-};
-#define LVX_GEMM_MAX_SUMSQ_PARTS(N_) ((N_) / 16)
-int lvx_gemm_sumsq_parts(int M, int N, int K);  // how many groups: the chosen tile's (N / 16 at most)
-// Who decides how many K groups a launch sums in (its order of summation): the first product as if it were launched alone (its bits
-// then do not depend on its company), the launch as a whole (products that are only ever launched together), or nobody: one
-// group (products launched with more or fewer others, like the context's projections of a group of layers).
-enum { LVX_GEMM_ORDER_FIRST = 0, LVX_GEMM_ORDER_LAUNCH = 1, LVX_GEMM_ORDER_ONE = 2 };
-struct lvx_gemm_segs_t {
-    int32_t n, order;
-    lvx_gemm_seg_t s[LVX_GEMM_MAX_SEGS];
-};
+int lvx_gemm_sumsq_parts(int M, int N, int K);  // partial sums of squares a row gets: the chosen tile's groups of columns (N / 16 at most)
+// Up to LVX_GEMM_MAX_SEGS projections of the same activations (see lvx_gemm_segs_t).
 lvx_status_t lvx_launch_linear_segments(const bf16_t *A, int64_t lda, int64_t ldw, const lvx_gemm_segs_t &segs, int M, int K, hipStream_t stream);
 // internal epilogue id of the GEMM kernel: plain store per segment (bf16 or fp32)
 #define LVX_EPI_SEGMENTS 100

@@ -1,0 +1,196 @@
+// Which kernel a call takes: the tile of a matrix product, of a convolution step, the workgroup form of the attention.  Rules on sizes
+// only, in plain host C++ with no GPU types, so that they can be evaluated for any size without a GPU.
+#pragma once
+#include <stdint.h>
+
+typedef uint16_t bf16_t;  // raw bf16 bits in memory
+
+constexpr int LVX_NUM_CU = 256;
+
+// Rounds of the chip that so many workgroups take, one per compute unit.
+static inline long lvx_rounds(long workgroups) { return (workgroups + LVX_NUM_CU - 1) / LVX_NUM_CU; }
+
+// ---- matrix products -----------------------------------------------------------------------------------------------------------
+// Several projections of the same activations in one GEMM launch: segment i owns the column tiles from tn_begin on (filled in
+// by the launcher) and has its own weight matrix [N][ldw], output (bf16, or fp32 if f32), output row stride and width.
+#define LVX_GEMM_MAX_SEGS 16
+struct lvx_gemm_seg_t {
+    const bf16_t *W;
+    void *C;
+    int64_t ldc;
+    int32_t N, tn_begin, f32, ld_sumsq;
+    // NULL, or [M][ld_sumsq] floats: besides the bf16 store, the kernel leaves for each row the sums of squares (taken on the fp32
+    // accumulators) of lvx_gemm_sumsq_parts(M, N, K) equal groups of columns: the partial sums of a row's RMS, added up in a fixed
+    // order by the consumer (no atomics: results stay bit-reproducible).  One segment only, N % 64 == 0.
+    float *sumsq;
+};
+#define LVX_GEMM_MAX_SUMSQ_PARTS(N_) ((N_) / 16)
+// Who decides how many K groups a launch sums in (its order of summation): the first product as if it were launched alone (its bits
+// then do not depend on its company), the launch as a whole (products that are only ever launched together), or nobody: one
+// group (products launched with more or fewer others, like the context's projections of a group of layers).
+enum { LVX_GEMM_ORDER_FIRST = 0, LVX_GEMM_ORDER_LAUNCH = 1, LVX_GEMM_ORDER_ONE = 2 };
+struct lvx_gemm_segs_t {
+    int32_t n, order;
+    lvx_gemm_seg_t s[LVX_GEMM_MAX_SEGS];
+};
+
+// The small tiles, widest first: id, BM, BN, WM, WN, NST, KG, columns per partial sum of squares (a wave's columns; 16 where K
+// groups reduce in LDS), and the time in microseconds that a compute unit needs per slab of such a tile (measured while the
+// tiles stream their weights from HBM; a slab is 128 bytes of every row in bf16 and in FP8 alike).
+#define LVX_GEMM_SMALL_TILES(X_)          \
+    X_(0, 64, 128, 2, 4, 6, 1, 32, 0.42f) \
+    X_(1, 64, 64, 2, 4, 4, 1, 16, 0.31f)  \
+    X_(2, 32, 64, 1, 4, 5, 2, 16, 0.235f) \
+    X_(3, 32, 32, 1, 2, 4, 4, 16, 0.16f)
+#define LVX_GEMM_SLAB_US_128X256 0.80f  // the 128 x 256 kernels, per slab and compute unit
+#define LVX_GEMM_SLAB_US_128X192 0.66f  // the same kernel with 128 x 192 tiles (bf16): 1886 x 2560 x 6912 80 -> 74 us, 2048 x 3072 x 3072 44 -> 40.5
+enum { LVX_GEMM_TILE_128X256 = -1, LVX_GEMM_TILE_128X192 = -2 };
+
+// Column tiles of width bn of the product(s).
+static inline long lvx_gemm_col_tiles(const lvx_gemm_segs_t *segs, int N, int bn) {
+    if (segs == nullptr || segs->n == 0) return (N + bn - 1) / bn;
+    long t = 0;
+    for (int i = 0; i < segs->n; ++i) t += (segs->s[i].N + bn - 1) / bn;
+    return t;
+}
+
+// Which small tile to use, or one of the large ones (128 x 192 only if `narrow` says that the caller has it): the one whose rounds of the
+// chip (a compute unit that gets two tiles needs twice the time, whether one after the other or side by side) times slabs
+// times time per slab is least.  A small tile costs more per flop but less per tile, so it wins exactly where the larger ones do
+// not fill the chip: at K = 2560, N = 2560 the 64 x 128 tile up to about 1500 rows, 64 x 64 up to 400, 32 x 64 up to 200.
+// The number of K groups fixes the order in which a product is summed, and a product that may be launched alone or with others must
+// give the same bits either way: segs->order says who decides it (see lvx_gemm_segs_t).
+static inline int lvx_gemm_pick_tile(const lvx_gemm_segs_t *segs, int M, int N, int n_slabs, bool narrow = false, double *cost_us = nullptr) {
+    const bool many = segs != nullptr && segs->n > 0;
+    const int order = many ? segs->order : LVX_GEMM_ORDER_LAUNCH;
+    int groups = order == LVX_GEMM_ORDER_ONE ? 1 : 0, best = LVX_GEMM_TILE_128X256;  // 0: not decided yet
+    for (int pass = order == LVX_GEMM_ORDER_FIRST ? 0 : 1; pass < 2; ++pass) {  // 0: the first product alone decides the groups; 1: the tile
+        const lvx_gemm_segs_t *sg = pass == 0 ? nullptr : segs;
+        const int n = many ? segs->s[0].N : N;
+        auto rounds = [&](int bm, int bn) { return (double)lvx_rounds((long)((M + bm - 1) / bm) * lvx_gemm_col_tiles(sg, n, bn)); };
+        double best_cost = groups <= 1 ? rounds(128, 256) * n_slabs * LVX_GEMM_SLAB_US_128X256 : 1e30;
+        int best_groups = 1;
+        best = LVX_GEMM_TILE_128X256;
+        if (narrow && groups <= 1 && rounds(128, 192) * n_slabs * LVX_GEMM_SLAB_US_128X192 < best_cost)
+            best_cost = rounds(128, 192) * n_slabs * LVX_GEMM_SLAB_US_128X192, best = LVX_GEMM_TILE_128X192;
+#define LVX_TILE_COST(ID_, BM_, BN_, WM_, WN_, NST_, KG_, PC_, US_)                                         \
+    if (groups == 0 || KG_ == groups) {                                                                     \
+        const double c_ = rounds(BM_, BN_) * ((n_slabs + KG_ - 1) / KG_ * KG_) * US_;                       \
+        if (c_ < best_cost) best_cost = c_, best = ID_, best_groups = KG_;                                  \
+    }
+        LVX_GEMM_SMALL_TILES(LVX_TILE_COST)
+#undef LVX_TILE_COST
+        groups = best_groups;
+        if (cost_us != nullptr) *cost_us = best_cost;
+    }
+    return best;
+}
+
+// Rows of a product that the 128 x 256 kernel takes in whole rounds of the chip, the rest (*rest_tile) going to a small tile in a second
+// launch; 0: all rows in one launch.  A product of 260 large tiles on 256 compute units takes two rounds, the second nearly empty:
+// 1560 x 5120 x 13824 as 1536 rows in one round and 24 rows in 64 x 64 tiles 306 -> 234 microseconds, x 5120 x 5120 124 -> 91.  Chosen where the sum of both, and a
+// launch's LVX_GEMM_LAUNCH_US, is less than best_us, the time of the single launch.  Only tiles without K groups, which sum in the
+// order of the large kernel: a row's bits are those of the single launch.  Partial sums of squares need one column grouping for all rows,
+// so such a product is not split.
+#define LVX_GEMM_LAUNCH_US 3.0
+static inline int lvx_gemm_split_rows(const lvx_gemm_segs_t *segs, int M, int N, int n_slabs, double best_us, int *rest_tile) {
+    const bool many = segs != nullptr && segs->n > 0;
+    if (many && segs->s[0].sumsq != nullptr) return 0;
+    const int n = many ? segs->s[0].N : N;
+    const long cols = lvx_gemm_col_tiles(segs, n, 256), total = (long)((M + 127) / 128) * cols, rounds = total / LVX_NUM_CU;
+    const int m1 = (int)(rounds * LVX_NUM_CU / cols * 128);
+    if (m1 == 0 || m1 >= M) return 0;
+    auto cost = [&](int m, int bm, int bn, double us) { return (double)lvx_rounds((long)((m + bm - 1) / bm) * lvx_gemm_col_tiles(segs, n, bn)) * n_slabs * us; };
+    double best = best_us - cost(m1, 128, 256, LVX_GEMM_SLAB_US_128X256) - LVX_GEMM_LAUNCH_US;
+    int tile = LVX_GEMM_TILE_128X256;
+#define LVX_TILE_COST(ID_, BM_, BN_, WM_, WN_, NST_, KG_, PC_, US_) \
+    if (KG_ == 1 && cost(M - m1, BM_, BN_, US_) < best) best = cost(M - m1, BM_, BN_, US_), tile = ID_;
+    LVX_GEMM_SMALL_TILES(LVX_TILE_COST)
+#undef LVX_TILE_COST
+    *rest_tile = tile;
+    return tile < 0 ? 0 : m1;
+}
+static inline int lvx_gemm_part_cols(int tile) {
+#define LVX_TILE_PART(ID_, BM_, BN_, WM_, WN_, NST_, KG_, PC_, US_) \
+    if (tile == ID_) return PC_;
+    LVX_GEMM_SMALL_TILES(LVX_TILE_PART)
+#undef LVX_TILE_PART
+    return 64;
+}
+
+// A product's launch: the tile, and the rows m1 that the 128 x 256 kernel takes before it (0: the tile takes all rows).
+struct lvx_gemm_plan_t {
+    int tile, m1;
+    double us;  // the single launch's time by the rule above
+};
+static inline lvx_gemm_plan_t lvx_gemm_plan(const lvx_gemm_segs_t *segs, int M, int N, int n_slabs, bool narrow) {
+    lvx_gemm_plan_t p = {0, 0, 0};
+    p.tile = lvx_gemm_pick_tile(segs, M, N, n_slabs, narrow, &p.us);
+    int rest = p.tile;
+    if (p.tile < 0) p.m1 = lvx_gemm_split_rows(segs, M, N, n_slabs, p.us, &rest);
+    if (p.m1 > 0) p.tile = rest;
+    return p;
+}
+
+// ---- convolution ---------------------------------------------------------------------------------------------------------------
+// The tiles with shared input rows: id, BM, BN, WM, WN, NST and the time in microseconds that a compute unit needs per stage (64
+// channels of three taps)
+#define LVX_CONV_ROW_TILES(X_)         \
+    X_(0, 64, 64, 2, 4, 4, 0.70)       \
+    X_(1, 128, 64, 4, 2, 3, 0.90)      \
+    X_(2, 256, 64, 4, 2, 2, 1.48)      \
+    X_(3, 192, 128, 4, 2, 2, 2.00)
+
+// The kernel of a step of M output pixels (rows of W) and N channels, n_slabs 64-wide slabs of the contraction, is the
+// one with the least rounds of the chip times slabs (or stages of three) times time of each: the 256 x 128 tiles of the linears' kernel
+// where they fill the chip (C_out is 128 ... 512 in the decoder this serves; 128-wide column tiles waste nothing there), the tiles with shared
+// input rows below that and where their rounds come out better, the 32 x 32 tile with four K groups for a few thousand outputs.  The kinds differ in the order of
+// summation, so the kind follows from max_m, the pixels of the longest step the layer takes: a pixel's bits do not depend on how many
+// frames arrive with it.  Measured (us a step, before: 256 x 128 only or the linears' small tiles): one 50 x 90 frame 384 -> 192 channels
+// 119, 61 -> 45; four 25 x 45 frames 512 -> 512 146 -> 105; four 240 x 400 64 -> 64 199 -> 139; two 200 x 360 192 -> 96 238 -> 202.
+enum { LVX_CONV_LARGE, LVX_CONV_ROWS, LVX_CONV_GROUPS };
+struct lvx_conv_plan_t {
+    int kind, tile;  // tile: of LVX_CONV_ROW_TILES or LVX_GEMM_SMALL_TILES
+};
+static inline lvx_conv_plan_t lvx_conv_plan(int W, int N, int n_slabs, int M, int max_m) {
+    int kind = -1, tile = -1;
+    for (int pass = 0; pass < 2; ++pass) {  // 0: the kind, at the longest step; 1: the tile, at this one
+        const int m = pass == 0 ? max_m : M;
+        double best = 1e30;
+        int best_kind = kind;
+        auto rounds = [&](long rows, int bm, int bn) { return (double)lvx_rounds((rows + bm - 1) / bm * ((N + bn - 1) / bn)); };
+        auto offer = [&](int k, int id, double us) {
+            if ((kind < 0 || k == kind) && us < best) best = us, best_kind = k, tile = id;
+        };
+        offer(LVX_CONV_LARGE, 0, rounds(m, 256, 128) * n_slabs * 0.82);
+        const long padded = (long)m / W * (W + 2);
+#define LVX_TILE_COST(ID_, BM_, BN_, WM_, WN_, NST_, US_) offer(LVX_CONV_ROWS, ID_, rounds(padded, BM_, BN_) * (n_slabs / 3) * US_);
+        LVX_CONV_ROW_TILES(LVX_TILE_COST)
+#undef LVX_TILE_COST
+#define LVX_TILE_COST(ID_, BM_, BN_, WM_, WN_, NST_, KG_, PC_, US_) \
+    if (KG_ > 2) offer(LVX_CONV_GROUPS, ID_, rounds(m, BM_, BN_) * ((n_slabs + KG_ - 1) / KG_ * KG_) * US_);
+        LVX_GEMM_SMALL_TILES(LVX_TILE_COST)
+#undef LVX_TILE_COST
+        kind = best_kind;
+    }
+    return {kind, tile};
+}
+
+// ---- attention -----------------------------------------------------------------------------------------------------------------
+#define LVX_KEY_TILE 64  // keys per V^T tile in the cache and per LDS stage of the attention kernel
+
+// Whether a workgroup takes 128 queries and splits the keys over its halves instead of 256 queries.  A round of the chip with
+// the split takes 0.62 to 0.66 of a round without (measured from 9 to 150 key tiles, head_dim 64 and 128: half the tiles per wave, but
+// twice the K / V stream per tile), so it pays where the smaller workgroups need less than half as many more rounds: always
+// while they fit one round, e.g. 12 heads x 1170 queries x 6240 keys 134 -> 90 us, but 20 x 1886 x 8487 (160 workgroups become 300)
+// 191 -> 236 us.  A last query tile of one or two waves' rows ends early and is not counted as a workgroup.  Up to 128 queries half
+// of the waves idle without the split; with less than 8 key tiles the exchange at the end then costs what it saves (9.3 against
+// 10.2 us at 4 tiles, 15.1 against 14.4 at 9).
+static inline bool lvx_attention_splits_keys(int n_q, int H, int n_keys) {
+    if (n_q <= 128 && n_keys <= 7 * LVX_KEY_TILE) return false;
+    auto rounds = [&](int qt) {
+        const long tiles = (n_q + qt - 1 - qt / 4) / qt;
+        return lvx_rounds((tiles > 0 ? tiles : 1) * H);
+    };
+    return 0.65 * rounds(128) < rounds(256);
+}

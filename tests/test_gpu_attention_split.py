@@ -13,18 +13,26 @@ from test_gpu_parity import DEV, LOG2E
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("D,H", [(128, 3), (64, 4), (128, 136), (64, 136)])   # 136 heads x 130 queries: 256-query workgroups
+# (head_dim, heads), query counts that take the split form (from 8 key tiles on, and above 128 queries from the first), query counts
+# that do not; test_launch_rules.py holds the rule to it
+KEY_COUNTS = (1, 63, 64, 65, 128, 129, 192, 200, 1024, 1030, 1090)
+GEOMETRIES = [((128, 3), (1, 31, 33, 127, 128, 129, 257), ()), ((64, 4), (1, 31, 33, 127, 128, 129, 257), ()),
+              ((128, 136), (130,), (200, 256)), ((64, 136), (130,), (200, 256))]
+
+
+@pytest.mark.parametrize("D,H", [g for g, _, _ in GEOMETRIES])
 @pytest.mark.parametrize("prescaled", [False, True])
 def test_attention_key_split_edges(lvx, D, H, prescaled):
     d = H * D
-    for n_keys in (1, 63, 64, 65, 128, 129, 192, 200, 1024, 1030, 1090):
+    n_qs = next(split + unsplit for g, split, unsplit in GEOMETRIES if g == (D, H))
+    for n_keys in KEY_COUNTS:
         cache = lvx.KVCache(lvx.cache_desc(1, H, D, 1, n_keys, 1, 1, 1), DEV)
         k = S.randn_bf16((n_keys, d), S.seed_of("sp_k", D, H, n_keys), device=DEV)
         v = S.randn_bf16((n_keys, d), S.seed_of("sp_v", D, H, n_keys), device=DEV)
         if n_keys >= 128:
             k[64:128] *= 24.0   # the second tile's logits dwarf the first's: the halves end with far apart references
         lvx.lvx_kvcache_set_sink(cache, 0, k, v)
-        for n_q in ((1, 31, 33, 127, 128, 129, 257) if H < 100 else (130, 256)):
+        for n_q in n_qs:
             q = S.randn_bf16((n_q, d), S.seed_of("sp_q", D, H, n_q), device=DEV)
             out = torch.full((n_q + 1, d), 7.0, dtype=torch.bfloat16, device=DEV)
             scale = 1.0 / math.sqrt(D)

@@ -76,15 +76,19 @@ def test_linear_bias_and_silu_epilogues(lvx):
     assert_close(c, O.silu(ref), "linear + bias + silu")
 
 
-@pytest.mark.parametrize("H,W,Ci,Co,frames", [
-    (7, 5, 64, 24, 3),          # 32 x 32 tiles, four K groups, 27 slabs
-    (45, 45, 64, 136, 2),       # shared rows, 64 x 64, ragged rows and columns
-    (77, 79, 128, 136, 1),      # shared rows, 128 x 64
-    (100, 101, 64, 72, 2),      # shared rows, 256 x 64 for two frames, 128 x 64 for one
-    (150, 151, 64, 136, 1),     # shared rows, 192 x 128
-    (2, 2, 64, 600, 160),       # rows of two pixels: tiles across many frames
-    (181, 181, 64, 256, 1),     # 256 x 128
-])
+# H, W, C_in, C_out, frames with the kernel the rule picks for a step of all frames; test_launch_rules.py holds the rule to it
+TILE_SHAPES = [
+    ((7, 5, 64, 24, 3), "32x32 k4"),               # 27 slabs over four K groups
+    ((45, 45, 64, 136, 2), "rows 64x64"),          # ragged rows and columns
+    ((77, 79, 128, 136, 1), "rows 128x64"),
+    ((100, 101, 64, 72, 2), "rows 256x64"),        # 128 x 64 for one frame
+    ((150, 151, 64, 136, 1), "rows 192x128"),
+    ((2, 2, 64, 600, 160), "rows 64x64"),          # rows of two pixels: tiles across many frames
+    ((181, 181, 64, 256, 1), "256x128"),
+]
+
+
+@pytest.mark.parametrize("H,W,Ci,Co,frames", [s for s, _ in TILE_SHAPES])
 def test_conv_tiles_and_chunking(lvx, H, W, Ci, Co, frames):
     """Every tile the rule can pick, against the oracle; a frame's bits do not depend on how many frames arrive with it."""
     x, w, b = conv_inputs("ct_%d_%d_%d_%d" % (H, W, Ci, Co), frames, H, W, Ci, Co, pad=8)

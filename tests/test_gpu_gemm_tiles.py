@@ -12,15 +12,24 @@ from test_gpu_parity import DEV, assert_close
 
 pytestmark = pytest.mark.gpu
 
-# M x N x K with the tile the launcher's rule picks for it (rows x columns, K groups)
-SHAPES = [(31, 24, 192), (33, 136, 320), (65, 1920, 448),                                 # 32 x 32, four groups
-          (64, 5760, 128), (63, 7000, 320), (95, 5000, 1088),                             # 32 x 64, two groups
-          (1, 8, 64), (64, 2560, 64), (250, 2568, 192), (257, 2560, 704),                 # 64 x 64
-          (600, 2560, 64), (577, 2696, 576), (1151, 1544, 832),                           # 64 x 128
-          (1170, 4616, 192), (1901, 2568, 128)]                                           # 128 x 256
+# M x N x K with the tile the launcher's rule picks for it (rows x columns, k: K groups); test_launch_rules.py holds the rule to it
+SHAPES = [((31, 24, 192), "32x32 k4"), ((33, 136, 320), "32x32 k4"), ((65, 1920, 448), "32x32 k4"),
+          ((64, 5760, 128), "32x64 k2"), ((63, 7000, 320), "32x64 k2"), ((95, 5000, 1088), "32x64 k2"),
+          ((1, 8, 64), "64x64"), ((64, 2560, 64), "64x64"), ((250, 2568, 192), "64x64"), ((257, 2560, 704), "64x64"),
+          ((600, 2560, 64), "64x128"), ((577, 2696, 576), "64x128"), ((1151, 1544, 832), "64x128"),
+          ((1170, 4616, 192), "128x192"), ((1901, 2568, 128), "128x192"),
+          ((1300, 5120, 128), "128x256"), ((1411, 4616, 192), "128x256")]
+FP8_SHAPES = [((1, 8, 128), "64x64"), ((33, 136, 640), "32x32 k4"), ((65, 1920, 896), "32x32 k4"), ((64, 5760, 256), "32x64 k2"),
+              ((95, 5000, 1152), "32x64 k2"), ((257, 2560, 1408), "64x64"), ((600, 2560, 128), "64x128"), ((1151, 1544, 1664), "64x128"),
+              ((1901, 2568, 256), "128x256")]
+# the same with the rows that the 128 x 256 kernel takes before the tile named here takes the rest (0: one launch)
+LARGE_SHAPES = [((1550, 5120, 1152), "64x64", 1536),   # 12 row tiles in one round, 14 rows in a small tile
+                ((1567, 5112, 1408), "64x64", 1536),   # the same with ragged columns, 31 rows
+                ((1550, 5112, 576), "128x192", 0), ((1886, 2568, 192), "128x192", 0), ((2048, 3072, 64), "128x192", 0)]
+FP8_SPLIT_SHAPES = [((1550, 5120, 1152), "64x64", 1536), ((1567, 5112, 1408), "64x64", 1536)]
 
 
-@pytest.mark.parametrize("M,N,K", SHAPES)
+@pytest.mark.parametrize("M,N,K", [s for s, _ in SHAPES])
 def test_linear_tile_edges(lvx, M, N, K):
     a = S.randn_bf16((M, K + 8), S.seed_of("gt_a", M, K), device=DEV)[:, :K]
     w = S.randn_bf16((N, K + 64), S.seed_of("gt_w", N, K), 1.0 / math.sqrt(K), device=DEV)[:, :K]
@@ -59,8 +68,7 @@ def test_product_bits_do_not_depend_on_its_company(lvx, M, N1, N2, K):
     assert torch.equal(c1, alone)
 
 
-@pytest.mark.parametrize("M,N,K", [(1, 8, 128), (33, 136, 640), (65, 1920, 896), (64, 5760, 256), (95, 5000, 1152), (257, 2560, 1408),
-                                   (600, 2560, 128), (1151, 1544, 1664)])
+@pytest.mark.parametrize("M,N,K", [s for s, _ in FP8_SHAPES])
 def test_linear_fp8_tile_edges(lvx, M, N, K):
     """FP8 codes are exact inputs: the product of the decoded values, scaled, is what every tile has to give."""
     aq, sa = lvx.lvx_fp8_quantize(S.randn_bf16((M, K), S.seed_of("g8_a", M, K), device=DEV), row_pad=16)
@@ -85,9 +93,7 @@ def test_linear_fp8_tile_edges(lvx, M, N, K):
     assert np.abs(S.to_f64(x) - (S.to_f64(r) + S.to_f64(g) * ref)).max() <= 1e-4 * math.sqrt(K)
 
 
-@pytest.mark.parametrize("M,N,K", [(1550, 5120, 1152),     # 12 row tiles in one round, 14 rows in a small tile
-                                   (1567, 5112, 1408),     # the same with ragged columns, 31 rows
-                                   (1550, 5112, 576), (1886, 2568, 192), (2048, 3072, 64)])   # 128 x 192 tiles, ragged and whole
+@pytest.mark.parametrize("M,N,K", [s for s, _, _ in LARGE_SHAPES])
 def test_rows_split_over_two_launches_and_narrow_tiles(lvx, M, N, K):
     a = S.randn_bf16((M, K + 8), S.seed_of("rs_a", M, K), device=DEV)[:, :K]
     w = S.randn_bf16((N, K + 64), S.seed_of("rs_w", N, K), 1.0 / math.sqrt(K), device=DEV)[:, :K]
@@ -115,7 +121,7 @@ def test_rows_split_over_two_launches_and_narrow_tiles(lvx, M, N, K):
     assert_close(c2, ref[:, :8], "second product")
 
 
-@pytest.mark.parametrize("M,N,K", [(1550, 5120, 1152), (1567, 5112, 1408)])
+@pytest.mark.parametrize("M,N,K", [s for s, _, _ in FP8_SPLIT_SHAPES])
 def test_fp8_rows_split_over_two_launches(lvx, M, N, K):
     aq, sa = lvx.lvx_fp8_quantize(S.randn_bf16((M, K), S.seed_of("r8_a", M, K), device=DEV), row_pad=16)
     wq, sw = lvx.lvx_fp8_quantize(S.randn_bf16((N, K), S.seed_of("r8_w", N, K), 1.0 / math.sqrt(K), device=DEV), row_pad=128)

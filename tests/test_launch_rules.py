@@ -1,0 +1,92 @@
+"""The rules that choose a kernel by size (csrc/lvx_launch_rules.h, plain C++), evaluated on the CPU: the GPU tests' shapes take
+the kernels that those tests say they take."""
+import ctypes as C
+import os
+import shutil
+import subprocess
+
+import pytest
+
+import test_gpu_attention_split as attention_tests
+import test_gpu_conv as conv_tests
+import test_gpu_gemm_tiles as gemm_tests
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2512_04677_amd", "csrc")
+SOURCE = r"""
+#include "lvx_launch_rules.h"
+extern "C" {
+// widths[n]: the products of one launch (n = 1, order < 0: a plain linear); out: tile, rows of the first launch, time by the rule
+void linear_plan(int M, int n, const int *widths, int order, int n_slabs, int narrow, int *tile, int *m1, double *us) {
+    lvx_gemm_segs_t segs = {};
+    segs.n = n;
+    segs.order = order;
+    for (int i = 0; i < n; ++i) segs.s[i].N = widths[i];
+    const lvx_gemm_plan_t p = lvx_gemm_plan(order < 0 ? nullptr : &segs, M, widths[0], n_slabs, narrow != 0);
+    *tile = p.tile, *m1 = p.m1, *us = p.us;
+}
+void conv_plan(int W, int N, int n_slabs, int M, int max_m, int *kind, int *tile) {
+    const lvx_conv_plan_t p = lvx_conv_plan(W, N, n_slabs, M, max_m);
+    *kind = p.kind, *tile = p.tile;
+}
+int splits_keys(int n_q, int H, int n_keys) { return lvx_attention_splits_keys(n_q, H, n_keys); }
+}
+"""
+SMALL = {0: "64x128", 1: "64x64", 2: "32x64 k2", 3: "32x32 k4", -1: "128x256", -2: "128x192"}
+ROWS = {0: "rows 64x64", 1: "rows 128x64", 2: "rows 256x64", 3: "rows 192x128"}
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("g++ not found")
+    d = tmp_path_factory.mktemp("rules")
+    (d / "rules.cpp").write_text(SOURCE)
+    lib = str(d / "librules.so")
+    r = subprocess.run([cxx, "-O1", "-Wall", "-Werror", "-std=c++17", "-shared", "-fPIC", "-I" + CSRC, str(d / "rules.cpp"), "-o", lib],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    return C.CDLL(lib)
+
+
+ORDER_ALONE, ORDER_FIRST, ORDER_LAUNCH, ORDER_ONE = -1, 0, 1, 2
+
+
+def linear_plan(rules, M, widths, K, order=ORDER_ALONE, fp8=False, narrow=True):
+    """(kernel of the product or of its last rows, rows of the 128 x 256 launch before it, microseconds by the rule)"""
+    tile, m1, us = C.c_int(), C.c_int(), C.c_double()
+    rules.linear_plan(M, len(widths), (C.c_int * len(widths))(*widths), order, K // (128 if fp8 else 64), int(narrow and not fp8), C.byref(tile), C.byref(m1), C.byref(us))
+    return SMALL[tile.value], m1.value, us.value
+
+
+def conv_plan(rules, H, W, c_in, c_out, max_frames, n_frames):
+    kind, tile = C.c_int(), C.c_int()
+    rules.conv_plan(W, c_out, 27 * c_in // 64, n_frames * H * W, max_frames * H * W, C.byref(kind), C.byref(tile))
+    return ("256x128", ROWS.get(tile.value), SMALL[tile.value])[kind.value]
+
+
+def test_gpu_gemm_shapes_take_the_kernels_they_name(rules):
+    for (M, N, K), kernel in gemm_tests.SHAPES:
+        assert linear_plan(rules, M, [N], K)[:2] == (kernel, 0), (M, N, K)
+    for (M, N, K), kernel in gemm_tests.FP8_SHAPES:
+        assert linear_plan(rules, M, [N], K, fp8=True)[:2] == (kernel, 0), (M, N, K)
+    for (M, N, K), kernel, m1 in gemm_tests.LARGE_SHAPES:
+        assert linear_plan(rules, M, [N], K)[:2] == (kernel, m1), (M, N, K)
+    for (M, N, K), kernel, m1 in gemm_tests.FP8_SPLIT_SHAPES:
+        assert linear_plan(rules, M, [N], K, fp8=True)[:2] == (kernel, m1), (M, N, K)
+    assert {k for _, k in gemm_tests.SHAPES} | {k for _, k, _ in gemm_tests.LARGE_SHAPES} == set(SMALL.values())
+
+
+def test_gpu_conv_shapes_take_the_kernels_they_name(rules):
+    for (H, W, c_in, c_out, frames), kernel in conv_tests.TILE_SHAPES:
+        assert conv_plan(rules, H, W, c_in, c_out, frames, frames) == kernel, (H, W, c_in, c_out, frames)
+    assert {k for _, k in conv_tests.TILE_SHAPES} == set(ROWS.values()) | {"256x128", "32x32 k4"}
+
+
+def test_gpu_attention_shapes_take_the_forms_they_name(rules):
+    for (D, H), split, unsplit in attention_tests.GEOMETRIES:
+        for n_keys in attention_tests.KEY_COUNTS:
+            for n_q in split:
+                assert rules.splits_keys(n_q, H, n_keys) or (n_q <= 128 and n_keys <= 7 * 64), (H, n_q, n_keys)
+            for n_q in unsplit:
+                assert not rules.splits_keys(n_q, H, n_keys), (H, n_q, n_keys)
