@@ -25,9 +25,9 @@ struct lvx_gemm_seg_t {
     float *sumsq;
 };
 #define LVX_GEMM_MAX_SUMSQ_PARTS(N_) ((N_) / 16)
-// Who decides how many K groups a launch sums in (its order of summation): the first product as if it were launched alone (its bits
-// then do not depend on its company), the launch as a whole (products that are only ever launched together), or nobody: one
-// group (products launched with more or fewer others, like the context's projections of a group of layers).
+// Who decides how many K groups a launch sums in (its order of summation): the first product as if it were launched alone, unless that
+// would cost its company too much (see lvx_gemm_pick_tile), the launch as a whole (products that are only ever launched together), or
+// nobody: one group (products launched with more or fewer others, like the context's projections of a group of layers).
 enum { LVX_GEMM_ORDER_FIRST = 0, LVX_GEMM_ORDER_LAUNCH = 1, LVX_GEMM_ORDER_ONE = 2 };
 struct lvx_gemm_segs_t {
     int32_t n, order;
@@ -58,17 +58,24 @@ static inline long lvx_gemm_col_tiles(const lvx_gemm_segs_t *segs, int N, int bn
 // chip (a compute unit that gets two tiles needs twice the time, whether one after the other or side by side) times slabs
 // times time per slab is least.  A small tile costs more per flop but less per tile, so it wins exactly where the larger ones do
 // not fill the chip: at K = 2560, N = 2560 the 64 x 128 tile up to about 1500 rows, 64 x 64 up to 400, 32 x 64 up to 200.
-// The number of K groups fixes the order in which a product is summed, and a product that may be launched alone or with others must
-// give the same bits either way: segs->order says who decides it (see lvx_gemm_segs_t).
+// The number of K groups fixes the order in which a product is summed; segs->order says who decides it (see lvx_gemm_segs_t).
+// LVX_GEMM_ORDER_FIRST takes the groups that suit the first product alone, so that its bits are those of a launch of its own, as long as
+// the launch then costs at most LVX_GEMM_FIRST_MAX of the 128 x 256 launch of both, and one group otherwise: a narrow product's K groups
+// have only the smallest tiles, and a wide second product in those took up to six times as long (1170 x (256 + 5120) x 5120: 68 us in 128 x
+// 256 tiles, 182 in 32 x 64; 4680 x (16 + 13824) x 5120: 541 and 2129).  The line lies below 1 because each further round of small tiles
+// also pays a start and a reduction that the time per slab does not hold: 48 x (416 + 9712) x 384, 0.80 by the rule, 9.3 and 10.5.
+#define LVX_GEMM_FIRST_MAX 0.75
 static inline int lvx_gemm_pick_tile(const lvx_gemm_segs_t *segs, int M, int N, int n_slabs, bool narrow = false, double *cost_us = nullptr) {
     const bool many = segs != nullptr && segs->n > 0;
     const int order = many ? segs->order : LVX_GEMM_ORDER_LAUNCH;
     int groups = order == LVX_GEMM_ORDER_ONE ? 1 : 0, best = LVX_GEMM_TILE_128X256;  // 0: not decided yet
-    for (int pass = order == LVX_GEMM_ORDER_FIRST ? 0 : 1; pass < 2; ++pass) {  // 0: the first product alone decides the groups; 1: the tile
+    // pass 0: the first product alone decides the groups; 1: the tile; 2: the tile once more, for one group
+    for (int pass = order == LVX_GEMM_ORDER_FIRST ? 0 : 1, last = 1; pass <= last; ++pass) {
         const lvx_gemm_segs_t *sg = pass == 0 ? nullptr : segs;
         const int n = many ? segs->s[0].N : N;
         auto rounds = [&](int bm, int bn) { return (double)lvx_rounds((long)((M + bm - 1) / bm) * lvx_gemm_col_tiles(sg, n, bn)); };
-        double best_cost = groups <= 1 ? rounds(128, 256) * n_slabs * LVX_GEMM_SLAB_US_128X256 : 1e30;
+        const double large_cost = rounds(128, 256) * n_slabs * LVX_GEMM_SLAB_US_128X256;
+        double best_cost = groups <= 1 ? large_cost : 1e30;
         int best_groups = 1;
         best = LVX_GEMM_TILE_128X256;
         if (narrow && groups <= 1 && rounds(128, 192) * n_slabs * LVX_GEMM_SLAB_US_128X192 < best_cost)
@@ -81,6 +88,7 @@ static inline int lvx_gemm_pick_tile(const lvx_gemm_segs_t *segs, int M, int N, 
         LVX_GEMM_SMALL_TILES(LVX_TILE_COST)
 #undef LVX_TILE_COST
         groups = best_groups;
+        if (pass == 1 && order == LVX_GEMM_ORDER_FIRST && groups > 1 && best_cost > LVX_GEMM_FIRST_MAX * large_cost) groups = 1, last = 2;
         if (cost_us != nullptr) *cost_us = best_cost;
     }
     return best;

@@ -54,9 +54,15 @@ def test_linear_tile_edges(lvx, M, N, K):
     assert np.abs(S.to_f64(x) - (S.to_f64(r) + S.to_f64(g) * ref)).max() <= 4.0 * bound
 
 
-@pytest.mark.parametrize("M,N1,N2,K", [(40, 512, 512, 512), (33, 520, 264, 320), (390, 1536, 512, 512)])
+# two products of one input: the first summed as alone (the launch as a whole would take other K groups for the last two), and
+# pairs of which the second is too wide for the groups that the first has alone
+PAIRS = [(40, 512, 512, 512), (33, 520, 264, 320), (390, 1536, 512, 512), (96, 1024, 2048, 512), (200, 2048, 2048, 512)]
+UNEQUAL_PAIRS = [(633, 32, 7000, 576), (1170, 256, 5120, 320)]
+
+
+@pytest.mark.parametrize("M,N1,N2,K", PAIRS)
 def test_product_bits_do_not_depend_on_its_company(lvx, M, N1, N2, K):
-    """A projection launched with another one of the same input sums in the same order as alone."""
+    """A projection launched with another one that is not far wider sums in the same order as alone."""
     a = S.randn_bf16((M, K), S.seed_of("co_a", M, K), device=DEV)
     w = S.randn_bf16((N1 + N2, K), S.seed_of("co_w", N1, N2, K), 1.0 / math.sqrt(K), device=DEV)
     c1 = torch.empty((M, N1), dtype=torch.float32, device=DEV)
@@ -66,6 +72,20 @@ def test_product_bits_do_not_depend_on_its_company(lvx, M, N1, N2, K):
     lvx.lvx_linear(a, w[:N1], alone, lvx.EPI_STORE_F32)
     torch.cuda.synchronize()
     assert torch.equal(c1, alone)
+
+
+@pytest.mark.parametrize("M,N1,N2,K", UNEQUAL_PAIRS)
+def test_narrow_product_beside_a_wide_one(lvx, M, N1, N2, K):
+    a = S.randn_bf16((M, K), S.seed_of("up_a", M, K), device=DEV)
+    w = S.randn_bf16((N1 + N2, K), S.seed_of("up_w", N1, N2, K), 1.0 / math.sqrt(K), device=DEV)
+    c1 = torch.full((M, N1 + 8), 7.0, dtype=torch.float32, device=DEV)
+    c2 = torch.full((M, N2 + 8), 7.0, dtype=torch.bfloat16, device=DEV)
+    lvx.lvx_linear_dual(a, w[:N1], w[N1:], c1[:, :N1], c2[:, :N2])
+    torch.cuda.synchronize()
+    ref = O.linear(S.to_f64(a), S.to_f64(w))
+    assert np.abs(S.to_f64(c1[:, :N1]) - ref[:, :N1]).max() <= 4.0 * K * 2.0 ** -24 + 1e-6     # as in test_linear_tile_edges
+    assert_close(c2[:, :N2], ref[:, N1:], "wide product")
+    assert bool((c1[:, N1:] == 7.0).all()) and bool((c2[:, N2:] == 7.0).all())
 
 
 @pytest.mark.parametrize("M,N,K", [s for s, _ in FP8_SHAPES])

@@ -2,6 +2,7 @@
 the kernels that those tests say they take."""
 import ctypes as C
 import os
+import random
 import shutil
 import subprocess
 
@@ -90,3 +91,35 @@ def test_gpu_attention_shapes_take_the_forms_they_name(rules):
                 assert rules.splits_keys(n_q, H, n_keys) or (n_q <= 128 and n_keys <= 7 * 64), (H, n_q, n_keys)
             for n_q in unsplit:
                 assert not rules.splits_keys(n_q, H, n_keys), (H, n_q, n_keys)
+
+
+def test_two_products_in_one_launch_never_cost_more_than_the_large_tiles(rules):
+    """Whatever groups the first product would have alone, a wide second product is not pressed into its tiles."""
+    rng = random.Random(3)
+
+    def log(lo, hi):
+        return int(round(lo * (hi / lo) ** rng.random()))
+    cases = [(1170, 256, 5120, 5120), (4680, 16, 13824, 5120), (256, 512, 5120, 5120), (48, 416, 9712, 384)]
+    cases += [(log(1, 5000), 8 * log(1, 1900), 8 * log(1, 1900), 64 * log(1, 216)) for _ in range(5000)]
+    kept = 0
+    for M, N1, N2, K in cases:
+        kernel, _, us = linear_plan(rules, M, [N1, N2], K, ORDER_FIRST)
+        tiles = -(-M // 128) * (-(-N1 // 256) + -(-N2 // 256))
+        assert us <= -(-tiles // 256) * (K // 64) * 0.8 * 1.0001, (M, N1, N2, K, kernel, us)
+        kept += "k" in kernel
+    assert kept > 100      # small pairs still run in groups
+
+
+def test_gpu_product_pairs_tell_the_orders_apart(rules):
+    """The pairs whose first product must not depend on its company: some would be summed in other groups if the launch decided."""
+    differ = 0
+    for M, N1, N2, K in gemm_tests.PAIRS:
+        def groups(*a):
+            return linear_plan(rules, *a)[0].partition(" ")[2]
+        alone = groups(M, [N1], K)
+        assert groups(M, [N1, N2], K, ORDER_FIRST) == alone, (M, N1, N2, K)
+        differ += groups(M, [N1, N2], K, ORDER_LAUNCH) != alone
+    assert differ >= 2
+    for M, N1, N2, K in gemm_tests.UNEQUAL_PAIRS:
+        assert linear_plan(rules, M, [N1], K)[0].endswith(("k2", "k4"))
+        assert "k" not in linear_plan(rules, M, [N1, N2], K, ORDER_FIRST)[0]
