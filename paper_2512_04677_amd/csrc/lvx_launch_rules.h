@@ -54,7 +54,9 @@ static inline long lvx_gemm_col_tiles(const lvx_gemm_segs_t *segs, int N, int bn
     return t;
 }
 
-// Which small tile to use, or one of the large ones (128 x 192 only if `narrow` says that the caller has it): the one whose rounds of the
+// Which small tile to use, or one of the large ones (128 x 192 only if `narrow` says that the caller has it, and only where that takes at
+// most LVX_GEMM_NARROW_MAX of the 128 x 256 tiles' time: 174 shapes at 0.825 by the rule, five rounds for four or three for three, ran in
+// 0.87 of it, but nine at 0.99, six rounds for five, in 1.015): the one whose rounds of the
 // chip (a compute unit that gets two tiles needs twice the time, whether one after the other or side by side) times slabs
 // times time per slab is least.  A small tile costs more per flop but less per tile, so it wins exactly where the larger ones do
 // not fill the chip: at K = 2560, N = 2560 the 64 x 128 tile up to about 1500 rows, 64 x 64 up to 400, 32 x 64 up to 200.
@@ -65,6 +67,7 @@ static inline long lvx_gemm_col_tiles(const lvx_gemm_segs_t *segs, int N, int bn
 // 256 tiles, 182 in 32 x 64; 4680 x (16 + 13824) x 5120: 541 and 2129).  The line lies below 1 because each further round of small tiles
 // also pays a start and a reduction that the time per slab does not hold: 48 x (416 + 9712) x 384, 0.80 by the rule, 9.3 and 10.5.
 #define LVX_GEMM_FIRST_MAX 0.75
+#define LVX_GEMM_NARROW_MAX 0.97
 static inline int lvx_gemm_pick_tile(const lvx_gemm_segs_t *segs, int M, int N, int n_slabs, bool narrow = false, double *cost_us = nullptr) {
     const bool many = segs != nullptr && segs->n > 0;
     const int order = many ? segs->order : LVX_GEMM_ORDER_LAUNCH;
@@ -78,7 +81,7 @@ static inline int lvx_gemm_pick_tile(const lvx_gemm_segs_t *segs, int M, int N, 
         double best_cost = groups <= 1 ? large_cost : 1e30;
         int best_groups = 1;
         best = LVX_GEMM_TILE_128X256;
-        if (narrow && groups <= 1 && rounds(128, 192) * n_slabs * LVX_GEMM_SLAB_US_128X192 < best_cost)
+        if (narrow && groups <= 1 && rounds(128, 192) * n_slabs * LVX_GEMM_SLAB_US_128X192 < LVX_GEMM_NARROW_MAX * best_cost)
             best_cost = rounds(128, 192) * n_slabs * LVX_GEMM_SLAB_US_128X192, best = LVX_GEMM_TILE_128X192;
 #define LVX_TILE_COST(ID_, BM_, BN_, WM_, WN_, NST_, KG_, PC_, US_)                                         \
     if (groups == 0 || KG_ == groups) {                                                                     \
@@ -99,15 +102,18 @@ static inline int lvx_gemm_pick_tile(const lvx_gemm_segs_t *segs, int M, int N, 
 // 1560 x 5120 x 13824 as 1536 rows in one round and 24 rows in 64 x 64 tiles 306 -> 234 microseconds, x 5120 x 5120 124 -> 91.  Chosen where the sum of both, and a
 // launch's LVX_GEMM_LAUNCH_US, is less than best_us, the time of the single launch.  Only tiles without K groups, which sum in the
 // order of the large kernel: a row's bits are those of the single launch.  Partial sums of squares need one column grouping for all rows,
-// so such a product is not split.
+// so such a product is not split.  Nor is one of more than LVX_GEMM_SPLIT_ROUNDS whole rounds: compute units drift apart from round to
+// round, so that the last, partial one begins before the one before it has ended (one whole round 0.77 to 0.89 of the single launch's
+// time, four 0.91 to 1.01, five 0.93 to 1.00, six to ten 0.98 to 1.10; 1.10: 4163 x 11984 x 1472, 156 us in one launch).
 #define LVX_GEMM_LAUNCH_US 3.0
+#define LVX_GEMM_SPLIT_ROUNDS 5
 static inline int lvx_gemm_split_rows(const lvx_gemm_segs_t *segs, int M, int N, int n_slabs, double best_us, int *rest_tile) {
     const bool many = segs != nullptr && segs->n > 0;
     if (many && segs->s[0].sumsq != nullptr) return 0;
     const int n = many ? segs->s[0].N : N;
     const long cols = lvx_gemm_col_tiles(segs, n, 256), total = (long)((M + 127) / 128) * cols, rounds = total / LVX_NUM_CU;
     const int m1 = (int)(rounds * LVX_NUM_CU / cols * 128);
-    if (m1 == 0 || m1 >= M) return 0;
+    if (m1 == 0 || m1 >= M || rounds > LVX_GEMM_SPLIT_ROUNDS) return 0;
     auto cost = [&](int m, int bm, int bn, double us) { return (double)lvx_rounds((long)((m + bm - 1) / bm) * lvx_gemm_col_tiles(segs, n, bn)) * n_slabs * us; };
     double best = best_us - cost(m1, 128, 256, LVX_GEMM_SLAB_US_128X256) - LVX_GEMM_LAUNCH_US;
     int tile = LVX_GEMM_TILE_128X256;

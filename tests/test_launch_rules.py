@@ -123,3 +123,15 @@ def test_gpu_product_pairs_tell_the_orders_apart(rules):
     for M, N1, N2, K in gemm_tests.UNEQUAL_PAIRS:
         assert linear_plan(rules, M, [N1], K)[0].endswith(("k2", "k4"))
         assert "k" not in linear_plan(rules, M, [N1, N2], K, ORDER_FIRST)[0]
+
+
+def test_near_ties_and_many_rounds_stay_with_one_large_launch(rules):
+    """Six rounds of 128 x 192 tiles for five of 128 x 256 (0.99 by the rule) ran slower, and so did rows split off after six or more
+    whole rounds; three for three (0.825) and one or two whole rounds gain."""
+    for M, N, K in [(5232, 6752, 4672), (2745, 12920, 2688), (3297, 10976, 5248), (5470, 6464, 9216), (3933, 8768, 2368),
+                    (4163, 11984, 1472), (4549, 14528, 3648), (4958, 10064, 5760)]:
+        assert linear_plan(rules, M, [N], K)[:2] == ("128x256", 0), (M, N, K)
+    assert linear_plan(rules, 5812, [14152], 4480, fp8=True)[:2] == ("128x256", 0)
+    assert linear_plan(rules, 1731, [5656], 2240)[0] == "128x192"
+    assert linear_plan(rules, 1560, [5120], 13824)[:2] == ("64x64", 1536)
+    assert linear_plan(rules, 3679, [4560], 7744)[:2] == ("64x64", 3584)
