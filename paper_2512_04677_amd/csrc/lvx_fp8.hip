@@ -129,7 +129,7 @@ int grid_for(size_t n_items) {
 }
 
 // ---- GEMM -------------------------------------------------------------------------------------------------------------
-template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, bool SPREAD>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N)
     lvx_gemm_fp8_kernel(const uint8_t *__restrict__ A, int64_t lda, const uint8_t *__restrict__ W, int64_t ldw,
                         const float *__restrict__ scale_a, const float *__restrict__ scale_w, bf16_t *C, int64_t ldc, int M, int N, int K,
@@ -214,8 +214,8 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N)
 #define LVX8_MFMAS(kk_, i0_, i1_)                                                                                \
     _Pragma("unroll") for (int i = i0_; i < i1_; ++i) _Pragma("unroll") for (int j = 0; j < FN; ++j)             \
         acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(af[(kk_) & 1][i], wf[(kk_) & 1][j], acc[i][j], 0, 0, 0, 0, 0, 0);
-#define LVX8_DMA_THIRD(third_) \
-    _Pragma("unroll") for (int q = 0; q < QPW; ++q) if ((q * 3) / QPW == (third_)) LVX8_DMA_ISSUE(nx2, kt_load, q);
+#define LVX8_DMA_PART(third_) \
+    _Pragma("unroll") for (int q = 0; q < QPW; ++q) if ((SPREAD ? (q * 3) / QPW : 0) == (third_)) LVX8_DMA_ISSUE(nx2, kt_load, q);
 
     f32x16_t acc[FM][FN];
 #pragma unroll
@@ -258,27 +258,26 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N)
     LVX8_READ_W(0, 0);
 
     // Slab t is in stage t % 3.  Per slab four MFMA groups (each k-step as two halves of the accumulator rows): the first three read the
-    // fragments still missing for what follows and issue a third of the DMA for slab t+2 each (into the stage that was read
-    // during slab t-1); then this wave's DMA for slab t+1 must have landed, one workgroup barrier, and the fourth group, which
-    // already reads k-step 0 of slab t+1.  (Two groups per slab, with all loads and the barrier in the middle, before: 4680 x 15360 x 5120 325
-    // -> 319 us, 4680 x 13824 x 5120 293 -> 284.)
+    // fragments still missing for what follows and issue the DMA for slab t+2 (into the stage that was read during slab t-1), a third each
+    // (SPREAD) or all of it behind the first; then this wave's DMA for slab t+1 must have landed, one workgroup barrier, and the
+    // fourth group, which already reads k-step 0 of slab t+1.  SPREAD: lvx_fp8_spreads_loads.
     int cur = 0, nxt = 1, nx2 = 2;
     for (int t = 0; t < n_k; ++t) {
         const int kt_load = t + 2 < last ? t + 2 : last;
         LVX8_READ_W(cur, 1);
         __builtin_amdgcn_sched_barrier(0);
         LVX8_MFMAS(0, 0, FM / 2);
-        LVX8_DMA_THIRD(0);
+        LVX8_DMA_PART(0);
         __builtin_amdgcn_sched_barrier(0);
         LVX8_READ_A(cur, 1, 0, FM / 2);
         __builtin_amdgcn_sched_barrier(0);
         LVX8_MFMAS(0, FM / 2, FM);
-        LVX8_DMA_THIRD(1);
+        LVX8_DMA_PART(1);
         __builtin_amdgcn_sched_barrier(0);
         LVX8_READ_A(cur, 1, FM / 2, FM);
         __builtin_amdgcn_sched_barrier(0);
         LVX8_MFMAS(1, 0, FM / 2);
-        LVX8_DMA_THIRD(2);
+        LVX8_DMA_PART(2);
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(QPW) : "memory");
         __syncthreads();
@@ -425,10 +424,15 @@ lvx_status_t lvx_launch_linear_fp8(const void *dev_aq, int64_t lda, const float 
         const int total = tiles_m * tiles_n;
         const int per_xcd = (total + 7) / 8;
         const dim3 grid(per_xcd * 8), block(512);
-#define LVX8_LAUNCH(EPI_)                                                                                                         \
-        hipLaunchKernelGGL((lvx_gemm_fp8_kernel<BM, BN, 2, 4, EPI_>), grid, block, 0, (hipStream_t)stream, (const uint8_t *)dev_aq, lda, \
+#define LVX8_LAUNCH_AS(EPI_, SPREAD_)                                                                                                      \
+        hipLaunchKernelGGL((lvx_gemm_fp8_kernel<BM, BN, 2, 4, EPI_, SPREAD_>), grid, block, 0, (hipStream_t)stream, (const uint8_t *)dev_aq, lda, \
                            (const uint8_t *)dev_wq, ldw, dev_scale_a, dev_scale_w, (bf16_t *)dev_c, ldc, rows, N, K, (const bf16_t *)dev_resid, \
                            ldr, dev_gate, tiles_m, tiles_n, per_xcd, amax_slots)
+#define LVX8_LAUNCH(EPI_)                     \
+        if (lvx_fp8_spreads_loads(K / 128))   \
+            LVX8_LAUNCH_AS(EPI_, true);       \
+        else                                  \
+            LVX8_LAUNCH_AS(EPI_, false)
         if (epi == LVX_EPI_STORE) {
             LVX8_LAUNCH(LVX_EPI_STORE);
         } else if (epi == LVX_EPI_GELU_TANH) {
@@ -439,6 +443,7 @@ lvx_status_t lvx_launch_linear_fp8(const void *dev_aq, int64_t lda, const float 
             LVX8_LAUNCH(LVX_EPI_RESID_GATE_F32);
         }
 #undef LVX8_LAUNCH
+#undef LVX8_LAUNCH_AS
         LVX_CHECK_HIP(hipGetLastError());
         if (m1 == 0) return LVX_OK;
     }

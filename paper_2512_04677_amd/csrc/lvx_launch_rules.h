@@ -146,6 +146,12 @@ static inline lvx_gemm_plan_t lvx_gemm_plan(const lvx_gemm_segs_t *segs, int M, 
     return p;
 }
 
+// FP8, 128 x 256 tiles: whether a slab's loads are spread over its matrix groups instead of issued behind the first.  Spread, they
+// take less from the matrix cores (from 16 slabs on 2.3 % faster on average, 4 % slower to 7 % faster, 110 shapes; 4680 x 15360 x 5120 355 ->
+// 339 us), but the last of them start later, which a product of few slabs need not make up for (below 16 slabs 0.5 % faster on
+// average, 10 % slower to 4 % faster, 144 shapes; 5971 x 7736 x 640 64 -> 68).
+static inline bool lvx_fp8_spreads_loads(int n_slabs) { return n_slabs >= 16; }
+
 // ---- convolution ---------------------------------------------------------------------------------------------------------------
 // The tiles with shared input rows: id, BM, BN, WM, WN, NST and the time in microseconds that a compute unit needs per stage (64
 // channels of three taps)

@@ -21,7 +21,8 @@ SHAPES = [((31, 24, 192), "32x32 k4"), ((33, 136, 320), "32x32 k4"), ((65, 1920,
           ((1300, 5120, 128), "128x256"), ((1411, 4616, 192), "128x256")]
 FP8_SHAPES = [((1, 8, 128), "64x64"), ((33, 136, 640), "32x32 k4"), ((65, 1920, 896), "32x32 k4"), ((64, 5760, 256), "32x64 k2"),
               ((95, 5000, 1152), "32x64 k2"), ((257, 2560, 1408), "64x64"), ((600, 2560, 128), "64x128"), ((1151, 1544, 1664), "64x128"),
-              ((1901, 2568, 256), "128x256")]
+              ((1901, 2568, 256), "128x256"),
+              ((1411, 4616, 1920), "128x256"), ((1411, 4616, 2048), "128x256")]      # 15 and 16 slabs: loads behind one matrix group, and spread
 # the same with the rows that the 128 x 256 kernel takes before the tile named here takes the rest (0: one launch)
 LARGE_SHAPES = [((1550, 5120, 1152), "64x64", 1536),   # 12 row tiles in one round, 14 rows in a small tile
                 ((1567, 5112, 1408), "64x64", 1536),   # the same with ragged columns, 31 rows

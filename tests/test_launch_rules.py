@@ -29,6 +29,7 @@ void conv_plan(int W, int N, int n_slabs, int M, int max_m, int *kind, int *tile
     const lvx_conv_plan_t p = lvx_conv_plan(W, N, n_slabs, M, max_m);
     *kind = p.kind, *tile = p.tile;
 }
+int fp8_spreads(int n_slabs) { return lvx_fp8_spreads_loads(n_slabs); }
 int splits_keys(int n_q, int H, int n_keys) { return lvx_attention_splits_keys(n_q, H, n_keys); }
 }
 """
@@ -71,6 +72,7 @@ def test_gpu_gemm_shapes_take_the_kernels_they_name(rules):
         assert linear_plan(rules, M, [N], K)[:2] == (kernel, 0), (M, N, K)
     for (M, N, K), kernel in gemm_tests.FP8_SHAPES:
         assert linear_plan(rules, M, [N], K, fp8=True)[:2] == (kernel, 0), (M, N, K)
+    assert {bool(rules.fp8_spreads(K // 128)) for (_, _, K), kernel in gemm_tests.FP8_SHAPES if kernel == "128x256"} == {False, True}
     for (M, N, K), kernel, m1 in gemm_tests.LARGE_SHAPES:
         assert linear_plan(rules, M, [N], K)[:2] == (kernel, m1), (M, N, K)
     for (M, N, K), kernel, m1 in gemm_tests.FP8_SPLIT_SHAPES:
