@@ -517,7 +517,7 @@ lvx_status_t lvx_launch_attention(const bf16_t *q, int64_t ld_q, int n_q, int H,
                 n_keys, cap);
     LVX_REQUIRE(scale > 0.f, LVX_ERR_INVALID_ARG, "attention: scale must be positive");
     LVX_REQUIRE(D == 64 || D == 128, LVX_ERR_UNSUPPORTED, "head_dim %d not supported (64 or 128)", D);
-    const bool two = lvx_attention_splits_keys(n_q, H, n_keys);
+    const bool two = lvx_attention_splits_keys(n_q, H, n_keys, D);
 #define LVX_ATTN_LAUNCH(D_, TP_, PRE_, QN_, KS_) \
     launch<D_, TP_, PRE_, QN_, KS_>(q, ld_q, n_q, H, k_packed, vt_packed, cap, n_keys, scale, out, ld_out, stream, amax_slots, qnorm)
     if (qnorm != nullptr) {  // the kernel normalises and scales the queries as it loads them (cross-attention of a bf16 stage)

@@ -201,16 +201,23 @@ static inline lvx_conv_plan_t lvx_conv_plan(int W, int N, int n_slabs, int M, in
 
 // Whether a workgroup takes 128 queries and splits the keys over its halves instead of 256 queries.  A round of the chip with
 // the split takes 0.62 to 0.66 of a round without (measured from 9 to 150 key tiles, head_dim 64 and 128: half the tiles per wave, but
-// twice the K / V stream per tile), so it pays where the smaller workgroups need less than half as many more rounds: always
+// twice the K / V stream per tile), up to 7 key tiles 0.69 to 0.85 (the exchange at the end is the same for every length), so it pays
+// where the smaller workgroups need less than half, or a third, as many more rounds: always
 // while they fit one round, e.g. 12 heads x 1170 queries x 6240 keys 134 -> 90 us, but 20 x 1886 x 8487 (160 workgroups become 300)
-// 191 -> 236 us.  A last query tile of one or two waves' rows ends early and is not counted as a workgroup.  Up to 128 queries half
-// of the waves idle without the split; with less than 8 key tiles the exchange at the end then costs what it saves (9.3 against
-// 10.2 us at 4 tiles, 15.1 against 14.4 at 9).
-static inline bool lvx_attention_splits_keys(int n_q, int H, int n_keys) {
-    if (n_q <= 128 && n_keys <= 7 * LVX_KEY_TILE) return false;
+// 191 -> 236 us, and 24 x 3441 x 187 (three rounds for two) 19.8 -> 21.3.  A last query tile that leaves every SIMD to a single wave, or most
+// SIMDs idle, takes about half the time at head_dim 128 (not at 64, where fewer MFMAs stand against the same softmax), so where it alone begins a round it counts for half of one (32 x 2142 x 1851, 79 rows behind one
+// whole round: 90 us, 96 split; 24 x 4118 x 3072, 22 rows behind three rounds of the split form: 155, 192 split; 22 x 2823 x 2136, 7 rows: 114,
+// 77 split).  With few key tiles a workgroup's start and end weigh more than its rows: the split form's last tile counts in full (24 x 2712 x
+// 192: 18.1 us, 20.5 split).  Up to 128 queries half of the waves idle without the split; with less than 8 key tiles the exchange then
+// costs what it saves (9.3 against 10.2 us at 4 tiles, 15.1 against 14.4 at 9).
+static inline bool lvx_attention_splits_keys(int n_q, int H, int n_keys, int head_dim) {
+    const bool few_tiles = n_keys <= 7 * LVX_KEY_TILE;
+    if (n_q <= 128 && few_tiles) return false;
     auto rounds = [&](int qt) {
-        const long tiles = (n_q + qt - 1 - qt / 4) / qt;
-        return lvx_rounds((tiles > 0 ? tiles : 1) * H);
+        const long full = n_q / qt, last = n_q % qt, whole = lvx_rounds(full * H), all = lvx_rounds((full + (last > 0)) * H);
+        if (full == 0 || last > (qt == 256 ? 128 : 32)) return (double)all;
+        if (few_tiles) return (double)(qt == 256 && last <= 64 ? whole : all);
+        return head_dim == 64 ? (double)all : 0.5 * (whole + all);
     };
-    return 0.65 * rounds(128) < rounds(256);
+    return (few_tiles ? 0.74 : 0.65) * rounds(128) < rounds(256);
 }

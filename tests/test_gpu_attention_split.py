@@ -14,17 +14,17 @@ pytestmark = pytest.mark.gpu
 
 
 # (head_dim, heads), query counts that take the split form (from 8 key tiles on, and above 128 queries from the first), query counts
-# that do not; test_launch_rules.py holds the rule to it
+# that do not, and some that take one or the other by the number of tiles; test_launch_rules.py holds the rule to it
 KEY_COUNTS = (1, 63, 64, 65, 128, 129, 192, 200, 1024, 1030, 1090)
-GEOMETRIES = [((128, 3), (1, 31, 33, 127, 128, 129, 257), ()), ((64, 4), (1, 31, 33, 127, 128, 129, 257), ()),
-              ((128, 136), (130,), (200, 256)), ((64, 136), (130,), (200, 256))]
+GEOMETRIES = [((128, 3), (1, 31, 33, 127, 128, 129, 257), (), ()), ((64, 4), (1, 31, 33, 127, 128, 129, 257), (), ()),
+              ((128, 136), (330,), (200, 256), (130,)), ((64, 136), (330,), (130, 200, 256), ())]
 
 
-@pytest.mark.parametrize("D,H", [g for g, _, _ in GEOMETRIES])
+@pytest.mark.parametrize("D,H", [g[0] for g in GEOMETRIES])
 @pytest.mark.parametrize("prescaled", [False, True])
 def test_attention_key_split_edges(lvx, D, H, prescaled):
     d = H * D
-    n_qs = next(split + unsplit for g, split, unsplit in GEOMETRIES if g == (D, H))
+    n_qs = next(split + unsplit + either for g, split, unsplit, either in GEOMETRIES if g == (D, H))
     for n_keys in KEY_COUNTS:
         cache = lvx.KVCache(lvx.cache_desc(1, H, D, 1, n_keys, 1, 1, 1), DEV)
         k = S.randn_bf16((n_keys, d), S.seed_of("sp_k", D, H, n_keys), device=DEV)

@@ -30,7 +30,7 @@ void conv_plan(int W, int N, int n_slabs, int M, int max_m, int *kind, int *tile
     *kind = p.kind, *tile = p.tile;
 }
 int fp8_spreads(int n_slabs) { return lvx_fp8_spreads_loads(n_slabs); }
-int splits_keys(int n_q, int H, int n_keys) { return lvx_attention_splits_keys(n_q, H, n_keys); }
+int splits_keys(int n_q, int H, int n_keys, int head_dim) { return lvx_attention_splits_keys(n_q, H, n_keys, head_dim); }
 }
 """
 SMALL = {0: "64x128", 1: "64x64", 2: "32x64 k2", 3: "32x32 k4", -1: "128x256", -2: "128x192"}
@@ -87,12 +87,14 @@ def test_gpu_conv_shapes_take_the_kernels_they_name(rules):
 
 
 def test_gpu_attention_shapes_take_the_forms_they_name(rules):
-    for (D, H), split, unsplit in attention_tests.GEOMETRIES:
+    for (D, H), split, unsplit, either in attention_tests.GEOMETRIES:
+        for n_q in either:
+            assert {rules.splits_keys(n_q, H, n_keys, D) for n_keys in attention_tests.KEY_COUNTS} == {0, 1}
         for n_keys in attention_tests.KEY_COUNTS:
             for n_q in split:
-                assert rules.splits_keys(n_q, H, n_keys) or (n_q <= 128 and n_keys <= 7 * 64), (H, n_q, n_keys)
+                assert rules.splits_keys(n_q, H, n_keys, D) or (n_q <= 128 and n_keys <= 7 * 64), (H, n_q, n_keys)
             for n_q in unsplit:
-                assert not rules.splits_keys(n_q, H, n_keys), (H, n_q, n_keys)
+                assert not rules.splits_keys(n_q, H, n_keys, D), (H, n_q, n_keys)
 
 
 def test_two_products_in_one_launch_never_cost_more_than_the_large_tiles(rules):
@@ -137,3 +139,14 @@ def test_near_ties_and_many_rounds_stay_with_one_large_launch(rules):
     assert linear_plan(rules, 1731, [5656], 2240)[0] == "128x192"
     assert linear_plan(rules, 1560, [5120], 13824)[:2] == ("64x64", 1536)
     assert linear_plan(rules, 3679, [4560], 7744)[:2] == ("64x64", 3584)
+
+
+def test_attention_splits_keys_only_where_that_is_faster(rules):
+    """(queries, heads, keys, head_dim) measured in both forms."""
+    for c in [(2423, 32, 64, 128), (3473, 24, 59, 64), (3728, 18, 128, 128), (2712, 24, 192, 64), (3441, 20, 187, 64), (2127, 32, 256, 128),
+              (4324, 18, 256, 128), (2991, 32, 384, 128), (2142, 32, 1851, 128), (4197, 16, 5755, 128), (4118, 24, 3072, 128),
+              (1886, 20, 8487, 128), (4680, 40, 24960, 128)]:
+        assert not rules.splits_keys(*c), c
+    for c in [(291, 2, 64, 128), (394, 12, 320, 128), (2396, 26, 256, 128), (3281, 20, 704, 64), (1170, 12, 6240, 128), (4686, 16, 3480, 128),
+              (2823, 22, 2136, 128), (3684, 18, 1920, 64), (3170, 40, 5376, 64), (3622, 18, 6976, 64)]:
+        assert rules.splits_keys(*c), c
