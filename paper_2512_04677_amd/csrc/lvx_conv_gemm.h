@@ -4,7 +4,7 @@
 // pixel.  Rows are therefore counted over padded pixels (x runs to W + 1; the two border columns are computed and dropped: 2 / W more
 // work), which makes the rows of all three taps BM + 2 consecutive rows: a stage holds those once, and the three taps' weights.  64 x 64:
 // 33 KB instead of 48 per three slabs; 192 x 128: 73 KB where 256 x 128 tiles took 108 for the same products.
-// K runs (dt, dy, 64 channels, dx); the order of summation is the same for every tile.
+// K runs (dt, dy, 64 channels, dx); the order of summation is the same for every tile, the 256 x 128 one of lvx_gemm.hip included.
 #pragma once
 #include "lvx_gemm_core.h"
 

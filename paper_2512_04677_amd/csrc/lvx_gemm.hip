@@ -100,11 +100,11 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N)
     }
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
     const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds_base + wave * 1024);
-    // byte offset of K slab kt in the A operand: plain GEMM kt * 128; convolution: the tap's shift in the padded volume plus
-    // the slab's channel offset inside the tap (wave-uniform scalar arithmetic)
-    auto a_slab = [&](int kt) -> size_t { return CONV ? lvx_conv_slab_offset(cm, kt) : (size_t)kt * ROW_B; };
+    // byte offset of the K slab to load in the rows of A and W: plain GEMM kt * 128 in both
+    lvx_conv_walk_t walk;
 #define LVX_DMA_ISSUE(stage_, kt_, q_)                                                                                      \
-    lvx_dma16((q_) < A_Q ? reinterpret_cast<const char *>(A) + a_off_ : reinterpret_cast<const char *>(W) + (size_t)(kt_) * ROW_B, \
+    lvx_dma16((q_) < A_Q ? reinterpret_cast<const char *>(A) + (CONV ? walk.a : (size_t)(kt_) * ROW_B)                      \
+                         : reinterpret_cast<const char *>(W) + (CONV ? walk.w : (size_t)(kt_) * ROW_B),                     \
               doff[q_], lds_wave + (uint32_t)((stage_) * STAGE_B + (q_) * NW * 1024))
 
     // fragment reads for v_mfma_f32_16x16x32_bf16: lane (l16, q4) reads row l16 of a 16-row block, k-chunk 4*ks + q4 of the
@@ -161,16 +161,11 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N)
 
     const int n_k = K / BK;
     const int last = n_k - 1;
-    {
-        const size_t a_off_ = a_slab(0);
 #pragma unroll
-        for (int q = 0; q < QPW; ++q) LVX_DMA_ISSUE(0, 0, q);
-    }
-    {
-        const size_t a_off_ = a_slab(last < 1 ? last : 1);
+    for (int q = 0; q < QPW; ++q) LVX_DMA_ISSUE(0, 0, q);
+    if (CONV) walk.next(cm);  // a convolution has at least 27 slabs
 #pragma unroll
-        for (int q = 0; q < QPW; ++q) LVX_DMA_ISSUE(1, (last < 1 ? last : 1), q);
-    }
+    for (int q = 0; q < QPW; ++q) LVX_DMA_ISSUE(1, (last < 1 ? last : 1), q);
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(QPW) : "memory");
     __syncthreads();
     LVX_DMA_READ_A(0, 0, 0, FM);
@@ -183,7 +178,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N)
     int cur = 0, nxt = 1, nx2 = 2;
     for (int t = 0; t < n_k; ++t) {
         const int kt_load = t + 2 < last ? t + 2 : last;
-        const size_t a_off_ = a_slab(kt_load);
+        if (CONV && t + 2 <= last) walk.next(cm);
         LVX_DMA_READ_W(cur, 1, 0, FN);
         __builtin_amdgcn_sched_barrier(0);
         LVX_DMA_MFMAS(0, 0, FM / 2);

@@ -31,8 +31,8 @@ struct lvx_gemm_args_t {
     lvx_conv_map_t conv;
 };
 
-// Convolution: byte offset in the padded volume of output pixel r's tap (0,0,0), and of K slab kt relative to it (the tap's shift
-// plus the slab's channel offset inside the tap: wave-uniform scalar arithmetic).
+// Convolution: byte offset in the padded volume of output pixel r's tap (0,0,0); and of K slab kt relative to it for the small tiles, which
+// walk K tap by tap (the tap's shift plus the slab's channel offset inside the tap: wave-uniform scalar arithmetic).
 __device__ __forceinline__ size_t lvx_conv_pixel_offset(const lvx_conv_map_t &cm, int r) {
     const int hw = cm.H * cm.W;
     const int t = r / hw, rem = r - t * hw;
@@ -44,6 +44,25 @@ __device__ __forceinline__ size_t lvx_conv_slab_offset(const lvx_conv_map_t &cm,
     const int dt = tap / 9, dy = (tap - dt * 9) / 3, dx = tap - dt * 9 - dy * 3;
     return ((size_t)dt * cm.frame_pitch + (size_t)dy * cm.row_pitch + (size_t)dx * cm.C) * sizeof(bf16_t) + (size_t)kc * 128;
 }
+
+// The walk of the 256 x 128 tiles, slab after slab: K runs (dt, dy, 64 channels, dx), the order of the tiles with shared input rows, so
+// that the steps of one layer may take either.  a: byte offset in the volume, as above; w: in a row of the weights.
+struct lvx_conv_walk_t {
+    size_t a = 0, w = 0;
+    int dx = 0, kc = 0, dy = 0;
+    __device__ __forceinline__ void next(const lvx_conv_map_t &cm) {
+        const int64_t tap = (int64_t)cm.C * (int)sizeof(bf16_t), row = (int64_t)cm.row_pitch * (int)sizeof(bf16_t), frame = (int64_t)cm.frame_pitch * (int)sizeof(bf16_t);
+        if (++dx < 3) {
+            a += tap, w += tap;
+        } else if (dx = 0, ++kc < cm.slabs_per_tap) {
+            a += 128 - 2 * tap, w += 128 - 2 * tap;
+        } else {  // from the last 64 channels of tap dx = 2 to the first of the next line's dx = 0
+            kc = 0;
+            a += 128 - 3 * tap + row, w += 128;
+            if (++dy == 3) dy = 0, a += frame - 3 * row;
+        }
+    }
+};
 
 // One MFMA operand fragment: the two 16-byte chunks of a lane's row.
 template <bool FP8>

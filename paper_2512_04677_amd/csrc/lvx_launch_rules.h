@@ -164,23 +164,24 @@ static inline bool lvx_fp8_spreads_loads(int n_slabs) { return n_slabs >= 16; }
 // The kernel of a step of M output pixels (rows of W) and N channels, n_slabs 64-wide slabs of the contraction, is the
 // one with the least rounds of the chip times slabs (or stages of three) times time of each: the 256 x 128 tiles of the linears' kernel
 // where they fill the chip (C_out is 128 ... 512 in the decoder this serves; 128-wide column tiles waste nothing there), the tiles with shared
-// input rows below that and where their rounds come out better, the 32 x 32 tile with four K groups for a few thousand outputs.  The kinds differ in the order of
-// summation, so the kind follows from max_m, the pixels of the longest step the layer takes: a pixel's bits do not depend on how many
-// frames arrive with it.  Measured (us a step, before: 256 x 128 only or the linears' small tiles): one 50 x 90 frame 384 -> 192 channels
-// 119, 61 -> 45; four 25 x 45 frames 512 -> 512 146 -> 105; four 240 x 400 64 -> 64 199 -> 139; two 200 x 360 192 -> 96 238 -> 202.
+// input rows below that and where their rounds come out better, the 32 x 32 tile with four K groups for a few thousand outputs.  A pixel's
+// bits must not depend on how many frames arrive with it: the first two kinds sum in one order, the K groups in another, so whether
+// these are taken follows from max_m, the pixels of the longest step the layer takes.  Measured (us a step, before: 256 x 128 only or the
+// linears' small tiles): one 50 x 90 frame 384 -> 192 channels 119, 61 -> 42; four 25 x 45 frames 512 -> 512 146 -> 105; four 240 x 400
+// 64 -> 64 199 -> 139; two 200 x 360 192 -> 96 238 -> 202.
 enum { LVX_CONV_LARGE, LVX_CONV_ROWS, LVX_CONV_GROUPS };
 struct lvx_conv_plan_t {
     int kind, tile;  // tile: of LVX_CONV_ROW_TILES or LVX_GEMM_SMALL_TILES
 };
 static inline lvx_conv_plan_t lvx_conv_plan(int W, int N, int n_slabs, int M, int max_m) {
-    int kind = -1, tile = -1;
-    for (int pass = 0; pass < 2; ++pass) {  // 0: the kind, at the longest step; 1: the tile, at this one
+    lvx_conv_plan_t plan = {LVX_CONV_LARGE, 0};
+    for (int pass = 0; pass < 2; ++pass) {  // 0: K groups or not, at the longest step; 1: the tile, at this one
         const int m = pass == 0 ? max_m : M;
+        const bool groups = pass == 1 && plan.kind == LVX_CONV_GROUPS;
         double best = 1e30;
-        int best_kind = kind;
         auto rounds = [&](long rows, int bm, int bn) { return (double)lvx_rounds((rows + bm - 1) / bm * ((N + bn - 1) / bn)); };
-        auto offer = [&](int k, int id, double us) {
-            if ((kind < 0 || k == kind) && us < best) best = us, best_kind = k, tile = id;
+        auto offer = [&](int kind, int tile, double us) {
+            if ((pass == 0 || (kind == LVX_CONV_GROUPS) == groups) && us < best) best = us, plan = {kind, tile};
         };
         offer(LVX_CONV_LARGE, 0, rounds(m, 256, 128) * n_slabs * 0.82);
         const long padded = (long)m / W * (W + 2);
@@ -191,9 +192,8 @@ static inline lvx_conv_plan_t lvx_conv_plan(int W, int N, int n_slabs, int M, in
     if (KG_ > 2) offer(LVX_CONV_GROUPS, ID_, rounds(m, BM_, BN_) * ((n_slabs + KG_ - 1) / KG_ * KG_) * US_);
         LVX_GEMM_SMALL_TILES(LVX_TILE_COST)
 #undef LVX_TILE_COST
-        kind = best_kind;
     }
-    return {kind, tile};
+    return plan;
 }
 
 // ---- attention -----------------------------------------------------------------------------------------------------------------

@@ -88,7 +88,15 @@ TILE_SHAPES = [
 ]
 
 
-@pytest.mark.parametrize("H,W,Ci,Co,frames", [s for s, _ in TILE_SHAPES])
+# the same with the kernels of steps of one, two, ... frames: 256 x 128 tiles and tiles with shared rows in one layer
+MIXED_SHAPES = [
+    ((97, 125, 64, 136, 2), ("rows 256x64", "256x128")),
+    ((82, 98, 64, 136, 3), ("rows 128x64", "rows 256x64", "256x128")),
+    ((104, 77, 128, 136, 3), ("rows 128x64", "rows 256x64", "256x128")),
+]
+
+
+@pytest.mark.parametrize("H,W,Ci,Co,frames", [s for s, _ in TILE_SHAPES] + [s for s, _ in MIXED_SHAPES])
 def test_conv_tiles_and_chunking(lvx, H, W, Ci, Co, frames):
     """Every tile the rule can pick, against the oracle; a frame's bits do not depend on how many frames arrive with it."""
     x, w, b = conv_inputs("ct_%d_%d_%d_%d" % (H, W, Ci, Co), frames, H, W, Ci, Co, pad=8)

@@ -84,6 +84,20 @@ def test_gpu_conv_shapes_take_the_kernels_they_name(rules):
     for (H, W, c_in, c_out, frames), kernel in conv_tests.TILE_SHAPES:
         assert conv_plan(rules, H, W, c_in, c_out, frames, frames) == kernel, (H, W, c_in, c_out, frames)
     assert {k for _, k in conv_tests.TILE_SHAPES} == set(ROWS.values()) | {"256x128", "32x32 k4"}
+    for (H, W, c_in, c_out, frames), kernels in conv_tests.MIXED_SHAPES:
+        assert tuple(conv_plan(rules, H, W, c_in, c_out, frames, n) for n in range(1, frames + 1)) == kernels, (H, W, c_in, c_out, frames)
+
+
+def test_conv_step_shorter_than_the_longest_takes_its_own_best_kernel(rules):
+    """Layers of up to `max_frames` frames whose longest step suits the tiles with shared rows and whose shorter one does not."""
+    for H, W, c_in, c_out, max_frames, n in [(109, 80, 448, 496, 4, 3), (42, 127, 448, 248, 8, 5), (84, 98, 384, 224, 4, 3), (21, 339, 64, 376, 4, 3)]:
+        assert conv_plan(rules, H, W, c_in, c_out, max_frames, max_frames).startswith("rows")
+        assert conv_plan(rules, H, W, c_in, c_out, max_frames, n) == "256x128"
+    # K groups sum in another order: a layer takes them for every step or for none
+    rng = random.Random(4)
+    for _ in range(2000):
+        s = (rng.randint(1, 60), rng.randint(1, 60), 64 * rng.randint(1, 4), 8 * rng.randint(1, 40), rng.randint(2, 8))
+        assert len({conv_plan(rules, *s, n).startswith("32x32") for n in range(1, s[4] + 1)}) == 1, s
 
 
 def test_gpu_attention_shapes_take_the_forms_they_name(rules):
