@@ -11,6 +11,7 @@ import pytest
 import test_gpu_attention_split as attention_tests
 import test_gpu_conv as conv_tests
 import test_gpu_gemm_tiles as gemm_tests
+import test_gpu_query_norm as query_norm_tests
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2512_04677_amd", "csrc")
 SOURCE = r"""
@@ -29,6 +30,7 @@ void conv_plan(int W, int N, int n_slabs, int M, int max_m, int *kind, int *tile
     const lvx_conv_plan_t p = lvx_conv_plan(W, N, n_slabs, M, max_m);
     *kind = p.kind, *tile = p.tile;
 }
+int sumsq_parts(int M, int N, int n_slabs) { return N / lvx_gemm_part_cols(lvx_gemm_pick_tile(nullptr, M, N, n_slabs)); }
 int fp8_spreads(int n_slabs) { return lvx_fp8_spreads_loads(n_slabs); }
 int splits_keys(int n_q, int H, int n_keys, int head_dim) { return lvx_attention_splits_keys(n_q, H, n_keys, head_dim); }
 }
@@ -98,6 +100,11 @@ def test_conv_step_shorter_than_the_longest_takes_its_own_best_kernel(rules):
     for _ in range(2000):
         s = (rng.randint(1, 60), rng.randint(1, 60), 64 * rng.randint(1, 4), 8 * rng.randint(1, 40), rng.randint(2, 8))
         assert len({conv_plan(rules, *s, n).startswith("32x32") for n in range(1, s[4] + 1)}) == 1, s
+
+
+def test_gpu_query_norm_shapes_leave_the_partial_sums_they_name(rules):
+    for (H, fh, fw, frames), parts in query_norm_tests.SHAPES:
+        assert rules.sumsq_parts(fh * fw * frames, 128 * H, 2 * H) == parts, (H, fh, fw, frames)
 
 
 def test_gpu_attention_shapes_take_the_forms_they_name(rules):
