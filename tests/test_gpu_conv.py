@@ -113,3 +113,22 @@ def test_conv_tiles_and_chunking(lvx, H, W, Ci, Co, frames):
     torch.cuda.synchronize()
     assert torch.equal(one, y)
     conv.close()
+
+
+@pytest.mark.parametrize("steps", [(9, 1, 2, 9, 3, 8, 9), (5, 4, 1, 1, 7, 2, 6)])
+def test_many_frames_of_few_pixels(lvx, steps):
+    """Steps whose frames are shared out over workgroups, after steps of every length: the history is read from where another share's
+    frames land."""
+    H, W, C = 3, 5, 64
+    n = sum(steps)
+    x, w, b = conv_inputs("mf_%d" % steps[0], n, H, W, C, 16, pad=8)
+    ref = O.causal_conv3d(S.to_f64(x), S.to_f64(w).reshape(16, 3, 3, 3, C), S.to_f64(b))
+    conv = lvx.CausalConv(C, 16, H, W, 9, DEV)
+    y = torch.empty((n, H, W, 16), dtype=torch.bfloat16, device=DEV)
+    at = 0
+    for k in steps:
+        conv.step(x[at:at + k], w, b, 0, y[at:at + k])
+        at += k
+    torch.cuda.synchronize()
+    assert_close(y, ref, "many frames, steps %s" % (steps,))
+    conv.close()
