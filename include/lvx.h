@@ -189,6 +189,8 @@ lvx_status_t lvx_kvcache_gather_sink_source(const lvx_kvcache_t *cache, int32_t 
  * Chunk-to-cache attention (Eq. 1; Appendix C attention paragraph: current tokens against the concatenation
  * of cached K/V and themselves):  O[n,h,:] = softmax_m(scale * <q[n,h,:], K[m,h,:]>) V[m,h,:] over the visible
  * prefix of `layer` (every key visible, no mask).  q, out: [n_q][ld] bf16.  bf16 MFMA, fp32 online softmax.
+ * The same call gives the same bits.  Where n_q and the heads are few, the keys are summed in two halves, so the last bits of a query's
+ * output may differ between calls that split the queries or heads differently.
  * Errors: STATE if the layer has no visible keys yet.
  * ------------------------------------------------------------------------------------------------ */
 lvx_status_t lvx_chunk_attention(const lvx_kvcache_t *cache, int32_t layer, const void *dev_q, int64_t ld_q,
@@ -213,7 +215,9 @@ typedef enum {
     LVX_EPI_STORE_F32 = 6   /* C = A W^T with C in fp32 (ldc in fp32 elements): no rounding of the accumulator */
 } lvx_epilogue_t;
 
-/* C[M][N] = epilogue(A[M][K] * W[N][K]^T), bf16 in/out, fp32 accumulate on MFMA.  K % 64 == 0, N % 8 == 0. */
+/* C[M][N] = epilogue(A[M][K] * W[N][K]^T), bf16 in/out, fp32 accumulate on MFMA.  K % 64 == 0, N % 8 == 0.
+ * The same call gives the same bits.  The order in which a product is summed depends on M, N and K (one, two or four K groups), so
+ * the last bits of a row may differ between calls that split the rows or columns differently. */
 lvx_status_t lvx_linear(const void *dev_a, int64_t lda, const void *dev_w, int64_t ldw, void *dev_c, int64_t ldc,
                         int32_t M, int32_t N, int32_t K, lvx_epilogue_t epi, const void *dev_resid, int64_t ldr,
                         const float *dev_gate, lvx_stream_t stream);
@@ -222,7 +226,9 @@ lvx_status_t lvx_linear(const void *dev_a, int64_t lda, const void *dev_w, int64
  * store, W1 / W2 share the row stride ldw.  c1_is_f32 != 0: C1 is fp32 (ldc1 in fp32 elements), its accumulators are stored
  * un-rounded -- what a key projection wants, whose result is normalised and rotated before the one rounding to bf16 that the
  * cache holds.  C2 is always bf16.  The block's own launches are built on the same segment mechanism: q | k (fp32) | v of the
- * self-attention in one launch, the context's K (fp32) and V of a group of layers in one launch.  K % 64 == 0, N1, N2 % 8 == 0. */
+ * self-attention in one launch, the context's K (fp32) and V of a group of layers in one launch.  K % 64 == 0, N1, N2 % 8 == 0.
+ * C1 has the bits of lvx_linear's unless the second product is so wide that it would be slowed down by the order of summation
+ * that suits the first alone; C2 may be summed in another order than alone. */
 lvx_status_t lvx_linear_dual(const void *dev_a, int64_t lda, const void *dev_w1, const void *dev_w2, int64_t ldw, void *dev_c1,
                              int64_t ldc1, int32_t c1_is_f32, void *dev_c2, int64_t ldc2, int32_t M, int32_t N1, int32_t N2, int32_t K,
                              lvx_stream_t stream);
@@ -234,7 +240,8 @@ lvx_status_t lvx_linear_dual(const void *dev_a, int64_t lda, const void *dev_w1,
  *     dev_scratch256: 256 bytes of device scratch (16-byte aligned).  cols % 16 == 0, ldq % 16 == 0.  Used for weights
  *     (once) and activations (every call) alike.
  *   lvx_linear_fp8: C[M][N] = epilogue(scale_a * scale_w * (Aq[M][K] . Wq[N][K]^T)), fp32 accumulate on the FP8 matrix
- *     cores, C / R / gate and the epilogues as in lvx_linear.  K % 128 == 0, N % 8 == 0, lda and ldw in bytes, % 16 == 0. */
+ *     cores, C / R / gate and the epilogues as in lvx_linear.  K % 128 == 0, N % 8 == 0, lda and ldw in bytes, % 16 == 0.
+ *     The order of summation depends on M, N and K as there, and for rows that go to a second launch on their place in M. */
 lvx_status_t lvx_fp8_quantize(const void *dev_x, int64_t ld, int32_t rows, int32_t cols, void *dev_q, int64_t ldq,
                               void *dev_scratch256, float *dev_scale, lvx_stream_t stream);
 lvx_status_t lvx_linear_fp8(const void *dev_aq, int64_t lda, const float *dev_scale_a, const void *dev_wq, int64_t ldw,
@@ -360,7 +367,7 @@ lvx_status_t lvx_sink_prefill(const lvx_stage_t *stage /* host */, lvx_kvcache_t
  * convolution of the decoder keeps its two most recent input frames and prepends them as causal context for the next frames).
  *   y[t, y, x, o] = act(bias[o] + sum_{dt,dy,dx,c} w[o][(dt*3+dy)*3+dx][c] * x[t+dt-2, y+dy-1, x+dx-1, c])
  * zeros outside the frame and before the first frame of the sequence; frames arrive in order over any number of steps and the
- * result equals the convolution of the whole sequence.  Channels last, bf16: x [n_frames][H][W][c_in], y [n_frames][H][W][c_out],
+ * result equals the convolution of the whole sequence, bit for bit whatever the steps' lengths on one handle.  Channels last, bf16: x [n_frames][H][W][c_in], y [n_frames][H][W][c_out],
  * w [c_out][27*c_in] with row stride ldw (taps time-major, then row, then column; channels innermost), bias fp32 [c_out] or
  * NULL, act 0 = none, 1 = SiLU.  fp32 accumulation on the matrix cores.  c_in % 64 == 0, c_out % 8 == 0.
  * The state (a zero-padded volume of max_frames + 2 frames, lvx_causal_conv_state_bytes) is caller-owned device memory,

@@ -55,11 +55,11 @@ static inline long lvx_gemm_col_tiles(const lvx_gemm_segs_t *segs, int N, int bn
 }
 
 // Which small tile to use, or one of the large ones (128 x 192 only if `narrow` says that the caller has it, and only where that takes at
-// most LVX_GEMM_NARROW_MAX of the 128 x 256 tiles' time: 174 shapes at 0.825 by the rule, five rounds for four or three for three, ran in
-// 0.87 of it, but nine at 0.99, six rounds for five, in 1.015): the one whose rounds of the
+// most LVX_GEMM_NARROW_MAX of the 128 x 256 tiles' time: 174 shapes at 0.825 by the rule, the same number of rounds, ran in 0.87 of it,
+// but nine at 0.99, six rounds for five, in 1.015): the one whose rounds of the
 // chip (a compute unit that gets two tiles needs twice the time, whether one after the other or side by side) times slabs
 // times time per slab is least.  A small tile costs more per flop but less per tile, so it wins exactly where the larger ones do
-// not fill the chip: at K = 2560, N = 2560 the 64 x 128 tile up to about 1500 rows, 64 x 64 up to 400, 32 x 64 up to 200.
+// not fill the chip: at N = K = 2560 32 x 32 up to 96 rows, 32 x 64 up to 192, 64 x 64 up to 384, 64 x 128 up to 768, 128 x 192 up to 2304.
 // The number of K groups fixes the order in which a product is summed; segs->order says who decides it (see lvx_gemm_segs_t).
 // LVX_GEMM_ORDER_FIRST takes the groups that suit the first product alone, so that its bits are those of a launch of its own, as long as
 // the launch then costs at most LVX_GEMM_FIRST_MAX of the 128 x 256 launch of both, and one group otherwise: a narrow product's K groups
@@ -100,9 +100,10 @@ static inline int lvx_gemm_pick_tile(const lvx_gemm_segs_t *segs, int M, int N, 
 // Rows of a product that the 128 x 256 kernel takes in whole rounds of the chip, the rest (*rest_tile) going to a small tile in a second
 // launch; 0: all rows in one launch.  A product of 260 large tiles on 256 compute units takes two rounds, the second nearly empty:
 // 1560 x 5120 x 13824 as 1536 rows in one round and 24 rows in 64 x 64 tiles 306 -> 234 microseconds, x 5120 x 5120 124 -> 91.  Chosen where the sum of both, and a
-// launch's LVX_GEMM_LAUNCH_US, is less than best_us, the time of the single launch.  Only tiles without K groups, which sum in the
-// order of the large kernel: a row's bits are those of the single launch.  Partial sums of squares need one column grouping for all rows,
-// so such a product is not split.  Nor is one of more than LVX_GEMM_SPLIT_ROUNDS whole rounds: compute units drift apart from round to
+// launch's LVX_GEMM_LAUNCH_US, is less than best_us, the time of the single launch.  Only tiles without K groups: in bf16 these sum in
+// the order of the large kernel, so a row's bits are those of the single launch (in FP8 the small tiles' matrix instruction takes 128
+// products at once, the large kernel's 64, so the rows behind the split may differ in their last bits).  Partial sums of squares need one
+// column grouping for all rows, so such a product is not split.  Nor is one of more than LVX_GEMM_SPLIT_ROUNDS whole rounds: compute units drift apart from round to
 // round, so that the last, partial one begins before the one before it has ended (one whole round 0.77 to 0.89 of the single launch's
 // time, four 0.91 to 1.01, five 0.93 to 1.00, six to ten 0.98 to 1.10; 1.10: 4163 x 11984 x 1472, 156 us in one launch).
 #define LVX_GEMM_LAUNCH_US 3.0
@@ -167,7 +168,7 @@ static inline bool lvx_fp8_spreads_loads(int n_slabs) { return n_slabs >= 16; }
 // input rows below that and where their rounds come out better, the 32 x 32 tile with four K groups for a few thousand outputs.  A pixel's
 // bits must not depend on how many frames arrive with it: the first two kinds sum in one order, the K groups in another, so whether
 // these are taken follows from max_m, the pixels of the longest step the layer takes.  Measured (us a step, before: 256 x 128 only or the
-// linears' small tiles): one 50 x 90 frame 384 -> 192 channels 119, 61 -> 42; four 25 x 45 frames 512 -> 512 146 -> 105; four 240 x 400
+// linears' small tiles; 260 random layers and steps against 256 x 128 tiles everywhere: none slower, geometric mean 1.57): one 50 x 90 frame 384 -> 192 channels 119, 61 -> 42; four 25 x 45 frames 512 -> 512 146 -> 105; four 240 x 400
 // 64 -> 64 199 -> 139; two 200 x 360 192 -> 96 238 -> 202.
 enum { LVX_CONV_LARGE, LVX_CONV_ROWS, LVX_CONV_GROUPS };
 struct lvx_conv_plan_t {
