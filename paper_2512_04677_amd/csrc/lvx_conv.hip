@@ -20,33 +20,34 @@ struct lvx_causal_conv {
 
 namespace {
 
-// One step's data movement.  A thread owns one 16-byte chunk of one interior pixel through frames_per_y of the frames: those of
+// One step's data movement.  A thread owns one 16-byte chunk of one interior pixel through all frames, or (SHARED) through frames_per_y: those of
 // blockIdx.y = 0 move the two most recent frames of the previous step to the front (read before anything is written: the frames overlap
 // when that step had a single one; last_frames = 0: the history is already in place), and all put the new frames behind them:
 // x [n_frames][H][W][c] -> P[2 + f][1 + y][1 + x][:].  The new frames that land where the history is read from belong to the thread that
 // reads it, whichever share they fall into.  The zero border is never written.  Bound by launches for
 // one small frame and by memory for several large ones; one launch instead of three took 5 us off a 100 x 180 x 384, four-frame step of
 // 545 us.
+template <bool SHARED>
 __global__ void __launch_bounds__(256) lvx_conv_advance_kernel(const bf16_t *__restrict__ x, bf16_t *vol, int n_frames, int frames_per_y, int last_frames,
                                                                int n_pixels, int W, int chunks_per_pixel, int64_t frame_elems, int row_pitch) {
     const size_t frame_chunks = (size_t)n_pixels * chunks_per_pixel;
-    const int f0 = (int)blockIdx.y * frames_per_y, f1 = f0 + frames_per_y < n_frames ? f0 + frames_per_y : n_frames;
+    const int share = SHARED ? (int)blockIdx.y : 0;
+    const int f0 = share * frames_per_y, f1 = SHARED && f0 + frames_per_y < n_frames ? f0 + frames_per_y : n_frames;
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < frame_chunks; i += (size_t)gridDim.x * 256) {
         const int pix = (int)(i / chunks_per_pixel), c = (int)(i % chunks_per_pixel);
         const int y = pix / W, xw = pix - y * W;
         bf16_t *at = vol + (size_t)(y + 1) * row_pitch + (size_t)((xw + 1) * chunks_per_pixel + c) * 8;
         auto put = [&](int f) { *reinterpret_cast<uint4 *>(at + (size_t)(f + 2) * frame_elems) = reinterpret_cast<const uint4 *>(x)[f * frame_chunks + i]; };
-        const bool history = blockIdx.y == 0 && last_frames > 0;
-        if (history) {
+        if (share == 0 && last_frames > 0) {
             const uint4 h0 = *reinterpret_cast<const uint4 *>(at + (size_t)last_frames * frame_elems);
             const uint4 h1 = *reinterpret_cast<const uint4 *>(at + (size_t)(last_frames + 1) * frame_elems);
             *reinterpret_cast<uint4 *>(at) = h0;
             *reinterpret_cast<uint4 *>(at + frame_elems) = h1;
-            for (int f = last_frames - 2; f < last_frames; ++f)
+            for (int f = last_frames - 2; SHARED && f < last_frames; ++f)
                 if (f >= f1 && f < n_frames) put(f);
         }
         for (int f = f0; f < f1; ++f)
-            if (blockIdx.y == 0 || last_frames == 0 || f < last_frames - 2 || f >= last_frames) put(f);
+            if (share == 0 || last_frames == 0 || f < last_frames - 2 || f >= last_frames) put(f);
     }
 }
 
@@ -131,8 +132,8 @@ extern "C" lvx_status_t lvx_causal_conv_step(lvx_causal_conv_t *c, const void *d
     // thread for all: 55 us the step, 34 as three launches)
     const int grid = grid_for((size_t)n_pixels * (d.c_in / 8)), most = grid < 1024 ? 1024 / grid : 1;
     const int shares = (n_frames + 3) / 4 < most ? (n_frames + 3) / 4 : most, per = (n_frames + shares - 1) / shares;
-    hipLaunchKernelGGL(lvx_conv_advance_kernel, dim3(grid, (n_frames + per - 1) / per), dim3(256), 0, st, (const bf16_t *)dev_x, c->vol, n_frames, per,
-                       c->last_frames, n_pixels, d.width, d.c_in / 8, c->frame_elems, row_pitch);
+    hipLaunchKernelGGL((shares > 1 ? lvx_conv_advance_kernel<true> : lvx_conv_advance_kernel<false>), dim3(grid, (n_frames + per - 1) / per), dim3(256), 0, st,
+                       (const bf16_t *)dev_x, c->vol, n_frames, per, c->last_frames, n_pixels, d.width, d.c_in / 8, c->frame_elems, row_pitch);
     LVX_CHECK_HIP(hipGetLastError());
     lvx_conv_map_t cm;
     cm.enabled = 1;
