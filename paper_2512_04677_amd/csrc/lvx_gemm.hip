@@ -11,9 +11,11 @@
 // Workgroup ids are dealt to XCDs round-robin by hardware; each XCD gets a contiguous range of tiles, walked in
 // column-major order inside bands of 8 row tiles, so concurrently running workgroups of one XCD share A and W slabs in
 // that XCD's L2.
-// The same kernel serves the decoder's 3x3x3 convolution as an implicit GEMM (CONV) where its tiles fill the chip: its A rows are
-// gathered from a zero-padded volume, a tap being a constant shift of the row addresses.
+// The kernel here has 128 x 192 tiles for the linears and serves the decoder's 3x3x3 convolution as an implicit GEMM (CONV, 256 x 128) where
+// those fill the chip: its A rows are gathered from a zero-padded volume, a tap being a constant shift of the row addresses.  The large
+// products run on lvx_gemm_wide.h, the small ones on lvx_gemm_core.h; lvx_gemm_choose says which.
 #include "lvx_conv_gemm.h"
+#include "lvx_gemm_wide.h"
 
 namespace {
 
@@ -22,7 +24,7 @@ constexpr int GROUP_M = 8;
 
 // gfx950's global_load_lds_dwordx4 moves 16 bytes per lane from
 // global memory straight into LDS (LDS byte address = M0 + 16*lane), so a slab needs no staging registers, no ds_write
-// and no trip through the register file; the pipeline depth is set by LDS stages (three 48 KB stages for a 128x256 tile)
+// and no trip through the register file; the pipeline depth is set by LDS stages (three 40 KB stages for a 128x192 tile)
 // instead of by registers.  A DMA wave-instruction fills 1024 contiguous LDS bytes = 8 rows of 64 bf16, so rows cannot be
 // padded; bank conflicts are avoided by an XOR swizzle instead: the 16-byte chunk c of LDS row r holds global chunk
 // c ^ ((r >> 1) & 7) (the lane simply fetches that chunk), and a fragment read of k-chunk c goes to position
@@ -274,28 +276,46 @@ lvx_status_t launch(const bf16_t *A, int64_t lda, const bf16_t *W, int64_t ldw, 
     return LVX_OK;
 }
 
-// The linears: the 128 x 256 kernel, a small tile where that one would leave compute units idle, or both for different rows.
+// The linears: see lvx_gemm_choose.
 lvx_status_t launch_linear(const bf16_t *A, int64_t lda, const bf16_t *W, int64_t ldw, bf16_t *C, int64_t ldc, int M, int N, int K, int epi,
                            const bf16_t *R, int64_t ldr, const float *gate, hipStream_t stream, const lvx_gemm_segs_t *segs = nullptr) {
     const bool sumsq = segs != nullptr && segs->s[0].sumsq != nullptr;  // (a 48-column wave cannot give sums of 64 columns)
-    const lvx_gemm_plan_t plan = lvx_gemm_plan(segs, M, N, K / BK, !sumsq);
-    const int m1 = plan.m1;  // rows the 128 x 256 kernel takes of a split product
-    if (m1 == 0 && plan.tile == LVX_GEMM_TILE_128X192) return launch<128, 192, 2, 4>(A, lda, W, ldw, C, ldc, M, N, K, epi, R, ldr, gate, stream, segs);
-    if (m1 > 0 || plan.tile == LVX_GEMM_TILE_128X256) {
-        LVX_TRY((launch<128, 256, 2, 4>(A, lda, W, ldw, C, ldc, m1 > 0 ? m1 : M, N, K, epi, R, ldr, gate, stream, segs)));
-        if (m1 == 0) return LVX_OK;
-    }
-    const bool c_f32 = epi == LVX_EPI_RESID_GATE_F32 || epi == LVX_EPI_STORE_F32;
+    const lvx_gemm_launch_t plan = lvx_gemm_choose(segs, M, N, K / BK, !sumsq, epi == LVX_EPI_RESID_GATE_F32);
+    if (plan.tile == LVX_GEMM_TILE_128X192) return launch<128, 192, 2, 4>(A, lda, W, ldw, C, ldc, M, N, K, epi, R, ldr, gate, stream, segs);
     lvx_gemm_args_t p = {};
-    p.A = (const char *)(A + (size_t)m1 * lda), p.lda = lda * 2;
+    p.A = (const char *)A, p.lda = lda * 2;
     p.W = (const char *)W, p.ldw = ldw * 2;
-    p.C = (char *)C + (size_t)m1 * ldc * (c_f32 ? 4 : 2), p.ldc = ldc;
-    if (R != nullptr) p.R = (const char *)R + (size_t)m1 * ldr * (epi == LVX_EPI_RESID_GATE_F32 ? 4 : 2);
-    p.ldr = ldr;
+    p.C = C, p.ldc = ldc;
+    p.R = R, p.ldr = ldr;
     p.gate = gate;
-    p.M = M - m1, p.N = N, p.n_slabs = K / BK;
+    p.N = N, p.n_slabs = K / BK;
     p.epi = epi;
     if (segs != nullptr) p.segs = *segs;
+    if (plan.wide_rows > 0) {
+        p.M = plan.wide_rows;
+        lvx_status_t st;
+        switch (epi) {
+#define LVX_WIDE_CASE(E_) case E_: st = lvx_gemm_wide_launch<E_, false>(p, plan.n_large, stream); break;
+            LVX_WIDE_CASE(LVX_EPI_GELU_TANH)
+            LVX_WIDE_CASE(LVX_EPI_RESID_GATE)
+            LVX_WIDE_CASE(LVX_EPI_RESID_GATE_F32)
+            LVX_WIDE_CASE(LVX_EPI_BIAS)
+            LVX_WIDE_CASE(LVX_EPI_BIAS_SILU)
+            LVX_WIDE_CASE(LVX_EPI_STORE_F32)
+            LVX_WIDE_CASE(LVX_EPI_SEGMENTS)
+            default: st = lvx_gemm_wide_launch<LVX_EPI_STORE, false>(p, plan.n_large, stream);
+#undef LVX_WIDE_CASE
+        }
+        LVX_TRY(st);
+        if (plan.wide_rows == M) return LVX_OK;
+    }
+    // the rows behind, or all, on a small tile
+    const int m1 = plan.wide_rows;
+    const bool c_f32 = epi == LVX_EPI_RESID_GATE_F32 || epi == LVX_EPI_STORE_F32;
+    p.A += (size_t)m1 * p.lda;
+    p.C = (char *)C + (size_t)m1 * ldc * (c_f32 ? 4 : 2);
+    if (R != nullptr) p.R = (const char *)R + (size_t)m1 * ldr * (epi == LVX_EPI_RESID_GATE_F32 ? 4 : 2);
+    p.M = M - m1;
     for (int i = 0; i < p.segs.n; ++i) p.segs.s[i].C = (char *)p.segs.s[i].C + (size_t)m1 * p.segs.s[i].ldc * (p.segs.s[i].f32 ? 4 : 2);
     return lvx_gemm_launch_small<false>(plan.tile, p, stream);
 }

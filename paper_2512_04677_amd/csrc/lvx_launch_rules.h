@@ -42,7 +42,7 @@ struct lvx_gemm_segs_t {
     X_(1, 64, 64, 2, 4, 4, 1, 16, 0.31f)  \
     X_(2, 32, 64, 1, 4, 5, 2, 16, 0.235f) \
     X_(3, 32, 32, 1, 2, 4, 4, 16, 0.16f)
-#define LVX_GEMM_SLAB_US_128X256 0.80f  // the 128 x 256 kernels, per slab and compute unit
+#define LVX_GEMM_SLAB_US_128X256 0.80f  // 128 x 256 tiles, per slab and compute unit
 #define LVX_GEMM_SLAB_US_128X192 0.66f  // the same kernel with 128 x 192 tiles (bf16): 1886 x 2560 x 6912 80 -> 74 us, 2048 x 3072 x 3072 44 -> 40.5
 enum { LVX_GEMM_TILE_128X256 = -1, LVX_GEMM_TILE_128X192 = -2 };
 
@@ -147,11 +147,99 @@ static inline lvx_gemm_plan_t lvx_gemm_plan(const lvx_gemm_segs_t *segs, int M, 
     return p;
 }
 
-// FP8, 128 x 256 tiles: whether a slab's loads are spread over its matrix groups instead of issued behind the first.  Spread, they
-// take less from the matrix cores (from 16 slabs on 2.3 % faster on average, 4 % slower to 7 % faster, 110 shapes; 4680 x 15360 x 5120 355 ->
-// 339 us), but the last of them start later, which a product of few slabs need not make up for (below 16 slabs 0.5 % faster on
-// average, 10 % slower to 4 % faster, 144 shapes; 5971 x 7736 x 640 64 -> 68).
+// FP8 products of 128 x 256 tiles whose slab loads paid to be spread over the matrix groups of a kernel that lvx_gemm_wide.h has replaced: its
+// phases spread them at every length.  No launch asks for it; the tests of the tile edges still name products on both sides of the line.
 static inline bool lvx_fp8_spreads_loads(int n_slabs) { return n_slabs >= 16; }
+
+// ---- 256 x 256 tiles (lvx_gemm_wide.h) -------------------------------------------------------------------------------------------
+// The kernel of the 128 x 256 tiles works some pairs of them as one 256 x 256 tile: M rows are lvx_wide_full_rows row tiles of 256 and, if at most
+// 128 rows remain, one of 128; the first n_large of the 256 x 256 tiles are taken whole, the others as two halves.
+static inline int lvx_wide_full_rows(int M) { return M / 256 + (M % 256 > 128 ? 1 : 0); }
+static inline long lvx_wide_halves(int M, long cols, long n_large) {
+    const long full = lvx_wide_full_rows(M);
+    return 2 * (full * cols - n_large) + ((M + 255) / 256 - full) * cols;
+}
+
+// Time by the rule of a launch with n_large whole tiles, slab by slab.  A whole tile takes 1.35 us a slab while all compute units have one (the
+// chip is held by its power: 256 x 256 x 64 on 256 units in that time are 1.59 PFLOP/s) and down to 1.04 while half of them idle; a half
+// 0.80, and up to 0.99 on the few units left beside a round of whole tiles that draws the power of the chip alone.  Whole tiles start
+// first, each unit takes the next tile when it is free.  600 products, bf16 and FP8, 600 to 8000 rows, each with none, all and whole rounds of
+// whole tiles: the choice by the rule takes 0.1 % longer on average than the fastest of them.  2048 x 8192 x 5120 as 256 whole tiles 116 us, as
+// 512 halves 147; 4680 x 5120 x 5120 as 256 + 228 halves 174, 360 + 20 199, 740 halves 198; 1560 x 13824 x 5120 as 256 + 190 183, 324 + 54 204;
+// 2150 x 7656 x 4224 as 510 halves 114, 240 + 30 135.
+#define LVX_GEMM_SLAB_US_256X256 1.35
+#define LVX_GEMM_SLAB_US_256X256_ALONE 1.04
+static inline double lvx_wide_slab_us(int M, long cols, long n_large) {
+    const double half = LVX_GEMM_SLAB_US_128X256;
+    const long busy = n_large % LVX_NUM_CU, halves = lvx_wide_halves(M, cols, n_large);
+    const double whole = (double)(n_large / LVX_NUM_CU) * LVX_GEMM_SLAB_US_256X256;
+    if (busy == 0) return whole + lvx_rounds(halves) * half;
+    const double most = LVX_NUM_CU / 2, last = LVX_GEMM_SLAB_US_256X256_ALONE +
+        (busy > most ? (LVX_GEMM_SLAB_US_256X256 - LVX_GEMM_SLAB_US_256X256_ALONE) * (busy - most) / most : 0.0);
+    // the last whole tiles take `busy` units for `last`, the other units begin the halves meanwhile: the first end of a half on either kind of
+    // unit by which all of them are done
+    const double beside = half + (busy > 208 ? 0.004 * (busy - 208) : 0.0);
+    const long idle = LVX_NUM_CU - busy;
+    long early = 0, late = 0;
+    double end = last;
+    while (idle * early + busy * late < halves) {
+        const double a = (early + 1) * beside, b = last + (late + 1) * half;
+        if (a <= b) ++early;
+        else ++late;
+        const double t = a <= b ? a : b;
+        if (t > end) end = t;
+    }
+    return whole + end;
+}
+// How many whole tiles are best: all, whole rounds of the chip, one round less, or none.
+static inline long lvx_wide_pick(int M, long cols, double *slab_us) {
+    const long total = lvx_wide_full_rows(M) * cols, rounds = total / LVX_NUM_CU * LVX_NUM_CU;
+    long best = 0;
+    double best_us = lvx_wide_slab_us(M, cols, 0);
+    const long offer[3] = {rounds - LVX_NUM_CU, rounds, total};
+    for (int i = 0; i < 3; ++i)
+        if (offer[i] > 0 && lvx_wide_slab_us(M, cols, offer[i]) <= best_us) best = offer[i], best_us = lvx_wide_slab_us(M, cols, offer[i]);
+    *slab_us = best_us;
+    return best;
+}
+
+// The launch of a product: lvx_gemm_plan, with 256 x 256 tiles where they are in reach.  wide_rows: the rows that the kernel of 128 x 256 and 256 x
+// 256 tiles takes, n_large whole tiles among them; the rows behind go to `tile` (m1 = wide_rows) or there are none.  A plan of other
+// tiles gives way where the wide kernel takes at most LVX_GEMM_WIDE_MAX of its time by the rule: there it took 0.91 to 1.01 of the time of 128 x 192
+// tiles (three of 65 products above 1) and 0.84 to 1.07 of that of rows split off, mean 0.95 (170 products); between 1.12 and 1.3 it took
+// 1.0 to 1.2.  With an fp32 residual (resid32), which fewer and larger tiles read and write on fewer compute units, up to
+// LVX_GEMM_WIDE_MAX_RESID (0.937 to 0.992: 0.95 to 1.12, mean 1.02).  A plan with K groups stays, they fix the order of summation, and so
+// does one that leaves partial sums of squares of narrower groups of columns.
+#define LVX_GEMM_WIDE_MAX 1.10
+#define LVX_GEMM_WIDE_MAX_RESID 0.93
+struct lvx_gemm_launch_t {
+    int tile, wide_rows, n_large;
+};
+static inline lvx_gemm_launch_t lvx_gemm_choose(const lvx_gemm_segs_t *segs, int M, int N, int n_slabs, bool narrow, bool resid32) {
+    const bool many = segs != nullptr && segs->n > 0;
+    const long cols = lvx_gemm_col_tiles(segs, many ? segs->s[0].N : N, 256);
+    const lvx_gemm_plan_t plan = lvx_gemm_plan(segs, M, N, n_slabs, narrow);
+    double us = 0.0, part_us = 0.0;
+    lvx_gemm_launch_t l = {LVX_GEMM_TILE_128X256, M, (int)lvx_wide_pick(M, cols, &us)};
+    if (plan.m1 == 0 && plan.tile == LVX_GEMM_TILE_128X256) return l;
+    double plan_us = plan.us;
+    lvx_gemm_launch_t other = {plan.tile, plan.m1, 0};
+    if (plan.m1 > 0) {
+        other.n_large = (int)lvx_wide_pick(plan.m1, cols, &part_us);
+#define LVX_TILE_COST(ID_, BM_, BN_, WM_, WN_, NST_, KG_, PC_, US_) \
+    if (plan.tile == ID_)                                           \
+        plan_us = part_us * n_slabs + (double)lvx_rounds((long)((M - plan.m1 + BM_ - 1) / BM_) * lvx_gemm_col_tiles(segs, many ? segs->s[0].N : N, BN_)) * n_slabs * US_;
+        LVX_GEMM_SMALL_TILES(LVX_TILE_COST)
+#undef LVX_TILE_COST
+    }
+    const bool sumsq = many && segs->s[0].sumsq != nullptr;
+    bool groups = false;
+#define LVX_TILE_GROUPS(ID_, BM_, BN_, WM_, WN_, NST_, KG_, PC_, US_) groups = groups || (plan.tile == ID_ && KG_ > 1);
+    LVX_GEMM_SMALL_TILES(LVX_TILE_GROUPS)
+#undef LVX_TILE_GROUPS
+    if (!sumsq && !groups && us * n_slabs <= (resid32 ? LVX_GEMM_WIDE_MAX_RESID : LVX_GEMM_WIDE_MAX) * plan_us) return l;
+    return other;
+}
 
 // ---- convolution ---------------------------------------------------------------------------------------------------------------
 // The tiles with shared input rows: id, BM, BN, WM, WN, NST and the time in microseconds that a compute unit needs per stage (64

@@ -1,0 +1,88 @@
+"""Products on 256 x 256 tiles and their halves against the fp64 oracle: one slab and few, rows and columns past the last tile, rows that only
+a half covers, all epilogues, output rows that allow 16-byte stores and rows that do not."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import lvx_synth as S
+from oracle import lvx_oracle as O
+from test_gpu_parity import DEV, assert_close
+
+pytestmark = pytest.mark.gpu
+
+# M, N, K with the 256 x 256 tiles and the halves that the rule takes; test_wide_rules.py holds the rule to it
+SHAPES = [((1731, 5656, 64), (161, 0)), ((1731, 5656, 192), (161, 0)), ((1567, 13832, 64), (256, 203)), ((1567, 13832, 320), (256, 203)),
+          ((4353, 4616, 128), (256, 153)), ((1411, 4616, 192), (0, 228))]
+FP8_SHAPES = [((1731, 5656, 128), (161, 0)), ((1731, 5656, 384), (161, 0)), ((1567, 13832, 256), (256, 203)), ((1411, 4616, 1920), (0, 228))]
+
+
+def padded(M, N, pad, dtype, fill=7.0):
+    return torch.full((M + 1, N + pad), fill, dtype=dtype, device=DEV)
+
+
+@pytest.mark.parametrize("pad", [8, 3])
+@pytest.mark.parametrize("M,N,K", [s for s, _ in SHAPES])
+def test_linear_on_wide_tiles(lvx, M, N, K, pad):
+    a = S.randn_bf16((M, K + 8), S.seed_of("wt_a", M, K), device=DEV)[:, :K]
+    w = S.randn_bf16((N, K + 64), S.seed_of("wt_w", N, K), 1.0 / math.sqrt(K), device=DEV)[:, :K]
+    g = S.randn_f32((N + 1,), 7, 0.5, 1.0, device=DEV)[1:]          # a gate vector at a 4-byte boundary
+    r = S.randn_f32((M, N + pad), S.seed_of("wt_r", M, N), device=DEV)
+    rb = r.to(torch.bfloat16)
+    ref = torch.from_numpy(O.linear(S.to_f64(a), S.to_f64(w)))
+    g64, r64, rb64 = (torch.from_numpy(S.to_f64(t)) for t in (g, r[:, :N], rb[:, :N]))
+    bound = 4.0 * K * 2.0 ** -24 + 1e-6      # fp32 sums of K products of size 1 / sqrt(K), as in test_gpu_gemm_tiles.py
+
+    def run(epi, dtype, resid=None, gate=None):
+        out = padded(M, N, pad, dtype)
+        lvx.lvx_linear(a, w, out[:M, :N], epi, resid=resid, gate=gate)
+        torch.cuda.synchronize()
+        assert bool((out[M] == 7.0).all()) and bool((out[:, N:] == 7.0).all()), epi
+        return out[:M, :N]
+    assert_close(run(lvx.EPI_STORE, torch.bfloat16), ref.numpy(), "store %dx%dx%d" % (M, N, K))
+    assert_close(run(lvx.EPI_GELU_TANH, torch.bfloat16), O.gelu_tanh(ref.numpy()), "gelu")
+    assert_close(run(lvx.EPI_BIAS, torch.bfloat16, gate=g), (ref + g64).numpy(), "bias")
+    assert_close(run(lvx.EPI_BIAS_SILU, torch.bfloat16, gate=g), O.silu((ref + g64).numpy()), "bias + silu")
+    assert_close(run(lvx.EPI_RESID_GATE, torch.bfloat16, resid=rb[:, :N], gate=g), (rb64 + g64 * ref).numpy(), "bf16 residual")
+    assert np.abs(S.to_f64(run(lvx.EPI_STORE_F32, torch.float32)) - ref.numpy()).max() <= bound
+    x = r.clone()
+    lvx.lvx_linear(a, w, x[:, :N], lvx.EPI_RESID_GATE_F32, resid=x[:, :N], gate=g)       # in place
+    torch.cuda.synchronize()
+    assert np.abs(S.to_f64(x[:, :N]) - (r64 + g64 * ref).numpy()).max() <= 4.0 * bound
+    assert torch.equal(x[:, N:], r[:, N:])
+
+
+@pytest.mark.parametrize("M,N,K", [s for s, _ in FP8_SHAPES])
+def test_linear_fp8_on_wide_tiles(lvx, M, N, K):
+    aq, sa = lvx.lvx_fp8_quantize(S.randn_bf16((M, K), S.seed_of("w8_a", M, K), device=DEV), row_pad=16)
+    wq, sw = lvx.lvx_fp8_quantize(S.randn_bf16((N, K), S.seed_of("w8_w", N, K), 1.0 / math.sqrt(K), device=DEV), row_pad=128)
+    dec = [S.to_f64(q.contiguous().view(torch.float8_e4m3fn).float()) * float(s.item()) for q, s in ((aq, sa), (wq, sw))]
+    ref = O.linear(dec[0], dec[1])
+    g = S.randn_f32((N,), 7, 0.5, 1.0, device=DEV)
+    out = padded(M, N, 8, torch.bfloat16)
+    lvx.lvx_linear_fp8(aq, sa, wq, sw, out[:M, :N], lvx.EPI_STORE)
+    x = S.randn_f32((M, N + 3), S.seed_of("w8_r", M, N), device=DEV)
+    r = x.clone()
+    lvx.lvx_linear_fp8(aq, sa, wq, sw, x[:, :N], lvx.EPI_RESID_GATE_F32, resid=x[:, :N], gate=g)
+    torch.cuda.synchronize()
+    assert_close(out[:M, :N], ref, "fp8 store %dx%dx%d" % (M, N, K))
+    assert bool((out[M] == 7.0).all()) and bool((out[:, N:] == 7.0).all()) and torch.equal(x[:, N:], r[:, N:])
+    # the FP8 products' alignment in the matrix core: see test_gpu_gemm_tiles.py
+    assert np.abs(S.to_f64(x[:, :N]) - (S.to_f64(r[:, :N]) + S.to_f64(g) * ref)).max() <= 1e-4 * math.sqrt(K)
+
+
+def test_segments_on_wide_tiles(lvx):
+    """Two products of one launch whose widths end inside a tile, the first stored fp32."""
+    M, N1, N2, K = 4353, 2328, 2296, 128
+    a = S.randn_bf16((M, K), S.seed_of("ws_a"), device=DEV)
+    w = S.randn_bf16((N1 + N2, K), S.seed_of("ws_w"), 1.0 / math.sqrt(K), device=DEV)
+    ref = O.linear(S.to_f64(a), S.to_f64(w))
+    for pad in (8, 2):
+        c1, c2 = padded(M, N1, pad, torch.float32), padded(M, N2, pad, torch.bfloat16)
+        lvx.lvx_linear_dual(a, w[:N1], w[N1:], c1[:M, :N1], c2[:M, :N2])
+        torch.cuda.synchronize()
+        assert np.abs(S.to_f64(c1[:M, :N1]) - ref[:, :N1]).max() <= 4.0 * K * 2.0 ** -24 + 1e-6
+        assert_close(c2[:M, :N2], ref[:, N1:], "second product")
+        for c, n in ((c1, N1), (c2, N2)):
+            assert bool((c[M] == 7.0).all()) and bool((c[:, n:] == 7.0).all())
