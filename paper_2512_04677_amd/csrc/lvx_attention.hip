@@ -27,6 +27,9 @@
 //     and different key tiles instead of different queries and the same tiles; a stage then carries two tiles, one for each half,
 //     and the halves' outputs meet in LDS at the end.  Both halves start from the first tile's row maximum (the second half, half a
 //     period behind, finds it in LDS): a later tile of scores that are all -inf then adds nothing, whichever half it falls to.
+//   * SPLIT (see lvx_attention_parts): a workgroup takes a range of the key tiles and leaves its queries' outputs in fp32, un-normalised, with their
+//     references and sums; lvx_attention_combine_kernel adds the ranges up in their order.  A range whose first tile has no finite
+//     score for a query takes that query's reference from the first tile that has one.
 //   * template switches: TP = 64-key tiles per pipeline phase (2 from 1024 visible keys on: half the barriers, pipeline fills and
 //     drains per key); PRE = the queries arrive multiplied by scale * log2(e) and the score accumulators start at minus the
 //     softmax reference, so a score leaves the MFMA as the exponent (one FMA per score less; used inside a block, where the
@@ -41,11 +44,11 @@ constexpr int KT = LVX_KEY_TILE;
 // keys, equal at 1560, 3 to 4 % faster from 6240 keys on)
 constexpr int TP2_MIN_KEYS = 16 * KT;
 
-template <int D, int TP, bool PRE, bool QN, int KS>
+template <int D, int TP, bool PRE, bool QN, int KS, bool SPLIT>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
     lvx_attention_kernel(const bf16_t *__restrict__ q, int64_t ld_q, int n_q, const bf16_t *__restrict__ kp,
                          const bf16_t *__restrict__ vtp, int cap, int n_keys, float c_exp2, bf16_t *__restrict__ out,
-                         int64_t ld_out, int n_qtiles, int total_wg, int per_xcd, uint32_t *amax_slots, lvx_attn_qnorm_t qn) {
+                         int64_t ld_out, int n_qtiles, int total_wg, int per_xcd, uint32_t *amax_slots, lvx_attn_qnorm_t qn, lvx_attn_parts_t parts) {
     constexpr int NWAVES = 8, QB = 2;     // QB blocks of 16 queries per wave
     constexpr int QT = 16 * QB * NWAVES / KS;
     constexpr int MK = D / 32;  // MFMA k-steps (32 wide) over head_dim
@@ -78,8 +81,16 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     const int xcd = blockIdx.x & 7;
     const int widx = xcd * per_xcd + (blockIdx.x >> 3);
     if (widx >= total_wg) return;
-    const int head = widx / n_qtiles;
+    const int per_head = SPLIT ? n_qtiles * parts.n : n_qtiles;
+    const int head = widx / per_head;
     const int qtile = widx % n_qtiles;
+    const int part = SPLIT ? (widx - head * per_head) / n_qtiles : 0;  // the workgroups that run together read the same range
+    int tile0 = 0;
+    if (SPLIT) {  // n_keys becomes the range's own count
+        const int tiles = (n_keys + KT - 1) / KT, tile1 = (part + 1) * tiles / parts.n;
+        tile0 = part * tiles / parts.n;
+        n_keys = (tile1 * KT < n_keys ? tile1 * KT : n_keys) - tile0 * KT;
+    }
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
@@ -144,8 +155,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     const int n_tiles = (n_keys + KT - 1) / KT;
     const int n_ph = (n_tiles + TS - 1) / TS;                          // phases: TP consecutive tiles for each key group
     const int n_mine = KS == 1 ? n_ph : (n_tiles + KS - 1 - kg) / KS;  // phases in which this wave's key group has a tile
-    const char *k_src = reinterpret_cast<const char *>(kp + (size_t)head * cap * D);   // K tile t at k_src + t * TILE_B
-    const char *v_src = reinterpret_cast<const char *>(vtp + (size_t)head * cap * D);  // V^T tile t at v_src + t * TILE_B
+    const char *k_src = reinterpret_cast<const char *>(kp + (size_t)head * cap * D) + (size_t)tile0 * TILE_B;   // K tile t at k_src + t * TILE_B
+    const char *v_src = reinterpret_cast<const char *>(vtp + (size_t)head * cap * D) + (size_t)tile0 * TILE_B;  // V^T tile t at v_src + t * TILE_B
 
     // ---- staging (direct to LDS) -----------------------------------------------------------------------------------------
     // DMA instruction e of this wave covers LDS rows [rows_per_instr * (wave + NWAVES*e), +rows_per_instr) of a tile.
@@ -238,6 +249,10 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     float sub[QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) mc[qb] = l_run[qb] = sub[qb] = 0.f;
+    // SPLIT: queries that have not met a finite score yet (their reference is still 0); any_unset: some query of the wave
+    bool unset[QB], any_unset = false;
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) unset[qb] = SPLIT && kg == 0;
     f32x4_t s[4 * TP][QB];
     bf16x8_t pb[QB][2 * TP];  // [qb][ks]: P^T for keys 32 ks + 8 q4 .. + 7, query 16 qb + l16
 
@@ -315,7 +330,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
            maximum as the new reference and the accumulators rescaled.  The four lane groups that share a query decide     \
            together (wave-wide vote); the final division by the row sum absorbs whatever reference was used. */            \
         float lsum[QB];                                                                                        \
-        bool rebase_ = (t_) == 0 && kg == 0;                                                                   \
+        bool rebase_ = ((t_) == 0 && kg == 0) || (SPLIT && any_unset);                                         \
         for (;;) {                                                                                             \
             if (rebase_) {                                                                                     \
                 _Pragma("unroll") for (int qb = 0; qb < QB; ++qb) {                                            \
@@ -324,14 +339,21 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
                         tmax = fmaxf(tmax, s[kb][qb][e]);                                                      \
                     tmax = fmaxf(tmax, __shfl_xor(tmax, 16));                                                  \
                     tmax = fmaxf(tmax, __shfl_xor(tmax, 32));                                                  \
-                    const bool first_ = (t_) == 0 && kg == 0;                                                  \
+                    const bool first_ = SPLIT ? unset[qb] : (t_) == 0 && kg == 0;                              \
                     const float tmc = PRE ? tmax + sub[qb] : tmax * c_exp2;                                    \
-                    const bool need = first_ || tmc > mc[qb] + 6.0f;                                           \
+                    const bool none_ = SPLIT && tmc == -INFINITY;                                              \
+                    const bool need = !none_ && (first_ || tmc > mc[qb] + 6.0f);                               \
+                    if (SPLIT) unset[qb] = first_ && none_;                                                    \
                     const float alpha = (need && !first_) ? __builtin_amdgcn_exp2f(mc[qb] - tmc) : 1.0f;       \
                     if (need) mc[qb] = tmc;                                                                    \
                     l_run[qb] *= alpha;                                                                        \
                     _Pragma("unroll") for (int i = 0; i < DB; ++i) _Pragma("unroll") for (int e = 0; e < 4; ++e) \
                         o[i][qb][e] *= alpha;                                                                  \
+                }                                                                                              \
+                if (SPLIT) {                                                                                   \
+                    bool un_ = false;                                                                          \
+                    _Pragma("unroll") for (int qb = 0; qb < QB; ++qb) un_ = un_ || unset[qb];                  \
+                    any_unset = __any(un_);                                                                    \
                 }                                                                                              \
             }                                                                                                  \
             if (PRE) {                                                                                         \
@@ -390,7 +412,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
         LVX_ATTN_Y(0);
         if (KS == 2 && q4 == 0) {
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb) first_ref[(qw * QB + qb) * 16 + l16] = mc[qb];
+            for (int qb = 0; qb < QB; ++qb) first_ref[(qw * QB + qb) * 16 + l16] = SPLIT && unset[qb] ? -INFINITY : mc[qb];
         }
         __syncthreads();
         for (int i = 1; i < n_ph; ++i) {
@@ -410,7 +432,16 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
         __syncthreads();
         if (KS == 2) {
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb) mc[qb] = first_ref[(qw * QB + qb) * 16 + l16];
+            for (int qb = 0; qb < QB; ++qb) {
+                mc[qb] = first_ref[(qw * QB + qb) * 16 + l16];
+                if (SPLIT && mc[qb] == -INFINITY) mc[qb] = 0.f, unset[qb] = true;
+            }
+            if (SPLIT) {
+                bool un = false;
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) un = un || unset[qb];
+                any_unset = __any(un);
+            }
         }
         for (int i = 1; i <= n_ph; ++i) {
             if (i < n_ph) LVX_ATTN_STAGE_DMA(i);
@@ -433,7 +464,9 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
     if (KS == 2) {
         static_assert(NWAVES / 2 * QB * DB * 1024 <= NS * TILE_B, "the exchanged outputs must fit the K ring");
-        if (n_mine == 0) mc[0] = mc[1] = -3.0e38f;  // a single tile: group 1 saw no key
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb)
+            if (n_mine == 0 || (SPLIT && l_tot[qb] == 0.f)) mc[qb] = -3.0e38f;  // a single tile: group 1 saw no key; SPLIT: nor a finite score
         float2 *stat = reinterpret_cast<float2 *>(vs);
         __syncthreads();
 #pragma unroll
@@ -450,12 +483,27 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
                 const float2 other = stat[(qw * QB + qb) * 64 + lane];
                 const float m = fmaxf(mc[qb], other.x), w_own = __builtin_amdgcn_exp2f(mc[qb] - m), w_other = __builtin_amdgcn_exp2f(other.x - m);
                 l_tot[qb] = l_tot[qb] * w_own + other.y * w_other;
+                mc[qb] = m;
 #pragma unroll
                 for (int db = 0; db < DB; ++db)
                     o[db][qb] = o[db][qb] * w_own + *reinterpret_cast<const f32x4_t *>(ks + (((qw * QB + qb) * DB + db) * 64 + lane) * 16) * w_other;
             }
     }
 
+    if (SPLIT) {
+        const size_t d_model = (size_t)parts.H * D;
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            if (KS == 2 && qb != grp) continue;
+            const int row = qtile * QT + qw * (16 * QB) + 16 * qb + l16;
+            if (row >= n_q) continue;
+            float *op = parts.o + ((size_t)part * n_q + row) * d_model + (size_t)head * D;
+#pragma unroll
+            for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4_t *>(op + 16 * db + 4 * q4) = o[db][qb];
+            if (q4 == 0) parts.stat[((size_t)part * n_q + row) * parts.H + head] = make_float2(mc[qb], l_tot[qb]);
+        }
+        return;
+    }
     uint32_t amax_b = 0;  // largest magnitude among the bf16 values this lane stores (bit pattern without sign)
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
@@ -492,19 +540,71 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
 }
 
-template <int D, int TP, bool PRE, bool QN, int KS>
+// Adds up the ranges of keys: out = sum_p w_p o_p / sum_p w_p l_p with w_p = 2^(m_p - max m), in the order of the ranges.  A thread
+// owns eight channels of one query and head.  Bound by memory: the ranges' fp32 outputs are read once.
+__global__ void __launch_bounds__(256) lvx_attention_combine_kernel(lvx_attn_parts_t parts, int n_q, int D, bf16_t *__restrict__ out, int64_t ld_out,
+                                                                    uint32_t *amax_slots) {
+    const int d_model = parts.H * D, chunks = d_model / 8;
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    uint32_t amax_b = 0;
+    if (i < (size_t)n_q * chunks) {
+        const int row = (int)(i / chunks), c = (int)(i % chunks), head = c / (D / 8);
+        float m = -3.0e38f, l = 0.f, v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        for (int p = 0; p < parts.n; ++p) {
+            const float2 st = parts.stat[((size_t)p * n_q + row) * parts.H + head];
+            if (!(st.y == 0.f)) m = fmaxf(m, st.x);
+        }
+        for (int p = 0; p < parts.n; ++p) {
+            const float2 st = parts.stat[((size_t)p * n_q + row) * parts.H + head];
+            const f32x4_t *src = reinterpret_cast<const f32x4_t *>(parts.o + ((size_t)p * n_q + row) * d_model) + 2 * c;
+            const f32x4_t a = src[0], b = src[1];
+            const float w = st.y == 0.f ? 0.f : __builtin_amdgcn_exp2f(st.x - m);  // (a range without a finite score weighs nothing)
+            l += w * st.y;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] += w * a[e], v[4 + e] += w * b[e];
+        }
+        const float inv = 1.0f / l;
+        u32x4_t y;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            y[e] = pack_bf16x2(v[2 * e] * inv, v[2 * e + 1] * inv);
+            const uint32_t lo = y[e] & 0x7fffu, hi = (y[e] >> 16) & 0x7fffu;
+            amax_b = amax_b > lo ? amax_b : lo;
+            amax_b = amax_b > hi ? amax_b : hi;
+        }
+        *reinterpret_cast<u32x4_t *>(out + (size_t)row * ld_out + 8 * c) = y;
+    }
+    if (amax_slots != nullptr) {  // as in the attention kernel, one atomic per wave
+#pragma unroll
+        for (int s = 32; s >= 1; s >>= 1) {
+            const uint32_t o = (uint32_t)__shfl_xor((int)amax_b, s);
+            amax_b = amax_b > o ? amax_b : o;
+        }
+        if ((threadIdx.x & 63) == 0 && amax_b != 0) atomicMax(amax_slots + ((blockIdx.x * 4 + (threadIdx.x >> 6)) & (LVX_AMAX_SLOTS - 1)), amax_b << 16);
+    }
+}
+
+template <int D, int TP, bool PRE, bool QN, int KS, bool SPLIT = false>
 lvx_status_t launch(const bf16_t *q, int64_t ld_q, int n_q, int H, const bf16_t *kp, const bf16_t *vtp, int cap, int n_keys,
-                    float scale, bf16_t *out, int64_t ld_out, hipStream_t stream, uint32_t *amax_slots, const lvx_attn_qnorm_t *qnorm = nullptr) {
+                    float scale, bf16_t *out, int64_t ld_out, hipStream_t stream, uint32_t *amax_slots, const lvx_attn_qnorm_t *qnorm = nullptr,
+                    const lvx_attn_parts_t *parts = nullptr) {
     constexpr int QT = 256 / KS;
     const int n_qtiles = (n_q + QT - 1) / QT;
-    const int total = n_qtiles * H;
+    lvx_attn_parts_t pt = {};
+    if (SPLIT) pt = *parts;
+    const int total = n_qtiles * H * (SPLIT ? pt.n : 1);
     const int per_xcd = (total + 7) / 8;
     const float c = scale * LVX_LOG2E;
     lvx_attn_qnorm_t qn = {};
     if (qnorm != nullptr) qn = *qnorm;
-    hipLaunchKernelGGL((lvx_attention_kernel<D, TP, PRE, QN, KS>), dim3(per_xcd * 8), dim3(512), 0, stream, q, ld_q, n_q, kp, vtp, cap,
-                       n_keys, c, out, ld_out, n_qtiles, total, per_xcd, amax_slots, qn);
+    hipLaunchKernelGGL((lvx_attention_kernel<D, TP, PRE, QN, KS, SPLIT>), dim3(per_xcd * 8), dim3(512), 0, stream, q, ld_q, n_q, kp, vtp, cap,
+                       n_keys, c, out, ld_out, n_qtiles, total, per_xcd, amax_slots, qn, pt);
     LVX_CHECK_HIP(hipGetLastError());
+    if (SPLIT) {
+        hipLaunchKernelGGL(lvx_attention_combine_kernel, dim3((unsigned)(((size_t)n_q * H * D / 8 + 255) / 256)), dim3(256), 0, stream, pt, n_q, D, out, ld_out,
+                           amax_slots);
+        LVX_CHECK_HIP(hipGetLastError());
+    }
     return LVX_OK;
 }
 
@@ -512,7 +612,7 @@ lvx_status_t launch(const bf16_t *q, int64_t ld_q, int n_q, int H, const bf16_t 
 
 lvx_status_t lvx_launch_attention(const bf16_t *q, int64_t ld_q, int n_q, int H, int D, const bf16_t *k_packed,
                                   const bf16_t *vt_packed, int cap, int n_keys, float scale, bf16_t *out, int64_t ld_out,
-                                  hipStream_t stream, uint32_t *amax_slots, bool q_prescaled, const lvx_attn_qnorm_t *qnorm) {
+                                  hipStream_t stream, uint32_t *amax_slots, bool q_prescaled, const lvx_attn_qnorm_t *qnorm, void *scratch) {
     LVX_REQUIRE(n_q > 0 && n_keys > 0 && n_keys <= cap && cap % KT == 0, LVX_ERR_SHAPE, "attention: n_q %d, n_keys %d, cap %d", n_q,
                 n_keys, cap);
     LVX_REQUIRE(scale > 0.f, LVX_ERR_INVALID_ARG, "attention: scale must be positive");
@@ -526,6 +626,18 @@ lvx_status_t lvx_launch_attention(const bf16_t *q, int64_t ld_q, int n_q, int H,
                     LVX_ERR_INVALID_ARG,
                     "attention: query norm needs head_dim 128, partial sums and a gain");
         return two ? LVX_ATTN_LAUNCH(128, 1, true, true, 2) : LVX_ATTN_LAUNCH(128, 1, true, true, 1);
+    }
+    if (q_prescaled && scratch != nullptr) {
+        const lvx_attn_split_t sp = lvx_attention_parts(n_q, H, n_keys, D);
+        if (sp.parts > 1) {
+            lvx_attn_parts_t pt = {(float *)scratch, nullptr, sp.parts, H};
+            pt.stat = (float2 *)(pt.o + (size_t)sp.parts * n_q * H * D);
+#define LVX_ATTN_LAUNCH_PARTS(D_, TP_, KS_) \
+    launch<D_, TP_, true, false, KS_, true>(q, ld_q, n_q, H, k_packed, vt_packed, cap, n_keys, scale, out, ld_out, stream, amax_slots, nullptr, &pt)
+            if (D == 64) return sp.halves ? LVX_ATTN_LAUNCH_PARTS(64, 1, 2) : LVX_ATTN_LAUNCH_PARTS(64, 1, 1);
+            return sp.halves ? LVX_ATTN_LAUNCH_PARTS(128, 1, 2) : LVX_ATTN_LAUNCH_PARTS(128, 2, 1);
+#undef LVX_ATTN_LAUNCH_PARTS
+        }
     }
     if (q_prescaled) {  // q already carries scale * log2(e): see PRE in the kernel
         if (D == 64) return two ? LVX_ATTN_LAUNCH(64, 1, true, false, 2) : LVX_ATTN_LAUNCH(64, 1, true, false, 1);

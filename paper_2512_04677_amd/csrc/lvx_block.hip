@@ -48,9 +48,10 @@ typedef lvx_prof_scope_t prof_scope_t;
 constexpr int CTX_GROUP = LVX_GEMM_MAX_SEGS / 2;
 
 struct ws_layout_t {
-    size_t u, big, qk32, q_sumsq, ctx_k32, ctx_kv, pack_k, pack_v, h, q8, q8_ctx, q8_misc, total;  // byte offsets
+    size_t u, big, qk32, q_sumsq, ctx_k32, ctx_kv, pack_k, pack_v, h, attn, q8, q8_ctx, q8_misc, total;  // byte offsets
     int64_t ld_q8, ld_q8c;                            // row strides (bytes) of the FP8 activation buffers
     int cap_ctx, ctx_group;
+    size_t attn_bytes;
     int64_t ld_u, ld_qkv, ld_cq, ld_ffn, ld_ckv;      // padded row strides (elements) of the bf16 workspace matrices
     int64_t ld_qk32;                                  // row stride (fp32 elements) of the un-rounded q | k columns
 };
@@ -102,6 +103,9 @@ ws_layout_t ws_layout(const lvx_stage_t *s, int n_tokens, int n_ctx) {
     w.pack_k = off;  off += round256((size_t)w.ctx_group * w.cap_ctx * d * 2);
     w.pack_v = off;  off += round256((size_t)w.ctx_group * w.cap_ctx * d * 2);
     w.h = off;       off += round256((size_t)n_tokens * d * 4);  // fp32 residual stream
+    w.attn = off;    // outputs of the self-attention's ranges of keys before they are added up
+    w.attn_bytes = lvx_attention_scratch_bytes(n_tokens, s->rope.n_heads, s->rope.head_dim);
+    off += round256(w.attn_bytes);
     w.q8 = w.q8_ctx = w.q8_misc = off;
     const size_t wide_in = d > (size_t)s->d_ffn ? d : (size_t)s->d_ffn;
     w.ld_q8 = (int64_t)wide_in + 128;
@@ -268,7 +272,7 @@ lvx_status_t run_block(const lvx_stage_t *s, int layer, lvx_kvcache *c, float *x
             prof_scope_t ps(LVX_PROF_ATTN_SELF, st);
             // the queries were written pre-scaled by the RoPE kernel above
             LVX_TRY(lvx_launch_attention(big, ldq, n, H, D, lvx_cache_k(c, layer), lvx_cache_vt(c, layer), c->cap_keys, c->state[layer].key_count,
-                                         scale, u, ldu, st, amax_out(), true));
+                                         scale, u, ldu, st, amax_out(), true, nullptr, L.attn_bytes > 0 ? ws + L.attn : nullptr));
         }
     } else {
         // the sink's un-rotated keys go into the cache's fp32 source storage: un-rounded from the projection in a bf16 stage,

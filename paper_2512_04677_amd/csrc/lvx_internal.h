@@ -97,10 +97,18 @@ struct lvx_attn_qnorm_t {
     int32_t n_parts, ld, d_model;
     float eps;
 };
+// Outputs of the ranges of keys that the workgroups of a split attention leave: o [n][n_q][H * D], un-normalised, with the reference and the sum
+// of each query and head, stat [n][n_q][H].
+struct lvx_attn_parts_t {
+    float *o;
+    float2 *stat;
+    int32_t n, H;
+};
+// scratch: NULL, or lvx_attention_scratch_bytes(n_q, H, D) for pre-scaled queries whose keys may be split over workgroups (16-byte aligned).
 lvx_status_t lvx_launch_attention(const bf16_t *q, int64_t ld_q, int n_q, int H, int D, const bf16_t *k_packed,
                                   const bf16_t *vt_packed, int cap, int n_keys, float scale, bf16_t *out, int64_t ld_out,
                                   hipStream_t stream, uint32_t *amax_slots = nullptr, bool q_prescaled = false,
-                                  const lvx_attn_qnorm_t *qnorm = nullptr);
+                                  const lvx_attn_qnorm_t *qnorm = nullptr, void *scratch = nullptr);
 // out = bf16((x ? x : 0) + dt * h) with h in fp32: the Euler step of the stage (x given) or the narrowing of a block's
 // fp32 residual stream (x NULL, dt 1).
 lvx_status_t lvx_launch_euler(const bf16_t *x, const float *h, float dt, bf16_t *out, size_t n_elems, hipStream_t stream);

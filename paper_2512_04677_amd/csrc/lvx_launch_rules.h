@@ -1,6 +1,7 @@
 // Which kernel a call takes: the tile of a matrix product, of a convolution step, the workgroup form of the attention.  Rules on sizes
 // only, in plain host C++ with no GPU types, so that they can be evaluated for any size without a GPU.
 #pragma once
+#include <stddef.h>
 #include <stdint.h>
 
 typedef uint16_t bf16_t;  // raw bf16 bits in memory
@@ -309,4 +310,40 @@ static inline bool lvx_attention_splits_keys(int n_q, int H, int n_keys, int hea
         return head_dim == 64 ? (double)all : 0.5 * (whole + all);
     };
     return (few_tiles ? 0.74 : 0.65) * rounds(128) < rounds(256);
+}
+
+// Into how many ranges of keys the self-attention of a block is split over workgroups (1: none), and whether a workgroup then takes 128 queries
+// with its range split once more over its halves (`halves`) instead of 256.  Few heads and queries leave compute units idle that the
+// ranges fill, but each range writes its outputs in fp32 and a second kernel reads them: about 7 us more, and the ranges' bytes at 4.1 TB/s
+// both ways.  Microseconds per tile of 64 keys: 256 queries 1.30 to 1.50 the more units work (head_dim 64: 1.08), 128 queries 0.88 (0.63).
+// Measured, alone -> split: 12 heads x 1170 queries x 6240 keys 89 -> 59 (2 ranges, 128 queries), 8 x 1800 x 4200 59 -> 45, 16 x 1200 x 5400 78 -> 64
+// (3 ranges, 256 queries), 20 x 1886 x 8487 175 -> 163, 4 x 390 x 1300 26 -> 21, head_dim 64, 8 x 900 x 4800 52 -> 28; no gain: 4 x 105 x
+// 560 16 -> 17, 30 x 1800 x 6000 144 -> 168.  More than four ranges were never best.  More than 256 workgroups of 256 queries stay as they are: there
+// the ranges' bytes weigh more than a partial round.
+#define LVX_ATTN_MAX_PARTS 4
+struct lvx_attn_split_t {
+    int parts;
+    bool halves;
+};
+static inline int lvx_attention_most_parts(int n_q, int H) { return (long)((n_q + 255) / 256) * H <= LVX_NUM_CU ? LVX_ATTN_MAX_PARTS : 1; }
+static inline lvx_attn_split_t lvx_attention_parts(int n_q, int H, int n_keys, int head_dim) {
+    const int most = lvx_attention_most_parts(n_q, H), tiles = (n_keys + LVX_KEY_TILE - 1) / LVX_KEY_TILE;
+    auto time = [&](int parts, bool halves) {
+        const long wgs = (long)(halves ? (n_q + 127) / 128 : (n_q + 255) / 256) * H * parts, busy = wgs < LVX_NUM_CU ? wgs : LVX_NUM_CU;
+        const double tile = halves ? (head_dim == 64 ? 0.63 : 0.88) : (head_dim == 64 ? 1.08 : 1.30 + 0.2 * busy / LVX_NUM_CU);
+        const double ranges = parts > 1 ? 7.0 + parts * 8.0 * n_q * H * head_dim / 4.1e6 : 0.0;
+        return (double)lvx_rounds(wgs) * ((tiles + parts - 1) / parts) * tile + 5.0 + ranges;
+    };
+    const double alone = time(1, lvx_attention_splits_keys(n_q, H, n_keys, head_dim));
+    lvx_attn_split_t best = {1, false};
+    double best_us = 0.94 * alone;
+    for (int parts = 2; parts <= most && parts <= tiles; ++parts)
+        for (int halves = 0; halves < 2; ++halves)
+            if (time(parts, halves != 0) < best_us) best_us = time(parts, halves != 0), best = {parts, halves != 0};
+    return best;
+}
+// Bytes of the ranges' outputs, references and sums.
+static inline size_t lvx_attention_scratch_bytes(int n_q, int H, int head_dim) {
+    const size_t most = (size_t)lvx_attention_most_parts(n_q, H);
+    return most <= 1 ? 0 : most * n_q * H * ((size_t)head_dim * 4 + 8);
 }

@@ -1,0 +1,58 @@
+"""The rule that splits a block's keys over workgroups (csrc/lvx_launch_rules.h), evaluated on the CPU."""
+import ctypes as C
+import random
+import shutil
+import subprocess
+
+import pytest
+
+import test_gpu_attention_parts as parts_tests
+from test_launch_rules import CSRC
+
+SOURCE = r"""
+#include "lvx_launch_rules.h"
+extern "C" int parts(int n_q, int H, int n_keys, int D) { const lvx_attn_split_t s = lvx_attention_parts(n_q, H, n_keys, D); return 2 * s.parts + s.halves; }
+extern "C" double scratch(int n_q, int H, int D) { return (double)lvx_attention_scratch_bytes(n_q, H, D); }
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("g++ not found")
+    d = tmp_path_factory.mktemp("parts_rules")
+    (d / "rules.cpp").write_text(SOURCE)
+    r = subprocess.run([cxx, "-O1", "-Wall", "-Werror", "-std=c++17", "-shared", "-fPIC", "-I" + CSRC, str(d / "rules.cpp"), "-o", str(d / "librules.so")],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    lib = C.CDLL(str(d / "librules.so"))
+    lib.scratch.restype = C.c_double
+    return lib
+
+
+def split(rules, n_q, H, n_keys, D):
+    r = rules.parts(n_q, H, n_keys, D)
+    return r // 2, bool(r % 2)
+
+
+def test_gpu_shapes_take_the_ranges_they_name(rules):
+    for (D, H, fh, fw, frames, window), form in parts_tests.SHAPES:
+        n = fh * fw * frames
+        assert split(rules, n, H, fh * fw + (window + 1) * n, D) == form, (D, H, n)
+
+
+def test_measured_choices(rules):
+    for c, form in {(1170, 12, 6240, 128): (2, True), (1200, 16, 5400, 128): (3, False), (390, 4, 1300, 128): (4, True), (900, 8, 4800, 64): (4, True)}.items():
+        assert split(rules, *c) == form, c
+    for c in [(105, 4, 560, 128), (48, 2, 168, 64), (1800, 30, 6000, 128), (4680, 40, 24960, 128), (1000, 40, 4000, 128)]:
+        assert split(rules, *c)[0] == 1, c
+
+
+def test_no_range_is_empty_and_the_scratch_holds_all(rules):
+    rng = random.Random(8)
+    for _ in range(20000):
+        n_q, H, n_keys, D = int(8000 ** rng.random()) + 1, rng.randint(1, 48), int(60000 ** rng.random()) + 1, rng.choice([64, 128])
+        parts, _ = split(rules, n_q, H, n_keys, D)
+        assert 1 <= parts <= -(-n_keys // 64)
+        assert parts == 1 or rules.scratch(n_q, H, D) >= parts * n_q * H * (4 * D + 8)
