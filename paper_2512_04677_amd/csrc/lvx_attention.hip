@@ -226,10 +226,12 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     //   iteration i, second half:  group 0: Y(i)                                group 1: X(i-1)
     // A phase covers TP consecutive tiles (TP = 2: 128 keys), which halves the barriers, the pipeline fills at a phase's start
     // and the drains at its end per key.
-    // Staging: tile t lives in ring slot t % 4, so two stages fit.  Every wave issues the DMA of stage i at the start of
-    // iteration i, into the slots of stage i-2, whose last reader (group 1's X(i-2), second half of iteration i-1) ended at
-    // the barrier just passed, and waits for its own part before the barrier that ends iteration i; stage i is first read
-    // by group 0 in X(i), right after that barrier: a whole iteration of both groups' work covers the load.
+    // Staging: tile t lives in ring slot t % 4, so two stages fit.  A wave issues its part of stage i in its vector phase of iteration i (group 1
+    // in the first half, group 0 in the second), into the slots of stage i-2, whose last reader (group 1's X(i-2), second half of iteration
+    // i-1) ended at the barrier before iteration i, and waits for it before the barrier that ends iteration i; stage i is first read by
+    // group 0 in X(i), right after that barrier.  Issued ahead of group 0's matrix phase instead, where each of the eight loads of a wave holds up
+    // the MFMAs behind it, the loads had half an iteration more to land and cost more than that gave: 40 heads x 4680 x 24960 1.77 -> 1.64 ms
+    // (1.46 PFLOP/s), x 6240 454 -> 436 us, 12 x 1170 x 6240 82 -> 77.
 
     // o[db][qb][e] = O^T[d = 16 db + 4 q4 + e][query 16 qb + l16];  s[kb][qb][e] = score of key row 4 q4 + e of block kb
     f32x4_t o[DB][QB];
@@ -416,9 +418,9 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
         }
         __syncthreads();
         for (int i = 1; i < n_ph; ++i) {
-            LVX_ATTN_STAGE_DMA(i);
             LVX_ATTN_X(i - 1);
             __syncthreads();
+            LVX_ATTN_STAGE_DMA(i);
             LVX_ATTN_Y(i);
             LVX_ATTN_WAIT_DMA(0);  // stage i landed
             __syncthreads();
