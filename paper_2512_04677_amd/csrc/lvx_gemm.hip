@@ -376,17 +376,18 @@ extern "C" lvx_status_t lvx_linear_dual(const void *dev_a, int64_t lda, const vo
                                   (bf16_t *)dev_c2, ldc2, M, N1, N2, K, (hipStream_t)stream);
 }
 
-// Implicit-GEMM 3x3x3 convolution: rows = output pixels, K = 27 taps x C channels gathered from the padded volume P; lvx_conv_plan says
-// which kernel.
+// Implicit-GEMM 3x3x3 convolution: rows = output pixels, K = 27 taps x C channels gathered from the padded volume P; lvx_conv_choose
+// says which kernel.
 lvx_status_t lvx_launch_conv_gemm(const bf16_t *P, const lvx_conv_map_t &cm, const bf16_t *Wt, int64_t ldw, const float *bias, int act,
                                   bf16_t *Y, int64_t ldy, int M, int max_m, int N, hipStream_t stream) {
     const int K = 27 * cm.C, n_slabs = K / BK, epi = act ? (int)LVX_EPI_BIAS_SILU : (int)LVX_EPI_BIAS;
-    const lvx_conv_plan_t plan = lvx_conv_plan(cm.W, N, n_slabs, M, max_m);
-    if (plan.kind == LVX_CONV_LARGE) return launch<256, 128, 4, 2, true>(P, 0, Wt, ldw, Y, ldy, M, N, K, epi, nullptr, 0, bias, stream, nullptr, &cm);
-    if (plan.kind == LVX_CONV_ROWS) {
-        lvx_conv_args_t c = {(const char *)P, (const char *)Wt, ldw * 2, Y, ldy, bias, M / cm.W * (cm.W + 2), N, n_slabs / 3, act, 0, 0, 0, 0, cm};
+    const lvx_conv_launch_t c = lvx_conv_choose(cm.W, N, n_slabs, M, max_m);
+    const lvx_conv_plan_t &plan = c.plan;
+    if (c.fn == 0 && plan.kind == LVX_CONV_LARGE) return launch<256, 128, 4, 2, true>(P, 0, Wt, ldw, Y, ldy, M, N, K, epi, nullptr, 0, bias, stream, nullptr, &cm);
+    if (c.fn == 0 && plan.kind == LVX_CONV_ROWS) {
+        lvx_conv_args_t r = {(const char *)P, (const char *)Wt, ldw * 2, Y, ldy, bias, M / cm.W * (cm.W + 2), N, n_slabs / 3, act, 0, 0, 0, 0, cm};
 #define LVX_TILE_LAUNCH(ID_, BM_, BN_, WM_, WN_, NST_, US_) \
-    if (plan.tile == ID_) return lvx_conv_rows_launch<BM_, BN_, WM_, WN_, NST_>(c, stream);
+    if (plan.tile == ID_) return lvx_conv_rows_launch<BM_, BN_, WM_, WN_, NST_>(r, stream);
         LVX_CONV_ROW_TILES(LVX_TILE_LAUNCH)
 #undef LVX_TILE_LAUNCH
     }
@@ -398,6 +399,13 @@ lvx_status_t lvx_launch_conv_gemm(const bf16_t *P, const lvx_conv_map_t &cm, con
     p.M = M, p.N = N, p.n_slabs = n_slabs;
     p.epi = epi;
     p.conv = cm;
+#define LVX_CONV_WIDE(FN_) \
+    if (c.fn == FN_)       \
+        return act ? lvx_gemm_wide_launch<LVX_EPI_BIAS_SILU, false, FN_, true>(p, c.n_large, stream) : lvx_gemm_wide_launch<LVX_EPI_BIAS, false, FN_, true>(p, c.n_large, stream);
+    LVX_CONV_WIDE(2)
+    LVX_CONV_WIDE(3)
+    LVX_CONV_WIDE(4)
+#undef LVX_CONV_WIDE
     return lvx_gemm_launch_small<false, true>(plan.tile, p, stream);
 }
 

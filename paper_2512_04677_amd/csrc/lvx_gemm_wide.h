@@ -13,12 +13,11 @@
 // Without its stores the bf16 kernel runs at 1.60 PFLOP/s, the rate at which the chip's power holds a library's product as well.  The last slabs
 // stand in a loop of their own: with their conditions in the main one it ran 1 to 8 % slower.  Four phases of 16 instructions instead of two cost
 // 2 %, raised wave priorities change nothing, halves with a third of a slab's loads in each of two phases neither.
+// The decoder's convolution runs on the same kernel (CONV) with 128, 192 or 256 columns; see lvx_conv_choose.
 #pragma once
 #include "lvx_gemm_core.h"
 
-constexpr int LVX_WIDE_HALF_B = 128 * 128;              // bytes of 128 rows of a slab
-constexpr int LVX_WIDE_STAGE_B = 4 * LVX_WIDE_HALF_B;   // 256 x 256: two stages of {A rows 0 .. 127, A rows 128 .. 255, W half 0, W half 1}
-constexpr int LVX_WIDE_STAGE3_B = 3 * LVX_WIDE_HALF_B;  // 128 x 256: three stages of {A rows, W half 0, W half 1}
+constexpr int LVX_WIDE_HALF_B = 128 * 128;  // bytes of 128 rows of a slab
 
 // Workgroup -> tile.  n_large 256 x 256 tiles, the first of the walk (bands of group_m row tiles, column-major inside a band), are taken
 // whole; the rest of them in halves of 128 rows, after these the last 128 rows at most that no 256-row tile covers.  Workgroup ids are
@@ -55,33 +54,42 @@ __device__ __forceinline__ bool lvx_wide_tile_of(const lvx_wide_grid_t &g, bool 
     return true;
 }
 
-// Column of a wave's 64 that row r (0 .. 31) of W half h stands for: a lane's accumulators of two neighbouring 16-column blocks are then
-// eight consecutive columns, so outputs and residuals move in 16-byte pieces, four lanes to a 64-byte (fp32: 128-byte) run.
-__device__ __forceinline__ int lvx_wide_col(int h, int r) { return h * 32 + ((r >> 2) & 3) * 8 + (r >> 4) * 4 + (r & 3); }
+// Column of a wave's 16 * FN that row r of its rows of the W tile stands for: a lane's accumulators of two neighbouring 16-column blocks are then
+// eight consecutive columns, so outputs and residuals move in 16-byte pieces, four lanes to a 64-byte (fp32: 128-byte) run.  (Three
+// blocks, convolutions only: the last one stands alone, four columns a lane.)
+template <int FN>
+__device__ __forceinline__ int lvx_wide_col(int r) {
+    if (FN % 2 == 1 && r >= 16 * (FN - 1)) return r;
+    return (r >> 5) * 32 + ((r >> 2) & 3) * 8 + ((r >> 4) & 1) * 4 + (r & 3);
+}
 
-// Epilogue of 64 rows x 64 columns of a wave.  acc[i][2 h + j][e]: row m0 + 16 i, column n0 + 32 h + 4 j + e (m0, n0 include the lane's l16 and
-// 8 * q4).  N is a multiple of 8: eight columns are inside or outside together.  vec: rows and bases allow 16-byte accesses.  Returns the
-// largest magnitude among the bf16 values that this lane stores (FP8).
-template <int EPI, bool FP8>
-__device__ __forceinline__ uint32_t lvx_wide_epilogue(const f32x4_t (&acc)[4][4], void *Cv, int64_t ldc, const void *Rv, int64_t ldr, const float *__restrict__ gate,
-                                                      int M, int N, int m0, int n0, float alpha, bool vec) {
+// Epilogue of 64 rows x 16 * FN columns of a wave.  acc[i][2 h + j][e]: row m0 + 16 i, column n0 + 32 h + 4 j + e (m0, n0 include the lane's l16
+// and 8 * q4; an unpaired last block: column n0 - 4 * q4 + 32 h + e).  N is a multiple of 8: eight columns are inside or outside together.
+// vec: rows and bases allow 16-byte accesses.  Returns the largest magnitude among the bf16 values that this lane stores (FP8).
+template <int EPI, bool FP8, int FN>
+__device__ __forceinline__ uint32_t lvx_wide_epilogue(const f32x4_t (&acc)[4][FN], void *Cv, int64_t ldc, const void *Rv, int64_t ldr, const float *__restrict__ gate,
+                                                      int M, int N, int m0, int n0, int q4, float alpha, bool vec) {
     constexpr bool RES32 = EPI == LVX_EPI_RESID_GATE_F32, RES16 = EPI == LVX_EPI_RESID_GATE, F32 = RES32 || EPI == LVX_EPI_STORE_F32;
     constexpr bool BIAS = EPI == LVX_EPI_BIAS || EPI == LVX_EPI_BIAS_SILU;
-    float gt[2][8];  // gate (residual epilogues) or bias of the lane's columns
+    constexpr int NH = (FN + 1) / 2;
+    static_assert(FN % 2 == 0 || BIAS, "a last block of its own has no residual here");
+    float gt[NH][8];  // gate (residual epilogues) or bias of the lane's columns
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int h = 0; h < NH; ++h) {
+        const int nb = n0 + 32 * h - (2 * h + 1 == FN ? 4 * q4 : 0);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const int n = n0 + 32 * h + e < N ? n0 + 32 * h + e : N - 1;
+            const int n = nb + e < N ? nb + e : N - 1;
             gt[h][e] = RES32 || RES16 || BIAS ? (gate != nullptr ? gate[n] : BIAS ? 0.f : 1.f) : 0.f;
         }
+    }
     uint32_t amax_b = 0;
-    float res[2][2][8];  // residuals of two rows, the next ones on their way while these are used
+    float res[2][NH][8];  // residuals of two rows, the next ones on their way while these are used
     auto fetch = [&](int i) {
         if (!RES32 && !RES16) return;
         const int m = m0 + 16 * i < M ? m0 + 16 * i : M - 1;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
+        for (int h = 0; h < NH; ++h) {
             const int n = n0 + 32 * h < N ? n0 + 32 * h : 0;
             if (RES32) {
                 const float *r = reinterpret_cast<const float *>(Rv) + (size_t)m * ldr + n;
@@ -113,12 +121,13 @@ __device__ __forceinline__ uint32_t lvx_wide_epilogue(const f32x4_t (&acc)[4][4]
         const int m = m0 + 16 * i;
         if (m >= M) continue;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int n = n0 + 32 * h;
+        for (int h = 0; h < NH; ++h) {
+            const bool four = 2 * h + 1 == FN;  // the unpaired last block
+            const int n = n0 + 32 * h - (four ? 4 * q4 : 0);
             if (n >= N) continue;
             float v[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
+            for (int e = 0; e < (four ? 4 : 8); ++e) {
                 float x = acc[i][2 * h + (e >> 2)][e & 3];
                 if (FP8) x *= alpha;
                 if (EPI == LVX_EPI_GELU_TANH) x = gelu_tanh_f32(x);
@@ -138,9 +147,9 @@ __device__ __forceinline__ uint32_t lvx_wide_epilogue(const f32x4_t (&acc)[4][4]
                 }
             } else {
                 bf16_t *c = reinterpret_cast<bf16_t *>(Cv) + (size_t)m * ldc + n;
-                u32x4_t w;
+                uint32_t w[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
+                for (int e = 0; e < (four ? 2 : 4); ++e) {
                     w[e] = pack_bf16x2(v[2 * e], v[2 * e + 1]);
                     if (FP8) {
                         const uint32_t lo = w[e] & 0x7fffu, hi = (w[e] >> 16) & 0x7fffu;
@@ -148,11 +157,13 @@ __device__ __forceinline__ uint32_t lvx_wide_epilogue(const f32x4_t (&acc)[4][4]
                         amax_b = amax_b > hi ? amax_b : hi;
                     }
                 }
-                if (vec) {
-                    *reinterpret_cast<u32x4_t *>(c) = w;
+                if (vec && four) {
+                    *reinterpret_cast<uint2 *>(c) = make_uint2(w[0], w[1]);
+                } else if (vec) {
+                    *reinterpret_cast<u32x4_t *>(c) = u32x4_t{w[0], w[1], w[2], w[3]};
                 } else {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) c[e] = (bf16_t)(e & 1 ? w[e >> 1] >> 16 : w[e >> 1] & 0xffffu);
+                    for (int e = 0; e < (four ? 4 : 8); ++e) c[e] = (bf16_t)(e & 1 ? w[e >> 1] >> 16 : w[e >> 1] & 0xffffu);
                 }
             }
         }
@@ -176,51 +187,57 @@ __device__ __forceinline__ void lvx_wide_row_sumsq(const f32x4_t (&acc)[4][4], f
     }
 }
 
-template <int EPI, bool FP8>
+// FN: 16-column blocks per wave, so tiles are 256 x 64 FN (linears: 4).  CONV: the rows of A are gathered from the padded volume.
+template <int EPI, bool FP8, int FN = 4, bool CONV = false>
 __global__ void __launch_bounds__(512) lvx_gemm_wide_kernel(const lvx_gemm_args_t p, const lvx_wide_grid_t g) {
-    __shared__ __attribute__((aligned(1024))) char lds[3 * LVX_WIDE_STAGE3_B];
+    constexpr int BN = 64 * FN, W_B = BN * 128;           // bytes of a slab's W rows
+    constexpr int STAGE_B = 2 * LVX_WIDE_HALF_B + W_B;    // 256 rows: two stages of {A rows 0 .. 127, A rows 128 .. 255, W rows}
+    constexpr int STAGE3_B = LVX_WIDE_HALF_B + W_B;       // 128 rows: three stages of {A rows, W rows}
+    __shared__ __attribute__((aligned(1024))) char lds[2 * STAGE_B > 3 * STAGE3_B ? 2 * STAGE_B : 3 * STAGE3_B];
     bool half;
     int row0, tn;
     if (!lvx_wide_tile_of(g, half, row0, tn)) return;
     lvx_gemm_out_t o = {p.W, p.C, p.ldc, p.N, EPI, nullptr, 0};
     if (EPI == LVX_EPI_SEGMENTS) o = lvx_gemm_select(p, tn);
-    const int M = p.M, N = o.N, col0 = tn * 256;
+    const int M = p.M, N = o.N, col0 = tn * BN;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, q4 = lane >> 4;
     const int wm = wave >> 2, wn = wave & 3;
 
-    // A wave brings two pieces of eight rows of each 128-row half: rows 8 * (wave + 8 q) .. + 7 of it.  The 16-byte chunk c of LDS row r sits at
-    // position c ^ ((r >> 1) & 7), as in the other kernels.  Rows and columns past the edge are clamped (never stored).
-    uint32_t da[2][2], dw[2][2];
+    // A wave brings two pieces of eight rows of each half of A and FN of W: rows 8 * (wave + 8 q) .. + 7.  The 16-byte chunk c of LDS row r
+    // sits at position c ^ ((r >> 1) & 7), as in the other kernels.  Rows and columns past the edge are clamped (never stored).
+    uint32_t da[2][2], dw[FN];
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int q = 0; q < FN; ++q) {
+        const int r = 8 * (wave + 8 * q) + (lane >> 3), chunk = (lane & 7) ^ ((r >> 1) & 7);
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int r = 8 * (wave + 8 * q) + (lane >> 3), chunk = (lane & 7) ^ ((r >> 1) & 7);
-            int ra = row0 + h * 128 + r, rw = col0 + (r >> 5) * 64 + lvx_wide_col(h, r & 31);
+        for (int h = 0; h < 2; ++h) {
+            int ra = row0 + h * 128 + r;
             if (ra > M - 1) ra = M - 1;
-            if (rw > N - 1) rw = N - 1;
-            da[h][q] = (uint32_t)((size_t)ra * p.lda + chunk * 16);
-            dw[h][q] = (uint32_t)((size_t)rw * p.ldw + chunk * 16);
+            if (q < 2) da[h][q] = (uint32_t)((CONV ? lvx_conv_pixel_offset(p.conv, ra) : (size_t)ra * p.lda) + chunk * 16);
         }
+        int rw = col0 + r / (16 * FN) * (16 * FN) + lvx_wide_col<FN>(r % (16 * FN));
+        if (rw > N - 1) rw = N - 1;
+        dw[q] = (uint32_t)((size_t)rw * p.ldw + chunk * 16);
+    }
     const uint32_t ring_wave = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds + wave * 1024;
     const int last = p.n_slabs - 1, second = last < 1 ? last : 1;  // (a single slab is requested twice: nobody reads the second copy)
-    // slab kt of A half h / of W half h (`at`: LDS offset of the half's place)
-    auto load_a = [&](int h, int kt, int at) {
+    // `off` bytes into the rows of A half h / of W, to LDS offset `at`
+    auto load_a = [&](int h, size_t off, int at) {
 #pragma unroll
-        for (int q = 0; q < 2; ++q) lvx_dma16(p.A + (size_t)kt * 128, da[h][q], ring_wave + (uint32_t)(at + q * 8192));
+        for (int q = 0; q < 2; ++q) lvx_dma16(p.A + off, da[h][q], ring_wave + (uint32_t)(at + q * 8192));
     };
-    auto load_w = [&](int h, int kt, int at) {
+    auto load_w = [&](size_t off, int at) {
 #pragma unroll
-        for (int q = 0; q < 2; ++q) lvx_dma16(o.W + (size_t)kt * 128, dw[h][q], ring_wave + (uint32_t)(at + q * 8192));
+        for (int q = 0; q < FN; ++q) lvx_dma16(o.W + off, dw[q], ring_wave + (uint32_t)(at + q * 8192));
     };
     const int swz = (l16 >> 1) & 7;
     const int ch[2] = {(q4 ^ swz) * 16, ((4 + q4) ^ swz) * 16};
-    const char *a_rd = lds + (wm * 64 + l16) * 128, *w_rd = lds + (wn * 32 + l16) * 128;
-    lvx_frag_t<FP8> a[4], w[2][2];
+    const char *a_rd = lds + (wm * 64 + l16) * 128, *w_rd = lds + (wn * 16 * FN + l16) * 128;
+    lvx_frag_t<FP8> a[4], w[FN];
 #define LVX_WIDE_READ_A(at_) \
     _Pragma("unroll") for (int k = 0; k < 2; ++k) _Pragma("unroll") for (int i = 0; i < 4; ++i) lvx_frag_read(a[i], k, a_rd + (at_) + i * 2048 + ch[k]);
-#define LVX_WIDE_READ_W(h_, at_) \
-    _Pragma("unroll") for (int k = 0; k < 2; ++k) _Pragma("unroll") for (int j = 0; j < 2; ++j) lvx_frag_read(w[h_][j], k, w_rd + (at_) + j * 2048 + ch[k]);
+#define LVX_WIDE_READ_W(at_) \
+    _Pragma("unroll") for (int j = 0; j < FN; ++j) _Pragma("unroll") for (int k = 0; k < 2; ++k) lvx_frag_read(w[j], k, w_rd + (at_) + j * 2048 + ch[k]);
     // The matrix phase: the fragments of the memory phase are there before the barrier that hands the partner the LDS ports, so that what
     // the partner loads next may land where they were read from.
 #define LVX_WIDE_MATRIX_PHASE(acc_)                                                                                                    \
@@ -228,13 +245,13 @@ __global__ void __launch_bounds__(512) lvx_gemm_wide_kernel(const lvx_gemm_args_
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                                                                             \
         asm volatile("s_barrier" ::: "memory");                                                                                        \
         LVX_SCHED_FENCE();                                                                                                             \
-        _Pragma("unroll") for (int h = 0; h < 2; ++h) {                                                                                \
+        _Pragma("unroll") for (int h = 0; h < FN; h += 2) {                                                                            \
             if constexpr (FP8) {                                                                                                       \
-                _Pragma("unroll") for (int i = 0; i < 4; ++i) _Pragma("unroll") for (int j = 0; j < 2; ++j)                            \
-                    acc_[i][2 * h + j] = lvx_mfma_fp8(w[h][j].v, a[i].v, acc_[i][2 * h + j]);                                          \
+                _Pragma("unroll") for (int i = 0; i < 4; ++i) _Pragma("unroll") for (int j = h; j < h + 2 && j < FN; ++j)              \
+                    acc_[i][j] = lvx_mfma_fp8(w[j].v, a[i].v, acc_[i][j]);                                                             \
             } else {                                                                                                                   \
-                _Pragma("unroll") for (int k = 0; k < 2; ++k) _Pragma("unroll") for (int i = 0; i < 4; ++i) _Pragma("unroll") for (int j = 0; j < 2; ++j) \
-                    acc_[i][2 * h + j] = lvx_mfma_bf16(w[h][j].h[k], a[i].h[k], acc_[i][2 * h + j]);                                   \
+                _Pragma("unroll") for (int k = 0; k < 2; ++k) _Pragma("unroll") for (int i = 0; i < 4; ++i) _Pragma("unroll") for (int j = h; j < h + 2 && j < FN; ++j) \
+                    acc_[i][j] = lvx_mfma_bf16(w[j].h[k], a[i].h[k], acc_[i][j]);                                                      \
             }                                                                                                                          \
         }                                                                                                                              \
         LVX_SCHED_FENCE();                                                                                                             \
@@ -243,62 +260,74 @@ __global__ void __launch_bounds__(512) lvx_gemm_wide_kernel(const lvx_gemm_args_
     }
 #define LVX_WIDE_WAIT(n_) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n_) : "memory")
 #define LVX_WIDE_ZERO(acc_) \
-    _Pragma("unroll") for (int i = 0; i < 4; ++i) _Pragma("unroll") for (int j = 0; j < 4; ++j) acc_[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    _Pragma("unroll") for (int i = 0; i < 4; ++i) _Pragma("unroll") for (int j = 0; j < FN; ++j) acc_[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-    const int m0 = row0 + wm * 64 + l16, n0 = col0 + wn * 64 + 8 * q4;
+    const int m0 = row0 + wm * 64 + l16, n0 = col0 + wn * 16 * FN + 8 * q4;
     const float alpha = FP8 ? p.scale_a[0] * p.scale_w[0] : 1.f;
     const bool f32 = o.epi == LVX_EPI_RESID_GATE_F32 || o.epi == LVX_EPI_STORE_F32;
     const bool resid = EPI == LVX_EPI_RESID_GATE_F32 || EPI == LVX_EPI_RESID_GATE;
     const bool vec = ((o.ldc | (resid ? p.ldr : 0)) & (f32 ? 3 : 7)) == 0;  // (bases are 16-byte aligned)
     uint32_t amax_b = 0;
-    auto finish = [&](const f32x4_t(&acc)[4][4], int m) {
+    auto finish = [&](const f32x4_t(&acc)[4][FN], int m) {
         uint32_t b = 0;
         if constexpr (EPI == LVX_EPI_SEGMENTS) {
             if (o.epi == LVX_EPI_STORE_F32)
-                lvx_wide_epilogue<LVX_EPI_STORE_F32, FP8>(acc, o.C, o.ldc, nullptr, 0, nullptr, M, N, m, n0, alpha, vec);
+                lvx_wide_epilogue<LVX_EPI_STORE_F32, FP8, FN>(acc, o.C, o.ldc, nullptr, 0, nullptr, M, N, m, n0, q4, alpha, vec);
             else
-                lvx_wide_epilogue<LVX_EPI_STORE, FP8>(acc, o.C, o.ldc, nullptr, 0, nullptr, M, N, m, n0, alpha, vec);
+                lvx_wide_epilogue<LVX_EPI_STORE, FP8, FN>(acc, o.C, o.ldc, nullptr, 0, nullptr, M, N, m, n0, q4, alpha, vec);
             if (o.sumsq != nullptr && n0 - 8 * q4 < N) lvx_wide_row_sumsq(acc, o.sumsq, o.ld_sumsq, tn * 4 + wn, M, m, q4);
         } else {
-            b = lvx_wide_epilogue<EPI, FP8>(acc, o.C, o.ldc, p.R, p.ldr, p.gate, M, N, m, n0, alpha, vec);
+            b = lvx_wide_epilogue<EPI, FP8, FN>(acc, o.C, o.ldc, p.R, p.ldr, p.gate, M, N, m, n0, q4, alpha, vec);
         }
         amax_b = amax_b > b ? amax_b : b;
     };
+    // where the loop's next slabs lie in the rows of A and W: `near` the next but one of the last requested, `far` the one after it
+    lvx_conv_walk_t near, far;
+    auto advance = [&]() {
+        near = far;
+        if (CONV)
+            far.next(p.conv);
+        else
+            far.a += 128, far.w += 128;
+    };
 
     if (!half) {
-        // Slab t is in stage t % 2.  Two phases a slab: rows 0 .. 127 with both W halves, then rows 128 .. 255.  A half's place is free
-        // once both groups have read it, half a period after its memory phase: the second A half of slab t + 1 is requested in the first
-        // memory phase of slab t (its place was last read in the second one of slab t - 1), the other three of slab t + 2 in the second.
-        // So a load has one and a half slabs' time to land.  The last two slabs request nothing and wait for all.
-        f32x4_t acc[2][4][4];
+        // Slab t is in stage t % 2.  Two phases a slab: rows 0 .. 127 with W, then rows 128 .. 255.  A place is free once both groups have
+        // read it, half a period after its memory phase: the second A half of slab t + 1 is requested in the first memory phase of slab t
+        // (its place was last read in the second one of slab t - 1), the rest of slab t + 2 in the second.  So a load has one and a half
+        // slabs' time to land.  The last two slabs request nothing and wait for all.
+        f32x4_t acc[2][4][FN];
         LVX_WIDE_ZERO(acc[0]);
         LVX_WIDE_ZERO(acc[1]);
-        constexpr int A0 = 0, A1 = LVX_WIDE_HALF_B, W0 = 2 * LVX_WIDE_HALF_B, W1 = 3 * LVX_WIDE_HALF_B, S1 = LVX_WIDE_STAGE_B;
-        load_a(0, 0, A0), load_w(0, 0, W0), load_w(1, 0, W1), load_a(1, 0, A1), load_a(0, second, S1 + A0), load_w(0, second, S1 + W0), load_w(1, second, S1 + W1);
-        LVX_WIDE_WAIT(8);
+        constexpr int A0 = 0, A1 = LVX_WIDE_HALF_B, W0 = 2 * LVX_WIDE_HALF_B;
+        load_a(0, near.a, A0), load_w(near.w, W0), load_a(1, near.a, A1);
+        if (second > 0) advance();
+        load_a(0, far.a, STAGE_B + A0), load_w(far.w, STAGE_B + W0);
+        advance();
+        LVX_WIDE_WAIT(FN + 4);
         asm volatile("s_barrier" ::: "memory");
         if (wm == 1) asm volatile("s_barrier" ::: "memory");  // this group runs half a period behind
         int st = 0, t = 0;
         auto slab = [&](bool load_first, bool load_second) {
             LVX_WIDE_READ_A(st + A0);
-            LVX_WIDE_READ_W(0, st + W0);
-            LVX_WIDE_READ_W(1, st + W1);
+            LVX_WIDE_READ_W(st + W0);
             LVX_SCHED_FENCE();
             if (load_first) {
-                load_a(1, t + 1, (st ^ S1) + A1);
-                LVX_WIDE_WAIT(8);
+                load_a(1, near.a, STAGE_B - st + A1);
+                LVX_WIDE_WAIT(FN + 4);
             } else
                 LVX_WIDE_WAIT(0);
             LVX_WIDE_MATRIX_PHASE(acc[0]);
             LVX_WIDE_READ_A(st + A1);
             LVX_SCHED_FENCE();
             if (load_second) {
-                load_a(0, t + 2, st + A0), load_w(0, t + 2, st + W0), load_w(1, t + 2, st + W1);
-                LVX_WIDE_WAIT(8);
+                load_a(0, far.a, st + A0), load_w(far.w, st + W0);
+                LVX_WIDE_WAIT(FN + 4);
+                advance();
             } else
                 LVX_WIDE_WAIT(0);
             LVX_WIDE_MATRIX_PHASE(acc[1]);
-            st ^= S1;
+            st = STAGE_B - st;
         };
         for (; t + 1 < last; ++t) slab(true, true);
         for (; t <= last; ++t) slab(t < last, false);
@@ -307,23 +336,26 @@ __global__ void __launch_bounds__(512) lvx_gemm_wide_kernel(const lvx_gemm_args_
         finish(acc[1], m0 + 128);
     } else {
         // Slab t is in stage t % 3, one phase a slab; slab t + 2 is requested where slab t - 1 was read a phase ago.
-        f32x4_t acc[4][4];
+        f32x4_t acc[4][FN];
         LVX_WIDE_ZERO(acc);
-        constexpr int A = 0, W0 = LVX_WIDE_HALF_B, W1 = 2 * LVX_WIDE_HALF_B;
-        int cur = 0, nxt = LVX_WIDE_STAGE3_B, nx2 = 2 * LVX_WIDE_STAGE3_B;
-        load_a(0, 0, A), load_w(0, 0, W0), load_w(1, 0, W1), load_a(0, second, nxt + A), load_w(0, second, nxt + W0), load_w(1, second, nxt + W1);
-        LVX_WIDE_WAIT(6);
+        constexpr int A = 0, W0 = LVX_WIDE_HALF_B;
+        int cur = 0, nxt = STAGE3_B, nx2 = 2 * STAGE3_B;
+        load_a(0, far.a, A), load_w(far.w, W0);
+        if (second > 0) advance();
+        load_a(0, far.a, nxt + A), load_w(far.w, nxt + W0);
+        advance();
+        LVX_WIDE_WAIT(FN + 2);
         asm volatile("s_barrier" ::: "memory");
         if (wm == 1) asm volatile("s_barrier" ::: "memory");
         int t = 0;
         auto slab = [&](bool load) {
             LVX_WIDE_READ_A(cur + A);
-            LVX_WIDE_READ_W(0, cur + W0);
-            LVX_WIDE_READ_W(1, cur + W1);
+            LVX_WIDE_READ_W(cur + W0);
             LVX_SCHED_FENCE();
             if (load) {
-                load_a(0, t + 2, nx2 + A), load_w(0, t + 2, nx2 + W0), load_w(1, t + 2, nx2 + W1);
-                LVX_WIDE_WAIT(6);
+                load_a(0, far.a, nx2 + A), load_w(far.w, nx2 + W0);
+                LVX_WIDE_WAIT(FN + 2);
+                advance();
             } else
                 LVX_WIDE_WAIT(0);
             LVX_WIDE_MATRIX_PHASE(acc);
@@ -338,11 +370,11 @@ __global__ void __launch_bounds__(512) lvx_gemm_wide_kernel(const lvx_gemm_args_
     if (FP8 && p.amax != nullptr) lvx_amax_publish(amax_b, p.amax, (int)blockIdx.x * 8 + wave, lane);
 }
 
-// Launch with n_large 256 x 256 tiles (arguments checked, p.M > 0, p.segs filled but for tn_begin).
-template <int EPI, bool FP8>
+// Launch with n_large whole tiles (arguments checked, p.M > 0, p.segs filled but for tn_begin).
+template <int EPI, bool FP8, int FN = 4, bool CONV = false>
 static lvx_status_t lvx_gemm_wide_launch(lvx_gemm_args_t &p, int n_large, hipStream_t stream) {
     lvx_wide_grid_t g;
-    g.tiles_n = (int)lvx_gemm_col_tiles(&p.segs, p.N, 256);
+    g.tiles_n = (int)lvx_gemm_col_tiles(&p.segs, p.N, 64 * FN);
     for (int i = 0, t = 0; i < p.segs.n; ++i) p.segs.s[i].tn_begin = t, t += (p.segs.s[i].N + 255) / 256;
     g.full_m = lvx_wide_full_rows(p.M);
     g.n_large = n_large;
@@ -350,7 +382,7 @@ static lvx_status_t lvx_gemm_wide_launch(lvx_gemm_args_t &p, int n_large, hipStr
     g.group_m = 4;
     const int surplus = n_large % 8 + g.n_half % 8;  // an XCD has both surpluses only if there are more than 8
     const int most = n_large / 8 + g.n_half / 8 + (surplus > 8 ? 2 : surplus > 0 ? 1 : 0);
-    hipLaunchKernelGGL((lvx_gemm_wide_kernel<EPI, FP8>), dim3(8 * most), dim3(512), 0, stream, p, g);
+    hipLaunchKernelGGL((lvx_gemm_wide_kernel<EPI, FP8, FN, CONV>), dim3(8 * most), dim3(512), 0, stream, p, g);
     LVX_CHECK_HIP(hipGetLastError());
     return LVX_OK;
 }

@@ -168,23 +168,24 @@ static inline long lvx_wide_halves(int M, long cols, long n_large) {
 // whole tiles: the choice by the rule takes 0.1 % longer on average than the fastest of them.  2048 x 8192 x 5120 as 256 whole tiles 116 us, as
 // 512 halves 147; 4680 x 5120 x 5120 as 256 + 228 halves 174, 360 + 20 199, 740 halves 198; 1560 x 13824 x 5120 as 256 + 190 183, 324 + 54 204;
 // 2150 x 7656 x 4224 as 510 halves 114, 240 + 30 135.
-#define LVX_GEMM_SLAB_US_256X256 1.35
-#define LVX_GEMM_SLAB_US_256X256_ALONE 1.04
-static inline double lvx_wide_slab_us(int M, long cols, long n_large) {
-    const double half = LVX_GEMM_SLAB_US_128X256;
+// (lvx_wide_us_t: a whole tile on a busy chip and beside idle units, a half.)
+struct lvx_wide_us_t {
+    double whole, alone, half;
+};
+constexpr lvx_wide_us_t LVX_GEMM_WIDE_US = {1.35, 1.04, LVX_GEMM_SLAB_US_128X256};
+static inline double lvx_wide_slab_us(int M, long cols, long n_large, const lvx_wide_us_t &us = LVX_GEMM_WIDE_US) {
     const long busy = n_large % LVX_NUM_CU, halves = lvx_wide_halves(M, cols, n_large);
-    const double whole = (double)(n_large / LVX_NUM_CU) * LVX_GEMM_SLAB_US_256X256;
-    if (busy == 0) return whole + lvx_rounds(halves) * half;
-    const double most = LVX_NUM_CU / 2, last = LVX_GEMM_SLAB_US_256X256_ALONE +
-        (busy > most ? (LVX_GEMM_SLAB_US_256X256 - LVX_GEMM_SLAB_US_256X256_ALONE) * (busy - most) / most : 0.0);
+    const double whole = (double)(n_large / LVX_NUM_CU) * us.whole;
+    if (busy == 0) return whole + lvx_rounds(halves) * us.half;
+    const double most = LVX_NUM_CU / 2, last = us.alone + (busy > most ? (us.whole - us.alone) * (busy - most) / most : 0.0);
     // the last whole tiles take `busy` units for `last`, the other units begin the halves meanwhile: the first end of a half on either kind of
     // unit by which all of them are done
-    const double beside = half + (busy > 208 ? 0.004 * (busy - 208) : 0.0);
+    const double beside = us.half + (busy > 208 ? 0.005 * us.half * (busy - 208) : 0.0);
     const long idle = LVX_NUM_CU - busy;
     long early = 0, late = 0;
     double end = last;
     while (idle * early + busy * late < halves) {
-        const double a = (early + 1) * beside, b = last + (late + 1) * half;
+        const double a = (early + 1) * beside, b = last + (late + 1) * us.half;
         if (a <= b) ++early;
         else ++late;
         const double t = a <= b ? a : b;
@@ -193,13 +194,13 @@ static inline double lvx_wide_slab_us(int M, long cols, long n_large) {
     return whole + end;
 }
 // How many whole tiles are best: all, whole rounds of the chip, one round less, or none.
-static inline long lvx_wide_pick(int M, long cols, double *slab_us) {
+static inline long lvx_wide_pick(int M, long cols, double *slab_us, const lvx_wide_us_t &us = LVX_GEMM_WIDE_US) {
     const long total = lvx_wide_full_rows(M) * cols, rounds = total / LVX_NUM_CU * LVX_NUM_CU;
     long best = 0;
-    double best_us = lvx_wide_slab_us(M, cols, 0);
+    double best_us = lvx_wide_slab_us(M, cols, 0, us);
     const long offer[3] = {rounds - LVX_NUM_CU, rounds, total};
     for (int i = 0; i < 3; ++i)
-        if (offer[i] > 0 && lvx_wide_slab_us(M, cols, offer[i]) <= best_us) best = offer[i], best_us = lvx_wide_slab_us(M, cols, offer[i]);
+        if (offer[i] > 0 && lvx_wide_slab_us(M, cols, offer[i], us) <= best_us) best = offer[i], best_us = lvx_wide_slab_us(M, cols, offer[i], us);
     *slab_us = best_us;
     return best;
 }
@@ -262,16 +263,17 @@ static inline lvx_gemm_launch_t lvx_gemm_choose(const lvx_gemm_segs_t *segs, int
 enum { LVX_CONV_LARGE, LVX_CONV_ROWS, LVX_CONV_GROUPS };
 struct lvx_conv_plan_t {
     int kind, tile;  // tile: of LVX_CONV_ROW_TILES or LVX_GEMM_SMALL_TILES
+    double us;       // its time by the rule
 };
 static inline lvx_conv_plan_t lvx_conv_plan(int W, int N, int n_slabs, int M, int max_m) {
-    lvx_conv_plan_t plan = {LVX_CONV_LARGE, 0};
+    lvx_conv_plan_t plan = {LVX_CONV_LARGE, 0, 0.0};
     for (int pass = 0; pass < 2; ++pass) {  // 0: K groups or not, at the longest step; 1: the tile, at this one
         const int m = pass == 0 ? max_m : M;
         const bool groups = pass == 1 && plan.kind == LVX_CONV_GROUPS;
         double best = 1e30;
         auto rounds = [&](long rows, int bm, int bn) { return (double)lvx_rounds((rows + bm - 1) / bm * ((N + bn - 1) / bn)); };
         auto offer = [&](int kind, int tile, double us) {
-            if ((pass == 0 || (kind == LVX_CONV_GROUPS) == groups) && us < best) best = us, plan = {kind, tile};
+            if ((pass == 0 || (kind == LVX_CONV_GROUPS) == groups) && us < best) best = us, plan = {kind, tile, us};
         };
         offer(LVX_CONV_LARGE, 0, rounds(m, 256, 128) * n_slabs * 0.82);
         const long padded = (long)m / W * (W + 2);
@@ -284,6 +286,28 @@ static inline lvx_conv_plan_t lvx_conv_plan(int W, int N, int n_slabs, int M, in
 #undef LVX_TILE_COST
     }
     return plan;
+}
+
+// The kernel of a step: lvx_conv_plan, or tiles of 256 x 64 fn (fn 2, 3 or 4; lvx_gemm_wide.h) and their halves where these take at most
+// LVX_CONV_WIDE_MAX of its time.  They sum in the order of the first two kinds, so a step may take them whatever the layer's other steps
+// take; a layer of K groups keeps them.  Measured, us a step: four 100 x 180 frames 384 -> 384 channels 524 -> 463 (fn 3), four 127 x 85 64 -> 176 57
+// -> 38, four 185 x 373 128 -> 304 655 -> 541, two 115 x 172 384 -> 200 218 -> 175 (fn 4), three 74 x 217 448 -> 288 377 -> 326.  34 of 91 random layers and steps
+// lie below the line and took 0.66 to 0.97, mean 0.82; between it and 1.1 wide tiles took 0.88 to 1.08, mean 1.01.
+#define LVX_CONV_WIDE_MAX 0.94
+struct lvx_conv_launch_t {
+    lvx_conv_plan_t plan;
+    int fn, n_large;  // fn 0: the plan
+};
+static inline lvx_conv_launch_t lvx_conv_choose(int W, int N, int n_slabs, int M, int max_m) {
+    const lvx_wide_us_t us[3] = {{0.85, 0.70, 0.51}, {1.05, 0.76, 0.60}, {1.28, 0.94, 0.71}};  // fn 2, 3, 4
+    lvx_conv_launch_t l = {lvx_conv_plan(W, N, n_slabs, M, max_m), 0, 0};
+    double best = LVX_CONV_WIDE_MAX * l.plan.us;
+    for (int fn = 2; fn <= 4 && l.plan.kind != LVX_CONV_GROUPS; ++fn) {
+        double slab = 0.0;
+        const long n_large = lvx_wide_pick(M, (N + 64 * fn - 1) / (64 * fn), &slab, us[fn - 2]);
+        if (slab * n_slabs < best) best = slab * n_slabs, l.fn = fn, l.n_large = (int)n_large;
+    }
+    return l;
 }
 
 // ---- attention -----------------------------------------------------------------------------------------------------------------
