@@ -202,7 +202,7 @@ lvx_status_t lvx_launch_linear_fp8(const void *dev_aq, int64_t lda, const float 
         LVX_REQUIRE(ldr >= N, LVX_ERR_SHAPE, "bad residual leading dimension");
     }
     if (M == 0) return LVX_OK;
-    const lvx_gemm_launch_t plan = lvx_gemm_choose(nullptr, M, N, K / 128, false, epi == LVX_EPI_RESID_GATE_F32);
+    const lvx_gemm_launch_t plan = lvx_gemm_choose(nullptr, M, N, K / 128);
     lvx_gemm_args_t p = {};
     p.A = (const char *)dev_aq, p.lda = lda;
     p.W = (const char *)dev_wq, p.ldw = ldw;
@@ -215,14 +215,16 @@ lvx_status_t lvx_launch_linear_fp8(const void *dev_aq, int64_t lda, const float 
     p.epi = (int)epi;
     if (plan.wide_rows > 0) {
         p.M = plan.wide_rows;
-        if (epi == LVX_EPI_STORE)
-            LVX_TRY((lvx_gemm_wide_launch<LVX_EPI_STORE, true>(p, plan.n_large, (hipStream_t)stream)));
-        else if (epi == LVX_EPI_GELU_TANH)
-            LVX_TRY((lvx_gemm_wide_launch<LVX_EPI_GELU_TANH, true>(p, plan.n_large, (hipStream_t)stream)));
-        else if (epi == LVX_EPI_RESID_GATE)
-            LVX_TRY((lvx_gemm_wide_launch<LVX_EPI_RESID_GATE, true>(p, plan.n_large, (hipStream_t)stream)));
-        else
-            LVX_TRY((lvx_gemm_wide_launch<LVX_EPI_RESID_GATE_F32, true>(p, plan.n_large, (hipStream_t)stream)));
+#define LVX8_WIDE(E_)                                                                                        \
+        if (epi == E_)                                                                                       \
+            LVX_TRY((plan.fn == 2   ? lvx_gemm_wide_launch<E_, true, 2>(p, plan.n_large, (hipStream_t)stream) \
+                     : plan.fn == 3 ? lvx_gemm_wide_launch<E_, true, 3>(p, plan.n_large, (hipStream_t)stream) \
+                                    : lvx_gemm_wide_launch<E_, true, 4>(p, plan.n_large, (hipStream_t)stream)));
+        LVX8_WIDE(LVX_EPI_STORE)
+        LVX8_WIDE(LVX_EPI_GELU_TANH)
+        LVX8_WIDE(LVX_EPI_RESID_GATE)
+        LVX8_WIDE(LVX_EPI_RESID_GATE_F32)
+#undef LVX8_WIDE
         if (plan.wide_rows == M) return LVX_OK;
     }
     // the rows behind, or all, on a small tile

@@ -1,4 +1,4 @@
-// Matrix products on 256 x 256 and 128 x 256 tiles in one launch (bf16 and FP8 operands).
+// Matrix products on tiles of 256 x 256, 192 or 128 and their halves of 128 rows in one launch (bf16 and FP8 operands).
 //
 // What bounds a large product is the power that its matrix instructions draw, if the loads keep up: 128 x 256 tiles bring 48 KB into LDS per 4.2
 // MFLOP, 256 x 256 tiles 64 KB per 8.4.  Eight waves in two groups of four (the two waves of a SIMD belong to different groups) take 128 x 64
@@ -13,7 +13,9 @@
 // Without its stores the bf16 kernel runs at 1.60 PFLOP/s, the rate at which the chip's power holds a library's product as well.  The last slabs
 // stand in a loop of their own: with their conditions in the main one it ran 1 to 8 % slower.  Four phases of 16 instructions instead of two cost
 // 2 %, raised wave priorities change nothing, halves with a third of a slab's loads in each of two phases neither.
-// The decoder's convolution runs on the same kernel (CONV) with 128, 192 or 256 columns; see lvx_conv_choose.
+// Tiles of 192 or 128 columns (FN = 3, 2) serve the products whose last round 256 columns leave half empty: 1560 x 5120 x 13824 with the residual 232
+// (rows split off to 64 x 64 tiles) -> 190, 1886 x 2560 x 2560 with it 32.9 (a kernel of 128 x 192 tiles) -> 31.4; which: lvx_gemm_choose.
+// The decoder's convolution runs on the same kernel (CONV); see lvx_conv_choose.
 #pragma once
 #include "lvx_gemm_core.h"
 
@@ -56,7 +58,7 @@ __device__ __forceinline__ bool lvx_wide_tile_of(const lvx_wide_grid_t &g, bool 
 
 // Column of a wave's 16 * FN that row r of its rows of the W tile stands for: a lane's accumulators of two neighbouring 16-column blocks are then
 // eight consecutive columns, so outputs and residuals move in 16-byte pieces, four lanes to a 64-byte (fp32: 128-byte) run.  (Three
-// blocks, convolutions only: the last one stands alone, four columns a lane.)
+// blocks: the last one stands alone, four columns a lane.)
 template <int FN>
 __device__ __forceinline__ int lvx_wide_col(int r) {
     if (FN % 2 == 1 && r >= 16 * (FN - 1)) return r;
@@ -72,7 +74,6 @@ __device__ __forceinline__ uint32_t lvx_wide_epilogue(const f32x4_t (&acc)[4][FN
     constexpr bool RES32 = EPI == LVX_EPI_RESID_GATE_F32, RES16 = EPI == LVX_EPI_RESID_GATE, F32 = RES32 || EPI == LVX_EPI_STORE_F32;
     constexpr bool BIAS = EPI == LVX_EPI_BIAS || EPI == LVX_EPI_BIAS_SILU;
     constexpr int NH = (FN + 1) / 2;
-    static_assert(FN % 2 == 0 || BIAS, "a last block of its own has no residual here");
     float gt[NH][8];  // gate (residual epilogues) or bias of the lane's columns
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
@@ -90,26 +91,33 @@ __device__ __forceinline__ uint32_t lvx_wide_epilogue(const f32x4_t (&acc)[4][FN
         const int m = m0 + 16 * i < M ? m0 + 16 * i : M - 1;
 #pragma unroll
         for (int h = 0; h < NH; ++h) {
-            const int n = n0 + 32 * h < N ? n0 + 32 * h : 0;
+            const bool four = 2 * h + 1 == FN;
+            const int nb = n0 + 32 * h - (four ? 4 * q4 : 0), n = nb < N ? nb : 0;
             if (RES32) {
                 const float *r = reinterpret_cast<const float *>(Rv) + (size_t)m * ldr + n;
                 if (vec) {
-                    const f32x4_t a = *reinterpret_cast<const f32x4_t *>(r), b = *reinterpret_cast<const f32x4_t *>(r + 4);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) res[i & 1][h][e] = a[e], res[i & 1][h][4 + e] = b[e];
+                    for (int c = 0; c < (four ? 1 : 2); ++c) {
+                        const f32x4_t a = *reinterpret_cast<const f32x4_t *>(r + 4 * c);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) res[i & 1][h][4 * c + e] = a[e];
+                    }
                 } else {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) res[i & 1][h][e] = r[e];
+                    for (int e = 0; e < (four ? 4 : 8); ++e) res[i & 1][h][e] = r[e];
                 }
             } else {
                 const bf16_t *r = reinterpret_cast<const bf16_t *>(Rv) + (size_t)m * ldr + n;
                 if (vec) {
-                    const u32x4_t a = *reinterpret_cast<const u32x4_t *>(r);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) res[i & 1][h][2 * e] = bf16_lo(a[e]), res[i & 1][h][2 * e + 1] = bf16_hi(a[e]);
+                    for (int c = 0; c < (four ? 1 : 2); ++c) {
+                        const uint2 a = *reinterpret_cast<const uint2 *>(r + 4 * c);
+                        res[i & 1][h][4 * c] = bf16_lo(a.x), res[i & 1][h][4 * c + 1] = bf16_hi(a.x);
+                        res[i & 1][h][4 * c + 2] = bf16_lo(a.y), res[i & 1][h][4 * c + 3] = bf16_hi(a.y);
+                    }
                 } else {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) res[i & 1][h][e] = bf16_bits_to_f32(r[e]);
+                    for (int e = 0; e < (four ? 4 : 8); ++e) res[i & 1][h][e] = bf16_bits_to_f32(r[e]);
                 }
             }
         }
@@ -140,10 +148,10 @@ __device__ __forceinline__ uint32_t lvx_wide_epilogue(const f32x4_t (&acc)[4][FN
                 float *c = reinterpret_cast<float *>(Cv) + (size_t)m * ldc + n;
                 if (vec) {
                     *reinterpret_cast<f32x4_t *>(c) = f32x4_t{v[0], v[1], v[2], v[3]};
-                    *reinterpret_cast<f32x4_t *>(c + 4) = f32x4_t{v[4], v[5], v[6], v[7]};
+                    if (!four) *reinterpret_cast<f32x4_t *>(c + 4) = f32x4_t{v[4], v[5], v[6], v[7]};
                 } else {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) c[e] = v[e];
+                    for (int e = 0; e < (four ? 4 : 8); ++e) c[e] = v[e];
                 }
             } else {
                 bf16_t *c = reinterpret_cast<bf16_t *>(Cv) + (size_t)m * ldc + n;
@@ -275,7 +283,7 @@ __global__ void __launch_bounds__(512) lvx_gemm_wide_kernel(const lvx_gemm_args_
                 lvx_wide_epilogue<LVX_EPI_STORE_F32, FP8, FN>(acc, o.C, o.ldc, nullptr, 0, nullptr, M, N, m, n0, q4, alpha, vec);
             else
                 lvx_wide_epilogue<LVX_EPI_STORE, FP8, FN>(acc, o.C, o.ldc, nullptr, 0, nullptr, M, N, m, n0, q4, alpha, vec);
-            if (o.sumsq != nullptr && n0 - 8 * q4 < N) lvx_wide_row_sumsq(acc, o.sumsq, o.ld_sumsq, tn * 4 + wn, M, m, q4);
+            if constexpr (FN == 4) if (o.sumsq != nullptr && n0 - 8 * q4 < N) lvx_wide_row_sumsq(acc, o.sumsq, o.ld_sumsq, tn * 4 + wn, M, m, q4);
         } else {
             b = lvx_wide_epilogue<EPI, FP8, FN>(acc, o.C, o.ldc, p.R, p.ldr, p.gate, M, N, m, n0, q4, alpha, vec);
         }
@@ -375,7 +383,7 @@ template <int EPI, bool FP8, int FN = 4, bool CONV = false>
 static lvx_status_t lvx_gemm_wide_launch(lvx_gemm_args_t &p, int n_large, hipStream_t stream) {
     lvx_wide_grid_t g;
     g.tiles_n = (int)lvx_gemm_col_tiles(&p.segs, p.N, 64 * FN);
-    for (int i = 0, t = 0; i < p.segs.n; ++i) p.segs.s[i].tn_begin = t, t += (p.segs.s[i].N + 255) / 256;
+    for (int i = 0, t = 0; i < p.segs.n; ++i) p.segs.s[i].tn_begin = t, t += (p.segs.s[i].N + 64 * FN - 1) / (64 * FN);
     g.full_m = lvx_wide_full_rows(p.M);
     g.n_large = n_large;
     g.n_half = (int)lvx_wide_halves(p.M, g.tiles_n, n_large);

@@ -44,7 +44,7 @@ struct lvx_gemm_segs_t {
     X_(2, 32, 64, 1, 4, 5, 2, 16, 0.235f) \
     X_(3, 32, 32, 1, 2, 4, 4, 16, 0.16f)
 #define LVX_GEMM_SLAB_US_128X256 0.80f  // 128 x 256 tiles, per slab and compute unit
-#define LVX_GEMM_SLAB_US_128X192 0.66f  // the same kernel with 128 x 192 tiles (bf16): 1886 x 2560 x 6912 80 -> 74 us, 2048 x 3072 x 3072 44 -> 40.5
+#define LVX_GEMM_SLAB_US_128X192 0.66f  // 128 x 192 tiles (halves of 192 columns on the wide kernel): 1886 x 2560 x 6912 80 -> 66 us, 2048 x 3072 x 3072 44 -> 40.5
 enum { LVX_GEMM_TILE_128X256 = -1, LVX_GEMM_TILE_128X192 = -2 };
 
 // Column tiles of width bn of the product(s).
@@ -55,7 +55,7 @@ static inline long lvx_gemm_col_tiles(const lvx_gemm_segs_t *segs, int N, int bn
     return t;
 }
 
-// Which small tile to use, or one of the large ones (128 x 192 only if `narrow` says that the caller has it, and only where that takes at
+// Which small tile to use, or one of the large ones (128 x 192 only if `narrow` says that the caller can use it, and only where that takes at
 // most LVX_GEMM_NARROW_MAX of the 128 x 256 tiles' time: 174 shapes at 0.825 by the rule, the same number of rounds, ran in 0.87 of it,
 // but nine at 0.99, six rounds for five, in 1.015): the one whose rounds of the
 // chip (a compute unit that gets two tiles needs twice the time, whether one after the other or side by side) times slabs
@@ -153,8 +153,8 @@ static inline lvx_gemm_plan_t lvx_gemm_plan(const lvx_gemm_segs_t *segs, int M, 
 static inline bool lvx_fp8_spreads_loads(int n_slabs) { return n_slabs >= 16; }
 
 // ---- 256 x 256 tiles (lvx_gemm_wide.h) -------------------------------------------------------------------------------------------
-// The kernel of the 128 x 256 tiles works some pairs of them as one 256 x 256 tile: M rows are lvx_wide_full_rows row tiles of 256 and, if at most
-// 128 rows remain, one of 128; the first n_large of the 256 x 256 tiles are taken whole, the others as two halves.
+// The wide kernel's tiles have 256 rows, or as halves 128: M rows are lvx_wide_full_rows row tiles of 256 and, if at most 128 rows remain, one of 128;
+// the first n_large of the 256-row tiles are taken whole, the others as two halves.
 static inline int lvx_wide_full_rows(int M) { return M / 256 + (M % 256 > 128 ? 1 : 0); }
 static inline long lvx_wide_halves(int M, long cols, long n_large) {
     const long full = lvx_wide_full_rows(M);
@@ -172,8 +172,9 @@ static inline long lvx_wide_halves(int M, long cols, long n_large) {
 struct lvx_wide_us_t {
     double whole, alone, half;
 };
-constexpr lvx_wide_us_t LVX_GEMM_WIDE_US = {1.35, 1.04, LVX_GEMM_SLAB_US_128X256};
-static inline double lvx_wide_slab_us(int M, long cols, long n_large, const lvx_wide_us_t &us = LVX_GEMM_WIDE_US) {
+// Tiles of 256 x 64 fn, fn = 2, 3, 4.
+constexpr lvx_wide_us_t LVX_GEMM_WIDE_US[3] = {{0.82, 0.68, 0.52}, {1.05, 0.80, 0.64}, {1.35, 1.04, LVX_GEMM_SLAB_US_128X256}};
+static inline double lvx_wide_slab_us(int M, long cols, long n_large, const lvx_wide_us_t &us = LVX_GEMM_WIDE_US[2]) {
     const long busy = n_large % LVX_NUM_CU, halves = lvx_wide_halves(M, cols, n_large);
     const double whole = (double)(n_large / LVX_NUM_CU) * us.whole;
     if (busy == 0) return whole + lvx_rounds(halves) * us.half;
@@ -194,7 +195,7 @@ static inline double lvx_wide_slab_us(int M, long cols, long n_large, const lvx_
     return whole + end;
 }
 // How many whole tiles are best: all, whole rounds of the chip, one round less, or none.
-static inline long lvx_wide_pick(int M, long cols, double *slab_us, const lvx_wide_us_t &us = LVX_GEMM_WIDE_US) {
+static inline long lvx_wide_pick(int M, long cols, double *slab_us, const lvx_wide_us_t &us = LVX_GEMM_WIDE_US[2]) {
     const long total = lvx_wide_full_rows(M) * cols, rounds = total / LVX_NUM_CU * LVX_NUM_CU;
     long best = 0;
     double best_us = lvx_wide_slab_us(M, cols, 0, us);
@@ -205,42 +206,51 @@ static inline long lvx_wide_pick(int M, long cols, double *slab_us, const lvx_wi
     return best;
 }
 
-// The launch of a product: lvx_gemm_plan, with 256 x 256 tiles where they are in reach.  wide_rows: the rows that the kernel of 128 x 256 and 256 x
-// 256 tiles takes, n_large whole tiles among them; the rows behind go to `tile` (m1 = wide_rows) or there are none.  A plan of other
-// tiles gives way where the wide kernel takes at most LVX_GEMM_WIDE_MAX of its time by the rule: there it took 0.91 to 1.01 of the time of 128 x 192
-// tiles (three of 65 products above 1) and 0.84 to 1.07 of that of rows split off, mean 0.95 (170 products); between 1.12 and 1.3 it took
-// 1.0 to 1.2.  With an fp32 residual (resid32), which fewer and larger tiles read and write on fewer compute units, up to
-// LVX_GEMM_WIDE_MAX_RESID (0.937 to 0.992: 0.95 to 1.12, mean 1.02).  A plan with K groups stays, they fix the order of summation, and so
-// does one that leaves partial sums of squares of narrower groups of columns.
-#define LVX_GEMM_WIDE_MAX 1.10
-#define LVX_GEMM_WIDE_MAX_RESID 0.93
+// The launch of a product: lvx_gemm_plan, with the wide tiles (256 x 64 fn and their halves) where they are in reach.  wide_rows: the rows that the
+// wide kernel takes, n_large whole tiles among them; the rows behind go to `tile` (m1 = wide_rows) or there are none.  Where the plan is
+// one of the large tiles (128 x 256 or 128 x 192), the wide kernel takes all rows.  Rows split off and the small tiles without K groups give way
+// where it takes no longer by the rule (0.66 to 0.84: 0.85 to 0.99 measured; 1.24 for the 64 x 128 tiles: 1.0 to 1.29).  A plan with K groups
+// stays, they fix the order of summation.  Narrower tiles, which move more bytes and power per product, are taken where they save a tenth by the
+// rule, which means where they leave fewer compute units idle: below 0.90 110 products of 900 to 9000 rows took 0.70 to 1.06 of the time of
+// 256-column tiles or of a 128 x 192 kernel of its own, mean 0.91 (1886 x 2560 x 2560 with residual 32.9 -> 31.4 us, 1560 x 5120 x 5120 with residual
+// 86.7 -> 79.9, 1560 x 5120 x 13824 232 -> 190); from 0.90 to 1 they took 0.98 to 1.11, mean 1.03 (4680 x 15360 x 5120 505 -> 520).
+// Partial sums of squares need columns by 64, so 256-column tiles, and a plan that leaves narrower ones stays.
+#define LVX_WIDE_NARROWER 0.90
 struct lvx_gemm_launch_t {
-    int tile, wide_rows, n_large;
+    int tile, wide_rows, fn, n_large;
 };
-static inline lvx_gemm_launch_t lvx_gemm_choose(const lvx_gemm_segs_t *segs, int M, int N, int n_slabs, bool narrow, bool resid32) {
-    const bool many = segs != nullptr && segs->n > 0;
-    const long cols = lvx_gemm_col_tiles(segs, many ? segs->s[0].N : N, 256);
-    const lvx_gemm_plan_t plan = lvx_gemm_plan(segs, M, N, n_slabs, narrow);
-    double us = 0.0, part_us = 0.0;
-    lvx_gemm_launch_t l = {LVX_GEMM_TILE_128X256, M, (int)lvx_wide_pick(M, cols, &us)};
-    if (plan.m1 == 0 && plan.tile == LVX_GEMM_TILE_128X256) return l;
-    double plan_us = plan.us;
-    lvx_gemm_launch_t other = {plan.tile, plan.m1, 0};
-    if (plan.m1 > 0) {
-        other.n_large = (int)lvx_wide_pick(plan.m1, cols, &part_us);
-#define LVX_TILE_COST(ID_, BM_, BN_, WM_, WN_, NST_, KG_, PC_, US_) \
-    if (plan.tile == ID_)                                           \
-        plan_us = part_us * n_slabs + (double)lvx_rounds((long)((M - plan.m1 + BM_ - 1) / BM_) * lvx_gemm_col_tiles(segs, many ? segs->s[0].N : N, BN_)) * n_slabs * US_;
-        LVX_GEMM_SMALL_TILES(LVX_TILE_COST)
-#undef LVX_TILE_COST
+static inline lvx_gemm_launch_t lvx_wide_best(const lvx_gemm_segs_t *segs, int M, int N, int fn_min, double *slab_us) {
+    lvx_gemm_launch_t l = {LVX_GEMM_TILE_128X256, M, 4, 0};
+    *slab_us = 1e30;
+    for (int fn = 4; fn >= fn_min; --fn) {
+        double us = 0.0;
+        const long n_large = lvx_wide_pick(M, lvx_gemm_col_tiles(segs, N, 64 * fn), &us, LVX_GEMM_WIDE_US[fn - 2]);
+        if (us < LVX_WIDE_NARROWER * *slab_us) *slab_us = us, l.fn = fn, l.n_large = (int)n_large;
     }
-    const bool sumsq = many && segs->s[0].sumsq != nullptr;
+    return l;
+}
+static inline lvx_gemm_launch_t lvx_gemm_choose(const lvx_gemm_segs_t *segs, int M, int N, int n_slabs) {
+    const bool many = segs != nullptr && segs->n > 0, sumsq = many && segs->s[0].sumsq != nullptr;
+    const int n = many ? segs->s[0].N : N, fn_min = sumsq ? 4 : 2;
+    const lvx_gemm_plan_t plan = lvx_gemm_plan(segs, M, N, n_slabs, !sumsq);
+    double us = 0.0, part_us = 0.0;
+    const lvx_gemm_launch_t wide = lvx_wide_best(segs, M, n, fn_min, &us);
+    if (plan.m1 == 0 && plan.tile < 0) return wide;
+    lvx_gemm_launch_t other = {plan.tile, plan.m1, 0, 0};
+    double plan_us = plan.us;
     bool groups = false;
-#define LVX_TILE_GROUPS(ID_, BM_, BN_, WM_, WN_, NST_, KG_, PC_, US_) groups = groups || (plan.tile == ID_ && KG_ > 1);
-    LVX_GEMM_SMALL_TILES(LVX_TILE_GROUPS)
-#undef LVX_TILE_GROUPS
-    if (!sumsq && !groups && us * n_slabs <= (resid32 ? LVX_GEMM_WIDE_MAX_RESID : LVX_GEMM_WIDE_MAX) * plan_us) return l;
-    return other;
+#define LVX_TILE_COST(ID_, BM_, BN_, WM_, WN_, NST_, KG_, PC_, US_)                                                                              \
+    if (plan.tile == ID_) {                                                                                                                      \
+        groups = KG_ > 1;                                                                                                                        \
+        if (plan.m1 > 0) {                                                                                                                       \
+            other = lvx_wide_best(segs, plan.m1, n, fn_min, &part_us);                                                                           \
+            other.tile = plan.tile;                                                                                                              \
+            plan_us = (part_us + (double)lvx_rounds((long)((M - plan.m1 + BM_ - 1) / BM_) * lvx_gemm_col_tiles(segs, n, BN_)) * US_) * n_slabs; \
+        }                                                                                                                                        \
+    }
+    LVX_GEMM_SMALL_TILES(LVX_TILE_COST)
+#undef LVX_TILE_COST
+    return !sumsq && !groups && us * n_slabs <= plan_us ? wide : other;
 }
 
 // ---- convolution ---------------------------------------------------------------------------------------------------------------

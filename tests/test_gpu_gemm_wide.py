@@ -1,5 +1,5 @@
-"""Products on 256 x 256 tiles and their halves against the fp64 oracle: one slab and few, rows and columns past the last tile, rows that only
-a half covers, all epilogues, output rows that allow 16-byte stores and rows that do not."""
+"""Products on tiles of 256 x 256, 192 or 128 and their halves against the fp64 oracle: one slab and few, rows and columns past the last tile, rows
+that only a half covers, all epilogues, output rows that allow 16-byte stores and rows that do not."""
 import math
 
 import numpy as np
@@ -12,10 +12,15 @@ from test_gpu_parity import DEV, assert_close
 
 pytestmark = pytest.mark.gpu
 
-# M, N, K with the 256 x 256 tiles and the halves that the rule takes; test_wide_rules.py holds the rule to it
-SHAPES = [((1731, 5656, 64), (161, 0)), ((1731, 5656, 192), (161, 0)), ((1567, 13832, 64), (256, 203)), ((1567, 13832, 320), (256, 203)),
-          ((4353, 4616, 128), (256, 153)), ((1411, 4616, 192), (0, 228))]
-FP8_SHAPES = [((1731, 5656, 128), (161, 0)), ((1731, 5656, 384), (161, 0)), ((1567, 13832, 256), (256, 203)), ((1411, 4616, 1920), (0, 228))]
+# M, N, K with the rows on wide tiles, their columns / 64, the whole tiles and the halves that the rule takes; test_wide_rules.py holds it to them
+SHAPES = [((1567, 13832, 64), (1567, 4, 256, 203)), ((1567, 13832, 320), (1567, 4, 256, 203)), ((1411, 4616, 192), (1411, 4, 0, 228)),
+          ((1033, 14432, 3840), (1024, 4, 228, 0)),
+          ((1731, 5656, 64), (1731, 3, 210, 0)), ((1731, 5656, 192), (1731, 3, 210, 0)), ((1281, 13272, 128), (1281, 3, 350, 70)),
+          ((4353, 4616, 128), (4353, 3, 425, 25)), ((1901, 2568, 192), (1901, 3, 0, 210)),
+          ((515, 9832, 64), (515, 2, 154, 77)), ((515, 9832, 192), (515, 2, 154, 77)), ((129, 10904, 128), (129, 2, 0, 172))]
+FP8_SHAPES = [((1567, 13832, 256), (1567, 4, 256, 203)), ((1411, 4616, 1920), (1411, 4, 0, 228)),
+              ((1731, 5656, 128), (1731, 3, 210, 0)), ((1731, 5656, 384), (1731, 3, 210, 0)), ((1901, 2568, 256), (1901, 3, 0, 210)),
+              ((515, 9832, 128), (515, 2, 154, 77)), ((129, 10904, 1920), (129, 2, 0, 172))]
 
 
 def padded(M, N, pad, dtype, fill=7.0):
@@ -72,9 +77,10 @@ def test_linear_fp8_on_wide_tiles(lvx, M, N, K):
     assert np.abs(S.to_f64(x[:, :N]) - (S.to_f64(r[:, :N]) + S.to_f64(g) * ref)).max() <= 1e-4 * math.sqrt(K)
 
 
-def test_segments_on_wide_tiles(lvx):
+@pytest.mark.parametrize("M,N1,N2", [(4353, 2328, 2296), (1567, 6920, 6912), (515, 4936, 4896)])
+def test_segments_on_wide_tiles(lvx, M, N1, N2):
     """Two products of one launch whose widths end inside a tile, the first stored fp32."""
-    M, N1, N2, K = 4353, 2328, 2296, 128
+    K = 128
     a = S.randn_bf16((M, K), S.seed_of("ws_a"), device=DEV)
     w = S.randn_bf16((N1 + N2, K), S.seed_of("ws_w"), 1.0 / math.sqrt(K), device=DEV)
     ref = O.linear(S.to_f64(a), S.to_f64(w))

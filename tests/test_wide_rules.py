@@ -1,4 +1,4 @@
-"""The rule that chooses 256 x 256 tiles (csrc/lvx_launch_rules.h), evaluated on the CPU."""
+"""The rule that chooses tiles of 256 x 256, 192 or 128 (csrc/lvx_launch_rules.h), evaluated on the CPU."""
 import ctypes as C
 import random
 import shutil
@@ -12,12 +12,12 @@ import test_launch_rules as base
 
 SOURCE = r"""
 #include "lvx_launch_rules.h"
-extern "C" void linear_choose(int M, int N, int n_slabs, int narrow, int resid32, int *tile, int *rows, int *large, int *halves) {
-    const lvx_gemm_launch_t l = lvx_gemm_choose(nullptr, M, N, n_slabs, narrow != 0, resid32 != 0);
-    *tile = l.tile, *rows = l.wide_rows, *large = l.n_large;
-    *halves = l.wide_rows > 0 ? (int)lvx_wide_halves(l.wide_rows, (N + 255) / 256, l.n_large) : 0;
+extern "C" void linear_choose(int M, int N, int n_slabs, int *tile, int *rows, int *fn, int *large, int *halves) {
+    const lvx_gemm_launch_t l = lvx_gemm_choose(nullptr, M, N, n_slabs);
+    *tile = l.tile, *rows = l.wide_rows, *fn = l.fn, *large = l.n_large;
+    *halves = l.wide_rows > 0 ? (int)lvx_wide_halves(l.wide_rows, (N + 64 * l.fn - 1) / (64 * l.fn), l.n_large) : 0;
 }
-extern "C" double wide_us(int M, int N, int n_large) { return lvx_wide_slab_us(M, (N + 255) / 256, n_large); }
+extern "C" double wide_us(int M, int N, int fn, int n_large) { return lvx_wide_slab_us(M, (N + 64 * fn - 1) / (64 * fn), n_large, LVX_GEMM_WIDE_US[fn - 2]); }
 """
 
 
@@ -36,47 +36,45 @@ def rules(tmp_path_factory):
     return lib
 
 
-def choose(rules, M, N, K, fp8=False, resid=False):
-    out = [C.c_int() for _ in range(4)]
-    rules.linear_choose(M, N, K // (128 if fp8 else 64), int(not fp8), int(resid), *(C.byref(o) for o in out))
-    return base.SMALL[out[0].value], out[1].value, out[2].value, out[3].value
+def choose(rules, M, N, K, fp8=False):
+    out = [C.c_int() for _ in range(5)]
+    rules.linear_choose(M, N, K // (128 if fp8 else 64), *(C.byref(o) for o in out))
+    return (base.SMALL[out[0].value],) + tuple(o.value for o in out[1:])
 
 
 def test_gpu_shapes_take_the_tiles_they_name(rules):
-    for resid in (False, True):
-        for (M, N, K), tiles in wide_tests.SHAPES:
-            assert choose(rules, M, N, K, resid=resid) == ("128x256", M) + tiles, (M, N, K)
-        for (M, N, K), tiles in wide_tests.FP8_SHAPES:
-            assert choose(rules, M, N, K, True, resid) == ("128x256", M) + tiles, (M, N, K)
-        # the shapes of the other tiles stay with them
-        for (M, N, K), kernel in gemm_tests.SHAPES:
-            assert choose(rules, M, N, K, resid=resid)[0] == kernel, (M, N, K)
-    # and so do the rows split off with their residual, but for one product that 120 whole tiles serve better
+    for (M, N, K), tiles in wide_tests.SHAPES:
+        assert choose(rules, M, N, K)[1:] == tiles, (M, N, K)
+    for (M, N, K), tiles in wide_tests.FP8_SHAPES:
+        assert choose(rules, M, N, K, True)[1:] == tiles, (M, N, K)
+    # the shapes of the small tiles stay with them, those of the large ones and the rows that they split off all go to the wide kernel
+    for (M, N, K), kernel in gemm_tests.SHAPES:
+        assert choose(rules, M, N, K)[:2] == (("128x256", M) if kernel in ("128x256", "128x192") else (kernel, 0)), (M, N, K)
     for (M, N, K), kernel, m1 in gemm_tests.LARGE_SHAPES:
-        assert choose(rules, M, N, K, resid=True)[:2] == ((kernel, m1) if (M, N, K) != (1550, 5112, 576) else ("128x256", M)), (M, N, K)
+        assert choose(rules, M, N, K)[1] == M, (M, N, K)
     for (M, N, K), kernel, m1 in gemm_tests.FP8_SPLIT_SHAPES:
-        assert choose(rules, M, N, K, True, True)[:2] == (kernel, m1), (M, N, K)
+        assert choose(rules, M, N, K, True)[1] == M, (M, N, K)
 
 
 def test_tiles_cover_all_rows_and_whole_tiles_never_cost_more(rules):
     rng = random.Random(5)
     for _ in range(20000):
         M, N = int(60000 ** rng.random()) + 1, 8 * (int(2600 ** rng.random()) + 1)
-        kernel, rows, large, halves = choose(rules, M, N, 64 * rng.randint(1, 200), resid=rng.random() < 0.5)
+        kernel, rows, fn, large, halves = choose(rules, M, N, 64 * rng.randint(1, 200))
         if rows == 0:
             continue
-        cols, full = -(-N // 256), rows // 256 + (rows % 256 > 128)
-        assert 0 <= large <= full * cols and (rows == M) == (kernel == "128x256")
+        cols, full = -(-N // (64 * fn)), rows // 256 + (rows % 256 > 128)
+        assert fn in (2, 3, 4) and 0 <= large <= full * cols and (rows == M) == (kernel == "128x256")
         # 128-row halves: two for each tile that is not whole, one for the last rows that no 256-row tile covers
         assert halves == 2 * (full * cols - large) + (cols if rows > 256 * full else 0)
-        assert rules.wide_us(rows, N, large) <= rules.wide_us(rows, N, 0) * (1 + 1e-12)
+        assert rules.wide_us(rows, N, fn, large) <= rules.wide_us(rows, N, fn, 0) * (1 + 1e-12)
 
 
 def test_measured_choices(rules):
-    """Whole tiles where they were faster, halves or other tiles where those were."""
-    for (M, N, K), (tile, large) in {(4680, 15360, 5120): ("128x256", 1024), (4680, 13824, 5120): ("128x256", 972), (4680, 5120, 13824): ("128x256", 256),
-                                     (1560, 13824, 5120): ("128x256", 256), (1886, 7680, 2560): ("128x256", 210), (1170, 6144, 1536): ("128x256", 0),
-                                     (1170, 4608, 1536): ("128x192", 0), (1886, 2560, 2560): ("128x192", 0), (1731, 5656, 2240): ("128x256", 161),
-                                     (2150, 7656, 4224): ("128x256", 0), (3128, 10568, 5376): ("64x64", 504), (2449, 7064, 1152): ("128x256", 256)}.items():
-        assert choose(rules, M, N, K)[::2] == (tile, large), (M, N, K)
-    assert choose(rules, 1576, 5120, 6208, resid=True)[:2] == ("64x64", 1536) and choose(rules, 4469, 2296, 9664, resid=True)[:2] == ("128x256", 4469)
+    """Whole tiles where they were faster, halves, narrower or other tiles where those were."""
+    for (M, N, K), tile in {(4680, 15360, 5120): (4680, 4, 1024), (4680, 13824, 5120): (4680, 4, 972), (4680, 5120, 13824): (4680, 4, 256),
+                            (1560, 13824, 5120): (1560, 4, 256), (1886, 7680, 2560): (1886, 4, 210), (1170, 6144, 1536): (1170, 4, 0),
+                            (1886, 2560, 2560): (1886, 3, 0), (1731, 5656, 2240): (1731, 3, 210), (1560, 5120, 5120): (1560, 3, 162),
+                            (1560, 5120, 13824): (1560, 3, 162), (2449, 7064, 1152): (2449, 3, 256), (427, 6656, 2368): (427, 2, 0),
+                            (3227, 2376, 2816): (3227, 3, 169), (1170, 1536, 6144): (0, 0, 0)}.items():
+        assert choose(rules, M, N, K)[1:4] == tile, (M, N, K)
