@@ -30,6 +30,7 @@
 //   * SPLIT (see lvx_attention_parts): a workgroup takes a range of the key tiles and leaves its queries' outputs in fp32, un-normalised, with their
 //     references and sums; lvx_attention_combine_kernel adds the ranges up in their order.  A range whose first tile has no finite
 //     score for a query takes that query's reference from the first tile that has one.
+//   * few keys for few queries take a kernel of their own, lvx_attention_few_kernel below (see lvx_attention_few).
 //   * template switches: TP = 64-key tiles per pipeline phase (2 from 1024 visible keys on: half the barriers, pipeline fills and
 //     drains per key); PRE = the queries arrive multiplied by scale * log2(e) and the score accumulators start at minus the
 //     softmax reference, so a score leaves the MFMA as the exponent (one FMA per score less; used inside a block, where the
@@ -542,6 +543,212 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
 }
 
+// Few keys for few queries: a workgroup takes 16 queries of one head, and its waves (up to eight) take the key tiles in turn, wave w tiles w, w + n_waves
+// and so on, each with a softmax of its own; their outputs meet in LDS.  What bounds such a call is the chain of latencies of one
+// workgroup, not the chip: so a wave loads its own tiles, all of one at once where LDS has the room (lvx_attention_few_apart), and no wave waits for
+// another before the end.  (Fragments straight from the cache to registers, 16 rows of 64 bytes an instruction, took 1 us a tile and compute unit.)
+template <int D, bool PRE, bool QN>
+__global__ void __launch_bounds__(512) lvx_attention_few_kernel(const bf16_t *__restrict__ q, int64_t ld_q, int n_q, const bf16_t *__restrict__ kp,
+                                                                const bf16_t *__restrict__ vtp, int cap, int n_keys, float c_exp2, bf16_t *__restrict__ out,
+                                                                int64_t ld_out, int n_qtiles, int total_wg, int per_xcd, uint32_t *amax_slots,
+                                                                lvx_attn_qnorm_t qn) {
+    static_assert(!QN || PRE, "normalised queries are also pre-scaled");
+    constexpr int MK = D / 32, DB = D / 16, TILE_B = KT * D * 2, K_ROW_B = D * 2, V_ROW_B = KT * 2, N_DMA = TILE_B / 1024;
+    extern __shared__ __attribute__((aligned(1024))) char few_lds[];  // per wave one tile of K, and of V^T behind it or in its place
+    __shared__ float2 stat[LVX_ATTN_FEW_WAVES * 16];
+
+    const int widx = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);  // a head's workgroups share an XCD, as above
+    if (widx >= total_wg) return;
+    const int head = widx / n_qtiles, row0 = widx % n_qtiles * 16;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = blockDim.x >> 6;
+    const int l16 = lane & 15, q4 = lane >> 4;
+    const int n_tiles = (n_keys + KT - 1) / KT;
+    const bool apart = lvx_attention_few_apart(n_waves, D);
+    const int wave_b = apart ? 2 * TILE_B : TILE_B;
+
+    // a tile's rows in LDS: order and swizzle as in the kernel above; a wave reads only what it has loaded itself
+    const char *k_src = reinterpret_cast<const char *>(kp + (size_t)head * cap * D), *v_src = reinterpret_cast<const char *>(vtp + (size_t)head * cap * D);
+    char *k_lds = few_lds + wave * wave_b, *v_lds = k_lds + (apart ? TILE_B : 0);
+    const uint32_t k_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)k_lds, v_base = k_base + (apart ? TILE_B : 0);
+#define LVX_FEW_DMA_K(t_)                                                                                              \
+    _Pragma("unroll") for (int e = 0; e < N_DMA; ++e) {                                                                \
+        constexpr int CPR = K_ROW_B / 16;                                                                              \
+        const int rr = (64 / CPR) * e + lane / CPR, swz = CPR == 16 ? (rr & 15) : ((rr >> 1) & 7);                     \
+        const int key = (rr & 32) | (((rr >> 2) & 3) << 3) | (((rr >> 4) & 1) << 2) | (rr & 3);                        \
+        lvx_dma16(k_src + (size_t)(t_) * TILE_B, (uint32_t)(key * K_ROW_B + ((lane % CPR) ^ swz) * 16), k_base + e * 1024); \
+    }
+#define LVX_FEW_DMA_V(t_)                                                                                              \
+    _Pragma("unroll") for (int e = 0; e < N_DMA; ++e) {                                                                \
+        const int rr = 8 * e + (lane >> 3);                                                                            \
+        lvx_dma16(v_src + (size_t)(t_) * TILE_B, (uint32_t)(rr * V_ROW_B + ((lane & 7) ^ ((rr >> 1) & 7)) * 16), v_base + e * 1024); \
+    }
+#define LVX_FEW_WAIT_DMA() asm volatile("s_waitcnt vmcnt(0)" ::: "memory")
+#define LVX_FEW_WAIT_LDS() asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory")
+    int row = row0 + l16;
+    if (row > n_q - 1) row = n_q - 1;
+    const bf16_t *qp = q + (size_t)row * ld_q + (size_t)head * D + q4 * 8;
+    bf16x8_t qf[MK];
+#pragma unroll
+    for (int m = 0; m < MK; ++m) qf[m] = *reinterpret_cast<const bf16x8_t *>(qp + 32 * m);
+    LVX_FEW_DMA_K(wave);
+    if (apart) {
+        LVX_FEW_DMA_V(wave);
+    }
+    if (QN) {
+        // RMSNorm of the query row, its gain and the logit scale, as in the kernel above; the four lanes of a row share its partial sums
+        const float4 *pp = reinterpret_cast<const float4 *>(qn.sumsq + (size_t)row * qn.ld);
+        float ss = 0.f;
+        for (int i0 = 0; 4 * i0 < qn.n_parts; i0 += 16) {
+            float4 p[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) p[i] = 4 * (i0 + 4 * i + q4) < qn.n_parts ? pp[i0 + 4 * i + q4] : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int left = qn.n_parts - 4 * (i0 + 4 * i + q4);
+                ss += ((0 < left ? p[i].x : 0.f) + (1 < left ? p[i].y : 0.f)) + ((2 < left ? p[i].z : 0.f) + (3 < left ? p[i].w : 0.f));
+            }
+        }
+        ss += __shfl_xor(ss, 16);
+        ss += __shfl_xor(ss, 32);
+        const float rinv = c_exp2 / sqrtf(ss / (float)qn.d_model + qn.eps);
+        const float *gp = qn.gain + head * D + q4 * 8;
+#pragma unroll
+        for (int m = 0; m < MK; ++m) {
+            const float4 g0 = *reinterpret_cast<const float4 *>(gp + 32 * m), g1 = *reinterpret_cast<const float4 *>(gp + 32 * m + 4);
+            const float gg[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
+            u32x4_t w = __builtin_bit_cast(u32x4_t, qf[m]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[e] = pack_bf16x2(bf16_lo(w[e]) * rinv * gg[2 * e], bf16_hi(w[e]) * rinv * gg[2 * e + 1]);
+            qf[m] = __builtin_bit_cast(bf16x8_t, w);
+        }
+    }
+
+    f32x4_t o[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db) o[db] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    float m_run = -INFINITY, l_run = 0.f;  // maximum (as an exponent of 2) of the query's scores so far, and this lane's share of their sum
+    for (int t = wave; t < n_tiles; t += n_waves) {
+        const bool more = t + n_waves < n_tiles;
+        LVX_FEW_WAIT_DMA();
+#pragma unroll
+        for (int m = 0; m < MK; ++m) asm volatile("" : "+v"(qf[m]));  // the compiler's own wait for the queries: here it costs nothing, behind the next loads it would wait for them
+        bf16x8_t kf[4][MK];
+#pragma unroll
+        for (int m = 0; m < MK; ++m)
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb)
+                kf[kb][m] = *reinterpret_cast<const bf16x8_t *>(k_lds + (kb * 16 + l16) * K_ROW_B + (((4 * m + q4) ^ (D == 128 ? l16 : (l16 >> 1) & 7)) * 16));
+        LVX_FEW_WAIT_LDS();
+        if (!apart) {
+            LVX_FEW_DMA_V(t);
+        } else if (more) {
+            LVX_FEW_DMA_K(t + n_waves);
+        }
+        f32x4_t s[4];
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) s[kb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int m = 0; m < MK; ++m)
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb) s[kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][m], qf[m], s[kb], 0, 0, 0);
+        const int left = n_keys - t * KT - 8 * q4;  // valid keys, counted from this lane group's first one
+        float m_new = m_run;
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (!PRE) s[kb][e] *= c_exp2;
+                if (32 * (kb >> 1) + 4 * (kb & 1) + e >= left) s[kb][e] = -INFINITY;
+                m_new = fmaxf(m_new, s[kb][e]);
+            }
+        m_new = fmaxf(m_new, __shfl_xor(m_new, 16));
+        m_new = fmaxf(m_new, __shfl_xor(m_new, 32));
+        const float ref = m_new == -INFINITY ? 0.f : m_new;  // (no finite score yet)
+        const float alpha = __builtin_amdgcn_exp2f(m_run - ref);
+        m_run = m_new;
+        float sum = 0.f;
+        bf16x8_t pb[2];
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float p = __builtin_amdgcn_exp2f(s[kb][e] - ref);
+                sum += p;
+                pb[kb >> 1][4 * (kb & 1) + e] = (__bf16)p;
+            }
+        l_run = l_run * alpha + sum;
+        if (t != wave) {
+#pragma unroll
+            for (int db = 0; db < DB; ++db) o[db] *= alpha;
+        }
+        if (!apart) LVX_FEW_WAIT_DMA();
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int db = 0; db < DB; ++db) {
+                const bf16x8_t vf = *reinterpret_cast<const bf16x8_t *>(v_lds + (db * 16 + l16) * V_ROW_B + (((4 * ks + q4) ^ ((l16 >> 1) & 7)) * 16));
+                o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pb[ks], o[db], 0, 0, 0);
+            }
+        LVX_FEW_WAIT_LDS();
+        if (more && apart) {
+            LVX_FEW_DMA_V(t + n_waves);
+        } else if (more) {
+            LVX_FEW_DMA_K(t + n_waves);
+        }
+    }
+#undef LVX_FEW_DMA_K
+#undef LVX_FEW_DMA_V
+#undef LVX_FEW_WAIT_DMA
+#undef LVX_FEW_WAIT_LDS
+    l_run += __shfl_xor(l_run, 16);
+    l_run += __shfl_xor(l_run, 32);
+#pragma unroll
+    for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4_t *>(k_lds + (db * 64 + lane) * 16) = o[db];  // (its own tiles are read)
+    if (q4 == 0) stat[wave * 16 + l16] = make_float2(m_run, l_run);
+    __syncthreads();
+
+    float m = -INFINITY, l = 0.f, w[LVX_ATTN_FEW_WAVES];
+#pragma unroll
+    for (int i = 0; i < LVX_ATTN_FEW_WAVES; ++i)
+        if (i < n_waves) m = fmaxf(m, stat[i * 16 + l16].x);
+#pragma unroll
+    for (int i = 0; i < LVX_ATTN_FEW_WAVES; ++i) {
+        w[i] = 0.f;
+        if (i < n_waves) {
+            const float2 st = stat[i * 16 + l16];
+            w[i] = st.y == 0.f ? 0.f : __builtin_amdgcn_exp2f(st.x - m);  // (a wave without a finite score weighs nothing)
+            l += w[i] * st.y;
+        }
+    }
+    const float inv = 1.0f / l;
+    uint32_t amax_b = 0;
+    if (row0 + l16 < n_q) {
+        bf16_t *op = out + (size_t)row * ld_out + (size_t)head * D + 4 * q4;
+        for (int db = wave; db < DB; db += n_waves) {
+            f32x4_t v = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < LVX_ATTN_FEW_WAVES; ++i)
+                if (i < n_waves) v += *reinterpret_cast<const f32x4_t *>(few_lds + i * wave_b + (db * 64 + lane) * 16) * w[i];
+            uint2 y;
+            y.x = pack_bf16x2(v[0] * inv, v[1] * inv);
+            y.y = pack_bf16x2(v[2] * inv, v[3] * inv);
+            *reinterpret_cast<uint2 *>(op + 16 * db) = y;
+            const uint32_t a0 = y.x & 0x7fffu, a1 = (y.x >> 16) & 0x7fffu, a2 = y.y & 0x7fffu, a3 = (y.y >> 16) & 0x7fffu;
+            const uint32_t b0 = a0 > a1 ? a0 : a1, b1 = a2 > a3 ? a2 : a3;
+            amax_b = amax_b > b0 ? amax_b : b0;
+            amax_b = amax_b > b1 ? amax_b : b1;
+        }
+    }
+    if (amax_slots != nullptr) {  // as above, one atomic per wave
+#pragma unroll
+        for (int s = 32; s >= 1; s >>= 1) {
+            const uint32_t o2 = (uint32_t)__shfl_xor((int)amax_b, s);
+            amax_b = amax_b > o2 ? amax_b : o2;
+        }
+        if (lane == 0 && amax_b != 0) atomicMax(amax_slots + ((widx * LVX_ATTN_FEW_WAVES + wave) & (LVX_AMAX_SLOTS - 1)), amax_b << 16);
+    }
+}
+
 // Adds up the ranges of keys: out = sum_p w_p o_p / sum_p w_p l_p with w_p = 2^(m_p - max m), in the order of the ranges.  A thread
 // owns eight channels of one query and head.  Bound by memory: the ranges' fp32 outputs are read once.
 __global__ void __launch_bounds__(256) lvx_attention_combine_kernel(lvx_attn_parts_t parts, int n_q, int D, bf16_t *__restrict__ out, int64_t ld_out,
@@ -610,6 +817,18 @@ lvx_status_t launch(const bf16_t *q, int64_t ld_q, int n_q, int H, const bf16_t 
     return LVX_OK;
 }
 
+template <int D, bool PRE, bool QN>
+lvx_status_t launch_few(const bf16_t *q, int64_t ld_q, int n_q, int H, const bf16_t *kp, const bf16_t *vtp, int cap, int n_keys, float scale, bf16_t *out,
+                        int64_t ld_out, hipStream_t stream, uint32_t *amax_slots, const lvx_attn_qnorm_t *qnorm) {
+    const int n_qtiles = (n_q + 15) / 16, total = n_qtiles * H, per_xcd = (total + 7) / 8, n_waves = lvx_attention_few_waves(n_keys);
+    lvx_attn_qnorm_t qn = {};
+    if (qnorm != nullptr) qn = *qnorm;
+    hipLaunchKernelGGL((lvx_attention_few_kernel<D, PRE, QN>), dim3(per_xcd * 8), dim3(64 * n_waves), lvx_attention_few_lds(n_waves, D), stream, q,
+                       ld_q, n_q, kp, vtp, cap, n_keys, scale * LVX_LOG2E, out, ld_out, n_qtiles, total, per_xcd, amax_slots, qn);
+    LVX_CHECK_HIP(hipGetLastError());
+    return LVX_OK;
+}
+
 }  // namespace
 
 lvx_status_t lvx_launch_attention(const bf16_t *q, int64_t ld_q, int n_q, int H, int D, const bf16_t *k_packed,
@@ -620,6 +839,9 @@ lvx_status_t lvx_launch_attention(const bf16_t *q, int64_t ld_q, int n_q, int H,
     LVX_REQUIRE(scale > 0.f, LVX_ERR_INVALID_ARG, "attention: scale must be positive");
     LVX_REQUIRE(D == 64 || D == 128, LVX_ERR_UNSUPPORTED, "head_dim %d not supported (64 or 128)", D);
     const bool two = lvx_attention_splits_keys(n_q, H, n_keys, D);
+    const bool few = lvx_attention_few(n_q, H, n_keys, D);
+#define LVX_ATTN_LAUNCH_FEW(D_, PRE_, QN_) \
+    launch_few<D_, PRE_, QN_>(q, ld_q, n_q, H, k_packed, vt_packed, cap, n_keys, scale, out, ld_out, stream, amax_slots, qnorm)
 #define LVX_ATTN_LAUNCH(D_, TP_, PRE_, QN_, KS_) \
     launch<D_, TP_, PRE_, QN_, KS_>(q, ld_q, n_q, H, k_packed, vt_packed, cap, n_keys, scale, out, ld_out, stream, amax_slots, qnorm)
     if (qnorm != nullptr) {  // the kernel normalises and scales the queries as it loads them (cross-attention of a bf16 stage)
@@ -627,7 +849,12 @@ lvx_status_t lvx_launch_attention(const bf16_t *q, int64_t ld_q, int n_q, int H,
                         qnorm->ld >= (qnorm->n_parts + 7) / 8 * 8 && qnorm->ld % 4 == 0 && qnorm->d_model == H * D,
                     LVX_ERR_INVALID_ARG,
                     "attention: query norm needs head_dim 128, partial sums and a gain");
+        if (few) return LVX_ATTN_LAUNCH_FEW(128, true, true);
         return two ? LVX_ATTN_LAUNCH(128, 1, true, true, 2) : LVX_ATTN_LAUNCH(128, 1, true, true, 1);
+    }
+    if (few) {
+        if (q_prescaled) return D == 64 ? LVX_ATTN_LAUNCH_FEW(64, true, false) : LVX_ATTN_LAUNCH_FEW(128, true, false);
+        return D == 64 ? LVX_ATTN_LAUNCH_FEW(64, false, false) : LVX_ATTN_LAUNCH_FEW(128, false, false);
     }
     if (q_prescaled && scratch != nullptr) {
         const lvx_attn_split_t sp = lvx_attention_parts(n_q, H, n_keys, D);
@@ -650,6 +877,7 @@ lvx_status_t lvx_launch_attention(const bf16_t *q, int64_t ld_q, int n_q, int H,
     if (two) return LVX_ATTN_LAUNCH(128, 1, false, false, 2);
     return n_keys >= TP2_MIN_KEYS ? LVX_ATTN_LAUNCH(128, 2, false, false, 1) : LVX_ATTN_LAUNCH(128, 1, false, false, 1);
 #undef LVX_ATTN_LAUNCH
+#undef LVX_ATTN_LAUNCH_FEW
 }
 
 static lvx_status_t chunk_attention_entry(const lvx_kvcache_t *c, int32_t layer, const void *dev_q, int64_t ld_q, int32_t n_q, float scale,

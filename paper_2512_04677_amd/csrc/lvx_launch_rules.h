@@ -346,6 +346,27 @@ static inline bool lvx_attention_splits_keys(int n_q, int H, int n_keys, int hea
     return (few_tiles ? 0.74 : 0.65) * rounds(128) < rounds(256);
 }
 
+// Whether workgroups of 16 queries whose waves each take key tiles of their own (lvx_attention_few_kernel) serve the call: where all of them are on
+// the chip at once (as many to a compute unit as its LDS holds, at most 4) and a wave has at most six tiles of head_dim 128 (twelve of 64).  Up to
+// 256 of them take 6.6 us and 0.35 (0.22 at head_dim 64) a tile: 105 x 4 heads x 280 keys 13.0 -> 9.2 us, 390 x 4 x 832 19.6 -> 12.5, 18 x 12 tiles
+// 18.2 -> 10.9; at 60 tiles 27.5 beside 27.9, at 85 36.9 beside 32.8.  Where a second round is needed each costs 4 us more: 320 x 22 tiles
+// 26.6 beside 22.0, 513 x 3 tiles 19.5 beside 16.2.  Up to 128 queries of head_dim 64 with a single tile stay (6.5 beside 6.7; above 128 8.2 -> 6.6).
+#define LVX_ATTN_FEW_WAVES 8
+// A wave's K and V^T tile stand beside each other in LDS (then both are loaded at once), or one after the other in the same place: up to 128 KB.
+constexpr bool lvx_attention_few_apart(int n_waves, int head_dim) { return n_waves * head_dim <= 512; }
+static inline int lvx_attention_few_waves(int n_keys) {
+    const int tiles = (n_keys + LVX_KEY_TILE - 1) / LVX_KEY_TILE;
+    return tiles < LVX_ATTN_FEW_WAVES ? tiles : LVX_ATTN_FEW_WAVES;
+}
+static inline size_t lvx_attention_few_lds(int n_waves, int head_dim) {
+    return (size_t)n_waves * (lvx_attention_few_apart(n_waves, head_dim) ? 2 : 1) * LVX_KEY_TILE * head_dim * 2;
+}
+static inline bool lvx_attention_few(int n_q, int H, int n_keys, int head_dim) {
+    const long workgroups = ((long)n_q + 15) / 16 * H, together = 160 * 1024 / ((long)lvx_attention_few_lds(lvx_attention_few_waves(n_keys), head_dim) + 1024);
+    if (head_dim == 64 && n_keys <= LVX_KEY_TILE && n_q <= 128) return false;
+    return workgroups <= LVX_NUM_CU * (together < 4 ? together : 4) && (int64_t)n_keys * head_dim <= 48 * LVX_KEY_TILE * 128;
+}
+
 // Into how many ranges of keys the self-attention of a block is split over workgroups (1: none), and whether a workgroup then takes 128 queries
 // with its range split once more over its halves (`halves`) instead of 256.  Few heads and queries leave compute units idle that the
 // ranges fill, but each range writes its outputs in fp32 and a second kernel reads them: about 7 us more, and the ranges' bytes at 4.1 TB/s

@@ -12,6 +12,8 @@ from test_launch_rules import CSRC
 SOURCE = r"""
 #include "lvx_launch_rules.h"
 extern "C" int parts(int n_q, int H, int n_keys, int D) { const lvx_attn_split_t s = lvx_attention_parts(n_q, H, n_keys, D); return 2 * s.parts + s.halves; }
+extern "C" int few(int n_q, int H, int n_keys, int D) { return lvx_attention_few(n_q, H, n_keys, D); }
+extern "C" double few_lds(int n_keys, int D) { return (double)lvx_attention_few_lds(lvx_attention_few_waves(n_keys), D); }
 extern "C" double scratch(int n_q, int H, int D) { return (double)lvx_attention_scratch_bytes(n_q, H, D); }
 """
 
@@ -27,7 +29,7 @@ def rules(tmp_path_factory):
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
     lib = C.CDLL(str(d / "librules.so"))
-    lib.scratch.restype = C.c_double
+    lib.scratch.restype = lib.few_lds.restype = C.c_double
     return lib
 
 
@@ -40,6 +42,24 @@ def test_gpu_shapes_take_the_ranges_they_name(rules):
     for (D, H, fh, fw, frames, window), form in parts_tests.SHAPES:
         n = fh * fw * frames
         assert split(rules, n, H, fh * fw + (window + 1) * n, D) == form, (D, H, n)
+        assert not rules.few(n, H, fh * fw + (window + 1) * n, D), (D, H, n)
+    for D, H, fh, fw, frames, window in parts_tests.FEW_SHAPES:
+        assert rules.few(fh * fw * frames, H, fh * fw + (window + 1) * fh * fw * frames, D), (D, H)
+
+
+def test_where_waves_take_key_tiles_of_their_own(rules):
+    """Where that was measured to be faster, and its LDS never more than 128 KB, nor more than a compute unit's for those that share it."""
+    for c, few in {(105, 4, 280, 128): 1, (105, 4, 40, 128): 1, (390, 4, 1300, 128): 1, (48, 2, 168, 64): 1, (256, 16, 3072, 128): 1, (250, 16, 6144, 64): 1,
+                   (48, 2, 24, 64): 0, (129, 2, 24, 64): 1, (257, 16, 400, 128): 0, (256, 16, 3073, 128): 0, (1024, 16, 64, 128): 1, (1025, 16, 64, 128): 0,
+                   (512, 16, 128, 128): 1, (513, 16, 128, 128): 0, (1170, 12, 257, 128): 0, (1170, 12, 6240, 128): 0, (4680, 40, 24960, 128): 0}.items():
+        assert rules.few(*c) == few, c
+    rng = random.Random(3)
+    for _ in range(20000):
+        n_q, H, n_keys, D = int(8000 ** rng.random()) + 1, rng.randint(1, 48), int(60000 ** rng.random()) + 1, rng.choice([64, 128])
+        lds = rules.few_lds(n_keys, D)
+        assert lds <= 128 * 1024
+        if rules.few(n_q, H, n_keys, D):
+            assert -(-(-(-n_q // 16) * H) // 256) * (lds + 1024) <= 160 * 1024
 
 
 def test_measured_choices(rules):

@@ -16,10 +16,12 @@ from test_gpu_parity import DEV, assert_close
 
 pytestmark = pytest.mark.gpu
 
-# head_dim, heads, frame_h, frame_w, chunk_frames, window with the ranges and the form; test_attention_parts_rules.py holds the rule to it
-SHAPES = [((128, 2, 10, 14, 1, 4), (4, True)),      # 13.1 tiles: ranges of 3 or 4, one of them the ragged last
-          ((128, 8, 5, 89, 1, 1), (3, True)), ((128, 8, 4, 107, 3, 2), (4, False)), ((128, 10, 19, 27, 3, 1), (3, False)),
-          ((64, 2, 10, 19, 1, 4), (4, True)), ((64, 8, 4, 107, 3, 2), (4, False))]
+# head_dim, heads, frame_h, frame_w, chunk_frames, window with the ranges and the form (ranges over workgroups), and those that workgroups of 16
+# queries with a range of keys a wave take instead; test_attention_parts_rules.py holds the rules to it
+SHAPES = [((128, 4, 15, 14, 3, 4), (4, True)),      # 52.5 tiles: ranges of 13 or 14, one of them the ragged last
+          ((128, 8, 4, 107, 3, 2), (4, False)), ((128, 10, 19, 27, 3, 1), (3, False)),
+          ((64, 4, 20, 21, 3, 4), (4, True)), ((64, 8, 4, 107, 3, 2), (4, False))]
+FEW_SHAPES = [(128, 2, 10, 14, 1, 4), (128, 8, 5, 89, 1, 1), (64, 2, 10, 19, 1, 4)]     # 13.1, 20.9 and 17.8 tiles over eight waves
 
 
 def axes(D):
@@ -28,10 +30,10 @@ def axes(D):
 
 
 @pytest.mark.parametrize("dead", [False, True])
-@pytest.mark.parametrize("shape", [s for s, _ in SHAPES])
+@pytest.mark.parametrize("shape", [s for s, _ in SHAPES] + FEW_SHAPES)
 def test_attention_over_ranges_of_keys(lvx, shape, dead):
     D, H, fh, fw, frames, window = shape
-    parts = dict(SHAPES)[shape][0]
+    parts = dict(SHAPES)[shape][0] if shape in dict(SHAPES) else 4
     d, fk, n = H * D, fh * fw, fh * fw * frames
     n_keys = fk + (window + 1) * n
     tag = "ap_%d_%d_%d" % (D, n, int(dead))
@@ -88,13 +90,14 @@ def test_attention_over_ranges_of_keys(lvx, shape, dead):
     cache.close()
 
 
-def test_fp8_block_whose_attention_is_split(lvx, monkeypatch):
+@pytest.mark.parametrize("heads,frame,chunk_frames", [(2, (10, 14), 1), (4, (15, 14), 3)])
+def test_fp8_block_whose_attention_is_split(lvx, monkeypatch, heads, frame, chunk_frames):
     """The amax of the combined output, not of a range, scales the next linear's codes (outliers in the context and the input as in the
     other FP8 block test)."""
-    monkeypatch.setitem(S.PRESETS, "parts", dict(n_heads=2, head_dim=128, frame_h=10, frame_w=14, chunk_frames=1, window=4, sink_frames=1,
+    monkeypatch.setitem(S.PRESETS, "parts", dict(n_heads=heads, head_dim=128, frame_h=frame[0], frame_w=frame[1], chunk_frames=chunk_frames, window=4, sink_frames=1,
                                                  rope_axes=(44, 42, 42), ffn=256, n_ctx=24))
     p, stage, cache, cfg, models, ws, w64, d, n, cfgx, modelsx = fp8_stage_setup(lvx, "parts", 1, "parts8")
-    for i in range(p["window"] + 2):
+    for i in range(p["window"] + (2 if heads == 2 else 0)):
         x = S.randn_bf16((n, d), S.seed_of("parts8_x", i), device=DEV)
         ctx = S.randn_bf16((p["n_ctx"], d), S.seed_of("parts8_ctx", i), device=DEV)
         mod6 = S.randn_f32((6, d), S.seed_of("parts8_mod", i), 0.2, device=DEV)
