@@ -146,7 +146,9 @@ __global__ void __launch_bounds__(512)
     }
     // no load may still be in flight when the workgroup releases its LDS
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    lvx_gemm_epilogue<FM, FN, EPI, false, true>(acc, acc, C, ldc, nullptr, 0, bias, M, N, tm * BM + wm * 64 + 4 * q4, tn * BN + wn * 64 + l16, 1.f);
+    float gt[FN];
+    lvx_gemm_gates<FN>(gt, EPI, bias, N, tn * BN + wn * 64 + l16);
+    lvx_gemm_epilogue<FM, FN, EPI, false, true>(acc, acc, C, ldc, nullptr, 0, gt, M, N, tm * BM + wm * 64 + 4 * q4, tn * BN + wn * 64 + l16, 1.f);
 #undef LVX_DMA_ISSUE
 #undef LVX_DMA_READ_A
 #undef LVX_DMA_READ_W

@@ -130,25 +130,28 @@ __device__ __forceinline__ lvx_gemm_out_t lvx_gemm_select(const lvx_gemm_args_t 
     return o;
 }
 
+// Per column block the gate (residual epilogues; 1 without one) or the bias (0) of this lane's column.
+template <int FN>
+__device__ __forceinline__ void lvx_gemm_gates(float (&gt)[FN], int epi, const float *__restrict__ gate, int N, int n0) {
+    const bool resid = epi == LVX_EPI_RESID_GATE || epi == LVX_EPI_RESID_GATE_F32, bias = epi == LVX_EPI_BIAS || epi == LVX_EPI_BIAS_SILU;
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+        const int n = n0 + j * 16 < N ? n0 + j * 16 : N - 1;
+        gt[j] = resid ? 1.f : 0.f;
+        if ((resid || bias) && gate != nullptr) gt[j] = gate[n];
+    }
+}
+
 // Epilogue.  Accumulator register e of 16 x 16 block (i,j) holds row m0 + 16i + e and column n0 + 16j of C (m0, n0 already
 // include the lane's 4*q4 / l16 offsets): for a fixed register, each group of 16 lanes writes 16 consecutive columns of one
 // row.  Rows outermost, column blocks innermost, so neighbouring 32-byte (fp32: 64-byte) runs of a cache line reach L2
 // together.  Interior tiles take the branch-free path; only tiles on the M or N edge check every element.
-// RPRE: the fp32 residual was fetched before the main loop (rres), else it is read here.  Returns the largest magnitude (bit
-// pattern without sign) among the bf16 values this lane stores, for FP8 products that feed another one.
+// RPRE: the fp32 residual was fetched before the main loop (rres), else it is read here; gt: lvx_gemm_gates.  Returns the largest
+// magnitude (bit pattern without sign) among the bf16 values this lane stores, for FP8 products that feed another one.
 template <int FM, int FN, int EPI, bool FP8, bool RPRE>
 __device__ __forceinline__ uint32_t lvx_gemm_epilogue(const f32x4_t (&acc)[FM][FN], const f32x4_t (&rres)[FM][FN], void *Cv, int64_t ldc, const void *Rv,
-                                                      int64_t ldr, const float *__restrict__ gate, int M, int N, int m0, int n0, float alpha) {
-    constexpr bool RESID = EPI == LVX_EPI_RESID_GATE || EPI == LVX_EPI_RESID_GATE_F32;
+                                                      int64_t ldr, const float (&gt)[FN], int M, int N, int m0, int n0, float alpha) {
     const bool interior = (m0 - (m0 & 12) + FM * 16 <= M) && (n0 - (n0 & 15) + FN * 16 <= N);
-    float gt[FN];  // per column block: the gate (residual epilogues) or the bias of this lane's column
-#pragma unroll
-    for (int j = 0; j < FN; ++j) {
-        const int n = n0 + j * 16 < N ? n0 + j * 16 : N - 1;
-        gt[j] = 1.f;
-        if (RESID && gate != nullptr) gt[j] = gate[n];
-        if (EPI == LVX_EPI_BIAS || EPI == LVX_EPI_BIAS_SILU) gt[j] = gate != nullptr ? gate[n] : 0.f;
-    }
     uint32_t amax_b = 0;
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
@@ -188,9 +191,9 @@ __device__ __forceinline__ uint32_t lvx_gemm_epilogue(const f32x4_t (&acc)[FM][F
 // one per epilogue as well).
 template <int FM, int FN, bool FP8, bool RPRE>
 __device__ __forceinline__ uint32_t lvx_gemm_epilogue_any(int epi, const f32x4_t (&acc)[FM][FN], const f32x4_t (&rres)[FM][FN], void *C, int64_t ldc,
-                                                          const void *R, int64_t ldr, const float *gate, int M, int N, int m0, int n0, float alpha) {
+                                                          const void *R, int64_t ldr, const float (&gt)[FN], int M, int N, int m0, int n0, float alpha) {
 #define LVX_EPI_CASE(E_) \
-    case E_: return lvx_gemm_epilogue<FM, FN, E_, FP8, RPRE>(acc, rres, C, ldc, R, ldr, gate, M, N, m0, n0, alpha);
+    case E_: return lvx_gemm_epilogue<FM, FN, E_, FP8, RPRE>(acc, rres, C, ldc, R, ldr, gt, M, N, m0, n0, alpha);
     switch (epi) {
         LVX_EPI_CASE(LVX_EPI_GELU_TANH)
         LVX_EPI_CASE(LVX_EPI_RESID_GATE)
@@ -198,7 +201,7 @@ __device__ __forceinline__ uint32_t lvx_gemm_epilogue_any(int epi, const f32x4_t
         LVX_EPI_CASE(LVX_EPI_BIAS)
         LVX_EPI_CASE(LVX_EPI_BIAS_SILU)
         LVX_EPI_CASE(LVX_EPI_STORE_F32)
-        default: return lvx_gemm_epilogue<FM, FN, LVX_EPI_STORE, FP8, RPRE>(acc, rres, C, ldc, R, ldr, gate, M, N, m0, n0, alpha);
+        default: return lvx_gemm_epilogue<FM, FN, LVX_EPI_STORE, FP8, RPRE>(acc, rres, C, ldc, R, ldr, gt, M, N, m0, n0, alpha);
     }
 #undef LVX_EPI_CASE
 }
@@ -232,6 +235,15 @@ __device__ __forceinline__ void lvx_amax_publish(uint32_t amax_b, uint32_t *slot
     if (lane == 0 && amax_b != 0) atomicMax(slots + (slot & (LVX_AMAX_SLOTS - 1)), amax_b << 16);
 }
 
+// Waits until the loads of a wave's current slab have landed: QPW of each of the `ahead` slabs requested behind it, at most MAX, may be in flight.
+template <int MAX, int QPW>
+__device__ __forceinline__ void lvx_wait_slab(int ahead) {
+    if constexpr (MAX > 0) {
+        if (ahead < MAX) return lvx_wait_slab<MAX - 1, QPW>(ahead);
+    }
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(MAX * QPW) : "memory");
+}
+
 // ---- small tiles ---------------------------------------------------------------------------------------------------------------
 // What bounds a product with few rows is how fast a compute unit can pull slabs out of L2 and HBM (about 50 bytes a nanosecond
 // with its LDS full of loads in flight, whatever the tile), so the tile is chosen to have as many compute units pull as there
@@ -242,6 +254,9 @@ __device__ __forceinline__ void lvx_amax_publish(uint32_t amax_b, uint32_t *slot
 // Measured (microseconds, weights read from HBM; before: the 128 x 256 kernel): 64 x 1920 x 6144 77 -> 16.5 (32 x 32, four
 // groups), 64 x 5760 x 1920 28 -> 10 (32 x 64, two groups), 256 x 2560 x 6912 95 -> 32 (64 x 64), 1170 x 1536 x 6144 69 -> 38
 // (64 x 128), the same shapes in FP8 40 -> 9.7, 16 -> 6.8, 50 -> 18, 38 -> 20.
+// Only slabs that exist are requested, and the residual and the gate or bias before the first of them: a short K is a chain of latencies, and
+// re-requests of the last slab (up to 5 loads for 2 slabs) and reads at its end were half a microsecond of each product of a 105-token stage
+// (the stage 255 -> 246 us); 1170 x 1536 x 6144 with the residual 33.4 -> 32.5.
 template <int BM, int BN, int WM, int WN, int NST, int KG, bool FP8, bool CONV>
 __global__ void __launch_bounds__(64 * WM * WN * KG) lvx_gemm_tile_kernel(const lvx_gemm_args_t p) {
     constexpr int NW = WM * WN, WTM = BM / WM, WTN = BN / WN, FM = WTM / 16, FN = WTN / 16;
@@ -278,10 +293,8 @@ __global__ void __launch_bounds__(64 * WM * WN * KG) lvx_gemm_tile_kernel(const 
         }
     }
     const uint32_t ring_wave = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)ring + wave * 1024);
-    const int last = n_slabs - 1;
-    auto issue = [&](int stage, int it) {  // the group's it-th slab; past the end: a harmless reload of the last slab
-        int kt = it * KG + kg;
-        kt = kt < last ? kt : last;
+    auto issue = [&](int stage, int it) {  // the group's it-th slab
+        const int kt = it * KG + kg;
         const size_t a_off = CONV ? lvx_conv_slab_offset(p.conv, kt) : (size_t)kt * 128;
 #pragma unroll
         for (int q = 0; q < QPW; ++q)
@@ -291,64 +304,87 @@ __global__ void __launch_bounds__(64 * WM * WN * KG) lvx_gemm_tile_kernel(const 
     const char *a_rd = ring + (wm * WTM + l16) * 128, *w_rd = ring + BM * 128 + (wn * WTN + l16) * 128;
     const int ch[2] = {(q4 ^ swz) * 16, ((4 + q4) ^ swz) * 16};
 
-    f32x4_t acc[FM][FN], rres[FM][FN];
+    f32x4_t acc[FM][FN];
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     const int m0 = tm * BM + wm * WTM + 4 * q4, n0 = tn * BN + wn * WTN + l16;
-    if (KG == 1 && o.epi == LVX_EPI_RESID_GATE_F32) {  // the residual's read overlaps the main loop
-        const float *R = reinterpret_cast<const float *>(p.R);
+    // what the end needs besides the product is on its way before the first slab: the blocks that this wave stores (all of its own, with K
+    // groups block kg of its wave position)
+    constexpr int SM = KG == 1 ? FM : 1, SN = KG == 1 ? FN : 1;
+    static_assert(KG == 1 || FM * FN <= KG, "a wave stores one block at most");
+    const int sm0 = KG == 1 ? m0 : m0 + kg / FN * 16, sn0 = KG == 1 ? n0 : n0 + kg % FN * 16;
+    const bool stores = KG == 1 || kg < FM * FN;
+    f32x4_t rres[SM][SN];
+    float gt[SN];
+    if (stores) {
+        lvx_gemm_gates<SN>(gt, o.epi, p.gate, N, sn0);
+        if (o.epi == LVX_EPI_RESID_GATE_F32) {
+            const float *R = reinterpret_cast<const float *>(p.R);
 #pragma unroll
-        for (int i = 0; i < FM; ++i)
+            for (int i = 0; i < SM; ++i)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int row = m0 + i * 16 + e < M ? m0 + i * 16 + e : M - 1;
+                for (int e = 0; e < 4; ++e) {
+                    const int row = sm0 + i * 16 + e < M ? sm0 + i * 16 + e : M - 1;
 #pragma unroll
-                for (int j = 0; j < FN; ++j) rres[i][j][e] = R[(size_t)row * p.ldr + (n0 + j * 16 < N ? n0 + j * 16 : N - 1)];
-            }
+                    for (int j = 0; j < SN; ++j) rres[i][j][e] = R[(size_t)row * p.ldr + (sn0 + j * 16 < N ? sn0 + j * 16 : N - 1)];
+                }
+        }
     }
+    const float scale_a = FP8 ? p.scale_a[0] : 1.f, scale_w = FP8 ? p.scale_w[0] : 1.f;
+    const int n_mine = KG == 1 ? n_slabs : (n_slabs - kg + KG - 1) / KG;  // the group's slabs
 #pragma unroll
-    for (int s = 0; s < NST - 1; ++s) issue(s, s);
-    int cur = 0, prv = NST - 1;
-    const int n_it = (n_slabs + KG - 1) / KG;
-    for (int t = 0; t < n_it; ++t) {
+    for (int s = 0; s < NST - 1; ++s)
+        if (s < n_mine) issue(s, s);
+    int cur = 0, prv = NST - 1, t = 0;
+    auto multiply = [&]() {
+        lvx_frag_t<FP8> a[FM], b[FN];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int j = 0; j < FN; ++j) lvx_frag_read(b[j], h, w_rd + cur * STAGE_B + j * 2048 + ch[h]);
+#pragma unroll
+            for (int i = 0; i < FM; ++i) lvx_frag_read(a[i], h, a_rd + cur * STAGE_B + i * 2048 + ch[h]);
+        }
+        if constexpr (FP8) {
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j) acc[i][j] = lvx_mfma_fp8(a[i].v, b[j].v, acc[i][j]);
+        } else {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int j = 0; j < FN; ++j) acc[i][j] = lvx_mfma_bf16(a[i].h[h], b[j].h[h], acc[i][j]);
+        }
+        prv = cur;
+        cur = cur + 1 == NST ? 0 : cur + 1;
+    };
+    for (; t + NST - 1 < n_mine; ++t) {
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 2) * QPW) : "memory");
         __syncthreads();
         LVX_SCHED_FENCE();
         issue(prv, t + NST - 1);
-        if (KG == 1 || t * KG + kg < n_slabs) {
-            lvx_frag_t<FP8> a[FM], b[FN];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-#pragma unroll
-                for (int j = 0; j < FN; ++j) lvx_frag_read(b[j], h, w_rd + cur * STAGE_B + j * 2048 + ch[h]);
-#pragma unroll
-                for (int i = 0; i < FM; ++i) lvx_frag_read(a[i], h, a_rd + cur * STAGE_B + i * 2048 + ch[h]);
-            }
-            if constexpr (FP8) {
-#pragma unroll
-                for (int i = 0; i < FM; ++i)
-#pragma unroll
-                    for (int j = 0; j < FN; ++j) acc[i][j] = lvx_mfma_fp8(a[i].v, b[j].v, acc[i][j]);
-            } else {
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-#pragma unroll
-                    for (int i = 0; i < FM; ++i)
-#pragma unroll
-                        for (int j = 0; j < FN; ++j) acc[i][j] = lvx_mfma_bf16(a[i].h[h], b[j].h[h], acc[i][j]);
-            }
-        }
-        prv = cur;
-        cur = cur + 1 == NST ? 0 : cur + 1;
+        multiply();
+    }
+    // the last slabs, all requested by now, in a loop of their own (in the one above its conditions cost long products 5 to 10 %); every group
+    // passes the same number of barriers
+    const int n_it = (n_slabs + KG - 1) / KG;
+    for (; t < n_it; ++t) {
+        lvx_wait_slab<NST - 2, QPW>(n_mine - 1 - t);
+        __syncthreads();
+        LVX_SCHED_FENCE();
+        if (KG == 1 || t < n_mine) multiply();
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load may still be in flight when the LDS is reused or released
 
-    const float alpha = FP8 ? p.scale_a[0] * p.scale_w[0] : 1.f;
+    const float alpha = scale_a * scale_w;
     uint32_t amax_b = 0;
     if constexpr (KG == 1) {
-        amax_b = lvx_gemm_epilogue_any<FM, FN, FP8, true>(o.epi, acc, rres, o.C, o.ldc, p.R, p.ldr, p.gate, M, N, m0, n0, alpha);
+        amax_b = lvx_gemm_epilogue_any<FM, FN, FP8, true>(o.epi, acc, rres, o.C, o.ldc, p.R, p.ldr, gt, M, N, m0, n0, alpha);
         if (o.sumsq != nullptr && n0 - l16 < N) lvx_gemm_row_sumsq<FM, FN>(acc, o.sumsq, o.ld_sumsq, (tn * BN + wn * WTN) / WTN, M, m0, l16);
     } else {
         // the groups' partial sums, added in the order of the groups; the 16 x 16 blocks of a wave position are dealt to its KG waves
@@ -360,15 +396,13 @@ __global__ void __launch_bounds__(64 * WM * WN * KG) lvx_gemm_tile_kernel(const 
 #pragma unroll
             for (int j = 0; j < FN; ++j) *reinterpret_cast<f32x4_t *>(red + ((((kg * NW + wave) * FM + i) * FN + j) * 64 + lane) * 4) = acc[i][j];
         __syncthreads();
-        for (int ij = kg; ij < PER; ij += KG) {
+        if (stores) {
             f32x4_t v[1][1];
-            v[0][0] = *reinterpret_cast<const f32x4_t *>(red + ((wave * PER + ij) * 64 + lane) * 4);
+            v[0][0] = *reinterpret_cast<const f32x4_t *>(red + ((wave * PER + kg) * 64 + lane) * 4);
 #pragma unroll
-            for (int g = 1; g < KG; ++g) v[0][0] += *reinterpret_cast<const f32x4_t *>(red + (((g * NW + wave) * PER + ij) * 64 + lane) * 4);
-            const int mb = m0 + ij / FN * 16, nb = n0 + ij % FN * 16;
-            const uint32_t a1 = lvx_gemm_epilogue_any<1, 1, FP8, false>(o.epi, v, v, o.C, o.ldc, p.R, p.ldr, p.gate, M, N, mb, nb, alpha);
-            amax_b = amax_b > a1 ? amax_b : a1;
-            if (o.sumsq != nullptr && nb - l16 < N) lvx_gemm_row_sumsq<1, 1>(v, o.sumsq, o.ld_sumsq, (nb - l16) / 16, M, mb, l16);
+            for (int g = 1; g < KG; ++g) v[0][0] += *reinterpret_cast<const f32x4_t *>(red + (((g * NW + wave) * PER + kg) * 64 + lane) * 4);
+            amax_b = lvx_gemm_epilogue_any<1, 1, FP8, true>(o.epi, v, rres, o.C, o.ldc, p.R, p.ldr, gt, M, N, sm0, sn0, alpha);
+            if (o.sumsq != nullptr && sn0 - l16 < N) lvx_gemm_row_sumsq<1, 1>(v, o.sumsq, o.ld_sumsq, (sn0 - l16) / 16, M, sm0, l16);
         }
     }
     if (FP8 && p.amax != nullptr) lvx_amax_publish(amax_b, p.amax, (int)blockIdx.x * NW * KG + wv, lane);

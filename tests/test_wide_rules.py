@@ -6,6 +6,7 @@ import subprocess
 
 import pytest
 
+import test_gpu_gemm_short as short_tests
 import test_gpu_gemm_tiles as gemm_tests
 import test_gpu_gemm_wide as wide_tests
 import test_launch_rules as base
@@ -47,6 +48,8 @@ def test_gpu_shapes_take_the_tiles_they_name(rules):
         assert choose(rules, M, N, K)[1:] == tiles, (M, N, K)
     for (M, N, K), tiles in wide_tests.FP8_SHAPES:
         assert choose(rules, M, N, K, True)[1:] == tiles, (M, N, K)
+    for (M, N, slabs), kernel in short_tests.SHAPES:
+        assert choose(rules, M, N, 64 * slabs)[:2] == (kernel, 0) and choose(rules, M, N, 128 * slabs, True)[:2] == (kernel, 0), (M, N, slabs)
     # the shapes of the small tiles stay with them, those of the large ones and the rows that they split off all go to the wide kernel
     for (M, N, K), kernel in gemm_tests.SHAPES:
         assert choose(rules, M, N, K)[:2] == (("128x256", M) if kernel in ("128x256", "128x192") else (kernel, 0)), (M, N, K)
