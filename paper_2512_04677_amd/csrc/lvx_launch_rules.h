@@ -348,8 +348,8 @@ static inline bool lvx_attention_splits_keys(int n_q, int H, int n_keys, int hea
 
 // Whether workgroups of 16 queries whose waves each take key tiles of their own (lvx_attention_few_kernel) serve the call: where all of them are on
 // the chip at once (as many to a compute unit as its LDS holds, at most 4) and a wave has at most six tiles of head_dim 128 (twelve of 64).  Up to
-// 256 of them take 6.6 us and 0.35 (0.22 at head_dim 64) a tile: 105 x 4 heads x 280 keys 13.0 -> 9.2 us, 390 x 4 x 832 19.6 -> 12.5, 18 x 12 tiles
-// 18.2 -> 10.9; at 60 tiles 27.5 beside 27.9, at 85 36.9 beside 32.8.  Where a second round is needed each costs 4 us more: 320 x 22 tiles
+// 256 of them take 6.6 us and 0.35 (0.22 at head_dim 64) a tile: 105 x 4 heads x 560 keys 14.1 -> 8.8 us, 390 x 4 x 1300 20.3 (over workgroups)
+// -> 16.2, x 72 10.3 -> 6.6, 105 x 4 x 40 with the query norm 8.7 -> 6.8; at 60 tiles 27.5 beside 27.9, at 85 36.9 beside 32.8.  Where a second round is needed each costs 4 us more: 320 x 22 tiles
 // 26.6 beside 22.0, 513 x 3 tiles 19.5 beside 16.2.  Up to 128 queries of head_dim 64 with a single tile stay (6.5 beside 6.7; above 128 8.2 -> 6.6).
 #define LVX_ATTN_FEW_WAVES 8
 // A wave's K and V^T tile stand beside each other in LDS (then both are loaded at once), or one after the other in the same place: up to 128 KB.
