@@ -309,6 +309,8 @@ typedef struct {
     int32_t ldw8_d, ldw8_ffn;          /* row strides (bytes) of the FP8 weights; 0 = dense */
 } lvx_stage_t;
 
+/* Bytes of device scratch that the calls below ask for (0: the descriptor or a size is refused).  Never less for more tokens: a workspace
+ * for the longest chunk serves a shorter one and a sink frame of no more tokens. */
 size_t lvx_workspace_bytes(const lvx_stage_t *stage /* host */, int32_t n_tokens, int32_t n_ctx);
 
 /* The cross-attention keys and values of layers [layer0, layer0 + n_layers) for one context, exactly as the blocks compute and

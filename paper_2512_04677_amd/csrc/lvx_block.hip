@@ -48,10 +48,10 @@ typedef lvx_prof_scope_t prof_scope_t;
 constexpr int CTX_GROUP = LVX_GEMM_MAX_SEGS / 2;
 
 struct ws_layout_t {
-    size_t u, big, qk32, q_sumsq, ctx_k32, ctx_kv, pack_k, pack_v, h, attn, q8, q8_ctx, q8_misc, total;  // byte offsets
+    size_t u, big, qk32, q_sumsq, ctx_k32, ctx_kv, pack_k, pack_v, h, q8, q8_ctx, q8_misc, total;  // byte offsets
     int64_t ld_q8, ld_q8c;                            // row strides (bytes) of the FP8 activation buffers
     int cap_ctx, ctx_group;
-    size_t attn_bytes;
+    size_t attn_bytes;                                // behind `total`: outputs of the self-attention's ranges of keys before they are added up
     int64_t ld_u, ld_qkv, ld_cq, ld_ffn, ld_ckv;      // padded row strides (elements) of the bf16 workspace matrices
     int64_t ld_qk32;                                  // row stride (fp32 elements) of the un-rounded q | k columns
 };
@@ -103,9 +103,6 @@ ws_layout_t ws_layout(const lvx_stage_t *s, int n_tokens, int n_ctx) {
     w.pack_k = off;  off += round256((size_t)w.ctx_group * w.cap_ctx * d * 2);
     w.pack_v = off;  off += round256((size_t)w.ctx_group * w.cap_ctx * d * 2);
     w.h = off;       off += round256((size_t)n_tokens * d * 4);  // fp32 residual stream
-    w.attn = off;    // outputs of the self-attention's ranges of keys before they are added up
-    w.attn_bytes = lvx_attention_scratch_bytes(n_tokens, s->rope.n_heads, s->rope.head_dim);
-    off += round256(w.attn_bytes);
     w.q8 = w.q8_ctx = w.q8_misc = off;
     const size_t wide_in = d > (size_t)s->d_ffn ? d : (size_t)s->d_ffn;
     w.ld_q8 = (int64_t)wide_in + 128;
@@ -116,7 +113,18 @@ ws_layout_t ws_layout(const lvx_stage_t *s, int n_tokens, int n_ctx) {
         w.q8_misc = off;  off += 1024;  // two amax slot arrays (2 x 256 bytes), activation and context scales
     }
     w.total = off;
+    w.attn_bytes = round256(lvx_attention_scratch_bytes(n_tokens, s->rope.n_heads, s->rope.head_dim));
     return w;
+}
+
+// What a call asks for whose blocks may split their self-attention: the layout and the ranges behind it, and no less than the most that a call with
+// fewer tokens asks for (longer chunks have no ranges, see lvx_attention_parts), so that a workspace of a longer chunk serves a shorter one.
+size_t ws_bytes_needed(const lvx_stage_t *s, int n_tokens, int n_ctx) {
+    const ws_layout_t w = ws_layout(s, n_tokens, n_ctx);
+    const int rows = lvx_attention_parts_rows(n_tokens, s->rope.n_heads);
+    if (rows == n_tokens || rows == 0) return w.total + w.attn_bytes;
+    const ws_layout_t r = ws_layout(s, rows, n_ctx);
+    return w.total > r.total + r.attn_bytes ? w.total : r.total + r.attn_bytes;
 }
 
 lvx_status_t check_stage(const lvx_stage_t *s, const lvx_kvcache *c, int n_tokens, int n_ctx, bool allow_sink_rows = false) {
@@ -272,7 +280,7 @@ lvx_status_t run_block(const lvx_stage_t *s, int layer, lvx_kvcache *c, float *x
             prof_scope_t ps(LVX_PROF_ATTN_SELF, st);
             // the queries were written pre-scaled by the RoPE kernel above
             LVX_TRY(lvx_launch_attention(big, ldq, n, H, D, lvx_cache_k(c, layer), lvx_cache_vt(c, layer), c->cap_keys, c->state[layer].key_count,
-                                         scale, u, ldu, st, amax_out(), true, nullptr, L.attn_bytes > 0 ? ws + L.attn : nullptr));
+                                         scale, u, ldu, st, amax_out(), true, nullptr, L.attn_bytes > 0 ? ws + L.total : nullptr));
         }
     } else {
         // the sink's un-rotated keys go into the cache's fp32 source storage: un-rounded from the projection in a bf16 stage,
@@ -383,7 +391,7 @@ lvx_status_t check_common(const lvx_stage_t *s, lvx_kvcache *c, void *x, int n, 
     LVX_REQUIRE(x != nullptr && ctx != nullptr && ws != nullptr, LVX_ERR_INVALID_ARG, "x, ctx or workspace is NULL");
     LVX_REQUIRE(lvx_aligned16(x) && lvx_aligned16(ctx) && (((uintptr_t)ws) & 255u) == 0, LVX_ERR_INVALID_ARG,
                 "x / ctx must be 16-byte and workspace 256-byte aligned");
-    const size_t need = lvx_workspace_bytes(s, n, n_ctx);
+    const size_t need = ws_bytes_needed(s, n, n_ctx);
     LVX_REQUIRE(ws_bytes >= need, LVX_ERR_SHAPE, "workspace too small: %zu bytes given, %zu needed", ws_bytes, need);
     LVX_REQUIRE(chunk_index >= 0 && t0 >= 0, LVX_ERR_INVALID_ARG, "chunk_index and t0 must be non-negative");
     return LVX_OK;
@@ -431,7 +439,7 @@ extern "C" lvx_status_t lvx_profile_read(double *ms_total, int64_t *launches) {
 
 extern "C" size_t lvx_workspace_bytes(const lvx_stage_t *stage, int32_t n_tokens, int32_t n_ctx) {
     if (check_stage(stage, nullptr, n_tokens, n_ctx) != LVX_OK) return 0;
-    return ws_layout(stage, n_tokens, n_ctx).total;
+    return ws_bytes_needed(stage, n_tokens, n_ctx);
 }
 
 extern "C" lvx_status_t lvx_context_kv(const lvx_stage_t *stage, int32_t layer0, int32_t n_layers, const void *dev_ctx, int32_t n_ctx,
@@ -525,9 +533,8 @@ extern "C" lvx_status_t lvx_sink_prefill(const lvx_stage_t *stage, lvx_kvcache_t
                 "x_sink / ctx must be 16-byte and workspace 256-byte aligned");
     LVX_REQUIRE(t_sink >= 0, LVX_ERR_INVALID_ARG, "t_sink must be non-negative");
     LVX_REQUIRE(lvx_aligned16(dev_x_out), LVX_ERR_INVALID_ARG, "x_out must be 16-byte aligned");
-    const size_t need = lvx_workspace_bytes(stage, n, n_ctx);
-    LVX_REQUIRE(ws_bytes >= need, LVX_ERR_SHAPE, "workspace too small: %zu bytes given, %zu needed", ws_bytes, need);
     const ws_layout_t L = ws_layout(stage, n, n_ctx);
+    LVX_REQUIRE(ws_bytes >= L.total, LVX_ERR_SHAPE, "workspace too small: %zu bytes given, %zu needed", ws_bytes, L.total);  // (its attention takes no ranges)
     const int d = stage->rope.n_heads * stage->rope.head_dim;
     float *h = (float *)((char *)dev_workspace + L.h);
     LVX_TRY(widen_in((const bf16_t *)dev_x_sink, h, (size_t)n * d, (hipStream_t)stream));

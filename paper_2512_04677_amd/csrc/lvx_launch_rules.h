@@ -373,14 +373,21 @@ static inline bool lvx_attention_few(int n_q, int H, int n_keys, int head_dim) {
 // both ways.  Microseconds per tile of 64 keys: 256 queries 1.30 to 1.50 the more units work (head_dim 64: 1.08), 128 queries 0.88 (0.63).
 // Measured, alone -> split: 12 heads x 1170 queries x 6240 keys 89 -> 59 (2 ranges, 128 queries), 8 x 1800 x 4200 59 -> 45, 16 x 1200 x 5400 78 -> 64
 // (3 ranges, 256 queries), 20 x 1886 x 8487 175 -> 163, 4 x 390 x 1300 26 -> 21, head_dim 64, 8 x 900 x 4800 52 -> 28; no gain: 4 x 105 x
-// 560 16 -> 17, 30 x 1800 x 6000 144 -> 168.  More than four ranges were never best.  More than 256 workgroups of 256 queries stay as they are: there
-// the ranges' bytes weigh more than a partial round.
+// 560 16 -> 17, 30 x 1800 x 6000 144 -> 168.  More than four ranges were never best.  Beyond 384 workgroups of 128 queries (256 queries where
+// that is more, and none above 256 heads) no key count makes ranges the faster form by this rule: they need as many rounds for each range then as the
+// undivided call needs for its share.  So no more rows than that take ranges, and no scratch is reserved for more.
 #define LVX_ATTN_MAX_PARTS 4
+#define LVX_ATTN_PARTS_WORKGROUPS 384
 struct lvx_attn_split_t {
     int parts;
     bool halves;
 };
-static inline int lvx_attention_most_parts(int n_q, int H) { return (long)((n_q + 255) / 256) * H <= LVX_NUM_CU ? LVX_ATTN_MAX_PARTS : 1; }
+// The most rows, n_q of them at most, whose keys may be split.
+static inline int lvx_attention_parts_rows(int n_q, int H) {
+    const int rows = H > LVX_NUM_CU ? 0 : 128 * (LVX_ATTN_PARTS_WORKGROUPS / H > 2 ? LVX_ATTN_PARTS_WORKGROUPS / H : 2);
+    return n_q < rows ? n_q : rows;
+}
+static inline int lvx_attention_most_parts(int n_q, int H) { return lvx_attention_parts_rows(n_q, H) == n_q ? LVX_ATTN_MAX_PARTS : 1; }
 static inline lvx_attn_split_t lvx_attention_parts(int n_q, int H, int n_keys, int head_dim) {
     const int most = lvx_attention_most_parts(n_q, H), tiles = (n_keys + LVX_KEY_TILE - 1) / LVX_KEY_TILE;
     auto time = [&](int parts, bool halves) {
@@ -397,7 +404,7 @@ static inline lvx_attn_split_t lvx_attention_parts(int n_q, int H, int n_keys, i
             if (time(parts, halves != 0) < best_us) best_us = time(parts, halves != 0), best = {parts, halves != 0};
     return best;
 }
-// Bytes of the ranges' outputs, references and sums.
+// Bytes of the ranges' outputs, references and sums, as many as there can be of them.
 static inline size_t lvx_attention_scratch_bytes(int n_q, int H, int head_dim) {
     const size_t most = (size_t)lvx_attention_most_parts(n_q, H);
     return most <= 1 ? 0 : most * n_q * H * ((size_t)head_dim * 4 + 8);

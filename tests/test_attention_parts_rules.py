@@ -76,3 +76,12 @@ def test_no_range_is_empty_and_the_scratch_holds_all(rules):
         parts, _ = split(rules, n_q, H, n_keys, D)
         assert 1 <= parts <= -(-n_keys // 64)
         assert parts == 1 or rules.scratch(n_q, H, D) >= parts * n_q * H * (4 * D + 8)
+
+
+def test_scratch_is_reserved_only_for_rows_that_may_take_ranges(rules):
+    """None where no key count splits; up to the longest such chunk all four ranges."""
+    for n_q, H in [(1536, 40), (2560, 24), (3072, 20), (1500, 40), (2048, 32), (4680, 40), (1537, 32), (129, 257), (49153, 1)]:
+        assert rules.scratch(n_q, H, 128) == 0
+        assert all(split(rules, n_q, H, 64 * t, D)[0] == 1 for t in range(1, 600) for D in (64, 128)), (n_q, H)
+    for n_q, H in [(1152, 40), (1536, 32), (4096, 12), (1170, 12), (256, 256), (49152, 1)]:
+        assert rules.scratch(n_q, H, 128) == 4.0 * n_q * H * (4 * 128 + 8)
