@@ -652,17 +652,17 @@ __global__ void __launch_bounds__(512) lvx_attention_few_kernel(const bf16_t *__
 #pragma unroll
             for (int kb = 0; kb < 4; ++kb) s[kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][m], qf[m], s[kb], 0, 0, 0);
         const int left = n_keys - t * KT - 8 * q4;  // valid keys, counted from this lane group's first one
-        float m_new = m_run;
+        float m_tile = -INFINITY;
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                if (!PRE) s[kb][e] *= c_exp2;
                 if (32 * (kb >> 1) + 4 * (kb & 1) + e >= left) s[kb][e] = -INFINITY;
-                m_new = fmaxf(m_new, s[kb][e]);
+                m_tile = fmaxf(m_tile, s[kb][e]);
             }
-        m_new = fmaxf(m_new, __shfl_xor(m_new, 16));
-        m_new = fmaxf(m_new, __shfl_xor(m_new, 32));
+        m_tile = fmaxf(m_tile, __shfl_xor(m_tile, 16));
+        m_tile = fmaxf(m_tile, __shfl_xor(m_tile, 32));
+        const float m_new = fmaxf(m_run, PRE ? m_tile : m_tile * c_exp2);
         const float ref = m_new == -INFINITY ? 0.f : m_new;  // (no finite score yet)
         const float alpha = __builtin_amdgcn_exp2f(m_run - ref);
         m_run = m_new;
@@ -672,7 +672,7 @@ __global__ void __launch_bounds__(512) lvx_attention_few_kernel(const bf16_t *__
         for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const float p = __builtin_amdgcn_exp2f(s[kb][e] - ref);
+                const float p = __builtin_amdgcn_exp2f(PRE ? s[kb][e] - ref : __builtin_fmaf(s[kb][e], c_exp2, -ref));  // (no scaled score of its own: one rounding)
                 sum += p;
                 pb[kb >> 1][4 * (kb & 1) + e] = (__bf16)p;
             }

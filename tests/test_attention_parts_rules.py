@@ -45,6 +45,8 @@ def test_gpu_shapes_take_the_ranges_they_name(rules):
         assert not rules.few(n, H, fh * fw + (window + 1) * n, D), (D, H, n)
     for D, H, fh, fw, frames, window in parts_tests.FEW_SHAPES:
         assert rules.few(fh * fw * frames, H, fh * fw + (window + 1) * fh * fw * frames, D), (D, H)
+    for H, D, frame, frames, window, few in parts_tests.LARGE_SCORES:
+        assert rules.few(frame * frames, H, frame + (window + 1) * frame * frames, D) == few, (H, D, frame)
 
 
 def test_where_waves_take_key_tiles_of_their_own(rules):

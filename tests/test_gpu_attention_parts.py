@@ -109,3 +109,38 @@ def test_fp8_block_whose_attention_is_split(lvx, monkeypatch, heads, frame, chun
         torch.cuda.synchronize()
         assert_fp8_close(x, ref, exact, "fp8 block step %d" % i)
     cache.close()
+
+
+# heads, head_dim, tokens a frame, frames a chunk, window: waves with tiles of their own (one and several tiles a wave, K and V^T apart and in one place), and
+# the kernel of the longer calls
+LARGE_SCORES = [(4, 128, 35, 3, 4, 1), (4, 128, 130, 3, 2, 1), (2, 128, 24, 1, 2, 1), (2, 64, 24, 2, 2, 1), (4, 64, 190, 1, 4, 1), (12, 128, 390, 3, 2, 0)]
+
+
+@pytest.mark.parametrize("H,D,frame,frames,window,few", LARGE_SCORES)
+def test_scores_far_from_zero_keep_their_differences(lvx, H, D, frame, frames, window, few):
+    """Scores of 2^22 and a small whole number each, exact in fp32, so that the scaled score, as a number of its own, is 1/8 apart from the next one
+    (a rounding there is 2.5 % of a weight, root mean square) while its difference from the reference is not."""
+    d, n = H * D, frame * frames
+    n_keys = frame + (window + 1) * n
+    g = torch.Generator().manual_seed(H * D + n)
+    k = torch.zeros((n_keys, H, D))
+    k[:, :, 0], k[:, :, 1:17] = 2048.0, torch.randint(-3, 4, (n_keys, H, 16), generator=g).float()
+    q = torch.zeros((n, H, D))
+    q[:, :, 0], q[:, :, 1:17] = 2048.0, torch.randint(-2, 3, (n, H, 16), generator=g).float()
+    k, q = (t.reshape(-1, d).to(torch.bfloat16).to(DEV) for t in (k, q))
+    v = S.randn_bf16((n_keys, d), S.seed_of("large_v", n, d), device=DEV)
+    cache = lvx.KVCache(lvx.cache_desc(1, H, D, frame, 1, frames, window, 1), DEV)
+    lvx.lvx_kvcache_set_sink(cache, 0, k[:frame], v[:frame])
+    for i in range(window + 1):
+        lvx.lvx_chunk_append_evict(cache, 0, k[frame + i * n:frame + (i + 1) * n].contiguous(), v[frame + i * n:frame + (i + 1) * n].contiguous(), i)
+    out = torch.empty((n, d), dtype=torch.bfloat16, device=DEV)
+    lvx.lvx_chunk_attention(cache, 0, q, 0.2, out)
+    torch.cuda.synchronize()
+    q64, k64, v64 = (S.to_f64(t).reshape(-1, H, D) for t in (q, k, v))
+    want = O.attention(q64, k64, v64, 0.2)
+    e = np.linalg.norm(S.to_f64(out).reshape(n, H, D) - want) / np.linalg.norm(want)
+    print("large scores %s: rel %.2e" % ((H, D, n, n_keys), e), flush=True)
+    # probabilities and outputs are rounded to bf16 once each, 2^-9 / sqrt(3) = 1.1e-3 root mean square (fewer than one key would have to decide an output
+    # for the probabilities' share to be larger), and a row sum of unrounded probabilities adds nothing
+    assert e <= 4e-3
+    cache.close()
