@@ -23,11 +23,14 @@ FP8_SHAPES = [((1, 8, 128), "64x64"), ((33, 136, 640), "32x32 k4"), ((65, 1920, 
               ((95, 5000, 1152), "32x64 k2"), ((257, 2560, 1408), "64x64"), ((600, 2560, 128), "64x128"), ((1151, 1544, 1664), "64x128"),
               ((1901, 2568, 256), "128x256"),
               ((1411, 4616, 1920), "128x256"), ((1411, 4616, 2048), "128x256")]      # 15 and 16 slabs: loads behind one matrix group, and spread
-# the same with the rows that the 128 x 256 kernel takes before the tile named here takes the rest (0: one launch)
-LARGE_SHAPES = [((1550, 5120, 1152), "64x64", 1536),   # 12 row tiles in one round, 14 rows in a small tile
-                ((1567, 5112, 1408), "64x64", 1536),   # the same with ragged columns, 31 rows
+# products that 128-row tiles alone would take as named (tile and the rows before it, 0: one launch; see lvx_gemm_plan); all their rows go to the wide kernel
+LARGE_SHAPES = [((1550, 5120, 1152), "64x64", 1536), ((1567, 5112, 1408), "64x64", 1536),
                 ((1550, 5112, 576), "128x192", 0), ((1886, 2568, 192), "128x192", 0), ((2048, 3072, 64), "128x192", 0)]
-FP8_SPLIT_SHAPES = [((1550, 5120, 1152), "64x64", 1536), ((1567, 5112, 1408), "64x64", 1536)]
+FP8_LARGE_SHAPES = [((1550, 5120, 1152), "64x64", 1536), ((1567, 5112, 1408), "64x64", 1536)]
+# products whose first rows go to the wide kernel in whole rounds and the rest, at the tile's row edges and between them, to a small tile in a second launch
+SPLIT_SHAPES = [((1665, 10536, 1088), "64x128", 1536), ((1728, 10448, 640), "64x128", 1536)]
+FP8_SPLIT_SHAPES = [((1665, 10552, 1408), "64x128", 1536), ((2181, 8136, 1280), "64x128", 2048), ((1728, 10688, 1536), "64x128", 1536)]
+SPLIT_PAIRS = [((1699, 5320, 5136, 1280), "64x128", 1536), ((2241, 3224, 4840, 512), "64x128", 2048)]
 
 
 @pytest.mark.parametrize("M,N,K", [s for s, _ in SHAPES])
@@ -114,7 +117,7 @@ def test_linear_fp8_tile_edges(lvx, M, N, K):
     assert np.abs(S.to_f64(x) - (S.to_f64(r) + S.to_f64(g) * ref)).max() <= 1e-4 * math.sqrt(K)
 
 
-@pytest.mark.parametrize("M,N,K", [s for s, _, _ in LARGE_SHAPES])
+@pytest.mark.parametrize("M,N,K", [s for s, _, _ in LARGE_SHAPES + SPLIT_SHAPES])
 def test_rows_split_over_two_launches_and_narrow_tiles(lvx, M, N, K):
     a = S.randn_bf16((M, K + 8), S.seed_of("rs_a", M, K), device=DEV)[:, :K]
     w = S.randn_bf16((N, K + 64), S.seed_of("rs_w", N, K), 1.0 / math.sqrt(K), device=DEV)[:, :K]
@@ -140,9 +143,35 @@ def test_rows_split_over_two_launches_and_narrow_tiles(lvx, M, N, K):
     assert_close(xb, S.to_f64(rb[:, :N]) + S.to_f64(g) * ref, "bf16 residual")
     assert np.abs(S.to_f64(c1) - ref).max() <= bound
     assert_close(c2, ref[:, :8], "second product")
+    # the last rows, in front of the others: a row's bits are the same wherever it stands
+    turned = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
+    lvx.lvx_linear(torch.roll(a, 200, 0), w, turned, lvx.EPI_STORE)
+    torch.cuda.synchronize()
+    assert torch.equal(torch.roll(turned, -200, 0), out[:M, :N])
 
 
-@pytest.mark.parametrize("M,N,K", [s for s, _, _ in FP8_SPLIT_SHAPES])
+@pytest.mark.parametrize("M,N1,N2,K", [s for s, _, _ in SPLIT_PAIRS])
+def test_rows_of_two_products_split_over_two_launches(lvx, M, N1, N2, K):
+    """Each product's output moves by its own row stride and element size."""
+    a = S.randn_bf16((M, K + 8), S.seed_of("sp_a", M, K), device=DEV)[:, :K]
+    w = S.randn_bf16((N1 + N2, K), S.seed_of("sp_w", N1, N2, K), 1.0 / math.sqrt(K), device=DEV)
+    ref = O.linear(S.to_f64(a), S.to_f64(w))
+    bound = 4.0 * K * 2.0 ** -24 + 1e-6
+    for dtype in (torch.float32, torch.bfloat16):
+        c1 = torch.full((M + 1, N1 + 8), 7.0, dtype=dtype, device=DEV)
+        c2 = torch.full((M + 1, N2 + 24), 7.0, dtype=torch.bfloat16, device=DEV)
+        lvx.lvx_linear_dual(a, w[:N1], w[N1:], c1[:M, :N1], c2[:M, :N2])
+        torch.cuda.synchronize()
+        if dtype == torch.float32:
+            assert np.abs(S.to_f64(c1[:M, :N1]) - ref[:, :N1]).max() <= bound
+        else:
+            assert_close(c1[:M, :N1], ref[:, :N1], "first product")
+        assert_close(c2[:M, :N2], ref[:, N1:], "second product")
+        for c, n in ((c1, N1), (c2, N2)):
+            assert bool((c[M] == 7.0).all()) and bool((c[:, n:] == 7.0).all())
+
+
+@pytest.mark.parametrize("M,N,K", [s for s, _, _ in FP8_LARGE_SHAPES + FP8_SPLIT_SHAPES])
 def test_fp8_rows_split_over_two_launches(lvx, M, N, K):
     aq, sa = lvx.lvx_fp8_quantize(S.randn_bf16((M, K), S.seed_of("r8_a", M, K), device=DEV), row_pad=16)
     wq, sw = lvx.lvx_fp8_quantize(S.randn_bf16((N, K), S.seed_of("r8_w", N, K), 1.0 / math.sqrt(K), device=DEV), row_pad=128)
@@ -158,3 +187,47 @@ def test_fp8_rows_split_over_two_launches(lvx, M, N, K):
     assert bool((out[M] == 7.0).all()) and bool((out[:, N:] == 7.0).all())
     # the FP8 products' alignment in the matrix core: see test_linear_fp8_tile_edges
     assert np.abs(S.to_f64(x) - (S.to_f64(r) + ref)).max() <= 1e-4 * math.sqrt(K)
+    g = S.randn_f32((N,), 7, 0.5, 1.0, device=DEV)
+    rb = r.to(torch.bfloat16)
+    xb = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
+    lvx.lvx_linear_fp8(aq, sa, wq, sw, xb, lvx.EPI_RESID_GATE, resid=rb, gate=g)
+    # the last rows, in front of the others: a row's bits are the same wherever it stands
+    turned = torch.empty((M, N), dtype=torch.float32, device=DEV)
+    lvx.lvx_linear_fp8(torch.roll(aq, 200, 0), sa, wq, sw, turned, lvx.EPI_RESID_GATE_F32, resid=torch.roll(r, 200, 0))
+    torch.cuda.synchronize()
+    assert_close(xb, S.to_f64(rb) + S.to_f64(g) * ref, "fp8 bf16 residual")
+    assert torch.equal(torch.roll(turned, -200, 0), x)
+
+
+# heads of 128, frame, FFN width of a block of one-frame chunks whose first FFN product has the rows of its output's largest value in the second launch
+SPLIT_BLOCK = (11, 45, 37, 10496)
+
+
+def test_largest_value_of_an_fp8_output_may_lie_behind_the_split(lvx):
+    """A block's FFN bit for bit as its public parts: the attentions add zero, so what the block adds is the FFN of its input, and the scale of the hidden
+    tensor's codes comes from the last row, whose values only the second launch sees."""
+    H, fh, fw, ffn = SPLIT_BLOCK
+    d, n = 128 * H, fh * fw
+    w = S.block_weights(d, ffn, 0, "sb", std=1.0 / math.sqrt(d), device=DEV)
+    w["W_o"], w["Wc_o"] = torch.zeros_like(w["W_o"]), torch.zeros_like(w["Wc_o"])
+    w["W_1"][:, 5] *= 8.0
+    stage = lvx.StageHandle([w], lvx.rope_desc(H, 128, (44, 42, 42), 10000.0, fh, fw), ffn, fp8=True)
+    cache = lvx.KVCache(lvx.cache_desc(1, H, 128, fh, fw, 1, 1, 1), DEV)
+    lvx.lvx_kvcache_set_sink(cache, 0, *(S.randn_bf16((n, d), S.seed_of("sb", s), device=DEV) for s in "kv"))
+    x = S.randn_bf16((n, d), S.seed_of("sb_x"), device=DEV)
+    x[n - 1, 5] = 300.0          # after the norm this row is little else than its channel 5
+    u, hidden, y = torch.empty_like(x), torch.empty((n, ffn), dtype=torch.bfloat16, device=DEV), x.float()
+    lvx.lvx_layernorm_modulate(x, None, None, 1e-6, u)
+    (uq, su), (q1, s1), (q2, s2) = (lvx.lvx_fp8_quantize(t) for t in (u, w["W_1"], w["W_2"]))
+    lvx.lvx_linear_fp8(uq, su, q1, s1, hidden, lvx.EPI_GELU_TANH)
+    hq, sh = lvx.lvx_fp8_quantize(hidden)
+    lvx.lvx_linear_fp8(hq, sh, q2, s2, y, lvx.EPI_RESID_GATE_F32, resid=y)
+    ctx = S.randn_bf16((24, d), S.seed_of("sb_ctx"), device=DEV)
+    ws = torch.empty(lvx.lvx_workspace_bytes(stage, n, 24), dtype=torch.uint8, device=DEV)
+    got = x.float()
+    lvx.lvx_dit_block_f32(stage, 0, cache, got, ctx, None, 0, 1, ws)
+    torch.cuda.synchronize()
+    top = hidden.float().abs().amax(1)
+    assert int(top.argmax()) == n - 1 and float(top[n - 1]) > 1.5 * float(top[:n - 1].max())
+    assert torch.equal(got, y)
+    cache.close()

@@ -77,7 +77,7 @@ def test_gpu_gemm_shapes_take_the_kernels_they_name(rules):
     assert {bool(rules.fp8_spreads(K // 128)) for (_, _, K), kernel in gemm_tests.FP8_SHAPES if kernel == "128x256"} == {False, True}
     for (M, N, K), kernel, m1 in gemm_tests.LARGE_SHAPES:
         assert linear_plan(rules, M, [N], K)[:2] == (kernel, m1), (M, N, K)
-    for (M, N, K), kernel, m1 in gemm_tests.FP8_SPLIT_SHAPES:
+    for (M, N, K), kernel, m1 in gemm_tests.FP8_LARGE_SHAPES:
         assert linear_plan(rules, M, [N], K, fp8=True)[:2] == (kernel, m1), (M, N, K)
     assert {k for _, k in gemm_tests.SHAPES} | {k for _, k, _ in gemm_tests.LARGE_SHAPES} == set(SMALL.values())
 

@@ -18,6 +18,13 @@ extern "C" void linear_choose(int M, int N, int n_slabs, int *tile, int *rows, i
     *tile = l.tile, *rows = l.wide_rows, *fn = l.fn, *large = l.n_large;
     *halves = l.wide_rows > 0 ? (int)lvx_wide_halves(l.wide_rows, (N + 64 * l.fn - 1) / (64 * l.fn), l.n_large) : 0;
 }
+extern "C" int pair_rows(int M, int N1, int N2, int n_slabs, int *tile) {
+    lvx_gemm_segs_t segs = {};
+    segs.n = 2, segs.order = LVX_GEMM_ORDER_FIRST, segs.s[0].N = N1, segs.s[1].N = N2;
+    const lvx_gemm_launch_t l = lvx_gemm_choose(&segs, M, N1, n_slabs);
+    *tile = l.tile;
+    return l.wide_rows;
+}
 extern "C" double wide_us(int M, int N, int fn, int n_large) { return lvx_wide_slab_us(M, (N + 64 * fn - 1) / (64 * fn), n_large, LVX_GEMM_WIDE_US[fn - 2]); }
 """
 
@@ -55,8 +62,17 @@ def test_gpu_shapes_take_the_tiles_they_name(rules):
         assert choose(rules, M, N, K)[:2] == (("128x256", M) if kernel in ("128x256", "128x192") else (kernel, 0)), (M, N, K)
     for (M, N, K), kernel, m1 in gemm_tests.LARGE_SHAPES:
         assert choose(rules, M, N, K)[1] == M, (M, N, K)
-    for (M, N, K), kernel, m1 in gemm_tests.FP8_SPLIT_SHAPES:
+    for (M, N, K), kernel, m1 in gemm_tests.FP8_LARGE_SHAPES:
         assert choose(rules, M, N, K, True)[1] == M, (M, N, K)
+    # rows that go to a small tile in a second launch
+    for shapes, fp8 in ((gemm_tests.SPLIT_SHAPES, False), (gemm_tests.FP8_SPLIT_SHAPES, True)):
+        for (M, N, K), kernel, rows in shapes:
+            assert 0 < rows < M and choose(rules, M, N, K, fp8)[:2] == (kernel, rows), (M, N, K)
+    heads, fh, fw, ffn = gemm_tests.SPLIT_BLOCK
+    assert 0 < choose(rules, fh * fw, ffn, 128 * heads, True)[1] < fh * fw
+    for (M, N1, N2, K), kernel, rows in gemm_tests.SPLIT_PAIRS:
+        tile = C.c_int()
+        assert 0 < rows < M and rules.pair_rows(M, N1, N2, K // 64, C.byref(tile)) == rows and base.SMALL[tile.value] == kernel, (M, N1, N2, K)
 
 
 def test_tiles_cover_all_rows_and_whole_tiles_never_cost_more(rules):
