@@ -148,7 +148,7 @@ __global__ void __launch_bounds__(512)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     float gt[FN];
     lvx_gemm_gates<FN>(gt, EPI, bias, N, tn * BN + wn * 64 + l16);
-    lvx_gemm_epilogue<FM, FN, EPI, false, true>(acc, acc, C, ldc, nullptr, 0, gt, M, N, tm * BM + wm * 64 + 4 * q4, tn * BN + wn * 64 + l16, 1.f);
+    lvx_gemm_epilogue<FM, FN, EPI, false>(acc, acc, C, ldc, nullptr, 0, gt, M, N, tm * BM + wm * 64 + 4 * q4, tn * BN + wn * 64 + l16, 1.f);
 #undef LVX_DMA_ISSUE
 #undef LVX_DMA_READ_A
 #undef LVX_DMA_READ_W

@@ -146,9 +146,9 @@ __device__ __forceinline__ void lvx_gemm_gates(float (&gt)[FN], int epi, const f
 // include the lane's 4*q4 / l16 offsets): for a fixed register, each group of 16 lanes writes 16 consecutive columns of one
 // row.  Rows outermost, column blocks innermost, so neighbouring 32-byte (fp32: 64-byte) runs of a cache line reach L2
 // together.  Interior tiles take the branch-free path; only tiles on the M or N edge check every element.
-// RPRE: the fp32 residual was fetched before the main loop (rres), else it is read here; gt: lvx_gemm_gates.  Returns the largest
+// rres: the fp32 residual, fetched before the main loop; gt: lvx_gemm_gates.  Returns the largest
 // magnitude (bit pattern without sign) among the bf16 values this lane stores, for FP8 products that feed another one.
-template <int FM, int FN, int EPI, bool FP8, bool RPRE>
+template <int FM, int FN, int EPI, bool FP8>
 __device__ __forceinline__ uint32_t lvx_gemm_epilogue(const f32x4_t (&acc)[FM][FN], const f32x4_t (&rres)[FM][FN], void *Cv, int64_t ldc, const void *Rv,
                                                       int64_t ldr, const float (&gt)[FN], int M, int N, int m0, int n0, float alpha) {
     const bool interior = (m0 - (m0 & 12) + FM * 16 <= M) && (n0 - (n0 & 15) + FN * 16 <= N);
@@ -162,7 +162,6 @@ __device__ __forceinline__ uint32_t lvx_gemm_epilogue(const f32x4_t (&acc)[FM][F
             bf16_t *cp = reinterpret_cast<bf16_t *>(Cv) + (size_t)m * ldc + n0;
             float *cpf = reinterpret_cast<float *>(Cv) + (size_t)m * ldc + n0;
             const bf16_t *rp = reinterpret_cast<const bf16_t *>(Rv) + (size_t)m * ldr + n0;
-            const float *rpf = reinterpret_cast<const float *>(Rv) + (size_t)m * ldr + n0;
 #pragma unroll
             for (int j = 0; j < FN; ++j) {
                 if (!interior && n0 + j * 16 >= N) continue;
@@ -173,7 +172,7 @@ __device__ __forceinline__ uint32_t lvx_gemm_epilogue(const f32x4_t (&acc)[FM][F
                 if (EPI == LVX_EPI_BIAS_SILU) v = v * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * v));
                 if (EPI == LVX_EPI_RESID_GATE) v = bf16_bits_to_f32(rp[j * 16]) + gt[j] * v;
                 if (EPI == LVX_EPI_RESID_GATE_F32)
-                    cpf[j * 16] = (RPRE ? rres[i][j][e] : rpf[j * 16]) + gt[j] * v;
+                    cpf[j * 16] = rres[i][j][e] + gt[j] * v;
                 else if (EPI == LVX_EPI_STORE_F32)
                     cpf[j * 16] = v;
                 else {
@@ -189,11 +188,11 @@ __device__ __forceinline__ uint32_t lvx_gemm_epilogue(const f32x4_t (&acc)[FM][F
 
 // The same with the epilogue chosen at run time (one uniform branch after the main loop: one kernel per tile and type instead of
 // one per epilogue as well).
-template <int FM, int FN, bool FP8, bool RPRE>
+template <int FM, int FN, bool FP8>
 __device__ __forceinline__ uint32_t lvx_gemm_epilogue_any(int epi, const f32x4_t (&acc)[FM][FN], const f32x4_t (&rres)[FM][FN], void *C, int64_t ldc,
                                                           const void *R, int64_t ldr, const float (&gt)[FN], int M, int N, int m0, int n0, float alpha) {
 #define LVX_EPI_CASE(E_) \
-    case E_: return lvx_gemm_epilogue<FM, FN, E_, FP8, RPRE>(acc, rres, C, ldc, R, ldr, gt, M, N, m0, n0, alpha);
+    case E_: return lvx_gemm_epilogue<FM, FN, E_, FP8>(acc, rres, C, ldc, R, ldr, gt, M, N, m0, n0, alpha);
     switch (epi) {
         LVX_EPI_CASE(LVX_EPI_GELU_TANH)
         LVX_EPI_CASE(LVX_EPI_RESID_GATE)
@@ -201,7 +200,7 @@ __device__ __forceinline__ uint32_t lvx_gemm_epilogue_any(int epi, const f32x4_t
         LVX_EPI_CASE(LVX_EPI_BIAS)
         LVX_EPI_CASE(LVX_EPI_BIAS_SILU)
         LVX_EPI_CASE(LVX_EPI_STORE_F32)
-        default: return lvx_gemm_epilogue<FM, FN, LVX_EPI_STORE, FP8, RPRE>(acc, rres, C, ldc, R, ldr, gt, M, N, m0, n0, alpha);
+        default: return lvx_gemm_epilogue<FM, FN, LVX_EPI_STORE, FP8>(acc, rres, C, ldc, R, ldr, gt, M, N, m0, n0, alpha);
     }
 #undef LVX_EPI_CASE
 }
@@ -384,7 +383,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KG) lvx_gemm_tile_kernel(const 
     const float alpha = scale_a * scale_w;
     uint32_t amax_b = 0;
     if constexpr (KG == 1) {
-        amax_b = lvx_gemm_epilogue_any<FM, FN, FP8, true>(o.epi, acc, rres, o.C, o.ldc, p.R, p.ldr, gt, M, N, m0, n0, alpha);
+        amax_b = lvx_gemm_epilogue_any<FM, FN, FP8>(o.epi, acc, rres, o.C, o.ldc, p.R, p.ldr, gt, M, N, m0, n0, alpha);
         if (o.sumsq != nullptr && n0 - l16 < N) lvx_gemm_row_sumsq<FM, FN>(acc, o.sumsq, o.ld_sumsq, (tn * BN + wn * WTN) / WTN, M, m0, l16);
     } else {
         // the groups' partial sums, added in the order of the groups; the 16 x 16 blocks of a wave position are dealt to its KG waves
@@ -401,7 +400,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KG) lvx_gemm_tile_kernel(const 
             v[0][0] = *reinterpret_cast<const f32x4_t *>(red + ((wave * PER + kg) * 64 + lane) * 4);
 #pragma unroll
             for (int g = 1; g < KG; ++g) v[0][0] += *reinterpret_cast<const f32x4_t *>(red + (((g * NW + wave) * PER + kg) * 64 + lane) * 4);
-            amax_b = lvx_gemm_epilogue_any<1, 1, FP8, true>(o.epi, v, rres, o.C, o.ldc, p.R, p.ldr, gt, M, N, sm0, sn0, alpha);
+            amax_b = lvx_gemm_epilogue_any<1, 1, FP8>(o.epi, v, rres, o.C, o.ldc, p.R, p.ldr, gt, M, N, sm0, sn0, alpha);
             if (o.sumsq != nullptr && sn0 - l16 < N) lvx_gemm_row_sumsq<1, 1>(v, o.sumsq, o.ld_sumsq, (sn0 - l16) / 16, M, sm0, l16);
         }
     }

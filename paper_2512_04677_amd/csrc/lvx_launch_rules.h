@@ -148,10 +148,6 @@ static inline lvx_gemm_plan_t lvx_gemm_plan(const lvx_gemm_segs_t *segs, int M, 
     return p;
 }
 
-// FP8 products of 128 x 256 tiles whose slab loads paid to be spread over the matrix groups of a kernel that lvx_gemm_wide.h has replaced: its
-// phases spread them at every length.  No launch asks for it; the tests of the tile edges still name products on both sides of the line.
-static inline bool lvx_fp8_spreads_loads(int n_slabs) { return n_slabs >= 16; }
-
 // ---- 256 x 256 tiles (lvx_gemm_wide.h) -------------------------------------------------------------------------------------------
 // The wide kernel's tiles have 256 rows, or as halves 128: M rows are lvx_wide_full_rows row tiles of 256 and, if at most 128 rows remain, one of 128;
 // the first n_large of the 256-row tiles are taken whole, the others as two halves.

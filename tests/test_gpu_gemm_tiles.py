@@ -12,7 +12,8 @@ from test_gpu_parity import DEV, assert_close
 
 pytestmark = pytest.mark.gpu
 
-# M x N x K with the tile the launcher's rule picks for it (rows x columns, k: K groups); test_launch_rules.py holds the rule to it
+# M x N x K with the tile the launcher's rule picks for it (rows x columns, k: K groups; 128x192 and 128x256: the wide kernel, whole tiles or halves);
+# test_launch_rules.py and test_wide_rules.py hold the rule to it
 SHAPES = [((31, 24, 192), "32x32 k4"), ((33, 136, 320), "32x32 k4"), ((65, 1920, 448), "32x32 k4"),
           ((64, 5760, 128), "32x64 k2"), ((63, 7000, 320), "32x64 k2"), ((95, 5000, 1088), "32x64 k2"),
           ((1, 8, 64), "64x64"), ((64, 2560, 64), "64x64"), ((250, 2568, 192), "64x64"), ((257, 2560, 704), "64x64"),
@@ -22,7 +23,7 @@ SHAPES = [((31, 24, 192), "32x32 k4"), ((33, 136, 320), "32x32 k4"), ((65, 1920,
 FP8_SHAPES = [((1, 8, 128), "64x64"), ((33, 136, 640), "32x32 k4"), ((65, 1920, 896), "32x32 k4"), ((64, 5760, 256), "32x64 k2"),
               ((95, 5000, 1152), "32x64 k2"), ((257, 2560, 1408), "64x64"), ((600, 2560, 128), "64x128"), ((1151, 1544, 1664), "64x128"),
               ((1901, 2568, 256), "128x256"),
-              ((1411, 4616, 1920), "128x256"), ((1411, 4616, 2048), "128x256")]      # 15 and 16 slabs: loads behind one matrix group, and spread
+              ((1411, 4616, 1920), "128x256"), ((1411, 4616, 2048), "128x256")]
 # products that 128-row tiles alone would take as named (tile and the rows before it, 0: one launch; see lvx_gemm_plan); all their rows go to the wide kernel
 LARGE_SHAPES = [((1550, 5120, 1152), "64x64", 1536), ((1567, 5112, 1408), "64x64", 1536),
                 ((1550, 5112, 576), "128x192", 0), ((1886, 2568, 192), "128x192", 0), ((2048, 3072, 64), "128x192", 0)]

@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 SHAPES = [((1, 7, 9, 1), 8), ((3, 5, 11, 1), 24),
           ((5, 9, 11, 2), 40),                        # 16-column sums of K groups
           ((3, 29, 31, 3), 12), ((5, 33, 25, 2), 20), ((9, 31, 31, 1), 36),    # 32-column sums of 64 x 128 tiles, ragged vectors
-          ((5, 43, 39, 2), 10), ((9, 31, 31, 2), 18)]                          # 64-column sums of 128 x 256 tiles, the last one half empty
+          ((5, 43, 39, 2), 10), ((9, 31, 31, 2), 18)]                          # 64-column sums of 256-column tiles, the last one half empty
 
 
 @pytest.mark.parametrize("shape", [s for s, _ in SHAPES])

@@ -31,7 +31,6 @@ void conv_plan(int W, int N, int n_slabs, int M, int max_m, int *kind, int *tile
     *kind = p.kind, *tile = p.tile;
 }
 int sumsq_parts(int M, int N, int n_slabs) { return N / lvx_gemm_part_cols(lvx_gemm_pick_tile(nullptr, M, N, n_slabs)); }
-int fp8_spreads(int n_slabs) { return lvx_fp8_spreads_loads(n_slabs); }
 int splits_keys(int n_q, int H, int n_keys, int head_dim) { return lvx_attention_splits_keys(n_q, H, n_keys, head_dim); }
 }
 """
@@ -74,7 +73,6 @@ def test_gpu_gemm_shapes_take_the_kernels_they_name(rules):
         assert linear_plan(rules, M, [N], K)[:2] == (kernel, 0), (M, N, K)
     for (M, N, K), kernel in gemm_tests.FP8_SHAPES:
         assert linear_plan(rules, M, [N], K, fp8=True)[:2] == (kernel, 0), (M, N, K)
-    assert {bool(rules.fp8_spreads(K // 128)) for (_, _, K), kernel in gemm_tests.FP8_SHAPES if kernel == "128x256"} == {False, True}
     for (M, N, K), kernel, m1 in gemm_tests.LARGE_SHAPES:
         assert linear_plan(rules, M, [N], K)[:2] == (kernel, m1), (M, N, K)
     for (M, N, K), kernel, m1 in gemm_tests.FP8_LARGE_SHAPES:
