@@ -256,21 +256,21 @@ def main():
         "value": round(frames_per_s, 4), "unit": "latent frames/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": round(ms_per_step, 3), "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "fp8 e4m3 linears (per-tensor dynamic scaling), bf16 attention" if args.fp8 else "bf16", "data": "synthetic",
-        "config": {"workload": "configs[4]: one denoise stage on one GPU, %d DiT blocks (hidden 5120, 40 heads x 128, FFN 13824, "
+        "config": {"workload": "one denoise stage on one GPU, %d DiT blocks (hidden 5120, 40 heads x 128, FFN 13824, "
                                "544 context tokens), chunk 3x1560=4680 tokens, rolling cache full: sink 1560 + 4 past chunks + self "
-                               "= 24960 keys per layer (the attention inside is configs[1])" % L,
+                               "= 24960 keys per layer" % L,
                    "n_layers": L, "chunk_tokens": n, "keys": n_k, "ms_per_chunk": round(ms_per_step, 3),
                    "ms_per_chunk_median": round(step_ms[len(step_ms) // 2], 3), "ms_per_chunk_min": round(step_ms[0], 3),
                    "ms_per_chunk_max": round(step_ms[-1], 3),
                    "stage_tflops": round(stage_fl / (seconds / args.steps) / 1e12, 2),
                    "stage_frac_of_bf16_peak": round(stage_fl / (seconds / args.steps) / 1e12 / PEAK_BF16_TFLOPS, 4)},
-        "roofline": {"kernel": "lvx_attention_kernel<128,2,true,false,1> (chunk-to-cache self-attention, configs[1] shape)", "bound": "mfma",
+        "roofline": {"kernel": "lvx_attention_kernel<128,2,true,false,1,false> (chunk-to-cache self-attention, 40 heads x 128, %d queries x %d keys)" % (n, n_k), "bound": "mfma",
                      "achieved": round(attn_tflops, 2), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(attn_tflops / PEAK_BF16_TFLOPS, 4), "traffic": ATTN_TRAFFIC_BYTES,
                      "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE); algorithmic: %d" % (2 * d * (2 * n + 2 * n_k)),
                      "flops_per_launch": attn_fl, "avg_launch_ms": round(attn_avg_ms, 4), "launches": attn_n,
                      "peak_note": "published dense bf16 MFMA peak (2.4 GHz). The chip is power-limited: under this kernel it clocks at about "
-                                  "2.0 GHz (see `clocks`), and a register-only MFMA loop on random operands sustains 1800 TFLOP/s (0.72 of "
+                                  "1.9 GHz (see `clocks`), and a register-only MFMA loop on random operands sustains 1800 TFLOP/s (0.72 of "
                                   "this peak), which is the ceiling a bf16 kernel faces here"},
     }
     out["clocks"] = clocks

@@ -189,8 +189,9 @@ lvx_status_t lvx_kvcache_gather_sink_source(const lvx_kvcache_t *cache, int32_t 
  * Chunk-to-cache attention (Eq. 1; Appendix C attention paragraph: current tokens against the concatenation
  * of cached K/V and themselves):  O[n,h,:] = softmax_m(scale * <q[n,h,:], K[m,h,:]>) V[m,h,:] over the visible
  * prefix of `layer` (every key visible, no mask).  q, out: [n_q][ld] bf16.  bf16 MFMA, fp32 online softmax.
- * The same call gives the same bits.  Where n_q and the heads are few, the keys are summed in two halves, so the last bits of a query's
- * output may differ between calls that split the queries or heads differently.
+ * The same call gives the same bits.  Where n_q and the heads are few, the keys are summed in two halves or in up to eight parts, so the
+ * last bits of a query's output may differ between calls that split the queries or heads differently (and between these calls and the
+ * block's own attention, which may also sum up to four ranges).
  * Errors: STATE if the layer has no visible keys yet.
  * ------------------------------------------------------------------------------------------------ */
 lvx_status_t lvx_chunk_attention(const lvx_kvcache_t *cache, int32_t layer, const void *dev_q, int64_t ld_q,
@@ -241,7 +242,7 @@ lvx_status_t lvx_linear_dual(const void *dev_a, int64_t lda, const void *dev_w1,
  *     (once) and activations (every call) alike.
  *   lvx_linear_fp8: C[M][N] = epilogue(scale_a * scale_w * (Aq[M][K] . Wq[N][K]^T)), fp32 accumulate on the FP8 matrix
  *     cores, C / R / gate and the epilogues as in lvx_linear.  K % 128 == 0, N % 8 == 0, lda and ldw in bytes, % 16 == 0.
- *     The order of summation depends on M, N and K as there, and for rows that go to a second launch on their place in M. */
+ *     The order of summation depends on M, N and K as there. */
 lvx_status_t lvx_fp8_quantize(const void *dev_x, int64_t ld, int32_t rows, int32_t cols, void *dev_q, int64_t ldq,
                               void *dev_scratch256, float *dev_scale, lvx_stream_t stream);
 lvx_status_t lvx_linear_fp8(const void *dev_aq, int64_t lda, const float *dev_scale_a, const void *dev_wq, int64_t ldw,
@@ -317,9 +318,9 @@ size_t lvx_workspace_bytes(const lvx_stage_t *stage /* host */, int32_t n_tokens
  * read them (the conditions C_i of Alg. 3 / Alg. 4 are one set per forward, so a stage prepares them for a group of layers in
  * one GEMM launch): K = RMSNorm(ctx Wc_k^T) * gc_k, V = ctx Wc_v^T, read back token-major as [n_layers][n_ctx][ld] bf16 each.
  * Exported for parity checks of that path; the blocks keep these tensors in the attention kernel's packed layout inside the
- * workspace.  n_layers is at most the stage's own group size (at most 8; the group is sized so that its tiles fill whole rounds
- * of the chip: 5 layers for 544 context rows at d_model 5120) -- LVX_ERR_SHAPE otherwise; bf16 stages only;
- * workspace >= lvx_workspace_bytes(stage, 1, n_ctx). */
+ * workspace.  n_layers is at most the stage's own group size (at most 8; the group is sized so that its 128 x 256 pieces fill whole
+ * rounds of the chip: 5 layers for 544 context rows at d_model 5120) -- LVX_ERR_SHAPE otherwise; bf16 stages only;
+ * a workspace of lvx_workspace_bytes(stage, 1, n_ctx) suffices. */
 lvx_status_t lvx_context_kv(const lvx_stage_t *stage /* host */, int32_t layer0, int32_t n_layers, const void *dev_ctx, int32_t n_ctx,
                             void *dev_k_out, void *dev_v_out, int64_t ld, void *dev_workspace, size_t ws_bytes, lvx_stream_t stream);
 

@@ -62,9 +62,11 @@ constexpr int WS_PAD = 64;
 
 size_t round256(size_t b) { return (b + 255) / 256 * 256; }
 
-// Layers per context-projection launch: the group size (at most CTX_GROUP) whose 128 x 256 tiles fill whole rounds of the
-// chip's 256 compute units best, i.e. the fewest rounds per layer (544 context rows, d_model 5120: 5 layers = 1000 tiles = 3.9
-// rounds, where 8 layers = 1600 tiles would need 7 rounds for 6.25 rounds of work).
+// Layers per context-projection launch: the group size (at most CTX_GROUP) whose 128 x 256 units fill whole rounds of the
+// chip's 256 compute units best, i.e. the fewest rounds per layer.  The launch itself takes whole 256-row tiles as well (lvx_gemm_choose), by
+// which other groups can be a little better, but the size is also what lvx_context_kv accepts and what the workspace is laid out for, and it costs
+// little: 544 rows, d_model 5120, microseconds a layer in groups of 1 to 8: 71 54 61 61 57 57 60 58 (5 taken); 257 x 1536: 12.3 6.3 5.1 4.9 4.5 4.5 4.3
+// 4.1 (7); 77 x 2560: 11.8 7.6 5.5 5.0 4.4 4.2 4.2 4.1 (8); 300 x 3072: 22.3 17.6 16.1 14.2 13.5 13.0 15.1 14.9 (7).
 int ctx_group_size(int n_layers, int n_ctx, size_t d) {
     const int max_g = n_layers < CTX_GROUP ? n_layers : CTX_GROUP;
     const long tiles_per_layer = (long)((n_ctx + 127) / 128) * 2 * (long)((d + 255) / 256);

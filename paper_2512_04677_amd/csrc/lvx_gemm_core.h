@@ -1,5 +1,5 @@
-// Pieces shared by the GEMM kernels (bf16 and FP8 operands): kernel arguments, epilogue, and the kernel for products whose
-// 128 x 256 tiles would leave most of the chip idle.
+// Pieces shared by the GEMM kernels (bf16 and FP8 operands): kernel arguments, epilogue, and the kernel for products that the tiles of
+// lvx_gemm_wide.h would leave most of the chip idle with.
 //
 // A 128-byte piece of a row (64 bf16 or 128 FP8 elements of the contraction) is the unit of everything here: a K slab is one
 // such piece of every row of the A and W tiles, an LDS row holds one, a direct-to-LDS wave instruction moves eight.  A lane of
@@ -250,7 +250,7 @@ __device__ __forceinline__ void lvx_wait_slab(int ahead) {
 // on different slabs of the same tile (slab t belongs to group t % KG, each group has a ring of its own; the accumulators meet in LDS at
 // the end, in a fixed order), which is how a 32 x 32 tile still has four slabs' loads and four MFMA chains going at once.
 // Per slab and group: wait for its slab, one barrier, issue the load NST - 1 slabs ahead into the stage just released, multiply.
-// Measured (microseconds, weights read from HBM; before: the 128 x 256 kernel): 64 x 1920 x 6144 77 -> 16.5 (32 x 32, four
+// Measured (microseconds, weights read from HBM; before: a kernel of 128 x 256 tiles): 64 x 1920 x 6144 77 -> 16.5 (32 x 32, four
 // groups), 64 x 5760 x 1920 28 -> 10 (32 x 64, two groups), 256 x 2560 x 6912 95 -> 32 (64 x 64), 1170 x 1536 x 6144 69 -> 38
 // (64 x 128), the same shapes in FP8 40 -> 9.7, 16 -> 6.8, 50 -> 18, 38 -> 20.
 // Only slabs that exist are requested, and the residual and the gate or bias before the first of them: a short K is a chain of latencies, and

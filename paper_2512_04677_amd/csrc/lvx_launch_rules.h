@@ -43,8 +43,11 @@ struct lvx_gemm_segs_t {
     X_(1, 64, 64, 2, 4, 4, 1, 16, 0.31f)  \
     X_(2, 32, 64, 1, 4, 5, 2, 16, 0.235f) \
     X_(3, 32, 32, 1, 2, 4, 4, 16, 0.16f)
-#define LVX_GEMM_SLAB_US_128X256 0.80f  // 128 x 256 tiles, per slab and compute unit
-#define LVX_GEMM_SLAB_US_128X192 0.66f  // 128 x 192 tiles (halves of 192 columns on the wide kernel): 1886 x 2560 x 6912 80 -> 66 us, 2048 x 3072 x 3072 44 -> 40.5
+// 128 x 256 and 128 x 192 tiles, per slab and compute unit, measured on kernels of such tiles.  lvx_gemm_wide_kernel has replaced those; it works such tiles
+// as halves of its own in the same time or less (LVX_GEMM_WIDE_US).  The rules down to lvx_gemm_plan still compare the small tiles with them, which
+// says where a product is small and in how many K groups it is summed; lvx_gemm_choose then puts what falls to them on the wide kernel.
+#define LVX_GEMM_SLAB_US_128X256 0.80f
+#define LVX_GEMM_SLAB_US_128X192 0.66f
 enum { LVX_GEMM_TILE_128X256 = -1, LVX_GEMM_TILE_128X192 = -2 };
 
 // Column tiles of width bn of the product(s).
@@ -98,15 +101,14 @@ static inline int lvx_gemm_pick_tile(const lvx_gemm_segs_t *segs, int M, int N, 
     return best;
 }
 
-// Rows of a product that the 128 x 256 kernel takes in whole rounds of the chip, the rest (*rest_tile) going to a small tile in a second
-// launch; 0: all rows in one launch.  A product of 260 large tiles on 256 compute units takes two rounds, the second nearly empty:
-// 1560 x 5120 x 13824 as 1536 rows in one round and 24 rows in 64 x 64 tiles 306 -> 234 microseconds, x 5120 x 5120 124 -> 91.  Chosen where the sum of both, and a
-// launch's LVX_GEMM_LAUNCH_US, is less than best_us, the time of the single launch.  Only tiles without K groups: in bf16 these sum in
-// the order of the large kernel, so a row's bits are those of the single launch (in FP8 the small tiles' matrix instruction takes 128
-// products at once, the large kernel's 64, so the rows behind the split may differ in their last bits).  Partial sums of squares need one
+// Rows of a product that fill whole rounds of the chip as 128 x 256 tiles, the rest (*rest_tile) going to a small tile in a second launch; 0: all
+// rows in one launch.  A product of 260 such tiles on 256 compute units takes two rounds, the second nearly empty.  Chosen where the sum of both, and a
+// launch's LVX_GEMM_LAUNCH_US, is less than best_us, the time of the single launch.  Only tiles without K groups: these sum in the order of the
+// wide kernel and with its matrix instructions, in bf16 and in FP8, so a row's bits are the same on either side of the split.  Partial sums of squares need one
 // column grouping for all rows, so such a product is not split.  Nor is one of more than LVX_GEMM_SPLIT_ROUNDS whole rounds: compute units drift apart from round to
-// round, so that the last, partial one begins before the one before it has ended (one whole round 0.77 to 0.89 of the single launch's
-// time, four 0.91 to 1.01, five 0.93 to 1.00, six to ten 0.98 to 1.10; 1.10: 4163 x 11984 x 1472, 156 us in one launch).
+// round, so that the last, partial one begins before the one before it has ended (one whole round 0.77 to 0.89 of the single launch's time on a kernel of 128 x 256
+// tiles, four 0.91 to 1.01, five 0.93 to 1.00, six to ten 0.98 to 1.10).  The wide kernel's halves make a last round cheaper, so most of these products now
+// run whole on it (1560 x 5120 x 13824 306 us in 128 x 256 tiles, 234 split, 190 now); see lvx_gemm_choose.
 #define LVX_GEMM_LAUNCH_US 3.0
 #define LVX_GEMM_SPLIT_ROUNDS 5
 static inline int lvx_gemm_split_rows(const lvx_gemm_segs_t *segs, int M, int N, int n_slabs, double best_us, int *rest_tile) {
@@ -134,7 +136,7 @@ static inline int lvx_gemm_part_cols(int tile) {
     return 64;
 }
 
-// A product's launch: the tile, and the rows m1 that the 128 x 256 kernel takes before it (0: the tile takes all rows).
+// What the rules above make of a product: the tile, and the rows m1 in whole rounds of 128 x 256 tiles before it (0: the tile takes all rows).
 struct lvx_gemm_plan_t {
     int tile, m1;
     double us;  // the single launch's time by the rule above
@@ -259,7 +261,7 @@ static inline lvx_gemm_launch_t lvx_gemm_choose(const lvx_gemm_segs_t *segs, int
     X_(3, 192, 128, 4, 2, 2, 2.00)
 
 // The kernel of a step of M output pixels (rows of W) and N channels, n_slabs 64-wide slabs of the contraction, is the
-// one with the least rounds of the chip times slabs (or stages of three) times time of each: the 256 x 128 tiles of the linears' kernel
+// one with the least rounds of the chip times slabs (or stages of three) times time of each: lvx_conv_large_kernel's 256 x 128 tiles
 // where they fill the chip (C_out is 128 ... 512 in the decoder this serves; 128-wide column tiles waste nothing there), the tiles with shared
 // input rows below that and where their rounds come out better, the 32 x 32 tile with four K groups for a few thousand outputs.  A pixel's
 // bits must not depend on how many frames arrive with it: the first two kinds sum in one order, the K groups in another, so whether
