@@ -232,7 +232,10 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     // i-1) ended at the barrier before iteration i, and waits for it before the barrier that ends iteration i; stage i is first read by
     // group 0 in X(i), right after that barrier.  Issued ahead of group 0's matrix phase instead, where each of the eight loads of a wave holds up
     // the MFMAs behind it, the loads had half an iteration more to land and cost more than that gave: 40 heads x 4680 x 24960 1.77 -> 1.64 ms
-    // (1.46 PFLOP/s), x 6240 454 -> 436 us, 12 x 1170 x 6240 82 -> 77.
+    // (1.46 PFLOP/s), x 6240 454 -> 436 us, 12 x 1170 x 6240 82 -> 77.  Not with head_dim 64, halves of the keys and a factor per score: there the vector
+    // phase is the longer one, and group 0 keeps its loads ahead of its matrix phase (two tiles' slots are free from the iteration's start):
+    // 12 geometries 1 to 2.5 % faster than with the loads behind the barrier, 6 heads x 1092 x 5824 66 us for 67.4.
+    constexpr bool EARLY_DMA = D == 64 && KS == 2 && !PRE;
 
     // o[db][qb][e] = O^T[d = 16 db + 4 q4 + e][query 16 qb + l16];  s[kb][qb][e] = score of key row 4 q4 + e of block kb
     f32x4_t o[DB][QB];
@@ -419,9 +422,10 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
         }
         __syncthreads();
         for (int i = 1; i < n_ph; ++i) {
+            if (EARLY_DMA) LVX_ATTN_STAGE_DMA(i);
             LVX_ATTN_X(i - 1);
             __syncthreads();
-            LVX_ATTN_STAGE_DMA(i);
+            if (!EARLY_DMA) LVX_ATTN_STAGE_DMA(i);
             LVX_ATTN_Y(i);
             LVX_ATTN_WAIT_DMA(0);  // stage i landed
             __syncthreads();
