@@ -118,6 +118,22 @@ def test_linear_fp8_tile_edges(lvx, M, N, K):
     assert np.abs(S.to_f64(x) - (S.to_f64(r) + S.to_f64(g) * ref)).max() <= 1e-4 * math.sqrt(K)
 
 
+@pytest.mark.parametrize("M,N,K", [s for s, k in SHAPES if k in ("32x32 k4", "64x64", "64x128")])
+def test_bf16_residual_in_place_at_tile_edges(lvx, M, N, K):
+    """Small tiles read the bf16 residual of several blocks before they store the first: rows and columns past the edge, output in its place."""
+    a = S.randn_bf16((M, K), S.seed_of("ri_a", M, K), device=DEV)
+    w = S.randn_bf16((N, K), S.seed_of("ri_w", N, K), 1.0 / math.sqrt(K), device=DEV)
+    g = S.randn_f32((N,), 7, 0.5, 1.0, device=DEV)
+    x = S.randn_f32((M + 1, N + 8), S.seed_of("ri_r", M, N), device=DEV).to(torch.bfloat16)
+    r = x.clone()
+    lvx.lvx_linear(a, w, x[:M, :N], lvx.EPI_RESID_GATE, resid=x[:M, :N], gate=g)
+    torch.cuda.synchronize()
+    ref = S.to_f64(r[:M, :N]) + S.to_f64(g) * O.linear(S.to_f64(a), S.to_f64(w))
+    # one rounding to bf16 (half a unit in the last place) of an fp32 sum of K products of size 1 / sqrt(K), times a gate of about 1
+    assert (np.abs(S.to_f64(x[:M, :N]) - ref) <= 2.0 ** -8 * np.abs(ref) + 4.0 * (4.0 * K * 2.0 ** -24 + 1e-6)).all()
+    assert torch.equal(x[M], r[M]) and torch.equal(x[:, N:], r[:, N:])
+
+
 @pytest.mark.parametrize("M,N,K", [s for s, _, _ in LARGE_SHAPES + SPLIT_SHAPES])
 def test_rows_split_over_two_launches_and_narrow_tiles(lvx, M, N, K):
     a = S.randn_bf16((M, K + 8), S.seed_of("rs_a", M, K), device=DEV)[:, :K]
