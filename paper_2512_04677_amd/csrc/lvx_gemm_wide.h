@@ -21,6 +21,11 @@
 
 constexpr int LVX_WIDE_HALF_B = 128 * 128;  // bytes of 128 rows of a slab
 
+template <bool V>
+struct lvx_bool_t {
+    static constexpr bool value = V;
+};
+
 // Workgroup -> tile.  n_large 256 x 256 tiles, the first of the walk (bands of group_m row tiles, column-major inside a band), are taken
 // whole; the rest of them in halves of 128 rows, after these the last 128 rows at most that no 256-row tile covers.  Workgroup ids are
 // dealt to the XCDs round-robin by hardware; each XCD gets a contiguous range of either kind, whole tiles first.  Where they do not divide by
@@ -58,10 +63,10 @@ __device__ __forceinline__ bool lvx_wide_tile_of(const lvx_wide_grid_t &g, bool 
 
 // Column of a wave's 16 * FN that row r of its rows of the W tile stands for: a lane's accumulators of two neighbouring 16-column blocks are then
 // eight consecutive columns, so outputs and residuals move in 16-byte pieces, four lanes to a 64-byte (fp32: 128-byte) run.  (Three
-// blocks: the last one stands alone, four columns a lane.)
+// blocks: the last one stands alone, four columns a lane.)  Plain fp32 outputs (`by_col`) keep their order: see lvx_gemm_wide_kernel.
 template <int FN>
-__device__ __forceinline__ int lvx_wide_col(int r) {
-    if (FN % 2 == 1 && r >= 16 * (FN - 1)) return r;
+__device__ __forceinline__ int lvx_wide_col(int r, bool by_col) {
+    if (by_col || (FN % 2 == 1 && r >= 16 * (FN - 1))) return r;
     return (r >> 5) * 32 + ((r >> 2) & 3) * 8 + ((r >> 4) & 1) * 4 + (r & 3);
 }
 
@@ -71,7 +76,7 @@ __device__ __forceinline__ int lvx_wide_col(int r) {
 template <int EPI, bool FP8, int FN>
 __device__ __forceinline__ uint32_t lvx_wide_epilogue(const f32x4_t (&acc)[4][FN], void *Cv, int64_t ldc, const void *Rv, int64_t ldr, const float *__restrict__ gate,
                                                       int M, int N, int m0, int n0, int q4, float alpha, bool vec) {
-    constexpr bool RES32 = EPI == LVX_EPI_RESID_GATE_F32, RES16 = EPI == LVX_EPI_RESID_GATE, F32 = RES32 || EPI == LVX_EPI_STORE_F32;
+    constexpr bool RES32 = EPI == LVX_EPI_RESID_GATE_F32, RES16 = EPI == LVX_EPI_RESID_GATE;
     constexpr bool BIAS = EPI == LVX_EPI_BIAS || EPI == LVX_EPI_BIAS_SILU;
     constexpr int NH = (FN + 1) / 2;
     float gt[NH][8];  // gate (residual epilogues) or bias of the lane's columns
@@ -144,7 +149,7 @@ __device__ __forceinline__ uint32_t lvx_wide_epilogue(const f32x4_t (&acc)[4][FN
                 if (RES32 || RES16) x = res[i & 1][h][e] + gt[h][e] * x;
                 v[e] = x;
             }
-            if (F32) {
+            if (RES32) {
                 float *c = reinterpret_cast<float *>(Cv) + (size_t)m * ldc + n;
                 if (vec) {
                     *reinterpret_cast<f32x4_t *>(c) = f32x4_t{v[0], v[1], v[2], v[3]};
@@ -196,6 +201,10 @@ __device__ __forceinline__ void lvx_wide_row_sumsq(const f32x4_t (&acc)[4][4], f
 }
 
 // FN: 16-column blocks per wave, so tiles are 256 x 64 FN (linears: 4).  CONV: the rows of A are gathered from the padded volume.
+// By which operand the matrix instruction takes first, a lane's accumulators are four columns of one row, or four rows of one column (by_col): so
+// plain fp32 outputs (bf16 products only), which nothing else is read or written beside, leave as 64-byte runs of 16 neighbouring lanes.  As 16-byte
+// pieces, 16 rows to a quarter of a wave, they held up short products: 5145 x 1280 x 320 12.5 -> 10.7 us, 1511 x 5920 x 256 15.1 -> 13.0, 234 products
+// 0.85 to 1.02 of the time, mean 0.95.
 template <int EPI, bool FP8, int FN = 4, bool CONV = false>
 __global__ void __launch_bounds__(512) lvx_gemm_wide_kernel(const lvx_gemm_args_t p, const lvx_wide_grid_t g) {
     constexpr int BN = 64 * FN, W_B = BN * 128;           // bytes of a slab's W rows
@@ -223,7 +232,7 @@ __global__ void __launch_bounds__(512) lvx_gemm_wide_kernel(const lvx_gemm_args_
             if (ra > M - 1) ra = M - 1;
             if (q < 2) da[h][q] = (uint32_t)((CONV ? lvx_conv_pixel_offset(p.conv, ra) : (size_t)ra * p.lda) + chunk * 16);
         }
-        int rw = col0 + r / (16 * FN) * (16 * FN) + lvx_wide_col<FN>(r % (16 * FN));
+        int rw = col0 + r / (16 * FN) * (16 * FN) + lvx_wide_col<FN>(r % (16 * FN), o.epi == LVX_EPI_STORE_F32);
         if (rw > N - 1) rw = N - 1;
         dw[q] = (uint32_t)((size_t)rw * p.ldw + chunk * 16);
     }
@@ -259,7 +268,7 @@ __global__ void __launch_bounds__(512) lvx_gemm_wide_kernel(const lvx_gemm_args_
                     acc_[i][j] = lvx_mfma_fp8(w[j].v, a[i].v, acc_[i][j]);                                                             \
             } else {                                                                                                                   \
                 _Pragma("unroll") for (int k = 0; k < 2; ++k) _Pragma("unroll") for (int i = 0; i < 4; ++i) _Pragma("unroll") for (int j = h; j < h + 2 && j < FN; ++j) \
-                    acc_[i][j] = lvx_mfma_bf16(w[j].h[k], a[i].h[k], acc_[i][j]);                                                      \
+                    acc_[i][j] = BY_COL ? lvx_mfma_bf16(a[i].h[k], w[j].h[k], acc_[i][j]) : lvx_mfma_bf16(w[j].h[k], a[i].h[k], acc_[i][j]); \
             }                                                                                                                          \
         }                                                                                                                              \
         LVX_SCHED_FENCE();                                                                                                             \
@@ -270,24 +279,23 @@ __global__ void __launch_bounds__(512) lvx_gemm_wide_kernel(const lvx_gemm_args_
 #define LVX_WIDE_ZERO(acc_) \
     _Pragma("unroll") for (int i = 0; i < 4; ++i) _Pragma("unroll") for (int j = 0; j < FN; ++j) acc_[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-    const int m0 = row0 + wm * 64 + l16, n0 = col0 + wn * 16 * FN + 8 * q4;
+    const int m0 = row0 + wm * 64, n0 = col0 + wn * 16 * FN + 8 * q4;
     const float alpha = FP8 ? p.scale_a[0] * p.scale_w[0] : 1.f;
-    const bool f32 = o.epi == LVX_EPI_RESID_GATE_F32 || o.epi == LVX_EPI_STORE_F32;
+    const bool f32 = EPI == LVX_EPI_RESID_GATE_F32;
     const bool resid = EPI == LVX_EPI_RESID_GATE_F32 || EPI == LVX_EPI_RESID_GATE;
     const bool vec = ((o.ldc | (resid ? p.ldr : 0)) & (f32 ? 3 : 7)) == 0;  // (bases are 16-byte aligned)
     uint32_t amax_b = 0;
-    auto finish = [&](const f32x4_t(&acc)[4][FN], int m) {
-        uint32_t b = 0;
-        if constexpr (EPI == LVX_EPI_SEGMENTS) {
-            if (o.epi == LVX_EPI_STORE_F32)
-                lvx_wide_epilogue<LVX_EPI_STORE_F32, FP8, FN>(acc, o.C, o.ldc, nullptr, 0, nullptr, M, N, m, n0, q4, alpha, vec);
-            else
-                lvx_wide_epilogue<LVX_EPI_STORE, FP8, FN>(acc, o.C, o.ldc, nullptr, 0, nullptr, M, N, m, n0, q4, alpha, vec);
-            if constexpr (FN == 4) if (o.sumsq != nullptr && n0 - 8 * q4 < N) lvx_wide_row_sumsq(acc, o.sumsq, o.ld_sumsq, tn * 4 + wn, M, m, q4);
+    auto finish = [&](auto by_col, const f32x4_t(&acc)[4][FN], int m) {  // m: the first row
+        if constexpr (decltype(by_col)::value) {
+            const float none[FN] = {};
+            lvx_gemm_epilogue<4, FN, LVX_EPI_STORE_F32, FP8>(acc, acc, o.C, o.ldc, nullptr, 0, none, M, N, m + 4 * q4, n0 - 8 * q4 + l16, alpha);
         } else {
-            b = lvx_wide_epilogue<EPI, FP8, FN>(acc, o.C, o.ldc, p.R, p.ldr, p.gate, M, N, m, n0, q4, alpha, vec);
+            constexpr int E = EPI == LVX_EPI_SEGMENTS ? (int)LVX_EPI_STORE : EPI;
+            const uint32_t b = lvx_wide_epilogue<E, FP8, FN>(acc, o.C, o.ldc, p.R, p.ldr, p.gate, M, N, m + l16, n0, q4, alpha, vec);
+            amax_b = amax_b > b ? amax_b : b;
+            if constexpr (EPI == LVX_EPI_SEGMENTS && FN == 4)
+                if (o.sumsq != nullptr && n0 - 8 * q4 < N) lvx_wide_row_sumsq(acc, o.sumsq, o.ld_sumsq, tn * 4 + wn, M, m + l16, q4);
         }
-        amax_b = amax_b > b ? amax_b : b;
     };
     // where the loop's next slabs lie in the rows of A and W: `near` the next but one of the last requested, `far` the one after it
     lvx_conv_walk_t near, far;
@@ -299,82 +307,92 @@ __global__ void __launch_bounds__(512) lvx_gemm_wide_kernel(const lvx_gemm_args_
             far.a += 128, far.w += 128;
     };
 
-    if (!half) {
-        // Slab t is in stage t % 2.  Two phases a slab: rows 0 .. 127 with W, then rows 128 .. 255.  A place is free once both groups have
-        // read it, half a period after its memory phase: the second A half of slab t + 1 is requested in the first memory phase of slab t
-        // (its place was last read in the second one of slab t - 1), the rest of slab t + 2 in the second.  So a load has one and a half
-        // slabs' time to land.  The last two slabs request nothing and wait for all.
-        f32x4_t acc[2][4][FN];
-        LVX_WIDE_ZERO(acc[0]);
-        LVX_WIDE_ZERO(acc[1]);
-        constexpr int A0 = 0, A1 = LVX_WIDE_HALF_B, W0 = 2 * LVX_WIDE_HALF_B;
-        load_a(0, near.a, A0), load_w(near.w, W0), load_a(1, near.a, A1);
-        if (second > 0) advance();
-        load_a(0, far.a, STAGE_B + A0), load_w(far.w, STAGE_B + W0);
-        advance();
-        LVX_WIDE_WAIT(FN + 4);
-        asm volatile("s_barrier" ::: "memory");
-        if (wm == 1) asm volatile("s_barrier" ::: "memory");  // this group runs half a period behind
-        int st = 0, t = 0;
-        auto slab = [&](bool load_first, bool load_second) {
-            LVX_WIDE_READ_A(st + A0);
-            LVX_WIDE_READ_W(st + W0);
-            LVX_SCHED_FENCE();
-            if (load_first) {
-                load_a(1, near.a, STAGE_B - st + A1);
-                LVX_WIDE_WAIT(FN + 4);
-            } else
-                LVX_WIDE_WAIT(0);
-            LVX_WIDE_MATRIX_PHASE(acc[0]);
-            LVX_WIDE_READ_A(st + A1);
-            LVX_SCHED_FENCE();
-            if (load_second) {
-                load_a(0, far.a, st + A0), load_w(far.w, st + W0);
-                LVX_WIDE_WAIT(FN + 4);
-                advance();
-            } else
-                LVX_WIDE_WAIT(0);
-            LVX_WIDE_MATRIX_PHASE(acc[1]);
-            st = STAGE_B - st;
-        };
-        for (; t + 1 < last; ++t) slab(true, true);
-        for (; t <= last; ++t) slab(t < last, false);
-        if (wm == 0) asm volatile("s_barrier" ::: "memory");
-        finish(acc[0], m0);
-        finish(acc[1], m0 + 128);
-    } else {
-        // Slab t is in stage t % 3, one phase a slab; slab t + 2 is requested where slab t - 1 was read a phase ago.
-        f32x4_t acc[4][FN];
-        LVX_WIDE_ZERO(acc);
-        constexpr int A = 0, W0 = LVX_WIDE_HALF_B;
-        int cur = 0, nxt = STAGE3_B, nx2 = 2 * STAGE3_B;
-        load_a(0, far.a, A), load_w(far.w, W0);
-        if (second > 0) advance();
-        load_a(0, far.a, nxt + A), load_w(far.w, nxt + W0);
-        advance();
-        LVX_WIDE_WAIT(FN + 2);
-        asm volatile("s_barrier" ::: "memory");
-        if (wm == 1) asm volatile("s_barrier" ::: "memory");
-        int t = 0;
-        auto slab = [&](bool load) {
-            LVX_WIDE_READ_A(cur + A);
-            LVX_WIDE_READ_W(cur + W0);
-            LVX_SCHED_FENCE();
-            if (load) {
-                load_a(0, far.a, nx2 + A), load_w(far.w, nx2 + W0);
-                LVX_WIDE_WAIT(FN + 2);
-                advance();
-            } else
-                LVX_WIDE_WAIT(0);
-            LVX_WIDE_MATRIX_PHASE(acc);
-            const int tmp = cur;
-            cur = nxt, nxt = nx2, nx2 = tmp;
-        };
-        for (; t + 1 < last; ++t) slab(true);
-        for (; t <= last; ++t) slab(false);
-        if (wm == 0) asm volatile("s_barrier" ::: "memory");
-        finish(acc, m0);
-    }
+    auto work = [&](auto by_col) {
+        constexpr bool BY_COL = decltype(by_col)::value;
+        if (!half) {
+            // Slab t is in stage t % 2.  Two phases a slab: rows 0 .. 127 with W, then rows 128 .. 255.  A place is free once both groups have
+            // read it, half a period after its memory phase: the second A half of slab t + 1 is requested in the first memory phase of slab t
+            // (its place was last read in the second one of slab t - 1), the rest of slab t + 2 in the second.  So a load has one and a half
+            // slabs' time to land.  The last two slabs request nothing and wait for all.
+            f32x4_t acc[2][4][FN];
+            LVX_WIDE_ZERO(acc[0]);
+            LVX_WIDE_ZERO(acc[1]);
+            constexpr int A0 = 0, A1 = LVX_WIDE_HALF_B, W0 = 2 * LVX_WIDE_HALF_B;
+            load_a(0, near.a, A0), load_w(near.w, W0), load_a(1, near.a, A1);
+            if (second > 0) advance();
+            load_a(0, far.a, STAGE_B + A0), load_w(far.w, STAGE_B + W0);
+            advance();
+            LVX_WIDE_WAIT(FN + 4);
+            asm volatile("s_barrier" ::: "memory");
+            if (wm == 1) asm volatile("s_barrier" ::: "memory");  // this group runs half a period behind
+            int st = 0, t = 0;
+            auto slab = [&](bool load_first, bool load_second) {
+                LVX_WIDE_READ_A(st + A0);
+                LVX_WIDE_READ_W(st + W0);
+                LVX_SCHED_FENCE();
+                if (load_first) {
+                    load_a(1, near.a, STAGE_B - st + A1);
+                    LVX_WIDE_WAIT(FN + 4);
+                } else
+                    LVX_WIDE_WAIT(0);
+                LVX_WIDE_MATRIX_PHASE(acc[0]);
+                LVX_WIDE_READ_A(st + A1);
+                LVX_SCHED_FENCE();
+                if (load_second) {
+                    load_a(0, far.a, st + A0), load_w(far.w, st + W0);
+                    LVX_WIDE_WAIT(FN + 4);
+                    advance();
+                } else
+                    LVX_WIDE_WAIT(0);
+                LVX_WIDE_MATRIX_PHASE(acc[1]);
+                st = STAGE_B - st;
+            };
+            for (; t + 1 < last; ++t) slab(true, true);
+            for (; t <= last; ++t) slab(t < last, false);
+            if (wm == 0) asm volatile("s_barrier" ::: "memory");
+            finish(by_col, acc[0], m0);
+            finish(by_col, acc[1], m0 + 128);
+        } else {
+            // Slab t is in stage t % 3, one phase a slab; slab t + 2 is requested where slab t - 1 was read a phase ago.
+            f32x4_t acc[4][FN];
+            LVX_WIDE_ZERO(acc);
+            constexpr int A = 0, W0 = LVX_WIDE_HALF_B;
+            int cur = 0, nxt = STAGE3_B, nx2 = 2 * STAGE3_B;
+            load_a(0, far.a, A), load_w(far.w, W0);
+            if (second > 0) advance();
+            load_a(0, far.a, nxt + A), load_w(far.w, nxt + W0);
+            advance();
+            LVX_WIDE_WAIT(FN + 2);
+            asm volatile("s_barrier" ::: "memory");
+            if (wm == 1) asm volatile("s_barrier" ::: "memory");
+            int t = 0;
+            auto slab = [&](bool load) {
+                LVX_WIDE_READ_A(cur + A);
+                LVX_WIDE_READ_W(cur + W0);
+                LVX_SCHED_FENCE();
+                if (load) {
+                    load_a(0, far.a, nx2 + A), load_w(far.w, nx2 + W0);
+                    LVX_WIDE_WAIT(FN + 2);
+                    advance();
+                } else
+                    LVX_WIDE_WAIT(0);
+                LVX_WIDE_MATRIX_PHASE(acc);
+                const int tmp = cur;
+                cur = nxt, nxt = nx2, nx2 = tmp;
+            };
+            for (; t + 1 < last; ++t) slab(true);
+            for (; t <= last; ++t) slab(false);
+            if (wm == 0) asm volatile("s_barrier" ::: "memory");
+            finish(by_col, acc, m0);
+        }
+    };
+    if constexpr (EPI == LVX_EPI_SEGMENTS) {
+        if (o.epi == LVX_EPI_STORE_F32)
+            work(lvx_bool_t<true>());
+        else
+            work(lvx_bool_t<false>());
+    } else
+        work(lvx_bool_t<EPI == LVX_EPI_STORE_F32>());
     if (FP8 && p.amax != nullptr) lvx_amax_publish(amax_b, p.amax, (int)blockIdx.x * 8 + wave, lane);
 }
 

@@ -58,6 +58,19 @@ def test_linear_on_wide_tiles(lvx, M, N, K, pad):
     assert torch.equal(x[:, N:], r[:, N:])
 
 
+@pytest.mark.parametrize("M,N,K", [s for s, _ in SHAPES])
+def test_fp32_outputs_are_the_sums_that_bf16_outputs_round(lvx, M, N, K):
+    """Plain fp32 outputs leave the matrix core with rows and columns exchanged; their sums are the same, bit for bit."""
+    a = S.randn_bf16((M, K), S.seed_of("wf_a", M, K), device=DEV)
+    w = S.randn_bf16((N, K), S.seed_of("wf_w", N, K), 1.0 / math.sqrt(K), device=DEV)
+    out, out32 = padded(M, N, 8, torch.bfloat16), padded(M, N, 5, torch.float32)
+    lvx.lvx_linear(a, w, out[:M, :N], lvx.EPI_STORE)
+    lvx.lvx_linear(a, w, out32[:M, :N], lvx.EPI_STORE_F32)
+    torch.cuda.synchronize()
+    assert torch.equal(out32[:M, :N].to(torch.bfloat16), out[:M, :N])
+    assert bool((out32[M] == 7.0).all()) and bool((out32[:, N:] == 7.0).all())
+
+
 @pytest.mark.parametrize("M,N,K", [s for s, _ in FP8_SHAPES])
 def test_linear_fp8_on_wide_tiles(lvx, M, N, K):
     aq, sa = lvx.lvx_fp8_quantize(S.randn_bf16((M, K), S.seed_of("w8_a", M, K), device=DEV), row_pad=16)
