@@ -31,7 +31,8 @@ struct lvx_bool_t {
 // dealt to the XCDs round-robin by hardware; each XCD gets a contiguous range of either kind, whole tiles first.  Where they do not divide by
 // 8 the first XCDs get one whole tile more and the last ones one half more, and an XCD's halves follow its whole tiles without a gap: a workgroup
 // that has nothing to do still takes its turn at a shader engine, and the next one then waits for a busy engine while another one
-// has an idle compute unit (6953 x 2120 x 2496, 243 whole tiles and 9 halves: 83 us with such gaps).
+// has an idle compute unit (6953 x 2120 x 2496, 243 whole tiles and 9 halves: 83 us with such gaps).  Of halves alone the last rows' stand beside the
+// others of their columns (283 x 13048 x 5824, behind all others: 60 us, they stream W once more; so 52).
 struct lvx_wide_grid_t {
     int32_t full_m, tiles_n, n_large, n_half, group_m;
 };
@@ -46,6 +47,13 @@ __device__ __forceinline__ bool lvx_wide_tile_of(const lvx_wide_grid_t &g, bool 
         idx = x * each_l + (x < more_l ? x : more_l) + i;
     } else {
         const int u = y * each_h + (y < more_h ? y : more_h) + i - mine_l, split = 2 * (total - g.n_large);
+        if (g.n_large == 0) {  // halves only: rows of 128 in bands of as many rows, the last ones among them, so that they find their columns of W in L2
+            const int rows = g.n_half / g.tiles_n, first = u / (2 * g.group_m * g.tiles_n) * 2 * g.group_m, at = u - first * g.tiles_n;
+            const int band = rows - first < 2 * g.group_m ? rows - first : 2 * g.group_m;
+            row0 = (first + at % band) * 128;
+            tn = at / band;
+            return true;
+        }
         idx = u < split ? g.n_large + (u >> 1) : total + u - split;
         sel = u < split ? u & 1 : 0;
     }

@@ -18,6 +18,9 @@ SHAPES = [((1567, 13832, 64), (1567, 4, 256, 203)), ((1567, 13832, 320), (1567, 
           ((1731, 5656, 64), (1731, 3, 210, 0)), ((1731, 5656, 192), (1731, 3, 210, 0)), ((1281, 13272, 128), (1281, 3, 350, 70)),
           ((4353, 4616, 128), (4353, 3, 425, 25)), ((1901, 2568, 192), (1901, 3, 0, 210)),
           ((515, 9832, 64), (515, 2, 154, 77)), ((515, 9832, 192), (515, 2, 154, 77)), ((129, 10904, 128), (129, 2, 0, 172))]
+# halves only, the last rows (a few of 128) beside those of the same columns: three rows of halves, and eight and one
+HALF_SHAPES = [((267, 6632, 192), (267, 2, 0, 156)), ((267, 10920, 128), (267, 3, 0, 171)), ((1129, 3752, 192), (1129, 3, 0, 180)),
+               ((1129, 5544, 128), (1129, 4, 0, 198))]
 FP8_SHAPES = [((1567, 13832, 256), (1567, 4, 256, 203)), ((1411, 4616, 1920), (1411, 4, 0, 228)),
               ((1731, 5656, 128), (1731, 3, 210, 0)), ((1731, 5656, 384), (1731, 3, 210, 0)), ((1901, 2568, 256), (1901, 3, 0, 210)),
               ((515, 9832, 128), (515, 2, 154, 77)), ((129, 10904, 1920), (129, 2, 0, 172))]
@@ -69,6 +72,17 @@ def test_fp32_outputs_are_the_sums_that_bf16_outputs_round(lvx, M, N, K):
     torch.cuda.synchronize()
     assert torch.equal(out32[:M, :N].to(torch.bfloat16), out[:M, :N])
     assert bool((out32[M] == 7.0).all()) and bool((out32[:, N:] == 7.0).all())
+
+
+@pytest.mark.parametrize("M,N,K", [s for s, _ in HALF_SHAPES])
+def test_halves_alone_cover_the_output(lvx, M, N, K):
+    a = S.randn_bf16((M, K), S.seed_of("wh_a", M, K), device=DEV)
+    w = S.randn_bf16((N, K), S.seed_of("wh_w", N, K), 1.0 / math.sqrt(K), device=DEV)
+    out = padded(M, N, 8, torch.bfloat16)
+    lvx.lvx_linear(a, w, out[:M, :N], lvx.EPI_STORE)
+    torch.cuda.synchronize()
+    assert_close(out[:M, :N], O.linear(S.to_f64(a), S.to_f64(w)), "halves %dx%dx%d" % (M, N, K))
+    assert bool((out[M] == 7.0).all()) and bool((out[:, N:] == 7.0).all())
 
 
 @pytest.mark.parametrize("M,N,K", [s for s, _ in FP8_SHAPES])

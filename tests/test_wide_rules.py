@@ -51,7 +51,7 @@ def choose(rules, M, N, K, fp8=False):
 
 
 def test_gpu_shapes_take_the_tiles_they_name(rules):
-    for (M, N, K), tiles in wide_tests.SHAPES:
+    for (M, N, K), tiles in wide_tests.SHAPES + wide_tests.HALF_SHAPES:
         assert choose(rules, M, N, K)[1:] == tiles, (M, N, K)
     for (M, N, K), tiles in wide_tests.FP8_SHAPES:
         assert choose(rules, M, N, K, True)[1:] == tiles, (M, N, K)
