@@ -206,9 +206,10 @@ static inline long lvx_wide_pick(int M, long cols, double *slab_us, const lvx_wi
 
 // The launch of a product: lvx_gemm_plan, with the wide tiles (256 x 64 fn and their halves) where they are in reach.  wide_rows: the rows that the
 // wide kernel takes, n_large whole tiles among them; the rows behind go to `tile` (m1 = wide_rows) or there are none.  Where the plan is
-// one of the large tiles (128 x 256 or 128 x 192), the wide kernel takes all rows.  Rows split off and the small tiles without K groups give way
-// where it takes no longer by the rule (0.66 to 0.84: 0.85 to 0.99 measured; 1.24 for the 64 x 128 tiles: 1.0 to 1.29).  A plan with K groups
-// stays, they fix the order of summation.  Narrower tiles, which move more bytes and power per product, are taken where they save a tenth by the
+// one of the large tiles (128 x 256 or 128 x 192), the wide kernel takes all rows.  Rows split off give way where it takes no longer by the rule.  Small
+// tiles for all rows stay: those with K groups fix the order of summation, and of those without only two rounds of 64 x 64 tiles beside one of 256 x 128
+// halves would give way, but two such tiles share a compute unit (29 products in bf16 0.79 to 1.01 of the halves' time, mean 0.92, 24 in FP8 0.85 to 1.02,
+// mean 0.95: 2110 x 936 x 3904 26.3 beside 29.2 us, 4335 x 432 x 1280 10.9 beside 12.9).  Narrower tiles, which move more bytes and power per product, are taken where they save a tenth by the
 // rule, which means where they leave fewer compute units idle: below 0.90 110 products of 900 to 9000 rows took 0.70 to 1.06 of the time of
 // 256-column tiles or of a 128 x 192 kernel of its own, mean 0.91 (1886 x 2560 x 2560 with residual 32.9 -> 31.4 us, 1560 x 5120 x 5120 with residual
 // 86.7 -> 79.9, 1560 x 5120 x 13824 232 -> 190); from 0.90 to 1 they took 0.98 to 1.11, mean 1.03 (4680 x 15360 x 5120 505 -> 520).
@@ -233,22 +234,15 @@ static inline lvx_gemm_launch_t lvx_gemm_choose(const lvx_gemm_segs_t *segs, int
     const lvx_gemm_plan_t plan = lvx_gemm_plan(segs, M, N, n_slabs, !sumsq);
     double us = 0.0, part_us = 0.0;
     const lvx_gemm_launch_t wide = lvx_wide_best(segs, M, n, fn_min, &us);
-    if (plan.m1 == 0 && plan.tile < 0) return wide;
-    lvx_gemm_launch_t other = {plan.tile, plan.m1, 0, 0};
-    double plan_us = plan.us;
-    bool groups = false;
-#define LVX_TILE_COST(ID_, BM_, BN_, WM_, WN_, NST_, KG_, PC_, US_)                                                                              \
-    if (plan.tile == ID_) {                                                                                                                      \
-        groups = KG_ > 1;                                                                                                                        \
-        if (plan.m1 > 0) {                                                                                                                       \
-            other = lvx_wide_best(segs, plan.m1, n, fn_min, &part_us);                                                                           \
-            other.tile = plan.tile;                                                                                                              \
-            plan_us = (part_us + (double)lvx_rounds((long)((M - plan.m1 + BM_ - 1) / BM_) * lvx_gemm_col_tiles(segs, n, BN_)) * US_) * n_slabs; \
-        }                                                                                                                                        \
-    }
+    if (plan.m1 == 0) return plan.tile < 0 ? wide : lvx_gemm_launch_t{plan.tile, 0, 0, 0};
+    lvx_gemm_launch_t split = lvx_wide_best(segs, plan.m1, n, fn_min, &part_us);
+    split.tile = plan.tile;
+    double rest_us = 0.0;
+#define LVX_TILE_COST(ID_, BM_, BN_, WM_, WN_, NST_, KG_, PC_, US_) \
+    if (plan.tile == ID_) rest_us = (double)lvx_rounds((long)((M - plan.m1 + BM_ - 1) / BM_) * lvx_gemm_col_tiles(segs, n, BN_)) * US_;
     LVX_GEMM_SMALL_TILES(LVX_TILE_COST)
 #undef LVX_TILE_COST
-    return !sumsq && !groups && us * n_slabs <= plan_us ? wide : other;
+    return us <= part_us + rest_us ? wide : split;
 }
 
 // ---- convolution ---------------------------------------------------------------------------------------------------------------

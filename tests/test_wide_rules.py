@@ -75,6 +75,12 @@ def test_gpu_shapes_take_the_tiles_they_name(rules):
         assert 0 < rows < M and rules.pair_rows(M, N1, N2, K // 64, C.byref(tile)) == rows and base.SMALL[tile.value] == kernel, (M, N1, N2, K)
 
 
+def test_small_tiles_without_k_groups_stay(rules):
+    """Two rounds of 64 x 64 tiles, two to a compute unit, are faster than one of 256 x 128 halves."""
+    for M, N, K in ((2110, 936, 3904), (4335, 432, 1280), (1364, 1464, 1792), (6038, 304, 4352)):
+        assert choose(rules, M, N, K)[:2] == ("64x64", 0), (M, N, K)
+
+
 def test_tiles_cover_all_rows_and_whole_tiles_never_cost_more(rules):
     rng = random.Random(5)
     for _ in range(20000):
