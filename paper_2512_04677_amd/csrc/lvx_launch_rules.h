@@ -294,7 +294,9 @@ static inline lvx_conv_plan_t lvx_conv_plan(int W, int N, int n_slabs, int M, in
 // LVX_CONV_WIDE_MAX of its time.  They sum in the order of the first two kinds, so a step may take them whatever the layer's other steps
 // take; a layer of K groups keeps them.  Measured, us a step: four 100 x 180 frames 384 -> 384 channels 524 -> 463 (fn 3), four 127 x 85 64 -> 176 57
 // -> 38, four 185 x 373 128 -> 304 655 -> 541, two 115 x 172 384 -> 200 218 -> 175 (fn 4), three 74 x 217 448 -> 288 377 -> 326.  34 of 91 random layers and steps
-// lie below the line and took 0.66 to 0.97, mean 0.82; between it and 1.1 wide tiles took 0.88 to 1.08, mean 1.01.
+// lie below the line and took 0.66 to 0.97, mean 0.82; between it and 1.1 wide tiles took 0.88 to 1.08, mean 1.01.  Whole tiles of 256 x 192 beside a
+// single round of 256 x 128: the rule prices both for a full chip, but 195 tiles on 256 units take 0.67 us a slab, not 0.82, and 130 wide ones their 0.76;
+// 12 steps took 1.10 to 1.16 of the round's time (94 x 179 384 -> 384 137 us, 157 wide), so the round keeps them.
 #define LVX_CONV_WIDE_MAX 0.94
 struct lvx_conv_launch_t {
     lvx_conv_plan_t plan;
@@ -303,10 +305,12 @@ struct lvx_conv_launch_t {
 static inline lvx_conv_launch_t lvx_conv_choose(int W, int N, int n_slabs, int M, int max_m) {
     const lvx_wide_us_t us[3] = {{0.85, 0.70, 0.51}, {1.05, 0.76, 0.60}, {1.28, 0.94, 0.71}};  // fn 2, 3, 4
     lvx_conv_launch_t l = {lvx_conv_plan(W, N, n_slabs, M, max_m), 0, 0};
+    const bool one_round = l.plan.kind == LVX_CONV_LARGE && lvx_rounds((long)((M + 255) / 256) * ((N + 127) / 128)) == 1;
     double best = LVX_CONV_WIDE_MAX * l.plan.us;
     for (int fn = 2; fn <= 4 && l.plan.kind != LVX_CONV_GROUPS; ++fn) {
         double slab = 0.0;
         const long n_large = lvx_wide_pick(M, (N + 64 * fn - 1) / (64 * fn), &slab, us[fn - 2]);
+        if (one_round && fn == 3 && n_large > 0) continue;
         if (slab * n_slabs < best) best = slab * n_slabs, l.fn = fn, l.n_large = (int)n_large;
     }
     return l;

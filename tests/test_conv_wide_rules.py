@@ -48,6 +48,8 @@ def test_gpu_shapes_take_the_kernels_they_name(rules):
 def test_measured_choices(rules):
     assert choose(rules, 100, 180, 384, 384, 4, 4)[:2] == (3, 512)
     assert choose(rules, 115, 172, 384, 200, 2, 2)[0] == 4
+    # one round of 256 x 128 tiles that leaves compute units idle is faster than half as many tiles of 256 x 192
+    assert choose(rules, 71, 59, 320, 384, 4, 4) == "256x128" and choose(rules, 94, 179, 384, 384, 3, 1) == "256x128"
     for s, kernel in {(50, 90, 384, 192, 1): "rows 64x64", (200, 360, 192, 96, 2): "rows 192x128", (240, 400, 64, 64, 4): "rows 256x64"}.items():
         assert choose(rules, *s, s[4]) == kernel, s
 

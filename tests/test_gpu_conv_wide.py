@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 # holds the rule to it
 SHAPES = [((95, 115, 64, 72, 3), "rows 192x128"), ((212, 114, 64, 72, 2), "256x128"),
           ((224, 47, 64, 72, 3), (2, 0, 247)), ((191, 84, 64, 72, 3), (2, 188, 1)),
-          ((187, 37, 64, 136, 3), (3, 0, 163)), ((149, 110, 64, 264, 1), (3, 128, 2)), ((110, 199, 64, 136, 3), (3, 256, 2)),
+          ((187, 37, 64, 136, 3), (3, 0, 163)), ((149, 110, 64, 264, 1), "256x128"), ((110, 199, 64, 136, 3), (3, 256, 2)),
           ((158, 24, 64, 392, 3), (4, 0, 178)), ((145, 226, 64, 200, 1), (4, 128, 1)), ((84, 98, 128, 248, 3), (4, 0, 193))]
 
 
